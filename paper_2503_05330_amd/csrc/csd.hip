@@ -38,6 +38,7 @@
 #include "csd_dag.cuh"
 #include "csd_index.cuh"
 #include "csd_kernels.cuh"
+#include "csd_launch.h"
 #include "csd_match.cuh"
 
 using namespace csd;
@@ -207,66 +208,17 @@ int check_draft_args(const csd_index* h, int32_t query_len, int32_t draft_len) {
   return CSD_OK;
 }
 
-// From this many rows on (256 CUs x 4 rows of the regular layout are resident at once) the
-// one-wave kernel runs with the small LDS layout.
-constexpr int64_t kSmallLdsRows = 2048;
 // Steps of up to this many tokens per path run fused in the one-wave kernel (a lane per new
 // position: at most a wave's worth).
 constexpr int32_t kFusedStepTokens = kWave;
 
 void launch_draft(const csd_index* h, const IndexView& v, const StepIn& in, const DraftArgs& a,
                   hipStream_t st) {
-  int64_t rows = (int64_t)v.P * v.N;
-  const uint32_t grid = xcd_grid(rows);
-  // scan mode, few rows: n_slices workgroups per row, the rows dealt to the 8 XCDs
-  const ScanSlices sl = h->slices;
-  const uint32_t scan_grid = sl.n > 1 ? (uint32_t)((rows + 7) / 8 * sl.n * 8) : grid;
-  if (h->indexed && v.eps > 0) {                         // one edit through the variant index
-    if (v.kmax <= 4) {                           // the usual gram lengths: predicates unrolled to 4
-      if (a.L <= 8) step_wave_kernel<8, true, LdsWaveFuzzy, true, 4><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-      else if (a.L <= 16) step_wave_kernel<16, true, LdsWaveFuzzy, true, 4><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-      else step_wave_kernel<32, true, LdsWaveFuzzy, true, 4><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-    }
-    else if (a.L <= 8) step_wave_kernel<8, true, LdsWaveFuzzy, true, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-    else if (a.L <= 16) step_wave_kernel<16, true, LdsWaveFuzzy, true, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-    else step_wave_kernel<32, true, LdsWaveFuzzy, true, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(true), 0, st>>>(v, in, a);
-  } else if (!h->indexed) {
-    // scan mode; the general kernels (POOLS) take the tree and list pools, own history,
-    // back-off and steps of several tokens
-    const bool general = a.pool_mode != CSD_POOL_DAG || v.options != 0 || in.n > 1;
-    const bool fuzzy = v.eps > 0, q4 = v.kmax <= 4;
-    auto* kernel = general ? (fuzzy ? (q4 ? step_scan_kernel<4, true, true> : step_scan_kernel<8, true, true>)
-                                    : (q4 ? step_scan_kernel<4, true, false> : step_scan_kernel<8, true, false>))
-                           : (fuzzy ? (q4 ? step_scan_kernel<4, false, true> : step_scan_kernel<8, false, true>)
-                                    : (q4 ? step_scan_kernel<4, false, false> : step_scan_kernel<8, false, false>));
-    kernel<<<scan_grid, kScanBlock, 0, st>>>(v, in, a, sl);
-  } else if (a.pool_mode != CSD_POOL_DAG || v.options != 0 || in.n > 1) {   // tree and list pools, own history, back-off, steps of several tokens: the general kernels
-    if (v.kmax <= 4) {                           // the usual gram lengths: loops unrolled to 4
-      if (a.L <= 8) step_wave_kernel<8, true, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-      else if (a.L <= 16) step_wave_kernel<16, true, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-      else step_wave_kernel<32, true, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    }
-    else if (a.L <= 8) step_wave_kernel<8, true, LdsWave, false, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    else if (a.L <= 16) step_wave_kernel<16, true, LdsWave, false, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    else step_wave_kernel<32, true, LdsWave, false, CSD_MAX_QUERY_LEN><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-  }
-  else if (v.kmax <= 4) {                        // the usual gram lengths: loops unrolled to 4
-    if (a.L <= 8 && rows >= kSmallLdsRows)       // more rows than fit the chip at once
-      step_wave_many_kernel<4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    else if (a.L <= 8)
-      step_wave_kernel<8, false, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    else if (a.L <= 16)
-      step_wave_kernel<16, false, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-    else
-      step_wave_kernel<32, false, LdsWave, false, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-  } else if (a.L <= 8 && rows >= kSmallLdsRows)
-    step_wave_many_kernel<8><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-  else if (a.L <= 8)
-    step_wave_kernel<8, false, LdsWave, false, 8><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-  else if (a.L <= 16)
-    step_wave_kernel<16, false, LdsWave, false, 8><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
-  else
-    step_wave_kernel<32, false, LdsWave, false, 8><<<grid, step_wave_threads(false), 0, st>>>(v, in, a);
+  if (!h->indexed) launch_step_scan(v, in, a, h->slices, st);
+  else if (v.eps > 0) launch_step_fuzzy(v, in, a, st);      // one edit through the variant index
+  // tree and list pools, own history, back-off, steps of several tokens: the general kernels
+  else if (a.pool_mode != CSD_POOL_DAG || v.options != 0 || in.n > 1) launch_step_general(v, in, a, st);
+  else launch_step(v, in, a, st);
 }
 
 // The device-side loops (many steps per launch) serve exact matching through the index with
@@ -274,21 +226,6 @@ void launch_draft(const csd_index* h, const IndexView& v, const StepIn& in, cons
 // per problem).
 bool multi_step_ok(const csd_index* h) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->view.N <= 16;
-}
-
-template <bool LOOP>
-void launch_multi(const csd_index* h, const MultiArgs& m, bool general, hipStream_t st) {
-  const uint32_t grid = (uint32_t)h->view.P, block = (uint32_t)h->view.N * kWave;
-  const int32_t L = m.a.L;
-  if (LOOP || general) {
-    if (L <= 8) step_multi_kernel<8, true, 4, LOOP><<<grid, block, 0, st>>>(h->view, m);
-    else if (L <= 16) step_multi_kernel<16, true, 4, LOOP><<<grid, block, 0, st>>>(h->view, m);
-    else step_multi_kernel<32, true, 4, LOOP><<<grid, block, 0, st>>>(h->view, m);
-  } else {
-    if (L <= 8) step_multi_kernel<8, false, 4, false><<<grid, block, 0, st>>>(h->view, m);
-    else if (L <= 16) step_multi_kernel<16, false, 4, false><<<grid, block, 0, st>>>(h->view, m);
-    else step_multi_kernel<32, false, 4, false><<<grid, block, 0, st>>>(h->view, m);
-  }
 }
 
 // Host-side bounds on the paths' lengths as they were before a call: put back when the call's
@@ -507,7 +444,7 @@ int csd_replay(csd_index* h, int32_t n_steps, const int32_t* d_tokens, const flo
       LengthBounds before(h);
       h->len_lo += chunk;
       h->len_hi = h->len_hi + chunk > h->cfg.max_len ? h->cfg.max_len : h->len_hi + chunk;
-      launch_multi<false>(h, m, general, as_stream(stream));
+      launch_multi(h->view, m, general, as_stream(stream));
       rc = before.launched("csd_replay");
       if (rc != CSD_OK) return rc;
       h->cur ^= chunk & 1;
@@ -595,7 +532,7 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
         LengthBounds before(h);
         h->len_hi = h->len_hi + (int64_t)chunk * (int64_t)n > h->cfg.max_len
                         ? h->cfg.max_len : h->len_hi + (int64_t)chunk * (int64_t)n;
-        launch_multi<true>(h, m, true, st);
+        launch_multi_loop(h->view, m, st);
         rc = before.launched("csd_accept_loop");
         if (rc != CSD_OK) return rc;
         h->cur ^= chunk & 1;
@@ -603,7 +540,6 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
       }
       return CSD_OK;
     }
-    const uint32_t grid = xcd_grid((int64_t)rows);
     for (int32_t s = 0; s < n_steps; ++s) {
       const int x = s & 1;
       LengthBounds before(h);
@@ -619,9 +555,7 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
       const LoopTail tail{d_future_tokens, d_future_probs, tok_of(x ^ 1),
                           d_future_probs ? prob_of(x ^ 1) : nullptr, cnt_of(x ^ 1), targets_of(x ^ 1),
                           d_path_len + (size_t)s * rows, (int32_t)n, h->cfg.max_len};
-      if (draft_len <= 8) step_loop_kernel<8, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a, tail);
-      else if (draft_len <= 16) step_loop_kernel<16, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a, tail);
-      else step_loop_kernel<32, 4><<<grid, step_wave_threads(false), 0, st>>>(v, in, a, tail);
+      launch_step_loop(v, in, a, tail, st);
       rc = before.launched("csd_accept_loop");
       if (rc != CSD_OK) return rc;
       h->cur ^= 1;

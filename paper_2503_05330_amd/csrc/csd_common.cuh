@@ -37,7 +37,7 @@ constexpr int kTailCap = CSD_MAX_QUERY_LEN + 1;   // most tokens a meta row keep
 // device array that a test harness reads back: where a step's time goes, row by row.
 #ifdef CSD_STAMPS
 constexpr int kStampSlots = 32;
-__device__ unsigned long long g_stamps[(1 << 14) * kStampSlots];
+static __device__ unsigned long long g_stamps[(1 << 14) * kStampSlots];
 #define CSD_STAMP(unit, n, value)                                                         \
   do {                                                                                    \
     if (threadIdx.x == 0 && (unit) < (1 << 14))                                           \

@@ -11,7 +11,7 @@
 
 namespace csd {
 
-__global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t gram_words, ScanSlices sl) {
+static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t gram_words, ScanSlices sl) {
   int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * 256;
   int64_t rows = (int64_t)ix.P * ix.N;
@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t gram_w
 }
 
 // Append only: one workgroup per (problem, path); the meta row is updated in place.
-__global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in) {
+static __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in) {
   int32_t row = blockIdx.x;
   int32_t p;
   Ctx c = make_ctx(ix, in, row, p);
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(16 * kWave) void step_multi_kernel(IndexView ix, Mu
   }
 }
 
-__global__ __launch_bounds__(256) void accept_kernel(int64_t rows, int32_t L,
+static __global__ __launch_bounds__(256) void accept_kernel(int64_t rows, int32_t L,
                                                      const int32_t* draft_tokens,
                                                      const int32_t* draft_len,
                                                      const int32_t* targets, int32_t* accept_len) {
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(256) void accept_kernel(int64_t rows, int32_t L,
 // emits itself), i.e. the next n of the path's future with a count, clipped at
 // max_len — and the targets the coming draft will be checked against, the L
 // future tokens behind them (-1 beyond the end).
-__global__ __launch_bounds__(256) void advance_kernel(int64_t rows, int32_t max_len, int32_t n,
+static __global__ __launch_bounds__(256) void advance_kernel(int64_t rows, int32_t max_len, int32_t n,
                                                       int32_t L, const int32_t* meta,
                                                       int32_t meta_stride, const int32_t* settled,
                                                       const int32_t* future_tok,
@@ -618,7 +618,7 @@ __global__ __launch_bounds__(256) void advance_kernel(int64_t rows, int32_t max_
 // advance_kernel and append_kernel in one launch (index mode): one workgroup per row works out
 // the row's step input, writes it where the draft launch behind it finds the targets, and
 // appends it.  The meta row is read before, and updated after, the workgroup's barrier.
-__global__ __launch_bounds__(256) void advance_append_kernel(
+static __global__ __launch_bounds__(256) void advance_append_kernel(
     IndexView ix, int32_t n, int32_t L, const int32_t* settled, const int32_t* future_tok,
     const float* future_prob, int32_t* step_tok, float* step_prob, int32_t* step_cnt,
     int32_t* targets, int32_t* path_len) {
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(256) void advance_append_kernel(
 
 // Plain copy of n 16-byte words: the known-size kernel that hardware traffic
 // counters are calibrated against.
-__global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src,
+static __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src,
                                                    uint4* __restrict__ dst, int64_t n) {
   int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < n; x += stride) dst[x] = src[x];
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ src
 // ---- debug dumps ------------------------------------------------------------
 
 // Scan mode: marks every match of every row in a bitmap [rows][words].
-__global__ __launch_bounds__(kScanBlock) void dump_match_bits_scan_kernel(IndexView ix, StepIn in,
+static __global__ __launch_bounds__(kScanBlock) void dump_match_bits_scan_kernel(IndexView ix, StepIn in,
                                                                           int32_t k, uint32_t* bits,
                                                                           int32_t words) {
   __shared__ LdsScan s;
@@ -708,7 +708,7 @@ __global__ __launch_bounds__(kWave) void dump_match_bits_wave_kernel(IndexView i
 }
 
 // counts[row] = number of set bits of the row (one workgroup per row)
-__global__ __launch_bounds__(256) void count_bits_kernel(const uint32_t* bits, int32_t words,
+static __global__ __launch_bounds__(256) void count_bits_kernel(const uint32_t* bits, int32_t words,
                                                          int32_t* counts) {
   __shared__ int total;
   if (threadIdx.x == 0) total = 0;
@@ -722,7 +722,7 @@ __global__ __launch_bounds__(256) void count_bits_kernel(const uint32_t* bits, i
 }
 
 // off[0] = 0, off[r+1] = off[r] + max(counts[r], 0); *bad = 1 if any count < 0
-__global__ void offsets_kernel(const int32_t* counts, int32_t rows, int32_t* off, int32_t* bad) {
+static __global__ void offsets_kernel(const int32_t* counts, int32_t rows, int32_t* off, int32_t* bad) {
   if (blockIdx.x != 0 || threadIdx.x != 0) return;
   int32_t acc = 0, any_bad = 0;
   off[0] = 0;
@@ -736,7 +736,7 @@ __global__ void offsets_kernel(const int32_t* counts, int32_t rows, int32_t* off
 }
 
 // Expands each row's bitmap into ascending (j, e) pairs (one wave per row).
-__global__ __launch_bounds__(64) void expand_bits_kernel(const uint32_t* bits, int32_t words,
+static __global__ __launch_bounds__(64) void expand_bits_kernel(const uint32_t* bits, int32_t words,
                                                          int32_t max_len, const int32_t* off,
                                                          int32_t* out_je, int64_t cap) {
   const uint32_t* b = bits + (int64_t)blockIdx.x * words;
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(64) void expand_bits_kernel(const uint32_t* bits, i
 // does and writes the edge entries, sorted by key, to tmp rows of kDumpStride
 // entries.  counts[row] = number of edges, or -1 if the row's DAG does not fit
 // the table as a whole.
-__global__ __launch_bounds__(kScanBlock) void dump_edge_rows_scan_kernel(
+static __global__ __launch_bounds__(kScanBlock) void dump_edge_rows_scan_kernel(
     IndexView ix, StepIn in, int32_t k, int32_t L, u64* tmp_keys, u64* tmp_vals, int32_t* counts) {
   constexpr int BLOCK = kScanBlock;
   __shared__ LdsScan s;
@@ -831,7 +831,7 @@ __global__ __launch_bounds__(kWave) void dump_edge_rows_wave_kernel(IndexView ix
   if (c.tid == 0) counts[row] = n_edges;
 }
 
-__global__ __launch_bounds__(256) void scatter_edges_kernel(const u64* tmp_keys,
+static __global__ __launch_bounds__(256) void scatter_edges_kernel(const u64* tmp_keys,
                                                             const u64* tmp_vals,
                                                             const int32_t* off, int32_t* out_duv,
                                                             uint64_t* out_cs, int64_t cap) {

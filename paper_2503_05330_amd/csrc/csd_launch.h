@@ -1,0 +1,25 @@
+// csd — launches of the decode step's kernels.  Every family of instantiations has a source
+// file of its own, so that they compile side by side.
+#pragma once
+
+#include "csd_kernels.cuh"
+
+namespace csd {
+
+// exact matching through the index, the usual step: DAG pool, at most one token per path
+void launch_step(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
+// the same with the tree and list pools, own history, back-off, steps of several tokens
+void launch_step_general(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
+// one-edit matching through the variant index
+void launch_step_fuzzy(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
+// matching by scan
+void launch_step_scan(const IndexView& v, const StepIn& in, const DraftArgs& a, const ScanSlices& sl,
+                      hipStream_t st);
+// one step of the accept-driven loop
+void launch_step_loop(const IndexView& v, const StepIn& in, const DraftArgs& a, const LoopTail& tail,
+                      hipStream_t st);
+// many steps per launch: a replay (general: tree and list pools, own history) / the accept-driven loop
+void launch_multi(const IndexView& v, const MultiArgs& m, bool general, hipStream_t st);
+void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);
+
+}  // namespace csd
