@@ -195,10 +195,22 @@ struct csd_index {
 namespace {
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-IndexView view_in_place(const csd_index* h) {     // lengths read and written in the same buffer
+IndexView view_in_place(const csd_index* h) {     // no append: lengths in one buffer
   IndexView v = h->view;
   v.meta_old = h->meta[h->cur];
   v.meta_new = h->meta[h->cur];
+  return v;
+}
+IndexView view_appending(const csd_index* h) {    // lengths read in one buffer, written in the other
+  IndexView v = h->view;
+  v.meta_old = h->meta[h->cur];
+  v.meta_new = h->meta[h->cur ^ 1];
+  return v;
+}
+IndexView view_appended(const csd_index* h) {     // behind such a launch, before `cur` follows
+  IndexView v = h->view;
+  v.meta_old = h->meta[h->cur ^ 1];
+  v.meta_new = h->meta[h->cur ^ 1];
   return v;
 }
 
@@ -226,6 +238,46 @@ void launch_draft(const csd_index* h, const IndexView& v, const StepIn& in, cons
 // per problem).
 bool multi_step_ok(const csd_index* h) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->view.N <= 16;
+}
+
+// Problems from which on an append that fills a good part of their indexes runs with one workgroup
+// per problem.  Measured, us, a thread per position with atomics on memory / a workgroup per
+// problem (the time is the problem's, 256 of them run side by side), histories appended as a
+// whole: 16 paths x 1024 tokens: 1 problem 14 / 24, 16: 28 / 31, 32: 42 / 31, 64: 70 / 29,
+// 1024: 1379 / 110; 32 x 2048: 16: 64 / 76, 32: 129 / 91; 64 x 4096: 16: 286 / 360,
+// 32: 593 / 359; one edit, 8 x 1024: 16: 51 / 52, 64: 134 / 58.
+constexpr int32_t kOwnedProblems = 24;
+// ... and their fill counts fit a CU's LDS (128 KB); with up to 2048 buckets the buckets fit too
+// (136 KB: one stream of whole lines instead of a line written for every posting; 1024 problems of
+// 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
+constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
+
+// Enqueues the append of a step's tokens; reads the paths' ends in v.meta_old and leaves the new
+// ones in v.meta_new (another buffer).  empty: no path has a token yet.
+void launch_append(const csd_index* h, const IndexView& v, const StepIn& in, bool empty, hipStream_t st) {
+  const int64_t rows = (int64_t)v.P * v.N;
+  const bool q4 = v.kmax <= 4;
+  const int64_t n_buckets = (int64_t)v.bucket_mask + 1;
+  // (an append of fewer tokens is not worth reading and writing all fill counts)
+  if (h->indexed && v.P >= kOwnedProblems && n_buckets <= kOwnedBuckets && (int64_t)v.N * in.n * 2 >= n_buckets) {
+    const bool table = n_buckets <= kTableBuckets;
+    auto* kernel =
+        v.eps > 0 ? (table ? (q4 ? append_problem_kernel<true, 4, true> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, true>)
+                           : (q4 ? append_problem_kernel<true, 4, false> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, false>))
+                  : (table ? (q4 ? append_problem_kernel<false, 4, true> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, true>)
+                           : (q4 ? append_problem_kernel<false, 4, false> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, false>));
+    const size_t lds = n_buckets * sizeof(int32_t) * (table ? 1 + kBucketWords : 1);
+    kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, empty ? 1 : 0);
+    return;
+  }
+  const int32_t block = (in.n <= kWave || rows > (1 << 22)) ? kWave : 256;
+  int64_t chunks = (in.n + block - 1) / block;
+  const int64_t most = ((int64_t)1 << 23) / rows;        // (bounds the grid; a workgroup loops over the rest)
+  chunks = chunks < most ? chunks : (most < 1 ? 1 : most);
+  auto* kernel = !h->indexed ? append_kernel<false, false, 4>
+                 : v.eps == 0 ? (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>)
+                              : (q4 ? append_kernel<true, true, 4> : append_kernel<true, true, CSD_MAX_QUERY_LEN>);
+  kernel<<<(uint32_t)(rows * chunks), block, 0, st>>>(v, in, (int32_t)chunks);
 }
 
 // Host-side bounds on the paths' lengths as they were before a call: put back when the call's
@@ -347,10 +399,10 @@ int csd_append(csd_index* h, const int32_t* d_tokens, const float* d_probs,
   LengthBounds before(h);
   int rc = note_append(h, d_counts != nullptr, n);
   if (rc != CSD_OK) return rc;
-  int64_t rows = (int64_t)h->view.P * h->view.N;
-  append_kernel<<<(uint32_t)rows, 256, 0, as_stream(stream)>>>(
-      view_in_place(h), StepIn{d_tokens, d_probs, d_counts, n});
-  return before.launched("csd_append");
+  launch_append(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
+  rc = before.launched("csd_append");
+  if (rc == CSD_OK) h->cur ^= 1;
+  return rc;
 }
 
 int csd_draft(csd_index* h, int32_t query_len, int32_t draft_len, int32_t* d_draft_tokens,
@@ -395,17 +447,14 @@ int csd_step(csd_index* h, const int32_t* d_tokens, const float* d_probs, const 
               d_token_scores, d_path_scores, d_targets, d_accept_len};
   if (h->indexed && n != 1 && (h->view.eps > 0 || n > kFusedStepTokens)) {
     // the one-wave kernels fuse the append of a few tokens per path (exact matching) or of
-    // one (one-edit matching); longer steps append first, with a workgroup per row
-    int64_t rows = (int64_t)h->view.P * h->view.N;
-    append_kernel<<<(uint32_t)rows, 256, 0, as_stream(stream)>>>(
-        view_in_place(h), StepIn{d_tokens, d_probs, d_counts, n});
-    launch_draft(h, view_in_place(h), StepIn{nullptr, nullptr, nullptr, 0}, a, as_stream(stream));
-    return before.launched("csd_step");
+    // one (one-edit matching); longer steps append first
+    launch_append(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
+    launch_draft(h, view_appended(h), StepIn{nullptr, nullptr, nullptr, 0}, a, as_stream(stream));
+    rc = before.launched("csd_step");
+    if (rc == CSD_OK) h->cur ^= 1;
+    return rc;
   }
-  IndexView v = h->view;
-  v.meta_old = h->meta[h->cur];
-  v.meta_new = h->meta[h->cur ^ 1];
-  launch_draft(h, v, StepIn{d_tokens, d_probs, d_counts, n}, a, as_stream(stream));
+  launch_draft(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, a, as_stream(stream));
   rc = before.launched("csd_step");
   if (rc == CSD_OK) h->cur ^= 1;
   return rc;
@@ -545,9 +594,7 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
       LengthBounds before(h);
       rc = note_append(h, true, (int32_t)n);
       if (rc != CSD_OK) return rc;
-      IndexView v = h->view;
-      v.meta_old = h->meta[h->cur];
-      v.meta_new = h->meta[h->cur ^ 1];
+      const IndexView v = view_appending(h);
       const StepIn in{tok_of(x), d_future_probs ? prob_of(x) : nullptr, cnt_of(x), (int32_t)n};
       DraftArgs a{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode,
                   d_draft_tokens + (size_t)s * rows * L, d_draft_len + (size_t)s * rows,
@@ -568,15 +615,19 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
       LengthBounds before(h);
       rc = note_append(h, true, (int32_t)n);
       if (rc != CSD_OK) return rc;
-      advance_append_kernel<<<(uint32_t)rows, 256, 0, st>>>(
-          view_in_place(h), (int32_t)n, draft_len, settled, d_future_tokens, d_future_probs, step_tok,
+      const bool q4 = h->view.kmax <= 4, fuzzy = h->view.eps > 0;
+      auto* kernel = fuzzy ? (q4 ? advance_append_kernel<true, 4> : advance_append_kernel<true, CSD_MAX_QUERY_LEN>)
+                           : (q4 ? advance_append_kernel<false, 4> : advance_append_kernel<false, CSD_MAX_QUERY_LEN>);
+      kernel<<<(uint32_t)rows, kWave, 0, st>>>(
+          view_appending(h), (int32_t)n, draft_len, settled, d_future_tokens, d_future_probs, step_tok,
           d_future_probs ? step_prob : nullptr, step_cnt, targets, d_path_len + (size_t)s * rows);
       DraftArgs a{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode,
                   d_draft_tokens + (size_t)s * rows * L, d_draft_len + (size_t)s * rows,
                   nullptr, nullptr, targets, d_accept_len + (size_t)s * rows};
-      launch_draft(h, view_in_place(h), StepIn{nullptr, nullptr, nullptr, 0}, a, st);
+      launch_draft(h, view_appended(h), StepIn{nullptr, nullptr, nullptr, 0}, a, st);
       rc = before.launched("csd_accept_loop");
       if (rc != CSD_OK) return rc;
+      h->cur ^= 1;
       continue;
     }
     advance_kernel<<<(uint32_t)((rows + 255) / 256), 256, 0, st>>>(

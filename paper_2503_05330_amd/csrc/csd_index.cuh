@@ -64,42 +64,6 @@ __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, Gr
   }
 }
 
-// Inserts the postings of the cnt <= 64 positions first .. first + cnt - 1 of path i by one
-// wave, a lane per position: every lane hashes its gram, reads the fill count of its first
-// bucket and claims a slot there — three round trips for all of them together.  A lane whose
-// first buckets are full (rare) leaves its posting to the whole wave.
-__device__ __forceinline__ void gram_insert_lanes(int32_t* gram, uint32_t mask, int32_t kmax,
-                                                  const Paths& y, int32_t i, int32_t old_i,
-                                                  int32_t first, int32_t cnt, int lane) {
-  const int32_t e = first + lane;
-  const bool mine = lane < cnt && e >= kmax;
-  uint32_t acc = kGramSeed;
-  for (int32_t g = 1; g <= kmax; ++g)                  // (idle lanes read the path's first token)
-    acc = gram_hash_add(acc, y.token(i, mine ? e - g : 0, old_i));
-  const GramHash gh = gram_hash_end(acc, kmax);
-  const int32_t pos = y.pos(i, e);
-  bool todo = mine;
-  for (uint32_t r = 0; r < 4u && r <= mask; ++r) {
-    if (wave_ballot(todo) == 0) return;
-    int32_t* b = gram_bucket(gram, gh, r, mask);
-    if (todo && b[0] < kBucketSlots) {
-      const int32_t c = atomicAdd(b, 1);
-      if (c < kBucketSlots) {
-        b[1 + c] = pos;
-        todo = false;
-      }
-    }
-  }
-  u64 left = wave_ballot(todo);
-  while (left) {                                       // their first four buckets were full
-    const int t = (int)__ffsll((long long)left) - 1;
-    left &= left - 1;
-    const GramHash g{(uint32_t)__builtin_amdgcn_readlane((int)gh.h, t),
-                     (uint32_t)__builtin_amdgcn_readlane((int)gh.step, t)};
-    gram_insert_from(gram, mask, g, 4u, __builtin_amdgcn_readlane(pos, t), lane);
-  }
-}
-
 // Split-phase insert of ONE new position by one wave, so that its two memory
 // round trips overlap the lookup's: lanes 0..3 look at the first four buckets of
 // the gram's sequence (sixteen were no faster and fetched twelve more lines per row).
@@ -181,9 +145,10 @@ __device__ __forceinline__ int32_t variant_posting(int32_t pos, int32_t v) {
 
 template <int SIZE>
 __device__ __forceinline__ GramHash variant_hash(const int32_t (&G)[SIZE], int32_t kmax, int32_t v) {
+  constexpr int kMost = SIZE < CSD_MAX_QUERY_LEN ? SIZE : CSD_MAX_QUERY_LEN;
   uint32_t acc = kGramSeed;
 #pragma unroll
-  for (int a = 0; a < CSD_MAX_QUERY_LEN; ++a)
+  for (int a = 0; a < kMost; ++a)
     if (a < kmax && a != v - 1) acc = gram_hash_add(acc, G[a]);
   return gram_hash_end(acc, v == 0 ? kmax : kmax - 1);
 }
@@ -191,20 +156,6 @@ __device__ __forceinline__ GramHash variant_hash(const int32_t (&G)[SIZE], int32
 template <int SIZE>
 __device__ __forceinline__ bool variant_is_new(const int32_t (&G)[SIZE], int32_t v) {
   return v < 2 || pick(G, v - 1) != pick(G, v - 2);
-}
-
-// Files position e of path i (e >= kmax) under every variant of the gram
-// before it, by one whole wave (bulk appends).
-__device__ __forceinline__ void gram_insert_variants(int32_t* gram, uint32_t mask, int32_t kmax,
-                                                     const Paths& y, int32_t i, int32_t e,
-                                                     int32_t old_i, int lane) {
-  if (e < kmax) return;
-  int32_t G[CSD_MAX_QUERY_LEN];
-#pragma unroll
-  for (int a = 0; a < CSD_MAX_QUERY_LEN; ++a) G[a] = y.token(i, a < kmax ? e - 1 - a : e - 1, old_i);
-  for (int32_t v = 0; v <= kmax; ++v)
-    if (variant_is_new(G, v))
-      gram_insert_from(gram, mask, variant_hash(G, kmax, v), 0u, variant_posting(y.pos(i, e), v), lane);
 }
 
 // Split-phase insert of ONE new position under its variants: the four groups
@@ -271,50 +222,292 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
   }
 }
 
-// Stores this row's share of the step (tokens, quantised probabilities, index
-// postings, new length and tail), reading the step input from memory.  Called
-// by all threads of the row's workgroup; handles any number of new tokens.
-template <int BLOCK, bool WITH_INDEX>
-__device__ __forceinline__ void append_row(const IndexView& ix, const Paths& y, int32_t p,
-                                           int32_t i, int32_t old_i, int32_t new_i, int tid) {
-  int64_t row = (int64_t)p * ix.N + i;
-  int32_t cnt = new_i - old_i;
-  uint32_t flags = 0;
-  // new meta row: word 0 = length, word 1+a = a-th token from the new end.  Every value is
-  // read before the barrier and written after it, so the row may be updated in place.
-  int32_t meta_val = 0;
-  if (tid == 0) meta_val = new_i;
-  else if (tid <= ix.tail_len) {
-    int32_t a = tid - 1;
-    if (a < cnt) meta_val = y.st[(int64_t)i * y.n + cnt - 1 - a];
-    else if (a < new_i) meta_val = y.meta_old[(int64_t)i * y.meta_stride + 1 + a - cnt];
+// Files the position of each lane of a wave (`mine`: the lane has one; G: the tokens before it,
+// newest first) in the index: under its gram, or (FUZZY) under every variant of it.  The slot
+// claims of all lanes and variants are atomics on the first buckets of their chains, in flight
+// together, without a look at the fill counts before: at most 8 of a bucket's 15 slots are taken
+// on average when a problem's histories are full, so few claims miss.  Those go on as claims in
+// the next three buckets, a lane at a time for itself, and what is left then (the long chain of
+// a frequent gram) is the whole wave's.
+template <bool FUZZY, int QC>
+__device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int32_t kmax,
+                                               const int32_t (&G)[QC], bool mine, int32_t pos, int lane) {
+  constexpr int kVariants = FUZZY ? QC + 1 : 1;
+  uint32_t todo = 0;                                     // variants of this lane that have no slot yet
+  int32_t claimed[kVariants];
+  uint32_t at[kVariants];                                // first bucket of the variant's chain
+#pragma unroll
+  for (int v = 0; v < kVariants; ++v) {
+    bool live = mine && v <= kmax;
+    if (v >= 2) live = live && G[v - 1] != G[v - 2];     // (else the same string as variant v - 1)
+    at[v] = variant_hash(G, kmax, v).h & mask;
+    claimed[v] = kBucketSlots;
+    todo |= live ? 1u << v : 0u;
   }
-  if (tid == 0) {
-    int32_t want = y.sc ? y.sc[i] : y.n;
-    want = want < 0 ? 0 : (want > y.n ? y.n : want);
-    if (want > cnt) flags |= CSD_STATUS_CAPACITY;
-  }
-  block_sync<BLOCK>();
-  if (tid <= ix.tail_len) ix.meta_new[row * ix.meta_stride + tid] = meta_val;
-  for (int32_t t = tid; t < cnt; t += BLOCK) {
-    int32_t v = y.st[(int64_t)i * y.n + t];
-    if (v < 0 || v >= ix.vocab) flags |= CSD_STATUS_TOKEN_RANGE;
-    ix.tok[row * ix.max_len + old_i + t] = v;
-    ix.pq[row * ix.max_len + old_i + t] = y.sp ? quantize_prob(y.sp[(int64_t)i * y.n + t]) : 65536u;
-  }
-  if (WITH_INDEX && ix.gram) {
-    int32_t* gram = ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords;
-    if (ix.eps == 0) {                                  // a lane per new position, 64 per wave and round
-      for (int32_t t0 = (tid / kWave) * kWave; t0 < cnt; t0 += BLOCK) {
-        const int32_t left = cnt - t0;
-        gram_insert_lanes(gram, ix.bucket_mask, ix.kmax, y, i, old_i, old_i + t0,
-                          left < kWave ? left : kWave, tid & 63);
+#pragma unroll
+  for (int v = 0; v < kVariants; ++v)
+    if (todo >> v & 1u) claimed[v] = atomicAdd(gram + (int64_t)at[v] * kBucketWords, 1);
+#pragma unroll
+  for (int v = 0; v < kVariants; ++v)
+    if (claimed[v] < kBucketSlots) {                     // (never without a claim)
+      gram[(int64_t)at[v] * kBucketWords + 1 + claimed[v]] = FUZZY ? variant_posting(pos, v) : pos;
+      todo &= ~(1u << v);
+    }
+  while (wave_ballot(todo != 0) != 0) {                  // uniform over the wave
+    const int32_t v = todo != 0 ? (int32_t)__ffs(todo) - 1 : 0;
+    const GramHash gh = variant_hash(G, kmax, v);
+    const int32_t posting = FUZZY ? variant_posting(pos, v) : pos;
+    bool open = todo != 0;
+    for (uint32_t r = 1; r < 4u && r <= mask; ++r) {
+      if (wave_ballot(open) == 0) break;
+      int32_t* b = gram_bucket(gram, gh, r, mask);
+      if (open && b[0] < kBucketSlots) {
+        const int32_t c = atomicAdd(b, 1);
+        if (c < kBucketSlots) {
+          b[1 + c] = posting;
+          open = false;
+        }
       }
-    } else {
-      for (int32_t t = tid / kWave; t < cnt; t += BLOCK / kWave)   // one wave per new position
-        gram_insert_variants(gram, ix.bucket_mask, ix.kmax, y, i, old_i + t, old_i, tid & 63);
+    }
+    u64 left = wave_ballot(open);
+    while (left) {                                       // their first four buckets were full
+      const int t = (int)__ffsll((long long)left) - 1;
+      left &= left - 1;
+      const GramHash g{(uint32_t)__builtin_amdgcn_readlane((int)gh.h, t),
+                       (uint32_t)__builtin_amdgcn_readlane((int)gh.step, t)};
+      gram_insert_from(gram, mask, g, 4u, __builtin_amdgcn_readlane(posting, t), lane);
+    }
+    todo &= todo - 1u;                                   // 0 stays 0
+  }
+}
+
+// The same where one workgroup files all new positions of a problem: `fill` holds the fill counts
+// of the problem's buckets in LDS, slots are claimed there, and the postings go to `slots` (bucket
+// b's from word 16 b + 1 on), in memory or in LDS too.  A lane has W consecutive positions: `tok`
+// are the QC tokens before the first of them, oldest first, and the W at the positions, `filed` has
+// a bit per position, `pos` is the first one's packed (path, index).
+template <bool FUZZY, int QC, int W>
+__device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill, uint32_t mask, int32_t kmax,
+                                                   const int32_t (&tok)[QC + W], uint32_t filed, int32_t pos) {
+  // positions that claim together: all of a lane's (one gram each), or one (its variants)
+  constexpr int kTogether = FUZZY ? 1 : W, kVariants = FUZZY ? QC + 1 : 1, kClaims = kTogether * kVariants;
+#pragma unroll
+  for (int x0 = 0; x0 < W; x0 += kTogether) {
+    GramHash gh[kClaims];
+    int32_t posting[kClaims], claimed[kClaims];
+    uint32_t todo = 0;
+#pragma unroll
+    for (int y = 0; y < kClaims; ++y) {
+      const int x = x0 + (FUZZY ? 0 : y), v = FUZZY ? y : 0;
+      int32_t G[QC];
+#pragma unroll
+      for (int a = 0; a < QC; ++a) G[a] = tok[QC + x - 1 - a];
+      bool live = (filed >> x & 1u) != 0 && v <= kmax;
+      if (v >= 2) live = live && G[v - 1] != G[v - 2];   // (else the same string as variant v - 1)
+      gh[y] = variant_hash(G, kmax, v);
+      posting[y] = FUZZY ? variant_posting(pos + x, v) : pos + x;
+      todo |= live ? 1u << y : 0u;
+    }
+#pragma unroll
+    for (int y = 0; y < kClaims; ++y) {
+      claimed[y] = kBucketSlots;
+      if (todo >> y & 1u) claimed[y] = atomicAdd(&fill[gh[y].h & mask], 1);
+    }
+#pragma unroll
+    for (int y = 0; y < kClaims; ++y)
+      if (claimed[y] < kBucketSlots) {                   // (never without a claim)
+        slots[(gh[y].h & mask) * kBucketWords + 1 + claimed[y]] = posting[y];
+        todo &= ~(1u << y);
+      }
+    // first bucket full: on along the chain (the table holds more slots than postings: ends)
+    if (wave_ballot(todo != 0) == 0) continue;
+#pragma unroll
+    for (int y = 0; y < kClaims; ++y) {
+      bool looking = (todo >> y & 1u) != 0;
+      uint32_t b = (gh[y].h + gh[y].step) & mask;
+      while (wave_ballot(looking) != 0) {                // uniform over the wave
+        if (looking) {
+          int32_t c = fill[b];                           // (a full bucket is passed without an atomic)
+          if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
+          if (c < kBucketSlots) {
+            slots[b * kBucketWords + 1 + c] = posting[y];
+            looking = false;
+          }
+          b = (b + gh[y].step) & mask;
+        }
+      }
     }
   }
+}
+
+// What the step appends to a path: its tokens t .. t + 63 (one per lane) with the tokens before
+// each, the path's length and the number of tokens it takes.  Everything lies at an address that
+// the kernel's arguments give (a new position's gram runs through the step's own tokens and the
+// old tail, which the meta row holds), so all loads are in flight together.
+// QC: compile-time bound (4 or 8) of the index's gram length; 0: no index.
+template <int QC>
+struct NewTokens {
+  int32_t t, token, len, want, offered;
+  float prob;
+  int32_t G[QC > 0 ? QC : 1];
+  __device__ __forceinline__ void load(const IndexView& ix, const StepIn& in, int64_t row, int32_t t_lane) {
+    const int32_t n = in.n;
+    const int32_t* st = in.tok + row * n;
+    const int32_t* meta = ix.meta_old + row * ix.meta_stride;
+    t = t_lane;
+    const int32_t tt = t < n ? t : 0;
+    token = st[tt];
+    prob = in.prob ? in.prob[row * n + tt] : 1.0f;
+#pragma unroll
+    for (int a = 0; a < QC; ++a) {
+      const int32_t back = a < ix.kmax ? a : 0;            // (words beyond the gram are not used)
+      G[a] = *(tt > back ? st + (tt - 1 - back) : meta + 1 + (back - tt));
+    }
+    want = in.counts ? in.counts[row] : n;
+    offered = n;
+    len = meta[0];
+  }
+  __device__ __forceinline__ int32_t most() const { return want < 0 ? 0 : (want > offered ? offered : want); }
+  __device__ __forceinline__ int32_t count(const IndexView& ix) const {
+    const int32_t room = ix.max_len - len;
+    return most() < room ? most() : room;
+  }
+  __device__ __forceinline__ bool mine(int32_t cnt) const { return t < cnt; }
+  __device__ __forceinline__ bool filed(const IndexView& ix, int32_t cnt) const {
+    return t < cnt && len + t >= ix.kmax;
+  }
+  __device__ __forceinline__ int32_t pos(const IndexView& ix, int32_t i) const { return (i << ix.eshift) | (len + t); }
+  // token and quantised probability to the history; returns the status bits to raise
+  __device__ __forceinline__ uint32_t store(const IndexView& ix, const StepIn& in, int64_t row, int32_t cnt) const {
+    if (!mine(cnt)) return 0u;
+    ix.tok[row * ix.max_len + len + t] = token;
+    ix.pq[row * ix.max_len + len + t] = in.prob ? quantize_prob(prob) : 65536u;
+    return (token < 0 || token >= ix.vocab) ? CSD_STATUS_TOKEN_RANGE : 0u;
+  }
+};
+
+// The path's new meta row (word 0 = length, word 1 + a = a-th token from the new end), by one wave.
+// Not written in place (meta_new is not meta_old): nothing else in the launch reads it.
+__device__ __forceinline__ void store_meta(const IndexView& ix, const StepIn& in, int64_t row, int32_t len,
+                                           int32_t cnt, int lane) {
+  if (lane > ix.tail_len) return;
+  const int32_t* st = in.tok + row * in.n;
+  const int32_t* meta = ix.meta_old + row * ix.meta_stride;
+  const int32_t a = lane - 1;
+  int32_t w = len + cnt;
+  if (lane > 0) w = a < cnt ? st[cnt - 1 - a] : (a < len + cnt ? meta[1 + a - cnt] : 0);
+  ix.meta_new[row * ix.meta_stride + lane] = w;
+}
+
+// The same with four consecutive tokens per lane (t a multiple of 4), for the kernel whose work is
+// bound by the instructions it issues: 16-byte loads and stores (at 4-byte alignment), one address.
+template <int QC>
+struct NewTokens4 {
+  int32_t t, len, want, offered;
+  int32_t tok[QC + 4];          // tokens t - QC .. t + 3
+  float prob[4];
+  struct __attribute__((packed, aligned(4))) Word4 { int32_t x[4]; };
+  __device__ __forceinline__ void load(const IndexView& ix, const StepIn& in, int64_t row, int32_t t_first,
+                                       int lane) {
+    const int32_t n = in.n;
+    const int32_t* st = in.tok + row * n;
+    const int32_t* meta = ix.meta_old + row * ix.meta_stride;
+    t = t_first + 4 * lane;
+    if (t + 4 <= n) {
+      const Word4 w = *reinterpret_cast<const Word4*>(st + t);
+#pragma unroll
+      for (int x = 0; x < 4; ++x) tok[QC + x] = w.x[x];
+      if (in.prob) {
+        const Word4 q = *reinterpret_cast<const Word4*>(in.prob + row * n + t);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) prob[x] = __int_as_float(q.x[x]);
+      }
+    } else {                                             // the row's end: nothing behind it is read
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        tok[QC + x] = st[t + x < n ? t + x : n - 1];
+        if (in.prob) prob[x] = in.prob[row * n + (t + x < n ? t + x : n - 1)];
+      }
+    }
+    if (t >= QC && t <= n) {
+#pragma unroll
+      for (int b = 0; b < QC; b += 4) {
+        const Word4 w = *reinterpret_cast<const Word4*>(st + t - QC + b);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) tok[b + x] = w.x[x];
+      }
+    } else {                                             // the row's start: before it lies the old tail
+#pragma unroll
+      for (int x = 0; x < QC; ++x) {
+        const int32_t at = t - QC + x, back = -1 - at;
+        tok[x] = at >= 0 ? st[at < n ? at : n - 1] : meta[1 + (back < ix.kmax ? back : 0)];
+      }
+    }
+    want = in.counts ? in.counts[row] : n;
+    offered = n;
+    len = meta[0];
+  }
+  __device__ __forceinline__ int32_t most() const { return want < 0 ? 0 : (want > offered ? offered : want); }
+  __device__ __forceinline__ int32_t count(const IndexView& ix) const {
+    const int32_t room = ix.max_len - len;
+    return most() < room ? most() : room;
+  }
+  __device__ __forceinline__ uint32_t filed(const IndexView& ix, int32_t cnt) const {   // bit x: position t + x
+    const int32_t last = cnt - t < 4 ? cnt - t : 4, first = ix.kmax - len - t;
+    const uint32_t below = last > 0 ? (1u << last) - 1u : 0u;
+    return first <= 0 ? below : (first < 4 ? below & ~((1u << first) - 1u) : 0u);
+  }
+  __device__ __forceinline__ int32_t pos(const IndexView& ix, int32_t i) const { return (i << ix.eshift) | (len + t); }
+  __device__ __forceinline__ uint32_t store(const IndexView& ix, const StepIn& in, int64_t row, int32_t cnt) const {
+    if (t >= cnt) return 0u;
+    int32_t* to = ix.tok + row * ix.max_len + len + t;
+    uint32_t* to_pq = ix.pq + row * ix.max_len + len + t;
+    Word4 w, q;
+    uint32_t flags = 0;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      w.x[x] = tok[QC + x];
+      q.x[x] = in.prob ? (int32_t)quantize_prob(prob[x]) : 65536;
+      if (t + x < cnt && (w.x[x] < 0 || w.x[x] >= ix.vocab)) flags = CSD_STATUS_TOKEN_RANGE;
+    }
+    if (t + 4 <= cnt) {
+      *reinterpret_cast<Word4*>(to) = w;
+      *reinterpret_cast<Word4*>(to_pq) = q;
+    } else {
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        if (t + x < cnt) {
+          to[x] = w.x[x];
+          to_pq[x] = (uint32_t)q.x[x];
+        }
+    }
+    return flags;
+  }
+};
+
+// Stores a share of what a step appends to path i of problem p: tokens, quantised probabilities
+// and postings of the step's tokens t_first + tid, then every t_stride-th, and (`head`) the new
+// meta row.  Called by whole waves, tid counting the threads that share the work.
+template <bool INDEX, bool FUZZY, int QC>
+__device__ __forceinline__ void append_positions(const IndexView& ix, const StepIn& in, int32_t p,
+                                                 int32_t i, int32_t t_first, int32_t t_stride,
+                                                 bool head, int tid) {
+  const int64_t row = (int64_t)p * ix.N + i;
+  const int lane = tid & (kWave - 1);
+  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
+  uint32_t flags = 0;
+  int32_t t0 = t_first + (tid - lane), cnt;
+  do {                                                   // uniform over the wave
+    NewTokens<INDEX ? QC : 0> x;
+    x.load(ix, in, row, t0 + lane);
+    cnt = x.count(ix);
+    if (head && tid == 0 && t0 == 0 && x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
+    flags |= x.store(ix, in, row, cnt);
+    if constexpr (INDEX)
+      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane);
+    if (head && t0 == 0) store_meta(ix, in, row, x.len, cnt, lane);
+    t0 += t_stride;
+  } while (t0 < cnt);
   if (flags) atomicOr(ix.status, flags);
 }
 

@@ -22,14 +22,78 @@ static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t
   if (t == 0) *ix.status = 0u;
 }
 
-// Append only: one workgroup per (problem, path); the meta row is updated in place.
-static __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in) {
-  int32_t row = blockIdx.x;
-  int32_t p;
-  Ctx c = make_ctx(ix, in, row, p);
-  int32_t old_i = c.y.old_len(c.i);
-  int32_t new_i = c.y.new_len(c.i, old_i);
-  append_row<256, true>(ix, c.y, p, c.i, old_i, new_i, c.tid);
+// Append only, any number of tokens per path: `chunks` workgroups per (problem, path), a thread
+// per new position.
+template <bool INDEX, bool FUZZY, int QC>
+__global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, int32_t chunks) {
+  const int32_t row = (int32_t)blockIdx.x / chunks, chunk = (int32_t)blockIdx.x - row * chunks;
+  const int32_t p = row / ix.N;
+  append_positions<INDEX, FUZZY, QC>(ix, in, p, row - p * ix.N, chunk * (int32_t)blockDim.x,
+                                     chunks * (int32_t)blockDim.x, chunk == 0, (int)threadIdx.x);
+}
+
+// The same with one workgroup per problem, for batches of problems: slots are claimed on fill
+// counts in LDS.  (Atomics on memory run at the memory's side of the fabric here, 1.1e10 per
+// second whatever the addresses.)  empty: the index holds no postings yet.  TABLE: the buckets
+// themselves are in LDS too, and go to memory as a whole.
+template <bool FUZZY, int QC, bool TABLE>
+__global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, StepIn in, int32_t empty) {
+  extern __shared__ int4 shared[];
+  const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
+  const int32_t p = (int32_t)blockIdx.x, n_buckets = (int32_t)ix.bucket_mask + 1;
+  int32_t* gram = ix.gram + (int64_t)p * n_buckets * kBucketWords;
+  int32_t* fill = reinterpret_cast<int32_t*>(shared);
+  int4* table = shared + n_buckets / 4;                  // (at least 4 buckets)
+  int32_t* slots = TABLE ? reinterpret_cast<int32_t*>(table) : gram;
+  // a wave per run of 256 positions of a path, the next run's loads in flight
+  constexpr int32_t kRun = 4 * kWave;
+  const int32_t runs = (in.n + kRun - 1) / kRun;
+  int32_t i = 0, run = __builtin_amdgcn_readfirstlane(tid >> 6);   // this wave's: path, run of it
+  auto settle = [&]() {                                  // run number -> (path, run)
+    while (run >= runs && i < ix.N) {
+      run -= runs;
+      ++i;
+    }
+  };
+  settle();
+  NewTokens4<QC> next;
+  auto request = [&]() {
+    if (i < ix.N) next.load(ix, in, (int64_t)p * ix.N + i, run * kRun, lane);   // uniform over the wave
+  };
+  request();
+  if (TABLE)
+    for (int32_t x = tid; x < n_buckets * 4; x += 1024)
+      table[x] = empty ? int4{-1, -1, -1, -1} : reinterpret_cast<const int4*>(gram)[x];
+  for (int32_t b = tid; b < n_buckets; b += 1024) fill[b] = empty ? 0 : gram[b * kBucketWords];
+  __syncthreads();
+  uint32_t flags = 0;
+  while (i < ix.N) {
+    const NewTokens4<QC> x = next;
+    const int32_t path = i;
+    const bool head = run == 0;
+    run += 16;
+    settle();
+    request();
+    const int64_t row = (int64_t)p * ix.N + path;
+    const int32_t cnt = x.count(ix);
+    flags |= x.store(ix, in, row, cnt);
+    file_positions_own<FUZZY, QC, 4>(slots, fill, ix.bucket_mask, ix.kmax, x.tok, x.filed(ix, cnt), x.pos(ix, path));
+    if (head) {                                          // the path's first run
+      if (lane == 0 && x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
+      store_meta(ix, in, row, x.len, cnt, lane);
+    }
+  }
+  __syncthreads();
+  if (TABLE) {
+    for (int32_t x = tid; x < n_buckets * 4; x += 1024) {
+      int4 words = table[x];
+      if ((x & 3) == 0) words.x = fill[x >> 2];
+      reinterpret_cast<int4*>(gram)[x] = words;
+    }
+  } else {
+    for (int32_t b = tid; b < n_buckets; b += 1024) gram[b * kBucketWords] = fill[b];
+  }
+  if (flags) atomicOr(ix.status, flags);
 }
 
 // Draft tokens, scores, length and (optionally) accept length of one row.
@@ -134,7 +198,7 @@ __global__ __launch_bounds__(kScanBlock) void step_scan_kernel(IndexView ix, Ste
   const int32_t old_i = me.old_len;
   c.len_i = me.new_len;
   cache_lens<BLOCK>(s, c.y, c.tid);
-  if (in.n > 0 && slice == 0) append_row<BLOCK, true>(ix, c.y, p, c.i, old_i, c.len_i, c.tid);
+  if (in.n > 0 && slice == 0) append_positions<false, false, QC>(ix, in, p, c.i, 0, BLOCK, true, c.tid);
   if (in.n <= 1) {                                       // the query follows from what is loaded
     int32_t cnt_i = c.len_i - old_i;
     c.q = a.k < c.len_i ? a.k : c.len_i;
@@ -333,8 +397,7 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
   if (APPENDS && POOLS && !FUZZY && in.n > 1) {
     // a step of several tokens appended by the drafting wave itself (nothing this step's
     // drafts read is written here)
-    const int32_t old_i = c.y.old_len(c.i);
-    append_row<kWave, true>(ix, c.y, p, c.i, old_i, c.y.new_len(c.i, old_i), lane);
+    append_positions<true, false, QC>(ix, in, p, c.i, 0, kWave, true, lane);
   }
   // the loop's tail needs the path's future from its new end on (lane x: x tokens further):
   // requested here, so that the load travels during the walk
@@ -470,7 +533,7 @@ __device__ __forceinline__ void step_wave_body(const IndexView& ix, const StepIn
     Ctx c = make_ctx(ix, in, row, p);
     c.tid = lane;
     if (FUZZY) wave_append_fuzzy(c, ix, p);
-    else wave_append<QC, POOLS, std::is_same<LDS, LdsWaveSmall>::value ? 1 : kInsertLanes>(c, ix, p);
+    else wave_append<QC, POOLS, std::is_same<LDS, LdsWaveSmall>::value ? 1 : kInsertLanes>(c, ix, in, p);
     return;
   }
   row_step<LCAP, POOLS, LDS, FUZZY, QC, !SPLIT>(s, ix, in, a, tail, row, lane);
@@ -615,10 +678,10 @@ static __global__ __launch_bounds__(256) void advance_kernel(int64_t rows, int32
   }
 }
 
-// advance_kernel and append_kernel in one launch (index mode): one workgroup per row works out
-// the row's step input, writes it where the draft launch behind it finds the targets, and
-// appends it.  The meta row is read before, and updated after, the workgroup's barrier.
-static __global__ __launch_bounds__(256) void advance_append_kernel(
+// advance_kernel and append_kernel in one launch (index mode): one wave per row works out the
+// row's step input, writes it where the draft launch behind it finds the targets, and appends it.
+template <bool FUZZY, int QC>
+__global__ __launch_bounds__(kWave) void advance_append_kernel(
     IndexView ix, int32_t n, int32_t L, const int32_t* settled, const int32_t* future_tok,
     const float* future_prob, int32_t* step_tok, float* step_prob, int32_t* step_cnt,
     int32_t* targets, int32_t* path_len) {
@@ -636,21 +699,19 @@ static __global__ __launch_bounds__(256) void advance_append_kernel(
     path_len[r] = len + grow;
   }
   const int32_t* ft = future_tok + r * max_len;
-  for (int32_t t = tid; t < n; t += 256) {
+  for (int32_t t = tid; t < n; t += kWave) {
     bool in = len + t < max_len;
     step_tok[r * n + t] = in ? ft[len + t] : 0;
     if (step_prob) step_prob[r * n + t] = in ? future_prob[r * max_len + len + t] : 0.0f;
   }
-  for (int32_t d = tid; d < L; d += 256) {
+  for (int32_t d = tid; d < L; d += kWave) {
     int32_t t = len + grow + d;
     targets[r * L + d] = t < max_len ? ft[t] : -1;
   }
-  __syncthreads();                      // the step input is read back by this workgroup below
-  int32_t p;
-  Ctx c = make_ctx(ix, StepIn{step_tok, step_prob, step_cnt, n}, (int32_t)r, p);
-  int32_t old_i = c.y.old_len(c.i);
-  int32_t new_i = c.y.new_len(c.i, old_i);
-  append_row<256, true>(ix, c.y, p, c.i, old_i, new_i, c.tid);
+  __syncthreads();                      // the step input is read back below
+  const int32_t p = (int32_t)r / ix.N;
+  append_positions<true, FUZZY, QC>(ix, StepIn{step_tok, step_prob, step_cnt, n}, p, (int32_t)r - p * ix.N, 0,
+                                    kWave, true, tid);
 }
 
 // Plain copy of n 16-byte words: the known-size kernel that hardware traffic

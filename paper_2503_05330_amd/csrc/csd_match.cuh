@@ -658,7 +658,7 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
   // (four of each; one with the layout of launches of thousands of rows, whose time is set by
   // what all rows together fetch and issue, not by a row's latency)
   constexpr int kFirst = std::is_same<LDS, LdsWaveSmall>::value ? 1 : 4;
-  ticket_used = APPENDS && y.n == 1 && cnt_i == 1;   // (longer steps are appended by append_row)
+  ticket_used = APPENDS && y.n == 1 && cnt_i == 1;   // (longer steps are appended by append_positions)
   if (ticket_used) ticket = insert_begin<QC, kFirst>(gram, c.bucket_mask, ix.kmax, me.tail, old_i, lane);
   GramHash gh{0u, 1u};
   int32_t word = -1;
@@ -738,12 +738,11 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
 // GENERAL: also compiled for steps of several tokens per path.
 // LANES: buckets of the insert's chain whose fill counts are read up front.
 template <int QC, bool GENERAL = false, int LANES = kInsertLanes>
-__device__ __forceinline__ void wave_append(const Ctx& c, const IndexView& ix, int32_t p) {
+__device__ __forceinline__ void wave_append(const Ctx& c, const IndexView& ix, const StepIn& in, int32_t p) {
   const int lane = c.tid;
   const Paths& y = c.y;
   if (GENERAL && y.n > 1) {
-    const int32_t old_i = y.old_len(c.i);
-    append_row<kWave, true>(ix, y, p, c.i, old_i, y.new_len(c.i, old_i), lane);
+    append_positions<true, false, QC>(ix, in, p, c.i, 0, kWave, true, lane);
     return;
   }
   if (y.n != 1) return;
