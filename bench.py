@@ -91,6 +91,9 @@ class Replay:
         self.flags |= (binding.INCLUDE_SELF if include_self else 0) | (binding.QUERY_BACKOFF if backoff else 0)
         self.ix = binding.Index(P, N, T, w.vocab, self.k, L, 1.0, 0, self.flags, device=dev,
                                 max_edits=max_edits, pool_mode=POOLS[pool])
+        # a launch per step, as in a decode loop: what is timed is a step that the next one waits for
+        # (left to itself, replay() runs the steps of a recorded trace side by side)
+        self.ix.set_steps_per_launch(1)
         mk = lambda shape, dt: torch.empty(shape, dtype=dt, device=dev)
         self.outs = dict(tokens=mk((T, P, N, L), torch.int32), length=mk((T, P, N), torch.int32),
                          token_scores=mk((T, P, N, L), torch.float32), path_scores=mk((T, P, N), torch.float32))
@@ -168,6 +171,7 @@ def batch_points(binding, torch, dev, w, tokens, probs, matches_per_problem_step
         pr = np.ascontiguousarray(np.broadcast_to(probs[0, :, :S].T[:, None, :], (S, P, N)))
         d_tok, d_pr = torch.from_numpy(tok).to(dev), torch.from_numpy(pr).to(dev)
         ix = binding.Index(P, N, T, w.vocab, k, L, 1.0, 0, flags, device=dev, max_edits=max_edits)
+        ix.set_steps_per_launch(1)
         outs = dict(tokens=torch.empty((S, P, N, L), dtype=torch.int32, device=dev),
                     length=torch.empty((S, P, N), dtype=torch.int32, device=dev),
                     token_scores=torch.empty((S, P, N, L), dtype=torch.float32, device=dev),
@@ -205,6 +209,7 @@ def batch_points_full_history(binding, torch, dev, w, tokens, probs, matches_per
         pr = np.ascontiguousarray(np.broadcast_to(probs[0].T[:, None, :], (T, P, N)))
         d_tok, d_pr = torch.from_numpy(tok).to(dev), torch.from_numpy(pr).to(dev)
         ix = binding.Index(P, N, T, w.vocab, k, L, 1.0, 0, flags, device=dev, max_edits=max_edits)
+        ix.set_steps_per_launch(1)
         outs = dict(tokens=torch.empty((K, P, N, L), dtype=torch.int32, device=dev),
                     length=torch.empty((K, P, N), dtype=torch.int32, device=dev),
                     token_scores=torch.empty((K, P, N, L), dtype=torch.float32, device=dev),

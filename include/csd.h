@@ -212,15 +212,17 @@ int csd_step(csd_index* index, const int32_t* d_tokens, const float* d_probs,
              int32_t* d_draft_tokens, int32_t* d_draft_len, float* d_token_scores,
              float* d_path_scores, const int32_t* d_targets, int32_t* d_accept_len, void* stream);
 
-/* n_steps consecutive decoding steps with one token per path and step, issued
- * from a host loop inside the library (no device-side loop): step t appends
- * d_tokens[t] (with d_probs[t], may be NULL), drafts into slice t of the
- * outputs and, if d_targets is given, checks slice t of it.
+/* n_steps consecutive decoding steps of a recorded trace, one token per path and
+ * step: step t appends d_tokens[t] (with d_probs[t], may be NULL), drafts into slice t
+ * of the outputs and, if d_targets is given, checks slice t of it.
  *   d_tokens [n_steps][P][N], d_probs same; d_draft_tokens [n_steps][P][N][draft_len],
  *   d_draft_len [n_steps][P][N], d_token_scores / d_path_scores likewise or NULL,
  *   d_targets [n_steps][P][N][draft_len] and d_accept_len [n_steps][P][N] or both NULL.
- * fused != 0: one csd_step launch per step; fused == 0: csd_append, csd_draft
- * and csd_accept launches per step.  Both give identical results. */
+ * fused != 0: the steps run side by side, since all their tokens are known: one launch
+ * appends them, a second one drafts every path at every step from the pool as it is at that
+ * step (vocab <= 2^24; up to max(1, 2^19 / (P*N)) steps at a time; csd_set_steps_per_launch
+ * chooses other forms), else one csd_step launch per step; fused == 0: csd_append, csd_draft
+ * and csd_accept launches per step.  All give identical results. */
 int csd_replay(csd_index* index, int32_t n_steps, const int32_t* d_tokens, const float* d_probs,
                int32_t query_len, int32_t draft_len, int32_t* d_draft_tokens,
                int32_t* d_draft_len, float* d_token_scores, float* d_path_scores,
@@ -253,8 +255,10 @@ int csd_accept_loop(csd_index* index, int32_t n_steps, const int32_t* d_future_t
                     void* d_scratch, size_t scratch_bytes, int32_t* d_draft_tokens,
                     int32_t* d_draft_len, int32_t* d_accept_len, int32_t* d_path_len, void* stream);
 
-/* How many steps one launch of csd_replay (fused != 0) and csd_accept_loop runs.
- * 1 (the default): a launch per step.  More: a device-side loop — one workgroup per
+/* How many steps one launch of csd_replay (fused != 0) and csd_accept_loop runs one after
+ * the other.  Until it is called csd_replay runs its steps side by side and csd_accept_loop
+ * a launch per step.  1: a launch per step (what a decode loop with a model between the steps
+ * does: csd_replay then takes as long per step).  More: a device-side loop — one workgroup per
  * problem, one wave per path, a workgroup barrier between steps — runs up to `steps`
  * steps per launch where the configuration allows it: exact matching through the index,
  * max_query_len <= 4, n_paths <= 16 (csd_accept_loop also needs twice the minimum of

@@ -154,7 +154,8 @@ class Index:
             raise CsdError(rc, what)
 
     def set_steps_per_launch(self, steps: int):
-        """Steps per launch of replay() and accept_loop() (1 = a launch per step)."""
+        """Steps that a launch of replay() and accept_loop() runs one after the other (1 = a launch
+        per step).  Until it is called replay() runs its steps side by side."""
         self._check(load().csd_set_steps_per_launch(self._h, steps), "csd_set_steps_per_launch")
 
     def reset(self):
@@ -225,7 +226,7 @@ class Index:
 
     def replay(self, n_steps, tokens, probs, query_len, draft_len, out=None, targets=None,
                accept_out=None, fused=True, scores=True):
-        """n_steps decode steps from a host loop inside the library.
+        """n_steps decode steps of a recorded trace, side by side in two launches.
         tokens / probs [n_steps][P][N]; outputs get a leading n_steps axis."""
         L, S = draft_len, n_steps
         if out is None:

@@ -63,12 +63,20 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t tok, pq, meta, status, gram, slices, total;
+  size_t tok, pq, meta, status, gram, slices, step_meta, total;
   int32_t n_slices;             // workgroups that share a row's scan (scan mode, few rows)
+  int32_t replay_steps;         // steps of a replay that run side by side
   int32_t meta_stride, eshift;
   uint32_t n_buckets;           // per (problem, gram length); 0 in scan mode
   size_t gram_words;
 };
+
+// Drafts of a replay that run side by side at most (a chip full of workgroups many times over;
+// their paths' ends take 8 to 25 MB).
+constexpr int64_t kReplayDrafts = 1 << 19;
+// ... and with a larger vocabulary than this a layer of the DAG may not fit the tables of the layout
+// that a launch of many drafts uses, though it fits the one of a launch per step: that one runs then.
+constexpr int32_t kReplayVocab = 1 << 24;
 
 // Rows (problem, path) up to which a row's scan is shared by several workgroups.
 constexpr int64_t kSlicedScanRows = 128;
@@ -161,6 +169,14 @@ Layout make_layout(const csd_config* c) {
     if (l.n_slices > 1)         // per row the match list and a state word
       at += align_up(rows * LdsScan::kMatch * sizeof(Match)) + align_up(rows * sizeof(u64));
   }
+  // the paths' ends after each step of a replay, for as many steps as give kReplayDrafts drafts
+  l.replay_steps = 0;
+  l.step_meta = at;
+  if (c->vocab <= kReplayVocab) {
+    const int64_t most = kReplayDrafts / (int64_t)rows;
+    l.replay_steps = (int32_t)(most < c->max_len ? most : c->max_len);
+    at += align_up((size_t)l.replay_steps * rows * l.meta_stride * sizeof(int32_t));
+  }
   l.total = at;
   return l;
 }
@@ -189,7 +205,10 @@ struct csd_index {
   bool indexed;
   uint32_t alpha_q;
   int64_t len_lo, len_hi;       // host-side bounds on every path's length
-  int32_t steps_per_launch;     // csd_replay / csd_accept_loop: steps one launch runs (1: a launch per step)
+  int32_t steps_per_launch;     // csd_replay / csd_accept_loop: steps one launch runs (1: a launch per step;
+                                //   0: not set, a replay's steps run side by side)
+  int32_t* step_meta;           // [replay_steps][P][N][meta_stride] see replay_append_kernel
+  int32_t replay_steps;
 };
 
 namespace {
@@ -280,6 +299,29 @@ void launch_append(const csd_index* h, const IndexView& v, const StepIn& in, boo
   kernel<<<(uint32_t)(rows * chunks), block, 0, st>>>(v, in, (int32_t)chunks);
 }
 
+// Enqueues `steps` steps of a replay side by side: the append of their tokens, which leaves the
+// paths' ends in v.meta_new (may be v.meta_old), and all their drafts.
+void launch_replay_steps(const csd_index* h, const IndexView& v, const ReplayIn& in, const DraftArgs& a,
+                         hipStream_t st) {
+  const bool q4 = v.kmax <= 4;
+  // whole paths per workgroup: as many as its 1024 threads have steps for, at most 16 (a line of
+  // tokens per step) and no more than there are
+  int32_t paths_log2 = 4;
+  while (paths_log2 > 0 && (((int64_t)in.steps << paths_log2) > 1024 || (1 << (paths_log2 - 1)) >= v.N)) --paths_log2;
+  const int64_t threads = (((int64_t)in.steps << paths_log2) + kWave - 1) / kWave * kWave;
+  const int64_t groups = (v.N + (1 << paths_log2) - 1) >> paths_log2;
+  auto* kernel = !h->indexed ? (q4 ? replay_append_kernel<false, false, 4> : replay_append_kernel<false, false, CSD_MAX_QUERY_LEN>)
+                 : v.eps == 0 ? (q4 ? replay_append_kernel<true, false, 4> : replay_append_kernel<true, false, CSD_MAX_QUERY_LEN>)
+                              : (q4 ? replay_append_kernel<true, true, 4> : replay_append_kernel<true, true, CSD_MAX_QUERY_LEN>);
+  kernel<<<(uint32_t)(v.P * groups), (uint32_t)(threads < 1024 ? threads : 1024), 0, st>>>(v, in, h->step_meta, paths_log2);
+  IndexView w = v;
+  w.meta_old = w.meta_new = h->step_meta;
+  if (!h->indexed) launch_replay_scan(w, in.steps, a, st);
+  else if (v.eps > 0) launch_replay_fuzzy(w, in.steps, a, st);
+  else if (a.pool_mode != CSD_POOL_DAG || v.options != 0) launch_replay_general(w, in.steps, a, st);
+  else launch_replay(w, in.steps, a, st);
+}
+
 // Host-side bounds on the paths' lengths as they were before a call: put back when the call's
 // launch fails, so that an error leaves the handle as it was.
 struct LengthBounds {
@@ -363,7 +405,9 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   h->view.eps = cfg->max_edits;
   h->view.options = (cfg->flags >> 2) & 3;
   h->alpha_q = to_alpha_q(cfg->alpha);
-  h->steps_per_launch = 1;
+  h->steps_per_launch = 0;
+  h->step_meta = reinterpret_cast<int32_t*>(base + l.step_meta);
+  h->replay_steps = l.replay_steps;
   rc = csd_reset(h, stream);
   if (rc != CSD_OK) {
     delete h;
@@ -494,6 +538,30 @@ int csd_replay(csd_index* h, int32_t n_steps, const int32_t* d_tokens, const flo
       h->len_lo += chunk;
       h->len_hi = h->len_hi + chunk > h->cfg.max_len ? h->cfg.max_len : h->len_hi + chunk;
       launch_multi(h->view, m, general, as_stream(stream));
+      rc = before.launched("csd_replay");
+      if (rc != CSD_OK) return rc;
+      h->cur ^= chunk & 1;
+      t += chunk;
+    }
+    return CSD_OK;
+  }
+  if (fused && h->steps_per_launch == 0 && h->replay_steps > 1 && n_steps > 1) {
+    for (int32_t t = 0; t < n_steps;) {
+      const int32_t chunk = n_steps - t < h->replay_steps ? n_steps - t : h->replay_steps;
+      const DraftArgs a{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode,
+                        d_draft_tokens + t * rows * L, d_draft_len + t * rows,
+                        d_token_scores ? d_token_scores + t * rows * L : nullptr,
+                        d_path_scores ? d_path_scores + t * rows : nullptr,
+                        d_targets ? d_targets + t * rows * L : nullptr,
+                        d_accept_len ? d_accept_len + t * rows : nullptr};
+      LengthBounds before(h);
+      for (int32_t s = 0; s < chunk; ++s) (void)note_append(h, false, 1);   // (there is room: checked above)
+      // (the ends alternate between their two buffers step by step, however many a launch takes)
+      IndexView v = h->view;
+      v.meta_old = h->meta[h->cur];
+      v.meta_new = h->meta[h->cur ^ (chunk & 1)];
+      launch_replay_steps(h, v, ReplayIn{d_tokens + t * rows, d_probs ? d_probs + t * rows : nullptr, chunk}, a,
+                          as_stream(stream));
       rc = before.launched("csd_replay");
       if (rc != CSD_OK) return rc;
       h->cur ^= chunk & 1;

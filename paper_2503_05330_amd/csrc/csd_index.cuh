@@ -351,19 +351,23 @@ struct NewTokens {
   float prob;
   int32_t G[QC > 0 ? QC : 1];
   __device__ __forceinline__ void load(const IndexView& ix, const StepIn& in, int64_t row, int32_t t_lane) {
-    const int32_t n = in.n;
-    const int32_t* st = in.tok + row * n;
+    load(ix, row, in.tok + row * in.n, in.prob ? in.prob + row * in.n : nullptr, 1, in.n,
+         in.counts ? in.counts + row : nullptr, t_lane);
+  }
+  // st, sp: the row's first new token and its probability (or null); `stride`: from one to the next
+  __device__ __forceinline__ void load(const IndexView& ix, int64_t row, const int32_t* st, const float* sp,
+                                       int64_t stride, int32_t n, const int32_t* count_of_row, int32_t t_lane) {
     const int32_t* meta = ix.meta_old + row * ix.meta_stride;
     t = t_lane;
     const int32_t tt = t < n ? t : 0;
-    token = st[tt];
-    prob = in.prob ? in.prob[row * n + tt] : 1.0f;
+    token = st[tt * stride];
+    prob = sp ? sp[tt * stride] : 1.0f;
 #pragma unroll
     for (int a = 0; a < QC; ++a) {
       const int32_t back = a < ix.kmax ? a : 0;            // (words beyond the gram are not used)
-      G[a] = *(tt > back ? st + (tt - 1 - back) : meta + 1 + (back - tt));
+      G[a] = *(tt > back ? st + (tt - 1 - back) * stride : meta + 1 + (back - tt));
     }
-    want = in.counts ? in.counts[row] : n;
+    want = count_of_row ? *count_of_row : n;
     offered = n;
     len = meta[0];
   }
@@ -378,10 +382,10 @@ struct NewTokens {
   }
   __device__ __forceinline__ int32_t pos(const IndexView& ix, int32_t i) const { return (i << ix.eshift) | (len + t); }
   // token and quantised probability to the history; returns the status bits to raise
-  __device__ __forceinline__ uint32_t store(const IndexView& ix, const StepIn& in, int64_t row, int32_t cnt) const {
+  __device__ __forceinline__ uint32_t store(const IndexView& ix, bool probs, int64_t row, int32_t cnt) const {
     if (!mine(cnt)) return 0u;
     ix.tok[row * ix.max_len + len + t] = token;
-    ix.pq[row * ix.max_len + len + t] = in.prob ? quantize_prob(prob) : 65536u;
+    ix.pq[row * ix.max_len + len + t] = probs ? quantize_prob(prob) : 65536u;
     return (token < 0 || token >= ix.vocab) ? CSD_STATUS_TOKEN_RANGE : 0u;
   }
 };
@@ -502,7 +506,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
     x.load(ix, in, row, t0 + lane);
     cnt = x.count(ix);
     if (head && tid == 0 && t0 == 0 && x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
-    flags |= x.store(ix, in, row, cnt);
+    flags |= x.store(ix, in.prob != nullptr, row, cnt);
     if constexpr (INDEX)
       file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane);
     if (head && t0 == 0) store_meta(ix, in, row, x.len, cnt, lane);

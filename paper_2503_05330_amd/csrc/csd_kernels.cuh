@@ -169,22 +169,11 @@ __device__ __forceinline__ void fetch_windows(LDS& s, const Ctx& c, int32_t M, i
 // does not run still costs it time).
 // QC: compile-time bound (4 or 8) of the query length: the comparison loops are unrolled to it.
 template <int QC, bool POOLS, bool FUZZY>
-__global__ __launch_bounds__(kScanBlock) void step_scan_kernel(IndexView ix, StepIn in,
-                                                               DraftArgs a, ScanSlices sl) {
+__device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in, const DraftArgs& a,
+                                          const ScanSlices& sl, int32_t row, int32_t slice) {
   constexpr int BLOCK = kScanBlock;
-  fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs) + sizeof(ScanSlices)>();
   __shared__ LdsScan s;
   __shared__ int32_t sh_base, sh_total, sh_last;
-  int32_t row, slice = 0;
-  if (sl.n == 1) {
-    row = xcd_row(ix.P * ix.N);
-  } else {                              // XCD x takes rows x, x + 8, ..: a row's slices share an L2
-    int32_t idx = (int32_t)(blockIdx.x >> 3);
-    slice = idx & (sl.n - 1);
-    row = (idx / sl.n) * 8 + (int32_t)(blockIdx.x & 7);
-    if (row >= ix.P * ix.N) row = -1;
-  }
-  if (row < 0) return;
   const int32_t unit = row * 8 + slice;                  // (timing build only)
   CSD_STAMP(unit, 0, CSD_CLOCK());
   CSD_STAMP(unit, 6, 0ull);
@@ -331,6 +320,23 @@ __global__ __launch_bounds__(kScanBlock) void step_scan_kernel(IndexView ix, Ste
     write_accept(a, row, o, target, c.tid);
   }
   CSD_STAMP(unit, 6, CSD_CLOCK());
+}
+
+template <int QC, bool POOLS, bool FUZZY>
+__global__ __launch_bounds__(kScanBlock) void step_scan_kernel(IndexView ix, StepIn in,
+                                                               DraftArgs a, ScanSlices sl) {
+  fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs) + sizeof(ScanSlices)>();
+  int32_t row, slice = 0;
+  if (sl.n == 1) {
+    row = xcd_row(ix.P * ix.N);
+  } else {                              // XCD x takes rows x, x + 8, ..: a row's slices share an L2
+    int32_t idx = (int32_t)(blockIdx.x >> 3);
+    slice = idx & (sl.n - 1);
+    row = (idx / sl.n) * 8 + (int32_t)(blockIdx.x & 7);
+    if (row >= ix.P * ix.N) row = -1;
+  }
+  if (row < 0) return;
+  scan_step<QC, POOLS, FUZZY>(ix, in, a, sl, row, slice);
 }
 
 // Index mode.  Per (problem, path) one wave64 runs the front end (matches with
@@ -629,6 +635,109 @@ __global__ __launch_bounds__(16 * kWave) void step_multi_kernel(IndexView ix, Mu
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   }
+}
+
+// A recorded trace (csd_replay): all tokens are known when the call is made, so its steps do not
+// wait for each other.  One launch appends the tokens of many steps and notes every path's end as
+// it is after each of them; a second one drafts all paths at all those steps side by side, each
+// from the ends of its own step: what lies beyond them in the histories and postings is not seen.
+// A launch per step leaves most of the chip idle and waits for its slowest row; this is bound by the
+// drafts a CU holds at once.  us for reset, append of the past and replay, a launch per step / this:
+// 16 paths x 1024 tokens, 64 steps 366 / 36; 64 x 4096, 48 steps 397 / 45; 64 problems of 16 x 1024,
+// 48 steps 504 / 116; 1024 problems, 24 steps 1477 / 691; one edit by scan, 16 x 1024, 32 steps
+// 622 / 61; one edit through the index, 64 x 4096, 24 steps 686 / 179.
+struct ReplayIn {
+  const int32_t* tok;           // [steps][P][N]
+  const float* prob;            // [steps][P][N] or null
+  int32_t steps;
+};
+
+// The append: a workgroup has 2^paths_log2 whole paths of a problem (so that the paths' ends can be
+// replaced in place: meta_new may be meta_old), a thread per new position; neighbouring threads
+// have neighbouring paths, whose tokens of a step lie side by side.
+// step_meta [steps][P][N][meta_stride]: the paths' ends after each step.
+template <bool INDEX, bool FUZZY, int QC>
+__global__ __launch_bounds__(1024) void replay_append_kernel(IndexView ix, ReplayIn in, int32_t* step_meta,
+                                                             int32_t paths_log2) {
+  const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
+  const int32_t paths = 1 << paths_log2, groups = (ix.N + paths - 1) >> paths_log2;
+  const int32_t p = (int32_t)blockIdx.x / groups, i0 = ((int32_t)blockIdx.x - p * groups) << paths_log2;
+  const int32_t i = i0 + (tid & (paths - 1)), at_once = (int32_t)blockDim.x >> paths_log2;
+  const bool on = i < ix.N;
+  const int64_t rows = (int64_t)ix.P * ix.N, row = (int64_t)p * ix.N + (on ? i : i0);
+  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
+  uint32_t flags = 0;
+  for (int32_t t0 = 0; t0 < in.steps; t0 += at_once) {   // uniform over the workgroup
+    const int32_t t = on ? t0 + (tid >> paths_log2) : in.steps;   // (idle: behind the last step)
+    NewTokens<QC> x;
+    x.load(ix, row, in.tok + row, in.prob ? in.prob + row : nullptr, rows, in.steps, nullptr, t);
+    const int32_t cnt = x.count(ix);
+    if (x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
+    flags |= x.store(ix, in.prob != nullptr, row, cnt);
+    if constexpr (INDEX)
+      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane);
+    if (t < in.steps) {
+      int32_t* end = step_meta + (t * rows + row) * ix.meta_stride;
+      end[0] = x.len + (t < cnt ? t + 1 : cnt);
+      for (int32_t a = ix.tail_len; a + 1 < ix.meta_stride; ++a) end[1 + a] = 0;
+      if (t < cnt) {
+        end[1] = x.token;
+#pragma unroll
+        for (int a = 0; a < QC; ++a)
+          if (a + 1 < ix.tail_len) end[2 + a] = x.G[a];
+      } else {                                           // the path was full before
+        const int32_t* meta = ix.meta_old + row * ix.meta_stride;
+        for (int32_t a = 0; a < ix.tail_len; ++a)
+          end[1 + a] = a < cnt ? in.tok[(cnt - 1 - a) * rows + row] : (a < x.len + cnt ? meta[1 + a - cnt] : 0);
+      }
+    }
+  }
+  __syncthreads();                                       // the old ends have been read, the new ones noted
+  for (int32_t x = tid; x < paths * ix.meta_stride; x += (int32_t)blockDim.x) {
+    const int32_t path = i0 + x / ix.meta_stride, w = x % ix.meta_stride;
+    if (path < ix.N) {
+      const int64_t r = (int64_t)p * ix.N + path;
+      ix.meta_new[r * ix.meta_stride + w] = step_meta[((in.steps - 1) * rows + r) * ix.meta_stride + w];
+    }
+  }
+  if (flags) atomicOr(ix.status, flags);
+}
+
+// Which (problem, step, path) a workgroup drafts: the steps of a problem lie together, so that an
+// XCD's L2 holds the problems that its workgroups are at.  Returns the row, or -1; ix and a become
+// those of the step.  (ix.meta_old: step_meta of the append.)
+__device__ __forceinline__ int32_t replay_unit(IndexView& ix, DraftArgs& a, int32_t steps) {
+  const int32_t unit = xcd_row(ix.P * ix.N * steps);
+  if (unit < 0) return -1;
+  const int32_t per_problem = ix.N * steps, p = unit / per_problem, rest = unit - p * per_problem;
+  const int32_t t = rest / ix.N, i = rest - t * ix.N;
+  const int64_t before = (int64_t)t * ix.P * ix.N;       // rows of the steps before
+  ix.meta_old += before * ix.meta_stride;
+  a.draft_tokens += before * a.L;
+  a.draft_len += before;
+  if (a.token_scores) a.token_scores += before * a.L;
+  if (a.path_scores) a.path_scores += before;
+  if (a.targets) {
+    a.targets += before * a.L;
+    a.accept_len += before;
+  }
+  return p * ix.N + i;
+}
+
+template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC>
+__global__ __launch_bounds__(kWave) void replay_wave_kernel(IndexView ix, int32_t steps, DraftArgs a) {
+  __shared__ LDS s;
+  const int32_t row = replay_unit(ix, a, steps);
+  if (row < 0) return;
+  row_step<LCAP, POOLS, LDS, FUZZY, QC, false>(s, ix, StepIn{nullptr, nullptr, nullptr, 0}, a, NoTail{}, row,
+                                               (int)threadIdx.x);
+}
+
+template <int QC, bool POOLS, bool FUZZY>
+__global__ __launch_bounds__(kScanBlock) void replay_scan_kernel(IndexView ix, int32_t steps, DraftArgs a) {
+  const int32_t row = replay_unit(ix, a, steps);
+  if (row < 0) return;
+  scan_step<QC, POOLS, FUZZY>(ix, StepIn{nullptr, nullptr, nullptr, 0}, a, ScanSlices{1, nullptr, nullptr}, row, 0);
 }
 
 static __global__ __launch_bounds__(256) void accept_kernel(int64_t rows, int32_t L,

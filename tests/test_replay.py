@@ -1,0 +1,107 @@
+"""csd_replay with its steps side by side against a launch per step (csd_set_steps_per_launch 1, the
+path that the other tests compare with the oracle): every output, the index left behind, status bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_05330_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("tokens", "length", "token_scores", "path_scores", "accept")
+
+
+def _same(a, b):
+    for key in KEYS:
+        x, y = a[key].cpu().numpy(), b[key].cpu().numpy()
+        assert np.array_equal(x.view(np.int32), y.view(np.int32)), key
+
+
+# paths around the 16 of a workgroup and a wave; steps around a workgroup's threads; several launches
+# (2^19 drafts each); options, pools and matchers; one and several problems
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,edits,flags,pool", [
+    (1, 16, 300, 3, 3, 8, 0, binding.MATCH_AUTO, 0),
+    (1, 17, 200, 65, 4, 10, 0, binding.MATCH_AUTO, 0),
+    (1, 1, 90, 70, 2, 4, 0, binding.MATCH_AUTO | binding.INCLUDE_SELF, 0),
+    (3, 5, 1300, 1100, 3, 8, 0, binding.MATCH_AUTO, 0),
+    (1, 66, 150, 64, 6, 32, 0, binding.MATCH_AUTO, 0),
+    (7, 64, 130, 33, 2, 16, 0, binding.MATCH_AUTO, 0),
+    (300, 30, 128, 66, 3, 8, 0, binding.MATCH_AUTO, 0),
+    (2, 9, 200, 40, 3, 6, 0, binding.MATCH_SCAN, 0),
+    (1, 16, 300, 32, 3, 8, 1, binding.MATCH_AUTO, 0),
+    (2, 20, 300, 31, 4, 10, 1, binding.MATCH_INDEX, 0),
+    (1, 6, 120, 50, 5, 17, 1, binding.MATCH_INDEX, 0),
+    (1, 5, 100, 20, 3, 5, 2, binding.MATCH_AUTO, 0),
+    (2, 13, 200, 30, 3, 7, 0, binding.MATCH_AUTO, 1),
+    (2, 13, 200, 31, 3, 7, 1, binding.MATCH_AUTO, 2),
+    (1, 8, 150, 30, 4, 6, 0, binding.MATCH_AUTO | binding.QUERY_BACKOFF, 0),
+    (1, 8, 150, 30, 4, 6, 0, binding.MATCH_INDEX | binding.QUERY_BACKOFF | binding.INCLUDE_SELF, 2),
+])
+@pytest.mark.parametrize("start", ("empty", "ragged", "full"))
+def test_steps_side_by_side(problems, paths, max_len, steps, query, draft, edits, flags, pool, start):
+    rng = np.random.default_rng(problems * 100 + paths + steps + query)
+    print("replay", problems, paths, max_len, steps, query, draft, edits, flags, pool, start, flush=True)
+    dev, V, T = torch.device("cuda:0"), 60, max_len
+    tokens = rng.integers(0, V, size=(problems, paths, T)).astype(np.int32)
+    motif = np.tile(rng.integers(0, V, size=(problems, 1, 50)).astype(np.int32), (1, 1, T // 50 + 1))[:, :, :T]
+    tokens = np.where(np.repeat(rng.random((problems, paths, T // 10 + 1)) < 0.5, 10, axis=2)[:, :, :T], motif, tokens)
+    probs = rng.random(tokens.shape).astype(np.float32)
+    counts = {"empty": np.zeros((problems, paths)), "ragged": rng.integers(0, T - steps, size=(problems, paths)),
+              # some paths full before the first step, some during the replay
+              "full": rng.integers(max(0, T - 2 * steps), T + 1, size=(problems, paths))}[start].astype(np.int32)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    later = (T // 3 + np.arange(steps + 1)) % T
+    d_tok, d_probs = put(tokens[:, :, later].transpose(2, 0, 1)), put(probs[:, :, later].transpose(2, 0, 1))
+    targets = rng.integers(0, V, size=(steps, problems, paths, draft)).astype(np.int32)
+    got = []
+    for per_launch in (0, 1):
+        ix = binding.Index(problems, paths, T, V, query, draft, 0.6, 0, flags, device=dev, max_edits=edits, pool_mode=pool)
+        if start != "empty":                              # (counts: the library does not know the lengths)
+            ix.append(put(tokens), put(probs), put(counts), T)
+        if per_launch:
+            ix.set_steps_per_launch(per_launch)
+        use_probs = d_probs[:steps].contiguous() if steps % 2 else None
+        out = ix.replay(steps, d_tok[:steps], use_probs, query, draft, targets=put(targets))
+        # the length of the drafts that the index now holds the basis for, and one step more
+        after = ix.draft(query, draft)
+        more = ix.step(d_tok[steps], None, torch.ones((problems, paths), dtype=torch.int32, device=dev), 1, query, draft)
+        got.append((out, after, more, ix.dump_matches(query, cap=1 << 23) if problems * paths < 500 else None, ix.status()))
+    (a, b, c, d, e), (a1, b1, c1, d1, e1) = got
+    _same(a, a1)
+    for x, y in ((b, b1), (c, c1)):
+        for key in KEYS[:4]:
+            assert torch.equal(x[key], y[key]), key
+    if d is not None:
+        assert np.array_equal(d[0], d1[0]) and np.array_equal(d[1], d1[1])
+    assert e == e1 and (e == 0 or start == "full")
+    assert int(a["length"].sum()) > 0 or start == "empty"
+
+
+def test_a_captured_replay_goes_on_from_where_it_was():
+    """An even number of steps leaves the paths' ends where it found them: a captured replay, run
+    again and again with other work between, appends again each time."""
+    rng = np.random.default_rng(3)
+    dev, P, N, T, V, S, k, L = torch.device("cuda:0"), 2, 6, 400, 30, 8, 3, 8
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    tokens = rng.integers(0, V, size=(5, S, P, N)).astype(np.int32)
+    past = put(rng.integers(0, V, size=(P, N, 300)).astype(np.int32))
+    by_graph, by_call = (binding.Index(P, N, T, V, k, L, device=dev) for _ in range(2))
+    by_call.set_steps_per_launch(1)
+    fed = put(tokens[0])
+    out = by_graph._outputs(L, True, lead=(S,))
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        by_graph.append(past)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            by_graph.replay(S, fed, None, k, L, out=out)
+    by_call.append(past)
+    for turn in range(5):
+        fed.copy_(put(tokens[turn]))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = by_call.replay(S, put(tokens[turn]), None, k, L)
+        for key in KEYS[:4]:
+            assert torch.equal(out[key], want[key]), (turn, key)
