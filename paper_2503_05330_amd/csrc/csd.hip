@@ -63,7 +63,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t tok, pq, meta, status, gram, slices, step_meta, total;
+  size_t tok, pq, meta, status, gram, slices, step_meta, rest, rest_list, total;
   int32_t n_slices;             // workgroups that share a row's scan (scan mode, few rows)
   int32_t replay_steps;         // steps of a replay that run side by side
   int32_t meta_stride, eshift;
@@ -71,9 +71,10 @@ struct Layout {
   size_t gram_words;
 };
 
-// Drafts of a replay that run side by side at most (a chip full of workgroups many times over;
-// their paths' ends take 8 to 25 MB).
+// Drafts of a replay that run side by side at most (a chip full of workgroups many times over), and
+// the share of a path's tokens: their notes then take a fifth of the histories and their index.
 constexpr int64_t kReplayDrafts = 1 << 19;
+constexpr int32_t kReplayShare = 4, kReplayFewSteps = 16;
 // ... and with a larger vocabulary than this a layer of the DAG may not fit the tables of the layout
 // that a launch of many drafts uses, though it fits the one of a launch per step: that one runs then.
 constexpr int32_t kReplayVocab = 1 << 24;
@@ -171,11 +172,17 @@ Layout make_layout(const csd_config* c) {
   }
   // the paths' ends after each step of a replay, for as many steps as give kReplayDrafts drafts
   l.replay_steps = 0;
-  l.step_meta = at;
+  l.step_meta = l.rest = l.rest_list = at;
   if (c->vocab <= kReplayVocab) {
-    const int64_t most = kReplayDrafts / (int64_t)rows;
-    l.replay_steps = (int32_t)(most < c->max_len ? most : c->max_len);
+    int64_t most = c->max_len / kReplayShare;
+    most = most > kReplayFewSteps ? most : kReplayFewSteps;
+    most = most < c->max_len ? most : c->max_len;
+    l.replay_steps = (int32_t)(most < kReplayDrafts / (int64_t)rows ? most : kReplayDrafts / (int64_t)rows);
     at += align_up((size_t)l.replay_steps * rows * l.meta_stride * sizeof(int32_t));
+    l.rest = at;
+    at += align_up(((size_t)l.replay_steps * rows / kQuadRows + 1) * sizeof(u64));
+    l.rest_list = at;
+    at += align_up(((size_t)l.replay_steps * rows + 1) * sizeof(int32_t));
   }
   l.total = at;
   return l;
@@ -208,6 +215,8 @@ struct csd_index {
   int32_t steps_per_launch;     // csd_replay / csd_accept_loop: steps one launch runs (1: a launch per step;
                                 //   0: not set, a replay's steps run side by side)
   int32_t* step_meta;           // [replay_steps][P][N][meta_stride] see replay_append_kernel
+  u64* rest;                    // [replay_steps * P * N / 16 + 1] see replay_quad_kernel
+  int32_t* rest_list;           // [1 + replay_steps * P * N] see RestList
   int32_t replay_steps;
 };
 
@@ -304,22 +313,25 @@ void launch_append(const csd_index* h, const IndexView& v, const StepIn& in, boo
 void launch_replay_steps(const csd_index* h, const IndexView& v, const ReplayIn& in, const DraftArgs& a,
                          hipStream_t st) {
   const bool q4 = v.kmax <= 4;
-  // whole paths per workgroup: as many as its 1024 threads have steps for, at most 16 (a line of
-  // tokens per step) and no more than there are
+  // whole paths per workgroup: as many as its threads have steps for, at most 16 (a line of
+  // tokens per step) and no more than there are (16 paths x 64 steps as one workgroup of 1024
+  // threads 11 us, as four of 256 6.4, as sixteen of 64 6.4; 1024 problems x 24 steps 40 / 37 / 40)
+  constexpr int32_t kReplayBlock = 256;
   int32_t paths_log2 = 4;
-  while (paths_log2 > 0 && (((int64_t)in.steps << paths_log2) > 1024 || (1 << (paths_log2 - 1)) >= v.N)) --paths_log2;
+  while (paths_log2 > 0 && (((int64_t)in.steps << paths_log2) > kReplayBlock || (1 << (paths_log2 - 1)) >= v.N)) --paths_log2;
   const int64_t threads = (((int64_t)in.steps << paths_log2) + kWave - 1) / kWave * kWave;
   const int64_t groups = (v.N + (1 << paths_log2) - 1) >> paths_log2;
   auto* kernel = !h->indexed ? (q4 ? replay_append_kernel<false, false, 4> : replay_append_kernel<false, false, CSD_MAX_QUERY_LEN>)
                  : v.eps == 0 ? (q4 ? replay_append_kernel<true, false, 4> : replay_append_kernel<true, false, CSD_MAX_QUERY_LEN>)
                               : (q4 ? replay_append_kernel<true, true, 4> : replay_append_kernel<true, true, CSD_MAX_QUERY_LEN>);
-  kernel<<<(uint32_t)(v.P * groups), (uint32_t)(threads < 1024 ? threads : 1024), 0, st>>>(v, in, h->step_meta, paths_log2);
+  kernel<<<(uint32_t)(v.P * groups), (uint32_t)(threads < kReplayBlock ? threads : kReplayBlock), 0, st>>>(v, in, h->step_meta, paths_log2,
+                                                                                          h->rest_list);
   IndexView w = v;
   w.meta_old = w.meta_new = h->step_meta;
   if (!h->indexed) launch_replay_scan(w, in.steps, a, st);
   else if (v.eps > 0) launch_replay_fuzzy(w, in.steps, a, st);
   else if (a.pool_mode != CSD_POOL_DAG || v.options != 0) launch_replay_general(w, in.steps, a, st);
-  else launch_replay(w, in.steps, a, st);
+  else launch_replay(w, in.steps, a, h->rest, RestList{h->rest_list, h->rest_list + 1}, st);
 }
 
 // Host-side bounds on the paths' lengths as they were before a call: put back when the call's
@@ -407,6 +419,8 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   h->alpha_q = to_alpha_q(cfg->alpha);
   h->steps_per_launch = 0;
   h->step_meta = reinterpret_cast<int32_t*>(base + l.step_meta);
+  h->rest = reinterpret_cast<u64*>(base + l.rest);
+  h->rest_list = reinterpret_cast<int32_t*>(base + l.rest_list);
   h->replay_steps = l.replay_steps;
   rc = csd_reset(h, stream);
   if (rc != CSD_OK) {

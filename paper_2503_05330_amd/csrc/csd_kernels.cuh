@@ -8,6 +8,7 @@
 #include "csd_dag.cuh"
 #include "csd_index.cuh"
 #include "csd_match.cuh"
+#include "csd_quad.cuh"
 
 namespace csd {
 
@@ -657,8 +658,9 @@ struct ReplayIn {
 // have neighbouring paths, whose tokens of a step lie side by side.
 // step_meta [steps][P][N][meta_stride]: the paths' ends after each step.
 template <bool INDEX, bool FUZZY, int QC>
-__global__ __launch_bounds__(1024) void replay_append_kernel(IndexView ix, ReplayIn in, int32_t* step_meta,
-                                                             int32_t paths_log2) {
+__global__ __launch_bounds__(256) void replay_append_kernel(IndexView ix, ReplayIn in, int32_t* step_meta,
+                                                             int32_t paths_log2, int32_t* rest_count) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *rest_count = 0;   // (of the drafts' launches behind this one)
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t paths = 1 << paths_log2, groups = (ix.N + paths - 1) >> paths_log2;
   const int32_t p = (int32_t)blockIdx.x / groups, i0 = ((int32_t)blockIdx.x - p * groups) << paths_log2;
@@ -706,8 +708,7 @@ __global__ __launch_bounds__(1024) void replay_append_kernel(IndexView ix, Repla
 // Which (problem, step, path) a workgroup drafts: the steps of a problem lie together, so that an
 // XCD's L2 holds the problems that its workgroups are at.  Returns the row, or -1; ix and a become
 // those of the step.  (ix.meta_old: step_meta of the append.)
-__device__ __forceinline__ int32_t replay_unit(IndexView& ix, DraftArgs& a, int32_t steps) {
-  const int32_t unit = xcd_row(ix.P * ix.N * steps);
+__device__ __forceinline__ int32_t replay_unit(IndexView& ix, DraftArgs& a, int32_t steps, int32_t unit) {
   if (unit < 0) return -1;
   const int32_t per_problem = ix.N * steps, p = unit / per_problem, rest = unit - p * per_problem;
   const int32_t t = rest / ix.N, i = rest - t * ix.N;
@@ -727,15 +728,30 @@ __device__ __forceinline__ int32_t replay_unit(IndexView& ix, DraftArgs& a, int3
 template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC>
 __global__ __launch_bounds__(kWave) void replay_wave_kernel(IndexView ix, int32_t steps, DraftArgs a) {
   __shared__ LDS s;
-  const int32_t row = replay_unit(ix, a, steps);
+  const int32_t row = replay_unit(ix, a, steps, xcd_row(ix.P * ix.N * steps));
   if (row < 0) return;
   row_step<LCAP, POOLS, LDS, FUZZY, QC, false>(s, ix, StepIn{nullptr, nullptr, nullptr, 0}, a, NoTail{}, row,
                                                (int)threadIdx.x);
 }
 
+// The rows that are left to a wave of their own.
+template <int LCAP, class LDS, int QC>
+__global__ __launch_bounds__(kWave) void replay_rest_kernel(IndexView ix, int32_t steps, DraftArgs a, RestList list) {
+  __shared__ LDS s;
+  const int32_t count = *list.count;
+  for (int32_t x = (int32_t)blockIdx.x; x < count; x += (int32_t)gridDim.x) {
+    IndexView v = ix;
+    DraftArgs b = a;
+    const int32_t row = replay_unit(v, b, steps, list.units[x]);
+    row_step<LCAP, false, LDS, false, QC, false>(s, v, StepIn{nullptr, nullptr, nullptr, 0}, b, NoTail{}, row,
+                                                 (int)threadIdx.x);
+    block_sync<kWave>();
+  }
+}
+
 template <int QC, bool POOLS, bool FUZZY>
 __global__ __launch_bounds__(kScanBlock) void replay_scan_kernel(IndexView ix, int32_t steps, DraftArgs a) {
-  const int32_t row = replay_unit(ix, a, steps);
+  const int32_t row = replay_unit(ix, a, steps, xcd_row(ix.P * ix.N * steps));
   if (row < 0) return;
   scan_step<QC, POOLS, FUZZY>(ix, StepIn{nullptr, nullptr, nullptr, 0}, a, ScanSlices{1, nullptr, nullptr}, row, 0);
 }

@@ -1,0 +1,369 @@
+// csd — drafts of rows with few matches, four or eight lanes per row: for launches of many
+// thousand drafts (a replay's steps side by side), which are bound by the instructions that all
+// rows issue.
+#pragma once
+
+#include "csd_common.cuh"
+#include "csd_index.cuh"
+
+namespace csd {
+
+constexpr int kQuadRows = kWave / 4;   // rows of a wave with a quad of lanes each
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// x of lane ^ R, for the other lanes of a group of G = 4 or 8: R = 1 .. G - 1
+template <int G, int R>
+__device__ __forceinline__ uint32_t group_other(uint32_t x) {
+  static_assert((G == 4 || G == 8) && R >= 1 && R < G, "a quad or half a DPP row");
+  constexpr int kFlip = R < 4 ? R : 7 - R;               // within a quad; R >= 4: behind the half row's mirror (^ 7)
+  constexpr int kQuad = kFlip == 1 ? 0xB1 : kFlip == 2 ? 0x4E : 0x1B;
+  if constexpr (R >= 4) x = dpp_move<0x141>(x);
+  return kFlip == 0 ? x : dpp_move<kQuad>(x);
+}
+// f(R) for lanes R apart, so that every lane of the group ends with what all of them have, for
+// operations that may meet a value twice
+template <int G, class F>
+__device__ __forceinline__ void group_stages(F&& f) {
+  f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{});
+  if constexpr (G == 8) f(std::integral_constant<int, 7>{});
+}
+
+struct __attribute__((packed, aligned(4))) Run4 { int32_t x[4]; };   // four words at any of them
+
+// The draft of a lane's unit (see replay_unit): where its data lies.
+struct UnitRow {
+  int32_t i, row, first;        // path; row among all steps' rows; the problem's first row at this step
+  const int32_t *tok, *lens;    // the problem's histories; its paths' ends at this step
+  const uint32_t* pq;
+  int64_t buckets;              // the problem's first bucket
+  __device__ __forceinline__ UnitRow(const IndexView& ix, uint32_t steps, uint32_t unit) {
+    const uint32_t N = (uint32_t)ix.N;
+    const uint32_t p = unit / (N * steps), in_problem = unit - p * (N * steps), t = in_problem / N;
+    i = (int32_t)(in_problem - t * N);
+    first = (int32_t)(t * (uint32_t)ix.P * N + p * N);
+    row = first + i;
+    const int64_t cells = (int64_t)(p * N) * ix.max_len;
+    tok = ix.tok + cells;
+    pq = ix.pq + cells;
+    lens = ix.meta_old + (int64_t)first * ix.meta_stride;
+    buckets = (int64_t)p * ((int64_t)ix.bucket_mask + 1);
+  }
+  // the path's length and newest tokens (newest first)
+  template <int QC>
+  __device__ __forceinline__ int32_t end(const IndexView& ix, int32_t (&Q)[QC]) const {
+    const int32_t* meta = lens + i * ix.meta_stride;
+    const int4 m0 = *reinterpret_cast<const int4*>(meta);
+    const int4 m1 = QC > 3 ? *reinterpret_cast<const int4*>(meta + (ix.kmax > 3 ? 4 : 0)) : int4{0, 0, 0, 0};
+    const int32_t tail[8] = {m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w, QC > 7 ? meta[ix.kmax > 7 ? 8 : 0] : 0};
+#pragma unroll
+    for (int x = 0; x < QC; ++x) Q[x] = tail[x];
+    return m0.x;
+  }
+};
+
+template <int QC>
+__device__ __forceinline__ GramHash gram_hash_of(const int32_t (&Q)[QC], int32_t kmax) {
+  uint32_t acc = kGramSeed;
+#pragma unroll
+  for (int x = 0; x < QC; ++x)
+    if (x < kmax) acc = gram_hash_add(acc, Q[x]);
+  return gram_hash_end(acc, kmax);
+}
+
+// A posting of a bucket: what it takes to verify it, loaded without a branch (an idle one reads the
+// problem's first cell).
+template <int QC>
+struct Posting {
+  bool cand;
+  int32_t e, len, gram[QC];
+  __device__ __forceinline__ void load(const IndexView& ix, const UnitRow& u, bool is_one, int32_t word) {
+    const int32_t j = word >> ix.eshift;
+    e = word & ((1 << ix.eshift) - 1);
+    cand = is_one && word >= 0 && j != u.i && j < ix.N;
+    len = u.lens[cand ? j * ix.meta_stride : 0];
+    const int32_t* at = u.tok + (cand ? (int32_t)__umul24((uint32_t)j, (uint32_t)ix.max_len) + e - ix.kmax : 0);
+#pragma unroll
+    for (int y = 0; y < QC; y += 4) {
+      const Run4 r = *reinterpret_cast<const Run4*>(at + y);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) gram[y + z] = r.x[z];
+    }
+  }
+  // (several postings' loads are in flight before the first is looked at: left to itself the
+  // compiler loads behind the comparisons)
+  __device__ __forceinline__ void arrive() {
+    consume_here(len);
+#pragma unroll
+    for (int y = 0; y < QC; ++y) consume_here(gram[y]);
+  }
+  __device__ __forceinline__ bool hit(const int32_t (&Q)[QC], int32_t kmax) const {
+    int32_t differ = 0;                                  // gram: oldest token first
+#pragma unroll
+    for (int y = 0; y < QC; ++y) differ |= y < kmax ? gram[y] ^ pick(Q, kmax - 1 - y) : 0;
+    return cand && e < len && differ == 0;
+  }
+  // position and layers that the match reaches, in one word
+  __device__ __forceinline__ uint32_t packed(int32_t word, int32_t L) const {
+    return (uint32_t)word | (uint32_t)(len - e < L ? len - e : L) << 25;
+  }
+};
+
+// The row's draft from its matches, one per lane of its group (`match`: as packed above; 0: none):
+// continuations into registers, then layer by layer Eq. 5's sums and the greedy rule (as in
+// walk_instances) by exchanges within the group, and the outputs of the rows with `write`.
+template <int G, int LCAP>
+__device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
+                                            bool write, int sub, const int32_t (&target)[(LCAP + G - 1) / G]) {
+  constexpr int kKept = (LCAP + G - 1) / G;              // layers whose choice a lane keeps and writes
+  constexpr int kCount = 24;                             // count (<= 8) above the probability sum (<= 2^19)
+  const int32_t L = a.L, rem = (int32_t)(match >> 25);
+  int32_t v[LCAP], pr[LCAP];
+  {
+    const int32_t pos = (int32_t)(match & ((1u << 25) - 1u));
+    const int32_t cell = (int32_t)__umul24((uint32_t)(pos >> ix.eshift), (uint32_t)ix.max_len) +
+                         (pos & ((1 << ix.eshift) - 1));
+#pragma unroll
+    for (int d = 0; d < LCAP; d += 4) {
+      const Run4 r = *reinterpret_cast<const Run4*>(u.tok + cell + d);
+      const Run4 s = *reinterpret_cast<const Run4*>(u.pq + cell + d);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        v[d + z] = r.x[z];
+        pr[d + z] = s.x[z];
+      }
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < LCAP; ++d) {
+    consume_here(v[d]);
+    consume_here(pr[d]);
+  }
+  int32_t kept_tok[kKept], n = 0, cur = 0;
+  u64 kept_key[kKept], key_sum = 0;
+#pragma unroll
+  for (int x = 0; x < kKept; ++x) {
+    kept_tok[x] = -1;
+    kept_key[x] = 0;
+  }
+  bool going = write;                                    // the same in a group's lanes
+  static_for<1, LCAP + 1>([&](auto layer) {
+    constexpr int d = layer();
+    if (d > L || wave_ballot(going) == 0) return;        // uniform over the wave
+    const bool alive = d <= rem;
+    const uint32_t vd = (uint32_t)v[d - 1], ud = d > 1 ? (uint32_t)v[d > 1 ? d - 2 : 0] : 0u;
+    const bool from_cur = alive && going && (d == 1 || (int32_t)ud == cur);
+    // the lanes with the same token (score_mode 1: with the same predecessor too)
+    const uint32_t own = alive ? (1u << kCount) + (uint32_t)pr[d - 1] : 0u;
+    uint32_t cs = own;
+    // (the moves are made before the comparisons: in a lane that a condition rules out, a move
+    // delivers nothing to the others)
+    const bool by_edge = a.score_mode != 0 && d > 1;     // uniform over the launch
+    static_for<1, G>([&](auto r) {
+      const uint32_t other_v = group_other<G, r()>(vd), other = group_other<G, r()>(own);
+      bool same_node = other_v == vd;
+      if (by_edge) {
+        const uint32_t other_u = group_other<G, r()>(ud);
+        same_node = same_node && other_u == ud;
+      }
+      cs += same_node ? other : 0u;
+    });
+    Cand best = cand_none();
+    if (from_cur) best = Cand{weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q), (int32_t)vd};
+    group_stages<G>([&](auto r) {
+      const uint32_t lo = group_other<G, r()>((uint32_t)best.key), hi = group_other<G, r()>((uint32_t)(best.key >> 32));
+      const uint32_t tv = group_other<G, r()>((uint32_t)best.v);
+      best = cand_best(best, Cand{((u64)hi << 32) | lo, (int32_t)tv});
+    });
+    going = going && best.v != INT_MAX;                  // else a leaf: no edge leaves cur
+    cur = best.v;
+    n = going ? d : n;
+    key_sum += going ? best.key : 0ull;
+    const bool keep = going && sub == (d - 1) / kKept;
+    kept_tok[(d - 1) % kKept] = keep ? best.v : kept_tok[(d - 1) % kKept];
+    kept_key[(d - 1) % kKept] = keep ? best.key : kept_key[(d - 1) % kKept];
+  });
+  int32_t same = 0;                                      // of this lane's layers, from its first on
+  bool all = true;
+#pragma unroll
+  for (int x = 0; x < kKept; ++x) {
+    const int32_t d = sub * kKept + x;
+    all = all && d < n && target[x] == kept_tok[x];
+    same += all ? 1 : 0;
+    if (write && d < L) {
+      a.draft_tokens[(int64_t)u.row * L + d] = kept_tok[x];
+      if (a.token_scores) a.token_scores[(int64_t)u.row * L + d] = key_to_score(kept_key[x]);
+    }
+  }
+  if (a.targets) {                                       // the first layer that differs
+    uint32_t stop = all ? (uint32_t)LCAP : (uint32_t)(sub * kKept + same);
+    group_stages<G>([&](auto r) {
+      const uint32_t other = group_other<G, r()>(stop);
+      stop = other < stop ? other : stop;
+    });
+    if (write && sub == 0) a.accept_len[u.row] = (int32_t)stop < n ? (int32_t)stop : n;
+  }
+  if (write && sub == 0) {
+    a.draft_len[u.row] = n;
+    if (a.path_scores) a.path_scores[u.row] = key_to_score(key_sum);
+  }
+}
+
+// The targets of the layers that this lane keeps.
+template <int G, int LCAP>
+__device__ __forceinline__ void load_targets(const DraftArgs& a, const UnitRow& u, int sub,
+                                             int32_t (&target)[(LCAP + G - 1) / G]) {
+  constexpr int kKept = (LCAP + G - 1) / G;
+#pragma unroll
+  for (int x = 0; x < kKept; ++x) {
+    const int32_t d = sub * kKept + x;
+    target[x] = a.targets ? a.targets[(int64_t)u.row * a.L + (d < a.L ? d : 0)] : 0;
+  }
+}
+
+// The first of this wave's `per_wave` units: XCD x takes a contiguous range of the units.
+__device__ __forceinline__ uint32_t wave_units(uint32_t per_wave) {
+  const uint32_t block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  return (block * (blockDim.x / kWave) + (threadIdx.x >> 6)) * per_wave;
+}
+
+// One draft per quad of lanes, sixteen per wave: exact matching through the index, DAG pool, query
+// of kmax tokens.  A lane takes four words of the row's first bucket, verifies its postings against
+// the histories, and the row's matches (at most four) go to a lane each.  No tables, no loop over
+// matches, and a wave's scalar instructions are shared by sixteen rows: with a wave per row those
+// kept the scalar unit busiest (539 scalar and 350 vector instructions a row; here 20 and 54).
+// What is left: four dependent round trips, whose loads gather 64 lines each.  Rows whose bucket is full (their chain may
+// go on), that have more than four matches or fewer tokens than a gram are left to the next
+// kernel: bit 4 r of rest[w] is row r of wave w.  (A list of them with one counter took 12 ns per
+// wave, the rate of atomics on one address, and its order spread a problem's rows over all L2s.)
+// ix.meta_old and a are those of the first step.
+template <int LCAP, int QC>
+__global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t steps, DraftArgs a, u64* rest) {
+  __shared__ uint32_t found[256];                        // [row of the workgroup][4] matches
+  const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), sub = tid & 3;
+  const uint32_t unit = wave_units(kQuadRows) + (uint32_t)(lane >> 2);
+  const bool on = unit < (uint32_t)(ix.P * ix.N * steps);
+  const UnitRow u(ix, (uint32_t)steps, on ? unit : 0u);
+  // ---- round trip 1: the path's end
+  int32_t Q[QC], target[LCAP / 4];
+  const int32_t len = u.end(ix, Q);
+  load_targets<4, LCAP>(a, u, sub, target);
+  // ---- round trip 2: the first bucket of the query
+  const int64_t bucket = u.buckets + (gram_hash_of(Q, ix.kmax).h & ix.bucket_mask);
+  const int4 w4 = *reinterpret_cast<const int4*>(ix.gram + bucket * kBucketWords + 4 * sub);
+  const int32_t word[4] = {w4.x, w4.y, w4.z, w4.w};
+  const int32_t count = (int32_t)dpp_move<0x00>((uint32_t)word[0]);
+  bool leave = len < ix.kmax || count >= kBucketSlots;   // to the next kernel
+  // ---- round trip 3: every posting's gram and its path's length
+  Posting<QC> post[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    const int32_t slot = 4 * sub + x - 1;
+    post[x].load(ix, u, !leave && slot >= 0 && slot < count, word[x]);
+  }
+  uint32_t hits = 0;
+#pragma unroll
+  for (int x = 0; x < 4; ++x) post[x].arrive();
+#pragma unroll
+  for (int x = 0; x < 4; ++x) hits |= post[x].hit(Q, ix.kmax) ? 1u << x : 0u;
+  // the row's matches, one per lane
+  const uint32_t mine = __popc(hits);
+  const uint32_t n0 = dpp_move<0x00>(mine), n1 = dpp_move<0x55>(mine), n2 = dpp_move<0xAA>(mine), n3 = dpp_move<0xFF>(mine);
+  const int32_t M = (int32_t)(n0 + n1 + n2 + n3);
+  leave = leave || M > 4;
+  uint32_t to = (sub > 0 ? n0 : 0u) + (sub > 1 ? n1 : 0u) + (sub > 2 ? n2 : 0u);
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+    if (hits >> x & 1u) {
+      if (to < 4) found[(tid & ~3) + to] = post[x].packed(word[x], a.L);
+      ++to;
+    }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (a row's lanes are of one wave)
+  // ---- round trip 4: the matches' continuations; walk, outputs
+  group_draft<4, LCAP>(ix, a, u, !leave && sub < M ? found[tid] : 0u, on && !leave, sub, target);
+  const u64 left = wave_ballot(on && leave && sub == 0);
+  if (lane == 0 && on) rest[unit / kQuadRows] = left;
+}
+
+// Rows for the kernel with a wave per row: their number and their units.
+struct RestList {
+  int32_t* count;
+  int32_t* units;
+};
+
+// The same with eight lanes per row, for the rows that replay_quad_kernel has left: the first
+// buckets of the query's chain, up to eight matches.  A wave takes the rows that one wave of that
+// kernel has left, eight at a time (a turn is a chain of four to eight round trips, 7 to 15 us: with
+// the rows of four waves there were more turns in a row, 64 problems x 48 steps 35 us instead of
+// 21), and a workgroup lists the rows with more matches or a longer chain for the kernel with a
+// wave per row (one reservation: atomics on one address take 12 ns each).
+constexpr uint32_t kLongChain = 3;     // buckets after which the wave per row, which reads four at once, takes over
+template <int LCAP, int QC>
+__global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
+                                                           RestList list) {
+  constexpr int G = 8, kWaves = 4, kRows = kQuadRows;
+  __shared__ uint32_t found_all[kWaves][kWave];          // [row of the turn][8] matches
+  __shared__ uint8_t todo_all[kWaves][kRows], left[kWaves * kRows];
+  __shared__ int32_t n_left, list_at;
+  const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x >> 6, sub = lane & (G - 1);
+  uint32_t* found = found_all[wave];
+  uint8_t* todo = todo_all[wave];
+  const uint32_t units = (uint32_t)(ix.P * ix.N * steps), first = wave_units(kRows);
+  // the rows' numbers, one after the other
+  const u64 rows = first < units ? rest[first / kQuadRows] : 0ull;     // the same in every lane
+  const uint32_t total = (uint32_t)__popcll(rows);
+  if (rows >> lane & 1ull) todo[__popcll(rows & ((1ull << lane) - 1ull))] = (uint8_t)(lane >> 2);
+  if (threadIdx.x == 0) n_left = 0;
+  __syncthreads();
+  for (uint32_t turn = 0; turn < total; turn += kWave / G) {   // uniform over the wave
+    const uint32_t nth = turn + (uint32_t)(lane / G);
+    const bool on = nth < total;
+    const uint32_t which = todo[on ? nth : turn];
+    const UnitRow u(ix, (uint32_t)steps, first + which);
+    int32_t Q[QC], target[(LCAP + G - 1) / G];
+    const int32_t len = u.end(ix, Q);
+    load_targets<G, LCAP>(a, u, sub, target);
+    const GramHash gh = gram_hash_of(Q, ix.kmax);
+    bool leave = len < ix.kmax;
+    int32_t M = 0;
+    bool looking = on && !leave;                         // the same in a group's lanes
+    for (uint32_t r = 0; wave_ballot(looking) != 0; ++r) {   // uniform over the wave
+      const int64_t bucket = u.buckets + ((gh.h + r * gh.step) & ix.bucket_mask);
+      const int2 w = *reinterpret_cast<const int2*>(ix.gram + bucket * kBucketWords + 2 * sub);
+      const int32_t word[2] = {w.x, w.y}, count = __shfl(w.x, lane & ~(G - 1));
+      Posting<QC> post[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const int32_t slot = 2 * sub + x - 1;
+        post[x].load(ix, u, looking && slot >= 0 && slot < count, word[x]);
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) post[x].arrive();
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const bool hit = post[x].hit(Q, ix.kmax);
+        const uint32_t hits = (uint32_t)(wave_ballot(hit) >> (lane & ~(G - 1))) & ((1u << G) - 1u);
+        const int32_t to = M + (int32_t)__popc(hits & ((1u << sub) - 1u));
+        if (hit && to < G) found[(lane & ~(G - 1)) + to] = post[x].packed(word[x], a.L);
+        M += (int32_t)__popc(hits);
+      }
+      const bool goes_on = count >= kBucketSlots && r < ix.bucket_mask;
+      leave = leave || (looking && (M > G || (goes_on && r + 1 >= kLongChain)));
+      looking = looking && goes_on && !leave;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS of this wave alone)
+    group_draft<G, LCAP>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);
+    if (on && leave && sub == 0) left[atomicAdd(&n_left, 1)] = (uint8_t)(wave * kRows + which);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the next turn's matches go to the same cells)
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && n_left > 0) list_at = atomicAdd(list.count, n_left);
+  __syncthreads();
+  for (int x = (int)threadIdx.x; x < n_left; x += 256)
+    list.units[list_at + x] = (int32_t)(first - (uint32_t)(wave * kRows) + left[x]);
+}
+
+}  // namespace csd

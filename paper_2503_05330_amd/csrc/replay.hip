@@ -6,6 +6,13 @@ namespace csd {
 // From this many drafts on the small LDS layout is used (as in launch_step).
 constexpr int64_t kSmallLdsDrafts = 2048;
 
+// From this many drafts on those with few matches are made with four or eight lanes each.  Three
+// kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
+// drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31, 49152 (64
+// problems x 16 paths x 48 steps) 73 / 50 (10 + 21 + 19), 393216 (1024 problems, 24 steps) 533 / 210
+// (60 + 76 + 74).
+constexpr int64_t kQuadDrafts = 1 << 15;
+
 template <class LDS, int QC>
 static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st) {
   const uint32_t grid = xcd_grid((int64_t)v.P * v.N * steps);
@@ -14,8 +21,33 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
   else replay_wave_kernel<32, false, LDS, false, QC><<<grid, kWave, 0, st>>>(v, steps, a);
 }
 
-void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st) {
-  const bool many = (int64_t)v.P * v.N * steps >= kSmallLdsDrafts;
+template <int LCAP, int QC>
+static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, const RestList& list,
+                         hipStream_t st) {
+  const int64_t drafts = (int64_t)v.P * v.N * steps;
+  const auto grid = [&](int64_t per_wave) { return (uint32_t)((drafts + 32 * per_wave - 1) / (32 * per_wave) * 8); };
+  replay_quad_kernel<LCAP, QC><<<grid(kQuadRows), 256, 0, st>>>(v, steps, a, rest);
+  replay_eight_kernel<LCAP, QC><<<grid(kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  // (as many as the chip holds at once: they share the list)
+  replay_rest_kernel<LCAP, LdsWave, QC><<<1024, kWave, 0, st>>>(v, steps, a, list);
+}
+
+void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, const RestList& list,
+                   hipStream_t st) {
+  const int64_t drafts = (int64_t)v.P * v.N * steps;
+  if (drafts >= kQuadDrafts && a.k == v.kmax) {
+    if (v.kmax <= 4) {
+      if (a.L <= 8) launch_quads<8, 4>(v, steps, a, rest, list, st);
+      else if (a.L <= 16) launch_quads<16, 4>(v, steps, a, rest, list, st);
+      else launch_quads<32, 4>(v, steps, a, rest, list, st);
+    } else {
+      if (a.L <= 8) launch_quads<8, 8>(v, steps, a, rest, list, st);
+      else if (a.L <= 16) launch_quads<16, 8>(v, steps, a, rest, list, st);
+      else launch_quads<32, 8>(v, steps, a, rest, list, st);
+    }
+    return;
+  }
+  const bool many = drafts >= kSmallLdsDrafts;
   if (v.kmax <= 4) many ? launch<LdsWaveSmall, 4>(v, steps, a, st) : launch<LdsWave, 4>(v, steps, a, st);
   else many ? launch<LdsWaveSmall, 8>(v, steps, a, st) : launch<LdsWave, 8>(v, steps, a, st);
 }

@@ -18,7 +18,7 @@ def _same(a, b):
 
 
 # paths around the 16 of a workgroup and a wave; steps around a workgroup's threads; several launches
-# (2^19 drafts each); options, pools and matchers; one and several problems
+# (a quarter of max_len steps each); options, pools and matchers; one and several problems
 @pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,edits,flags,pool", [
     (1, 16, 300, 3, 3, 8, 0, binding.MATCH_AUTO, 0),
     (1, 17, 200, 65, 4, 10, 0, binding.MATCH_AUTO, 0),
@@ -75,6 +75,49 @@ def test_steps_side_by_side(problems, paths, max_len, steps, query, draft, edits
         assert np.array_equal(d[0], d1[0]) and np.array_equal(d[1], d1[1])
     assert e == e1 and (e == 0 or start == "full")
     assert int(a["length"].sum()) > 0 or start == "empty"
+
+
+# enough drafts for the kernels with four and eight lanes per draft: drafts of one to 30 tokens, grams
+# of two to six, rows with no, few, many and hundreds of matches (two symbols: chains of full
+# buckets), edge scoring, more than 64 paths, short paths, a wave's sixteen rows across problems
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,mode,warm", [
+    (64, 16, 200, 40, 3, 8, 60, 0, 150),
+    (64, 17, 160, 31, 4, 13, 60, 1, 120),
+    (3, 70, 640, 160, 6, 30, 40, 0, 90),
+    (1, 64, 2100, 520, 5, 16, 2000, 0, 150),
+    (1100, 5, 60, 7, 2, 5, 2, 1, 40),
+    (2100, 2, 64, 8, 1, 1, 300, 0, 50),
+    (130, 16, 100, 20, 3, 7, 9, 0, 0),
+])
+def test_many_drafts_side_by_side(problems, paths, max_len, steps, query, draft, vocab, mode, warm):
+    rng = np.random.default_rng(problems + paths + vocab)
+    print("many", problems, paths, max_len, steps, query, draft, vocab, mode, warm, flush=True)
+    dev, T = torch.device("cuda:0"), max_len
+    assert problems * paths * steps >= 1 << 15 and steps <= max(T // 4, 16)     # in one launch
+    tokens = rng.integers(0, vocab, size=(problems, paths, T)).astype(np.int32)
+    pool = rng.integers(0, vocab, size=(problems, 1, 12, 10)).astype(np.int32)      # segments in any order
+    order = rng.integers(0, 12, size=(problems, paths, T // 10 + 1))
+    shared = np.take_along_axis(np.repeat(pool, paths, axis=1), order[..., None], axis=2).reshape(problems, paths, -1)[:, :, :T]
+    tokens = np.where(rng.random(tokens.shape) < 0.9, shared, tokens)
+    # (few distinct probabilities: equal weights, decided by the lower token)
+    probs = (rng.integers(0, 5, size=tokens.shape) / 4.0).astype(np.float32)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    targets = put(np.concatenate([tokens, tokens], 2)[:, :, warm + 1:warm + 1 + steps + draft].astype(np.int32))
+    targets = targets.unfold(2, draft, 1)[:, :, :steps].permute(2, 0, 1, 3).contiguous()
+    by_step = lambda a: put(a[:, :, warm:warm + steps].transpose(2, 0, 1))
+    got = []
+    for per_launch in (0, 1):
+        ix = binding.Index(problems, paths, T, vocab, query, draft, 0.7, mode, binding.MATCH_INDEX, device=dev)
+        if warm:
+            counts = np.where(np.arange(paths) % 5 == 4, warm // 3, warm) + np.zeros((problems, 1))
+            ix.append(put(tokens[:, :, :warm]), put(probs[:, :, :warm]), put(counts.astype(np.int32)), warm)
+        if per_launch:
+            ix.set_steps_per_launch(per_launch)
+        got.append((ix.replay(steps, by_step(tokens), by_step(probs), query, draft, targets=targets), ix.status()))
+    (a, status), (b, status1) = got
+    _same(a, b)
+    assert status == status1 == 0
+    assert int(a["length"].sum()) > 0 and int(a["accept"].sum()) > 0
 
 
 def test_a_captured_replay_goes_on_from_where_it_was():
