@@ -3,16 +3,21 @@
 Argument marshalling only: every step of the drafting path runs in the HIP
 kernels of libcsd.so.  PyTorch supplies device memory and the stream.  There is
 no CPU fallback: if the library is missing or a call fails, this raises.
+The calls of a decode loop marshal in native code (_csd_torch.so) where their
+arguments are the usual ones, else, and where buffers for the outputs are given,
+here.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
 import torch
 
-from .build import LIBRARY, build_library
+from .build import BINDING, LIBRARY, build_binding, build_library
 
 MATCH_AUTO, MATCH_SCAN, MATCH_INDEX = 0, 1, 2
 INCLUDE_SELF, QUERY_BACKOFF = 4, 8      # options OR-ed to a MATCH_* value
@@ -44,15 +49,19 @@ class CsdError(RuntimeError):
 
 
 _lib = None
+_native = None
 _vp = ctypes.c_void_p
 
 
 def load() -> ctypes.CDLL:
-    """Loads libcsd.so (building it first only if it has never been built)."""
-    global _lib
+    """Loads libcsd.so and the binding's native part (building them first only if they have never
+    been built)."""
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIBRARY):
             build_library()
+        if not os.path.exists(BINDING):
+            build_binding()
         lib = ctypes.CDLL(LIBRARY)
         i32, i64 = ctypes.c_int32, ctypes.c_int64
         cfgp = ctypes.POINTER(Config)
@@ -78,6 +87,8 @@ def load() -> ctypes.CDLL:
         for name in EXPORTS:
             if name != "csd_strerror":
                 getattr(lib, name).restype = ctypes.c_int
+        loader = importlib.machinery.ExtensionFileLoader("_csd_torch", BINDING)
+        _native = importlib.util.module_from_spec(importlib.util.spec_from_loader("_csd_torch", loader))
         _lib = lib
     return _lib
 
@@ -113,7 +124,8 @@ def _ptr(t: Optional[torch.Tensor], dtype, numel: Optional[int] = None):
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """torch.cuda.current_stream().cuda_stream, without the object around it (3.4 us a call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class Index:
@@ -137,6 +149,11 @@ class Index:
                                ctypes.byref(self._h))
         if rc != OK:
             raise CsdError(rc, "csd_create")
+        self._device_index = -1 if self.device.index is None else self.device.index
+
+    def _pool(self):
+        """What every native call starts with."""
+        return self._h.value if self._h else 0, _stream(), self._device_index, self.P, self.N
 
     def close(self):
         if getattr(self, "_h", None):
@@ -159,12 +176,18 @@ class Index:
         self._check(load().csd_set_steps_per_launch(self._h, steps), "csd_set_steps_per_launch")
 
     def reset(self):
+        rc = _native.reset(*self._pool())
+        if rc is not None:
+            return self._check(rc, "csd_reset")
         self._check(load().csd_reset(self._h, _stream()), "csd_reset")
 
     def append(self, tokens, probs=None, counts=None, n=None):
         """tokens [P][N][n] int32, probs same float32 or None, counts [P][N] int32 or None."""
         if n is None:
             n = tokens.numel() // self.rows
+        rc = _native.append(*self._pool(), n, tokens, probs, counts)
+        if rc is not None:
+            return self._check(rc, "csd_append")
         self._check(load().csd_append(self._h, _ptr(tokens, torch.int32, self.rows * n),
                                       _ptr(probs, torch.float32, self.rows * n),
                                       _ptr(counts, torch.int32, self.rows), n, _stream()),
@@ -174,6 +197,10 @@ class Index:
         """Returns dict(tokens [P][N][L], length [P][N], token_scores, path_scores)."""
         P, N, L = self.P, self.N, draft_len
         if out is None:
+            got = _native.draft(*self._pool(), query_len, draft_len, scores)
+            if got is not None:
+                self._check(got[0], "csd_draft")
+                return got[1]
             out = dict(tokens=torch.empty((P, N, L), dtype=torch.int32, device=self.device),
                        length=torch.empty((P, N), dtype=torch.int32, device=self.device),
                        token_scores=torch.empty((P, N, L), dtype=torch.float32,
@@ -190,6 +217,10 @@ class Index:
 
     def accept(self, draft_tokens, draft_len_t, targets, draft_len, out=None):
         if out is None:
+            got = _native.accept(*self._pool(), draft_len, draft_tokens, draft_len_t, targets)
+            if got is not None:
+                self._check(got[0], "csd_accept")
+                return got[1]
             out = torch.empty((self.P, self.N), dtype=torch.int32, device=self.device)
         self._check(load().csd_accept(self._h, _ptr(draft_tokens, torch.int32, self.rows * draft_len),
                                       _ptr(draft_len_t, torch.int32, self.rows),
@@ -209,6 +240,10 @@ class Index:
         """One fused decode step (append + draft [+ accept]) in one launch."""
         L = draft_len
         if out is None:
+            got = _native.step(*self._pool(), n, query_len, draft_len, scores, tokens, probs, counts, targets, accept_out)
+            if got is not None:
+                self._check(got[0], "csd_step")
+                return got[1]
             out = self._outputs(L, scores)
         if targets is not None and accept_out is None:
             accept_out = torch.empty((self.P, self.N), dtype=torch.int32, device=self.device)
@@ -230,6 +265,11 @@ class Index:
         tokens / probs [n_steps][P][N]; outputs get a leading n_steps axis."""
         L, S = draft_len, n_steps
         if out is None:
+            got = _native.replay(*self._pool(), n_steps, query_len, draft_len, scores, tokens, probs, fused, targets,
+                                 accept_out)
+            if got is not None:
+                self._check(got[0], "csd_replay")
+                return got[1]
             out = self._outputs(L, scores, lead=(S,))
         if targets is not None and accept_out is None:
             accept_out = torch.empty((S, self.P, self.N), dtype=torch.int32, device=self.device)

@@ -1,4 +1,5 @@
-"""Compiles the HIP sources under csrc/ into libcsd.so (gfx950 only)."""
+"""Compiles the HIP sources under csrc/ into libcsd.so (gfx950 only), and the native part of the
+PyTorch binding."""
 from __future__ import annotations
 
 import glob
@@ -12,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = sorted(glob.glob(os.path.join(HERE, "csrc", "*.hip")))
 LIBRARY = os.path.join(HERE, "libcsd.so")
+BINDING = os.path.join(HERE, "_csd_torch.so")
 
 # -packed-fp32-ops is switched off on purpose: the compiler must not form packed
 # FP32 instructions from ordinary float code in this library.
@@ -20,7 +22,7 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 
 
 def build_library() -> str:
-    """One object per source, compiled side by side, and one link."""
+    """One object per source, compiled side by side, and one link; then the binding on top of it."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         raise RuntimeError("hipcc not found: the csd HIP library cannot be built")
@@ -35,7 +37,25 @@ def build_library() -> str:
         with ThreadPoolExecutor(max_workers=min(16, os.cpu_count() or 1)) as pool:
             list(pool.map(compile_one, zip(SOURCES, objects)))
         subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIBRARY, *objects])
+    build_binding()
     return LIBRARY
+
+
+def build_binding() -> str:
+    """_csd_torch.so, linked to libcsd.so beside it."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    gxx = shutil.which("g++") or "/usr/bin/g++"
+    includes = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], *include_paths()]
+    libs = library_paths()
+    subprocess.check_call([gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                           *[x for i in includes for x in ("-isystem" if i != includes[0] else "-I", i)],
+                           os.path.join(HERE, "csrc", "binding.cpp"), "-o", BINDING,
+                           *["-L" + p for p in libs], "-L" + HERE, "-l:libcsd.so", "-lc10", "-ltorch_cpu", "-ltorch",
+                           "-ltorch_python", "-Wl,-rpath,$ORIGIN"])
+    return BINDING
 
 
 if __name__ == "__main__":

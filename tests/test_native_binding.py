@@ -1,0 +1,79 @@
+"""The native part of the binding: it takes the usual arguments only, and what it returns is what
+the Python part returns and raises."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_05330_amd import binding
+
+
+def test_unusual_arguments_are_left_to_python():
+    binding.load()
+    native, pool = binding._native, (0, 0, -1, 2, 3)
+    x = torch.zeros((2, 3, 4), dtype=torch.int32)                          # not on a device
+    assert native.append(*pool, 4, x, None, None) is None
+    assert native.append(*pool, 4, None, None, None) is None               # tokens are not optional
+    assert native.append(*pool, 4.0, x, None, None) is None
+    assert native.append(*pool, 1 << 40, x, None, None) is None
+    assert native.append(*pool) is None
+    assert native.append(*pool, True, x, None, None) is None
+    assert native.draft(*pool, 3, -1, True) is None
+    assert native.draft(*pool, 3, 4, 1) is None
+    assert native.draft(*pool, np.int64(3), 4, True) is None
+    assert native.accept(*pool, 4, x, x, x) is None
+    assert native.step(*pool, 1, 3, 4, True, x, None, None, None, None) is None
+    assert native.replay(*pool, 1, 3, 4, True, x, None, True, None, None) is None
+    assert native.reset("", 0, -1, 2, 3) is None
+    assert native.reset(0, 0, 500, 2, 3) is None
+    assert native.reset(*pool) == binding.ERR_INVALID_ARG                  # no handle
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scores", (True, False))
+def test_the_same_from_both_parts(scores):
+    dev, P, N, T, k, L, S = torch.device("cuda:0"), 2, 5, 60, 3, 6, 4
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    draw = lambda *shape: torch.randint(0, 6, shape, generator=gen, device=dev, dtype=torch.int32)
+    past, tokens, targets = draw(P, N, 40), draw(S, P, N), draw(S, P, N, L)
+    probs = torch.rand((S, P, N), generator=gen, device=dev)
+
+    def outputs(lead=()):
+        mk = lambda shape, dt: torch.empty(tuple(lead) + shape, dtype=dt, device=dev)
+        return dict(tokens=mk((P, N, L), torch.int32), length=mk((P, N), torch.int32),
+                    token_scores=mk((P, N, L), torch.float32) if scores else None,
+                    path_scores=mk((P, N), torch.float32) if scores else None)
+
+    results = []
+    for native in (True, False):
+        ix = binding.Index(P, N, T, 6, k, L, device="cuda" if native else dev)
+        give = (lambda *lead: None) if native else lambda *lead: outputs(lead)
+        ix.append(past)
+        got = [ix.draft(k, L, out=give(), scores=scores)]
+        acc = None if native else torch.empty((P, N), dtype=torch.int32, device=dev)
+        got.append({"accept": ix.accept(got[0]["tokens"], got[0]["length"], targets[0], L, out=acc)})
+        got.append(ix.step(tokens[0], probs[0], None, 1, k, L, out=give(), targets=targets[0], scores=scores))
+        got.append(ix.step(tokens[1], None, torch.ones((P, N), dtype=torch.int32, device=dev), 1, k, L, out=give(),
+                           scores=scores))
+        got.append(ix.replay(S, tokens, probs, k, L, out=give(S), targets=targets, scores=scores))
+        kept = torch.empty((S, P, N), dtype=torch.int32, device=dev)
+        got.append(ix.replay(S, tokens, None, k, L, out=give(S), targets=targets, accept_out=kept, fused=False, scores=scores))
+        assert got[-1]["accept"] is kept
+        results.append(got)
+        for call, error in ((lambda: ix.append(past.float()), TypeError), (lambda: ix.append(past[:, :, ::2]), TypeError),
+                            (lambda: ix.append(past[0], n=40), ValueError), (lambda: ix.append(past.cpu()), TypeError),
+                            (lambda: ix.step(None, None, None, 1, k, L, out=give()), binding.CsdError),
+                            (lambda: ix.draft(k, L + 1), binding.CsdError), (lambda: ix.draft(k, -1), RuntimeError),
+                            (lambda: ix.append(past), binding.CsdError)):
+            with pytest.raises(error):
+                call()
+        ix.reset()
+        assert int(ix.draft(k, L, out=give())["length"].sum()) == 0
+    for a, b in zip(*results):
+        assert list(a) == list(b)
+        for key in a:
+            if a[key] is None or b[key] is None:
+                assert a[key] is None and b[key] is None
+                continue
+            assert a[key].dtype == b[key].dtype and a[key].shape == b[key].shape and a[key].is_contiguous(), key
+            assert torch.equal(a[key], b[key]), key
