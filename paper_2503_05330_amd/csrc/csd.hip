@@ -256,8 +256,9 @@ void launch_draft(const csd_index* h, const IndexView& v, const StepIn& in, cons
                   hipStream_t st) {
   if (!h->indexed) launch_step_scan(v, in, a, h->slices, st);
   else if (v.eps > 0) launch_step_fuzzy(v, in, a, st);      // one edit through the variant index
-  // tree and list pools, own history, back-off, steps of several tokens: the general kernels
-  else if (a.pool_mode != CSD_POOL_DAG || v.options != 0 || in.n > 1) launch_step_general(v, in, a, st);
+  // tree and list pools, own history, back-off: the general kernels
+  else if (a.pool_mode != CSD_POOL_DAG || v.options != 0) launch_step_general(v, in, a, st);
+  else if (in.n > 1) launch_step_several(v, in, a, st);
   else launch_step(v, in, a, st);
 }
 

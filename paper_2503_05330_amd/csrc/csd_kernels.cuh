@@ -373,7 +373,8 @@ struct LoopTail {
 // One decode step of one row by one wave: front end, DAG, walk, outputs, accept, tail.
 // APPENDS: the wave also appends the row's tokens and files them in the index (false: another
 // wave of the workgroup does, see wave_append).  s: the row's on-chip state.
-template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool APPENDS, class TAIL>
+// MULTI: also compiled for steps of several tokens (POOLS: for these, the tree and list pools and the options).
+template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool APPENDS, class TAIL, bool MULTI = POOLS>
 __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const StepIn& in,
                                          const DraftArgs& a, const TAIL& tail, int32_t row, int lane) {
   int32_t p;
@@ -393,7 +394,7 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
   VariantTicket tickets;
   bool ticket_used;
   int32_t M = FUZZY ? wave_front_end_fuzzy<LCAP, QC, APPENDS>(s, c, ix, p, a.k, L, wi, tickets, ticket_used)
-                    : wave_front_end<LCAP, QC, APPENDS, POOLS>(s, c, ix, p, a.k, L, wi, ticket, ticket_used);
+                    : wave_front_end<LCAP, QC, APPENDS, MULTI>(s, c, ix, p, a.k, L, wi, ticket, ticket_used);
   block_sync<kWave>();
 #ifdef CSD_STAMPS
   if (lane == 0 && row < (1 << 14)) {
@@ -401,7 +402,7 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
     g_stamps[row * kStampSlots + 9] = (unsigned long long)M;
   }
 #endif
-  if (APPENDS && POOLS && !FUZZY && in.n > 1) {
+  if (APPENDS && MULTI && !FUZZY && in.n > 1) {
     // a step of several tokens appended by the drafting wave itself (nothing this step's
     // drafts read is written here)
     append_positions<true, false, QC>(ix, in, p, c.i, 0, kWave, true, lane);
@@ -527,7 +528,7 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
 }
 
 // The row of this workgroup: its first wave drafts, a second wave appends.
-template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, class TAIL>
+template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool MULTI, class TAIL>
 __device__ __forceinline__ void step_wave_body(const IndexView& ix, const StepIn& in,
                                                const DraftArgs& a, const TAIL& tail) {
   constexpr bool SPLIT = step_wave_threads(FUZZY) > kWave;
@@ -540,17 +541,17 @@ __device__ __forceinline__ void step_wave_body(const IndexView& ix, const StepIn
     Ctx c = make_ctx(ix, in, row, p);
     c.tid = lane;
     if (FUZZY) wave_append_fuzzy(c, ix, p);
-    else wave_append<QC, POOLS, std::is_same<LDS, LdsWaveSmall>::value ? 1 : kInsertLanes>(c, ix, in, p);
+    else wave_append<QC, MULTI, std::is_same<LDS, LdsWaveSmall>::value ? 1 : kInsertLanes>(c, ix, in, p);
     return;
   }
-  row_step<LCAP, POOLS, LDS, FUZZY, QC, !SPLIT>(s, ix, in, a, tail, row, lane);
+  row_step<LCAP, POOLS, LDS, FUZZY, QC, !SPLIT, TAIL, MULTI>(s, ix, in, a, tail, row, lane);
 }
 
-template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC>
+template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool MULTI = POOLS>
 __global__ __launch_bounds__(step_wave_threads(FUZZY)) void step_wave_kernel(IndexView ix, StepIn in,
                                                                              DraftArgs a) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs)>();
-  step_wave_body<LCAP, POOLS, LDS, FUZZY, QC>(ix, in, a, NoTail{});
+  step_wave_body<LCAP, POOLS, LDS, FUZZY, QC, MULTI>(ix, in, a, NoTail{});
 }
 
 // The same for launches of thousands of rows (exact matching, drafts of up to 8 tokens), where
@@ -560,17 +561,17 @@ template <int QC>
 __global__ __launch_bounds__(step_wave_threads(false)) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void step_wave_many_kernel(IndexView ix, StepIn in, DraftArgs a) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs)>();
-  step_wave_body<8, false, LdsWaveSmall, false, QC>(ix, in, a, NoTail{});
+  step_wave_body<8, false, LdsWaveSmall, false, QC, false>(ix, in, a, NoTail{});
 }
 
 // One step of the accept-driven loop in one launch: a step of up to L + 1 tokens per path
 // (general instantiation, exact matching), then the tail that prepares the next step.
-template <int LCAP, int QC>
+template <int LCAP, int QC, bool POOLS>
 __global__ __launch_bounds__(step_wave_threads(false)) void step_loop_kernel(IndexView ix, StepIn in,
                                                                              DraftArgs a,
                                                                              LoopTail tail) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs) + sizeof(LoopTail)>();
-  step_wave_body<LCAP, true, LdsWave, false, QC>(ix, in, a, tail);
+  step_wave_body<LCAP, POOLS, LdsWave, false, QC, true>(ix, in, a, tail);
 }
 
 // Many steps per launch (the device-side form of the host loops csd_replay and

@@ -8,7 +8,9 @@ namespace csd {
 
 // exact matching through the index, the usual step: DAG pool, at most one token per path
 void launch_step(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
-// the same with the tree and list pools, own history, back-off, steps of several tokens
+// the same for steps of several tokens
+void launch_step_several(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
+// the same with the tree and list pools, own history, back-off
 void launch_step_general(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);
 // one-edit matching through the variant index
 void launch_step_fuzzy(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);

@@ -1,5 +1,5 @@
 // csd — launches of the general step through the index: tree and list pools, own history,
-// back-off, steps of several tokens.
+// back-off.
 #include "csd_launch.h"
 
 namespace csd {
