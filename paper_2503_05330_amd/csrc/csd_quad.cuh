@@ -224,10 +224,9 @@ __device__ __forceinline__ void load_targets(const DraftArgs& a, const UnitRow& 
   }
 }
 
-// The first of this wave's `per_wave` units: XCD x takes a contiguous range of the units.
-__device__ __forceinline__ uint32_t wave_units(uint32_t per_wave) {
-  const uint32_t block = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  return (block * (blockDim.x / kWave) + (threadIdx.x >> 6)) * per_wave;
+// The first of this workgroup's `per_block` units: XCD x takes a contiguous range of the units.
+__device__ __forceinline__ uint32_t block_units(uint32_t per_block) {
+  return ((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * per_block;
 }
 
 // One draft per quad of lanes, sixteen per wave: exact matching through the index, DAG pool, query
@@ -244,7 +243,7 @@ template <int LCAP, int QC>
 __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t steps, DraftArgs a, u64* rest) {
   __shared__ uint32_t found[256];                        // [row of the workgroup][4] matches
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), sub = tid & 3;
-  const uint32_t unit = wave_units(kQuadRows) + (uint32_t)(lane >> 2);
+  const uint32_t unit = block_units(4 * kQuadRows) + (uint32_t)(tid >> 2);
   const bool on = unit < (uint32_t)(ix.P * ix.N * steps);
   const UnitRow u(ix, (uint32_t)steps, on ? unit : 0u);
   // ---- round trip 1: the path's end
@@ -295,30 +294,43 @@ struct RestList {
 };
 
 // The same with eight lanes per row, for the rows that replay_quad_kernel has left: the first
-// buckets of the query's chain, up to eight matches.  A wave takes the rows that one wave of that
-// kernel has left, eight at a time (a turn is a chain of four to eight round trips, 7 to 15 us: with
-// the rows of four waves there were more turns in a row, 64 problems x 48 steps 35 us instead of
-// 21), and a workgroup lists the rows with more matches or a longer chain for the kernel with a
-// wave per row (one reservation: atomics on one address take 12 ns each).
+// buckets of the query's chain, up to eight matches.  A workgroup pools the rows that WAVES waves of
+// that kernel have left (one in eight, most of them because their first bucket is full), and its
+// waves take eight each.  A turn is a chain of five to nine round trips, so what counts is one
+// turn for most waves and all of them resident at once: 1024 problems x 24 steps 74 us with the rows
+// of four waves pooled, 60 with those of sixteen.  It lists the rows with more matches or a
+// longer chain for the kernel with a wave per row (one reservation: atomics on one address take 12 ns each).
 constexpr uint32_t kLongChain = 3;     // buckets after which the wave per row, which reads four at once, takes over
-template <int LCAP, int QC>
+template <int WAVES, int LCAP, int QC>
 __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
                                                            RestList list) {
-  constexpr int G = 8, kWaves = 4, kRows = kQuadRows;
+  constexpr int G = 8, kWaves = 4, kRows = WAVES * kQuadRows;   // rows of the workgroup
+  static_assert(WAVES <= kWave && kRows <= 256, "a lane per wave of the other kernel, a byte per row");
   __shared__ uint32_t found_all[kWaves][kWave];          // [row of the turn][8] matches
-  __shared__ uint8_t todo_all[kWaves][kRows], left[kWaves * kRows];
-  __shared__ int32_t n_left, list_at;
+  __shared__ uint8_t todo[kRows], left[kRows];
+  __shared__ int32_t n_todo, n_left, list_at;
   const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x >> 6, sub = lane & (G - 1);
   uint32_t* found = found_all[wave];
-  uint8_t* todo = todo_all[wave];
-  const uint32_t units = (uint32_t)(ix.P * ix.N * steps), first = wave_units(kRows);
-  // the rows' numbers, one after the other
-  const u64 rows = first < units ? rest[first / kQuadRows] : 0ull;     // the same in every lane
-  const uint32_t total = (uint32_t)__popcll(rows);
-  if (rows >> lane & 1ull) todo[__popcll(rows & ((1ull << lane) - 1ull))] = (uint8_t)(lane >> 2);
-  if (threadIdx.x == 0) n_left = 0;
+  const uint32_t units = (uint32_t)(ix.P * ix.N * steps), first = block_units(kRows);
+  if (wave == 0) {                                       // the rows' numbers, one after the other
+    u64 rows = 0;
+    if (lane < WAVES && first + (uint32_t)(lane * kQuadRows) < units) rows = rest[first / kQuadRows + lane];
+    int32_t at = 0, total = 0;
+#pragma unroll
+    for (int x = 0; x < WAVES; ++x) {
+      const int32_t n = __builtin_amdgcn_readlane((int)__popcll(rows), x);
+      at = lane == x ? total : at;
+      total += n;
+    }
+    for (; rows; rows &= rows - 1) todo[at++] = (uint8_t)(lane * kQuadRows + (((int)__ffsll((long long)rows) - 1) >> 2));
+    if (lane == 0) {
+      n_todo = total;
+      n_left = 0;
+    }
+  }
   __syncthreads();
-  for (uint32_t turn = 0; turn < total; turn += kWave / G) {   // uniform over the wave
+  const uint32_t total = (uint32_t)__builtin_amdgcn_readfirstlane(n_todo);
+  for (uint32_t turn = (uint32_t)(wave * (kWave / G)); turn < total; turn += kWaves * (kWave / G)) {   // uniform over the wave
     const uint32_t nth = turn + (uint32_t)(lane / G);
     const bool on = nth < total;
     const uint32_t which = todo[on ? nth : turn];
@@ -330,9 +342,14 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     bool leave = len < ix.kmax;
     int32_t M = 0;
     bool looking = on && !leave;                         // the same in a group's lanes
+    auto bucket = [&](uint32_t r) {
+      const int64_t b = u.buckets + ((gh.h + r * gh.step) & ix.bucket_mask);
+      return *reinterpret_cast<const int2*>(ix.gram + b * kBucketWords + 2 * sub);
+    };
+    int2 next = bucket(0);
     for (uint32_t r = 0; wave_ballot(looking) != 0; ++r) {   // uniform over the wave
-      const int64_t bucket = u.buckets + ((gh.h + r * gh.step) & ix.bucket_mask);
-      const int2 w = *reinterpret_cast<const int2*>(ix.gram + bucket * kBucketWords + 2 * sub);
+      const int2 w = next;
+      next = bucket(r + 1);                              // (in flight while this one is looked through)
       const int32_t word[2] = {w.x, w.y}, count = __shfl(w.x, lane & ~(G - 1));
       Posting<QC> post[2];
 #pragma unroll
@@ -356,14 +373,14 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS of this wave alone)
     group_draft<G, LCAP>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);
-    if (on && leave && sub == 0) left[atomicAdd(&n_left, 1)] = (uint8_t)(wave * kRows + which);
+    if (on && leave && sub == 0) left[atomicAdd(&n_left, 1)] = (uint8_t)which;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the next turn's matches go to the same cells)
   }
   __syncthreads();
   if (threadIdx.x == 0 && n_left > 0) list_at = atomicAdd(list.count, n_left);
   __syncthreads();
   for (int x = (int)threadIdx.x; x < n_left; x += 256)
-    list.units[list_at + x] = (int32_t)(first - (uint32_t)(wave * kRows) + left[x]);
+    list.units[list_at + x] = (int32_t)(first + left[x]);
 }
 
 }  // namespace csd

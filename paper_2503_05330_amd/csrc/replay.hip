@@ -9,8 +9,8 @@ constexpr int64_t kSmallLdsDrafts = 2048;
 // From this many drafts on those with few matches are made with four or eight lanes each.  Three
 // kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
 // drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31, 49152 (64
-// problems x 16 paths x 48 steps) 73 / 50 (10 + 21 + 19), 393216 (1024 problems, 24 steps) 533 / 210
-// (60 + 76 + 74).
+// problems x 16 paths x 48 steps) 73 / 50 (10 + 20 + 19), 393216 (1024 problems, 24 steps) 533 / 195
+// (60 + 60 + 75).
 constexpr int64_t kQuadDrafts = 1 << 15;
 
 template <class LDS, int QC>
@@ -21,13 +21,19 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
   else replay_wave_kernel<32, false, LDS, false, QC><<<grid, kWave, 0, st>>>(v, steps, a);
 }
 
+// From this many drafts on a workgroup of replay_eight_kernel pools sixteen waves' rows: below, its
+// workgroups with four fit the chip at once and have fewer turns (64 problems x 48 steps, 49152
+// drafts, 20 us; 1024 problems x 24 steps, 393216 drafts, 74 us with four waves' rows, 60 with sixteen).
+constexpr int64_t kPooledDrafts = 1 << 17;
+
 template <int LCAP, int QC>
 static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, const RestList& list,
                          hipStream_t st) {
   const int64_t drafts = (int64_t)v.P * v.N * steps;
-  const auto grid = [&](int64_t per_wave) { return (uint32_t)((drafts + 32 * per_wave - 1) / (32 * per_wave) * 8); };
-  replay_quad_kernel<LCAP, QC><<<grid(kQuadRows), 256, 0, st>>>(v, steps, a, rest);
-  replay_eight_kernel<LCAP, QC><<<grid(kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  const auto grid = [&](int64_t rows) { return (uint32_t)((drafts + 8 * rows - 1) / (8 * rows) * 8); };   // rows per workgroup
+  replay_quad_kernel<LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest);
+  if (drafts >= kPooledDrafts) replay_eight_kernel<16, LCAP, QC><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  else replay_eight_kernel<4, LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   // (as many as the chip holds at once: they share the list)
   replay_rest_kernel<LCAP, LdsWave, QC><<<1024, kWave, 0, st>>>(v, steps, a, list);
 }
