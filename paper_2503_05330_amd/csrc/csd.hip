@@ -63,7 +63,7 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t tok, pq, meta, status, gram, slices, step_meta, rest, rest_list, total;
+  size_t tok, pq, meta, status, gram, slices, done, step_meta, rest, rest_list, total;
   int32_t n_slices;             // workgroups that share a row's scan (scan mode, few rows)
   int32_t replay_steps;         // steps of a replay that run side by side
   int32_t meta_stride, eshift;
@@ -170,6 +170,8 @@ Layout make_layout(const csd_config* c) {
     if (l.n_slices > 1)         // per row the match list and a state word
       at += align_up(rows * LdsScan::kMatch * sizeof(Match)) + align_up(rows * sizeof(u64));
   }
+  l.done = at;
+  at += align_up((rows < kSplitRows ? rows : kSplitRows) * kBucketWords * sizeof(int32_t));
   // the paths' ends after each step of a replay, for as many steps as give kReplayDrafts drafts
   l.replay_steps = 0;
   l.step_meta = l.rest = l.rest_list = at;
@@ -209,6 +211,7 @@ struct csd_index {
   int cur;
   size_t gram_words;
   ScanSlices slices;
+  int32_t* done;                // [min(P * N, kSplitRows)][16] see append_kernel
   bool indexed;
   uint32_t alpha_q;
   int64_t len_lo, len_hi;       // host-side bounds on every path's length
@@ -223,7 +226,7 @@ struct csd_index {
 namespace {
 hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-IndexView view_in_place(const csd_index* h) {     // no append: lengths in one buffer
+IndexView view_in_place(const csd_index* h) {     // no append, or one that replaces the ends: lengths in one buffer
   IndexView v = h->view;
   v.meta_old = h->meta[h->cur];
   v.meta_new = h->meta[h->cur];
@@ -232,12 +235,6 @@ IndexView view_in_place(const csd_index* h) {     // no append: lengths in one b
 IndexView view_appending(const csd_index* h) {    // lengths read in one buffer, written in the other
   IndexView v = h->view;
   v.meta_old = h->meta[h->cur];
-  v.meta_new = h->meta[h->cur ^ 1];
-  return v;
-}
-IndexView view_appended(const csd_index* h) {     // behind such a launch, before `cur` follows
-  IndexView v = h->view;
-  v.meta_old = h->meta[h->cur ^ 1];
   v.meta_new = h->meta[h->cur ^ 1];
   return v;
 }
@@ -281,9 +278,11 @@ constexpr int32_t kOwnedProblems = 24;
 // 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
 constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
 
-// Enqueues the append of a step's tokens; reads the paths' ends in v.meta_old and leaves the new
-// ones in v.meta_new (another buffer).  empty: no path has a token yet.
-void launch_append(const csd_index* h, const IndexView& v, const StepIn& in, bool empty, hipStream_t st) {
+// Enqueues the append of a step's tokens.  The paths' ends are replaced in place and `cur` stays, as
+// with csd_draft: captured once, the launch appends again at every replay of the graph.
+// empty: no path has a token yet.
+void launch_append(const csd_index* h, const StepIn& in, bool empty, hipStream_t st) {
+  const IndexView v = view_in_place(h);
   const int64_t rows = (int64_t)v.P * v.N;
   const bool q4 = v.kmax <= 4;
   const int64_t n_buckets = (int64_t)v.bucket_mask + 1;
@@ -296,17 +295,17 @@ void launch_append(const csd_index* h, const IndexView& v, const StepIn& in, boo
                   : (table ? (q4 ? append_problem_kernel<false, 4, true> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, true>)
                            : (q4 ? append_problem_kernel<false, 4, false> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, false>));
     const size_t lds = n_buckets * sizeof(int32_t) * (table ? 1 + kBucketWords : 1);
-    kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, empty ? 1 : 0);
+    kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
-  const int32_t block = (in.n <= kWave || rows > (1 << 22)) ? kWave : 256;
+  const int32_t block = (in.n <= kWave || rows > kSplitRows) ? kWave : 256;
   int64_t chunks = (in.n + block - 1) / block;
-  const int64_t most = ((int64_t)1 << 23) / rows;        // (bounds the grid; a workgroup loops over the rest)
-  chunks = chunks < most ? chunks : (most < 1 ? 1 : most);
+  const int64_t most = rows <= kSplitRows ? ((int64_t)1 << 23) / rows : 1;   // (bounds the grid; a workgroup loops over the rest)
+  chunks = chunks < most ? chunks : most;
   auto* kernel = !h->indexed ? append_kernel<false, false, 4>
                  : v.eps == 0 ? (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>)
                               : (q4 ? append_kernel<true, true, 4> : append_kernel<true, true, CSD_MAX_QUERY_LEN>);
-  kernel<<<(uint32_t)(rows * chunks), block, 0, st>>>(v, in, (int32_t)chunks);
+  kernel<<<(uint32_t)(rows * chunks), block, 0, st>>>(v, in, (int32_t)chunks, h->done);
 }
 
 // Enqueues `steps` steps of a replay side by side: the append of their tokens, which leaves the
@@ -373,6 +372,20 @@ int csd_workspace_bytes(const csd_config* cfg, size_t* out_bytes) {
   return CSD_OK;
 }
 
+// created: the handle is new (nothing of the workspace is known).
+static int reset(csd_index* h, bool created, void* stream) {
+  int64_t work = (int64_t)h->view.P * h->view.N * h->view.meta_stride;
+  if ((int64_t)h->gram_words > work) work = (int64_t)h->gram_words;
+  int64_t blocks = (work + 255) / 256;
+  if (blocks > 4096) blocks = 4096;
+  reset_kernel<<<(uint32_t)blocks, 256, 0, as_stream(stream)>>>(view_in_place(h),
+                                                                 (int64_t)h->gram_words, h->slices,
+                                                                 created ? h->done : nullptr);
+  CSD_HIP(hipGetLastError());
+  h->len_lo = h->len_hi = 0;
+  return CSD_OK;
+}
+
 int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes, void* stream,
                csd_index** out_index) {
   if (!out_index) return CSD_ERR_INVALID_ARG;
@@ -410,6 +423,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
     h->slices.state = reinterpret_cast<u64*>(base + l.slices +
                                              align_up(rows * LdsScan::kMatch * sizeof(Match)));
   }
+  h->done = reinterpret_cast<int32_t*>(base + l.done);
   h->view.P = cfg->n_problems;
   h->view.N = cfg->n_paths;
   h->view.max_len = cfg->max_len;
@@ -423,7 +437,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   h->rest = reinterpret_cast<u64*>(base + l.rest);
   h->rest_list = reinterpret_cast<int32_t*>(base + l.rest_list);
   h->replay_steps = l.replay_steps;
-  rc = csd_reset(h, stream);
+  rc = reset(h, true, stream);
   if (rc != CSD_OK) {
     delete h;
     return rc;
@@ -438,18 +452,7 @@ int csd_destroy(csd_index* index) {
   return CSD_OK;
 }
 
-int csd_reset(csd_index* h, void* stream) {
-  if (!h) return CSD_ERR_INVALID_ARG;
-  int64_t work = (int64_t)h->view.P * h->view.N * h->view.meta_stride;
-  if ((int64_t)h->gram_words > work) work = (int64_t)h->gram_words;
-  int64_t blocks = (work + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  reset_kernel<<<(uint32_t)blocks, 256, 0, as_stream(stream)>>>(view_in_place(h),
-                                                                 (int64_t)h->gram_words, h->slices);
-  CSD_HIP(hipGetLastError());
-  h->len_lo = h->len_hi = 0;
-  return CSD_OK;
-}
+int csd_reset(csd_index* h, void* stream) { return h ? reset(h, false, stream) : CSD_ERR_INVALID_ARG; }
 
 int csd_append(csd_index* h, const int32_t* d_tokens, const float* d_probs,
                const int32_t* d_counts, int32_t n, void* stream) {
@@ -458,10 +461,8 @@ int csd_append(csd_index* h, const int32_t* d_tokens, const float* d_probs,
   LengthBounds before(h);
   int rc = note_append(h, d_counts != nullptr, n);
   if (rc != CSD_OK) return rc;
-  launch_append(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
-  rc = before.launched("csd_append");
-  if (rc == CSD_OK) h->cur ^= 1;
-  return rc;
+  launch_append(h, StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
+  return before.launched("csd_append");
 }
 
 int csd_draft(csd_index* h, int32_t query_len, int32_t draft_len, int32_t* d_draft_tokens,
@@ -507,11 +508,9 @@ int csd_step(csd_index* h, const int32_t* d_tokens, const float* d_probs, const 
   if (h->indexed && n != 1 && (h->view.eps > 0 || n > kFusedStepTokens)) {
     // the one-wave kernels fuse the append of a few tokens per path (exact matching) or of
     // one (one-edit matching); longer steps append first
-    launch_append(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
-    launch_draft(h, view_appended(h), StepIn{nullptr, nullptr, nullptr, 0}, a, as_stream(stream));
-    rc = before.launched("csd_step");
-    if (rc == CSD_OK) h->cur ^= 1;
-    return rc;
+    launch_append(h, StepIn{d_tokens, d_probs, d_counts, n}, before.hi == 0, as_stream(stream));
+    launch_draft(h, view_in_place(h), StepIn{nullptr, nullptr, nullptr, 0}, a, as_stream(stream));
+    return before.launched("csd_step");
   }
   launch_draft(h, view_appending(h), StepIn{d_tokens, d_probs, d_counts, n}, a, as_stream(stream));
   rc = before.launched("csd_step");
@@ -702,15 +701,14 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
       auto* kernel = fuzzy ? (q4 ? advance_append_kernel<true, 4> : advance_append_kernel<true, CSD_MAX_QUERY_LEN>)
                            : (q4 ? advance_append_kernel<false, 4> : advance_append_kernel<false, CSD_MAX_QUERY_LEN>);
       kernel<<<(uint32_t)rows, kWave, 0, st>>>(
-          view_appending(h), (int32_t)n, draft_len, settled, d_future_tokens, d_future_probs, step_tok,
+          view_in_place(h), (int32_t)n, draft_len, settled, d_future_tokens, d_future_probs, step_tok,
           d_future_probs ? step_prob : nullptr, step_cnt, targets, d_path_len + (size_t)s * rows);
       DraftArgs a{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode,
                   d_draft_tokens + (size_t)s * rows * L, d_draft_len + (size_t)s * rows,
                   nullptr, nullptr, targets, d_accept_len + (size_t)s * rows};
-      launch_draft(h, view_appended(h), StepIn{nullptr, nullptr, nullptr, 0}, a, st);
+      launch_draft(h, view_in_place(h), StepIn{nullptr, nullptr, nullptr, 0}, a, st);
       rc = before.launched("csd_accept_loop");
       if (rc != CSD_OK) return rc;
-      h->cur ^= 1;
       continue;
     }
     advance_kernel<<<(uint32_t)((rows + 255) / 256), 256, 0, st>>>(

@@ -228,10 +228,11 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
 // together, without a look at the fill counts before: at most 8 of a bucket's 15 slots are taken
 // on average when a problem's histories are full, so few claims miss.  Those go on as claims in
 // the next three buckets, a lane at a time for itself, and what is left then (the long chain of
-// a frequent gram) is the whole wave's.
-template <bool FUZZY, int QC>
+// a frequent gram) is the whole wave's.  meanwhile(): called while the first claims are in flight.
+template <bool FUZZY, int QC, class MEANWHILE>
 __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int32_t kmax,
-                                               const int32_t (&G)[QC], bool mine, int32_t pos, int lane) {
+                                               const int32_t (&G)[QC], bool mine, int32_t pos, int lane,
+                                               MEANWHILE&& meanwhile) {
   constexpr int kVariants = FUZZY ? QC + 1 : 1;
   uint32_t todo = 0;                                     // variants of this lane that have no slot yet
   int32_t claimed[kVariants];
@@ -247,6 +248,7 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
 #pragma unroll
   for (int v = 0; v < kVariants; ++v)
     if (todo >> v & 1u) claimed[v] = atomicAdd(gram + (int64_t)at[v] * kBucketWords, 1);
+  meanwhile();
 #pragma unroll
   for (int v = 0; v < kVariants; ++v)
     if (claimed[v] < kBucketSlots) {                     // (never without a claim)
@@ -390,17 +392,30 @@ struct NewTokens {
   }
 };
 
-// The path's new meta row (word 0 = length, word 1 + a = a-th token from the new end), by one wave.
-// Not written in place (meta_new is not meta_old): nothing else in the launch reads it.
-__device__ __forceinline__ void store_meta(const IndexView& ix, const StepIn& in, int64_t row, int32_t len,
-                                           int32_t cnt, int lane) {
+// The path's new meta row (word 0 = length, word 1 + a = a-th token from the new end) after cnt new
+// tokens, a word per lane of one wave, into the rows `to` that nobody reads meanwhile.
+__device__ __forceinline__ void store_end(const IndexView& ix, const StepIn& in, int64_t row, int32_t len,
+                                          int32_t cnt, int32_t* to, int lane) {
   if (lane > ix.tail_len) return;
   const int32_t* st = in.tok + row * in.n;
   const int32_t* meta = ix.meta_old + row * ix.meta_stride;
   const int32_t a = lane - 1;
   int32_t w = len + cnt;
   if (lane > 0) w = a < cnt ? st[cnt - 1 - a] : (a < len + cnt ? meta[1 + a - cnt] : 0);
-  ix.meta_new[row * ix.meta_stride + lane] = w;
+  to[row * ix.meta_stride + lane] = w;
+}
+// The same in two halves, for an end that is replaced in place: no branch between them, so a lane's
+// word is stored behind all lanes' loads.
+__device__ __forceinline__ int32_t end_word(const IndexView& ix, const StepIn& in, int64_t row, int32_t len,
+                                            int32_t cnt, int lane) {
+  const int32_t a = lane - 1;
+  const bool tail = a >= 0 && a < ix.tail_len, fresh = tail && a < cnt, kept = tail && !fresh && a < len + cnt;
+  const int32_t token = in.tok[row * in.n + (fresh ? cnt - 1 - a : 0)];
+  const int32_t before = ix.meta_old[row * ix.meta_stride + (kept ? 1 + a - cnt : 0)];
+  return lane == 0 ? len + cnt : (fresh ? token : (kept ? before : 0));
+}
+__device__ __forceinline__ void store_end_word(const IndexView& ix, int64_t row, int32_t word, int lane) {
+  if (lane <= ix.tail_len) ix.meta_new[row * ix.meta_stride + lane] = word;
 }
 
 // The same with four consecutive tokens per lane (t a multiple of 4), for the kernel whose work is
@@ -490,12 +505,14 @@ struct NewTokens4 {
 };
 
 // Stores a share of what a step appends to path i of problem p: tokens, quantised probabilities
-// and postings of the step's tokens t_first + tid, then every t_stride-th, and (`head`) the new
-// meta row.  Called by whole waves, tid counting the threads that share the work.
-template <bool INDEX, bool FUZZY, int QC>
+// and postings of the step's tokens t_first + tid, then every t_stride-th.  Called by whole waves,
+// tid counting the threads that share the work.  `head`: this share raises the status bit of a full
+// path.  at_end(end): called once by every wave, when all that it needs of the path's old end has
+// arrived; `end` is the new one (end_word).
+template <bool INDEX, bool FUZZY, int QC, class AT_END>
 __device__ __forceinline__ void append_positions(const IndexView& ix, const StepIn& in, int32_t p,
                                                  int32_t i, int32_t t_first, int32_t t_stride,
-                                                 bool head, int tid) {
+                                                 bool head, int tid, AT_END&& at_end) {
   const int64_t row = (int64_t)p * ix.N + i;
   const int lane = tid & (kWave - 1);
   int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
@@ -505,14 +522,36 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
     NewTokens<INDEX ? QC : 0> x;
     x.load(ix, in, row, t0 + lane);
     cnt = x.count(ix);
+    const bool last = t0 + t_stride >= cnt;
+    int32_t end = 0;
+    if (last) end = end_word(ix, in, row, x.len, cnt, lane);
     if (head && tid == 0 && t0 == 0 && x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
     flags |= x.store(ix, in.prob != nullptr, row, cnt);
-    if constexpr (INDEX)
-      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane);
-    if (head && t0 == 0) store_meta(ix, in, row, x.len, cnt, lane);
+    auto sign_off = [&]() {
+      if (!last) return;
+      consume_here(end);
+      at_end(end);
+    };
+    if constexpr (INDEX) {
+#pragma unroll
+      for (int a = 0; a < QC; ++a) consume_here(x.G[a]);
+      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, sign_off);
+    } else {
+      sign_off();
+    }
     t0 += t_stride;
   } while (t0 < cnt);
   if (flags) atomicOr(ix.status, flags);
+}
+
+// ... the whole of it, by the waves of one workgroup.  The new end goes to meta_new: a row that
+// nobody reads in this launch, or, for one wave, over the old one.
+template <bool INDEX, bool FUZZY, int QC>
+__device__ __forceinline__ void append_path(const IndexView& ix, const StepIn& in, int32_t p, int32_t i,
+                                            int32_t threads, int tid) {
+  append_positions<INDEX, FUZZY, QC>(ix, in, p, i, 0, threads, true, tid, [&](int32_t end) {
+    if (tid < kWave) store_end_word(ix, (int64_t)p * ix.N + i, end, tid);   // uniform over the wave
+  });
 }
 
 }  // namespace csd

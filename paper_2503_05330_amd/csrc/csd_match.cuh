@@ -671,7 +671,7 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
   // (four of each; one with the layout of launches of thousands of rows, whose time is set by
   // what all rows together fetch and issue, not by a row's latency)
   constexpr int kFirst = std::is_same<LDS, LdsWaveSmall>::value ? 1 : 4;
-  ticket_used = APPENDS && y.n == 1 && cnt_i == 1;   // (longer steps are appended by append_positions)
+  ticket_used = APPENDS && y.n == 1 && cnt_i == 1;   // (longer steps are appended by append_path)
   if (ticket_used) ticket = insert_begin<QC, kFirst>(gram, c.bucket_mask, ix.kmax, me.tail, old_i, lane);
   GramHash gh{0u, 1u};
   int32_t word = -1;
@@ -755,7 +755,7 @@ __device__ __forceinline__ void wave_append(const Ctx& c, const IndexView& ix, c
   const int lane = c.tid;
   const Paths& y = c.y;
   if (GENERAL && y.n > 1) {
-    append_positions<true, false, QC>(ix, in, p, c.i, 0, kWave, true, lane);
+    append_path<true, false, QC>(ix, in, p, c.i, kWave, lane);
     return;
   }
   if (y.n != 1) return;

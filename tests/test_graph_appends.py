@@ -1,0 +1,105 @@
+"""Calls that append, captured in a HIP graph: every replay goes on from where the paths are, also with
+eager calls on the same handle in between, as the same calls made one by one do (which other tests
+compare with the oracle)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_05330_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("tokens", "length", "token_scores", "path_scores")
+
+
+def _put(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _tokens(rng, problems, paths, n, vocab):
+    """Histories with segments in common."""
+    motif = np.tile(rng.integers(0, vocab, size=(problems, 1, 40)), (1, 1, n // 40 + 1))[:, :, :n]
+    shared = np.repeat(rng.random((problems, paths, n // 20 + 1)) < 0.6, 20, axis=2)[:, :, :n]
+    return np.where(shared, motif, rng.integers(0, vocab, size=(problems, paths, n))).astype(np.int32)
+
+
+def _same(got, want, keys=KEYS):
+    for key in keys:
+        assert torch.equal(got[key], want[key]), key
+
+
+def _captured(call):
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        kept = call()
+    return graph, kept
+
+
+# a workgroup for a path's tokens and several of them; a workgroup per problem (24 problems, a good
+# part of the index at once); matching by scan; a step that appends first (many tokens, or one-edit
+# matching); the ends of an odd number of appends
+@pytest.mark.parametrize("problems,paths,max_len,query,edits,flags,call,n", [
+    (1, 4, 4000, 3, 0, binding.MATCH_INDEX, "append", 1),
+    (1, 4, 4000, 3, 0, binding.MATCH_INDEX, "append", 600),
+    (2, 3, 2000, 6, 0, binding.MATCH_INDEX, "append", 257),
+    (1, 4, 2000, 3, 1, binding.MATCH_INDEX, "append", 300),
+    (1, 4, 2000, 3, 0, binding.MATCH_SCAN, "append", 300),
+    (1, 4, 700, 3, 1, binding.MATCH_SCAN, "append", 65),
+    (24, 5, 300, 3, 0, binding.MATCH_INDEX, "append", 40),
+    (24, 5, 720, 3, 1, binding.MATCH_INDEX, "append", 210),
+    (1, 4, 900, 3, 0, binding.MATCH_INDEX, "step", 70),
+    (2, 5, 400, 3, 1, binding.MATCH_INDEX, "step", 3),
+    (24, 5, 720, 3, 0, binding.MATCH_INDEX, "step", 100),
+    (2, 5, 400, 3, 0, binding.MATCH_INDEX, "replay", 3),
+    (2, 5, 400, 3, 1, binding.MATCH_SCAN, "replay", 3),
+    (2, 5, 400, 5, 0, binding.MATCH_INDEX, "loop", 3),
+    (2, 5, 400, 3, 1, binding.MATCH_INDEX, "loop", 3),
+])
+def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, query, edits, flags, call, n):
+    print("captured", problems, paths, max_len, query, edits, flags, call, n, flush=True)
+    rng = np.random.default_rng(problems + paths + max_len + n)
+    turns, L, V, warm = (3 if n > 200 and problems > 1 else 5), 6, (30 if n > 3 else 3), 20
+    fed_at = [_tokens(rng, problems, paths, n, V) for _ in range(turns)]
+    if call == "replay":
+        fed_at = [a.transpose(2, 0, 1) for a in fed_at]
+    elif call == "loop":
+        fed_at = [_tokens(rng, problems, paths, max_len, V)] * turns
+    past, between = (_put(_tokens(rng, problems, paths, k, V)) for k in (warm, 7))
+    by_graph, by_call = (binding.Index(problems, paths, max_len, V, query, L, 0.5, 0, flags, device="cuda:0", max_edits=edits)
+                         for _ in range(2))
+    fed = _put(fed_at[0])
+
+    def go(ix, tokens, out):
+        if call == "append":
+            ix.append(tokens)
+            out = ix.draft(query, L, out=out)
+            out["accept"] = ix.accept(out["tokens"], out["length"], out["tokens"], L)
+        elif call == "step":
+            out = ix.step(tokens, None, None, n, query, L, out=out)
+        elif call == "replay":
+            out = ix.replay(n, tokens, None, query, L, out=out, fused=False)
+        else:
+            out = ix.accept_loop(n, tokens, None, query, L, min_scratch=True)
+        return out
+    for ix in (by_graph, by_call):
+        ix.append(past)
+    graph, out = _captured(lambda: go(by_graph, fed, None))
+    keys = ("tokens", "length", "accept", "path_len") if call == "loop" else KEYS
+    drafted = 0
+    for turn in range(turns):
+        fed.copy_(_put(fed_at[turn]))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = go(by_call, _put(fed_at[turn]), None)
+        _same(out, want, keys)
+        drafted += int(want["length"].sum())
+        if turn == 1:                                     # an eager call in between
+            for ix in (by_graph, by_call):
+                ix.append(between)
+            _same(by_graph.draft(query, L), by_call.draft(query, L))
+    a, b = (ix.dump_matches(query, cap=1 << 22) for ix in (by_graph, by_call))
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+    assert drafted > 0
+    assert by_graph.status() == by_call.status() == 0
