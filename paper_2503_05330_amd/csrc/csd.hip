@@ -280,8 +280,8 @@ constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
 
 // Enqueues the append of a step's tokens.  The paths' ends are replaced in place and `cur` stays, as
 // with csd_draft: captured once, the launch appends again at every replay of the graph.
-// empty: no path has a token yet.
-void launch_append(const csd_index* h, const StepIn& in, bool empty, hipStream_t st) {
+// maybe_empty: no call has appended since the reset (a graph may have: the host does not see that).
+void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipStream_t st) {
   const IndexView v = view_in_place(h);
   const int64_t rows = (int64_t)v.P * v.N;
   const bool q4 = v.kmax <= 4;
@@ -295,7 +295,7 @@ void launch_append(const csd_index* h, const StepIn& in, bool empty, hipStream_t
                   : (table ? (q4 ? append_problem_kernel<false, 4, true> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, true>)
                            : (q4 ? append_problem_kernel<false, 4, false> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, false>));
     const size_t lds = n_buckets * sizeof(int32_t) * (table ? 1 + kBucketWords : 1);
-    kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, empty ? 1 : 0, h->meta[h->cur ^ 1]);
+    kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
   const int32_t block = (in.n <= kWave || rows > kSplitRows) ? kWave : 256;

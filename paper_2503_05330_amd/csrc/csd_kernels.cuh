@@ -57,13 +57,15 @@ __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, in
 
 // The same with one workgroup per problem, for batches of problems: slots are claimed on fill
 // counts in LDS.  (Atomics on memory run at the memory's side of the fabric here, 1.1e10 per
-// second whatever the addresses.)  empty: the index holds no postings yet.  TABLE: the buckets
+// second whatever the addresses.)  maybe_empty: the caller has appended nothing since the reset;
+// whether the index holds postings all the same (of a graph's appends) the paths' lengths tell, which
+// arrive while the LDS is cleared.  TABLE: the buckets
 // themselves are in LDS too, and go to memory as a whole.  The paths' ends are replaced in place, by
 // way of `ends`, rows like theirs (1024 problems of 16 x 1024 tokens 110.4 us; where `ends` stay the
 // new ends 109; 114 to 118 by way of LDS, with a lane per word before or after the loop or with the
 // tokens from the lanes that have them: registers and instructions of the loop are what counts here).
 template <bool FUZZY, int QC, bool TABLE>
-__global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, StepIn in, int32_t empty, int32_t* ends) {
+__global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, StepIn in, int32_t maybe_empty, int32_t* ends) {
   extern __shared__ int4 shared[];
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t p = (int32_t)blockIdx.x, n_buckets = (int32_t)ix.bucket_mask + 1;
@@ -87,11 +89,21 @@ __global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, Step
     if (i < ix.N) next.load(ix, in, (int64_t)p * ix.N + i, run * kRun, lane);   // uniform over the wave
   };
   request();
-  if (TABLE)
-    for (int32_t x = tid; x < n_buckets * 4; x += 1024)
-      table[x] = empty ? int4{-1, -1, -1, -1} : reinterpret_cast<const int4*>(gram)[x];
-  for (int32_t b = tid; b < n_buckets; b += 1024) fill[b] = empty ? 0 : gram[b * kBucketWords];
-  __syncthreads();
+  bool empty = false;
+  if (maybe_empty) {                                     // uniform over the launch
+    int32_t lens = 0;
+    for (int32_t j = tid; j < ix.N; j += 1024) lens |= ix.meta_old[((int64_t)p * ix.N + j) * ix.meta_stride];
+    if (TABLE)
+      for (int32_t x = tid; x < n_buckets * 4; x += 1024) table[x] = int4{-1, -1, -1, -1};
+    for (int32_t b = tid; b < n_buckets; b += 1024) fill[b] = 0;
+    empty = __syncthreads_or(lens) == 0;
+  }
+  if (!empty) {                                          // (each thread the words that it has cleared)
+    if (TABLE)
+      for (int32_t x = tid; x < n_buckets * 4; x += 1024) table[x] = reinterpret_cast<const int4*>(gram)[x];
+    for (int32_t b = tid; b < n_buckets; b += 1024) fill[b] = gram[b * kBucketWords];
+    __syncthreads();
+  }
   uint32_t flags = 0;
   while (i < ix.N) {
     const NewTokens4<QC> x = next;

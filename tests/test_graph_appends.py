@@ -103,3 +103,43 @@ def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, q
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
     assert drafted > 0
     assert by_graph.status() == by_call.status() == 0
+
+
+# the buckets of a problem in LDS, and their fill counts only
+@pytest.mark.parametrize("paths,max_len,edits,n", [(5, 300, 0, 40), (6, 800, 1, 360)])
+def test_a_bulk_append_keeps_what_a_graph_has_appended(paths, max_len, edits, n):
+    """An index that no call has appended to since its reset is not empty if a graph has: a bulk append
+    (24 problems: a workgroup per problem) keeps the graph's postings, captured or not."""
+    print("bulk behind a graph", paths, max_len, edits, n, flush=True)
+    rng = np.random.default_rng(paths + n)
+    P, L, V, k = 24, 6, 6, 3
+    make = lambda: binding.Index(P, paths, max_len, V, k, L, 0.5, 0, binding.MATCH_INDEX, device="cuda:0", max_edits=edits)
+    part = [_put(_tokens(rng, P, paths, n, V)) for _ in range(2)]
+    want = make()
+    for tokens in part:
+        want.append(tokens)
+    by_graph, mixed = make(), make()
+    fed = part[0].clone()
+    twice, _ = _captured(lambda: by_graph.append(fed))     # captured on an empty index, replayed twice
+    small = part[0][:, :, :1].contiguous()                 # (an append too small for a workgroup per problem)
+    few, _ = _captured(lambda: mixed.append(small))
+    mixed.reset()                                          # nothing of the capture has run: no call knows of the graph's tokens
+    for tokens in part:
+        fed.copy_(tokens)
+        torch.cuda.synchronize()
+        twice.replay()
+        torch.cuda.synchronize()
+    for t in range(n):
+        small.copy_(part[0][:, :, t:t + 1])
+        torch.cuda.synchronize()
+        few.replay()
+        torch.cuda.synchronize()
+    mixed.append(part[1])
+    ref = want.draft(k, L)
+    assert int(ref["length"].sum()) > 0
+    b = want.dump_matches(k, cap=1 << 22)
+    for ix in (by_graph, mixed):
+        _same(ix.draft(k, L), ref)
+        a = ix.dump_matches(k, cap=1 << 22)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+        assert ix.status() == 0
