@@ -321,13 +321,15 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
         slots[(gh[y].h & mask) * kBucketWords + 1 + claimed[y]] = posting[y];
         todo &= ~(1u << y);
       }
-    // first bucket full: on along the chain (the table holds more slots than postings: ends)
+    // first bucket full: on along the chain, once through all buckets at most (the table holds more
+    // slots than positions, but positions may have been filed twice: a launch that leaves the paths'
+    // new ends in the other buffer, captured and replayed; their postings are dropped when it is full)
     if (wave_ballot(todo != 0) == 0) continue;
 #pragma unroll
     for (int y = 0; y < kClaims; ++y) {
       bool looking = (todo >> y & 1u) != 0;
       uint32_t b = (gh[y].h + gh[y].step) & mask;
-      while (wave_ballot(looking) != 0) {                // uniform over the wave
+      for (uint32_t r = 1; r <= mask && wave_ballot(looking) != 0; ++r) {   // uniform over the wave
         if (looking) {
           int32_t c = fill[b];                           // (a full bucket is passed without an atomic)
           if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);

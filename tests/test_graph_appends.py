@@ -143,3 +143,31 @@ def test_a_bulk_append_keeps_what_a_graph_has_appended(paths, max_len, edits, n)
         a = ix.dump_matches(k, cap=1 << 22)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
         assert ix.status() == 0
+
+
+@pytest.mark.parametrize("edits", (0, 1))
+def test_a_bulk_append_to_a_full_index_ends(edits):
+    """A single captured step writes its ends to the other buffer: replayed again and again it files
+    the same positions, until the index has no slot left.  A bulk append to such an index ends (what
+    it finds no slot for is dropped), and a reset makes the handle whole again."""
+    print("bulk, full index", edits, flush=True)
+    rng = np.random.default_rng(edits)
+    P, N, T, V, k, L = 24, 4, 32, 5, 3, 4
+    make = lambda: binding.Index(P, N, T, V, k, L, 0.5, 0, binding.MATCH_INDEX, device="cuda:0", max_edits=edits)
+    past, more = _put(_tokens(rng, P, N, 8, V)), _put(_tokens(rng, P, N, 16, V))
+    ix = make()
+    ix.append(past)
+    token = past[:, :, 0].contiguous()
+    graph, _ = _captured(lambda: ix.step(token, None, None, 1, k, L))
+    for turn in range(300):                                # 4 postings a replay, or up to 16; 240 or 960 slots
+        token.copy_(past[:, :, turn % 8])
+        graph.replay()
+    torch.cuda.synchronize()
+    ix.append(more)
+    torch.cuda.synchronize()
+    ix.reset()
+    fresh = make()
+    for index in (ix, fresh):
+        index.append(more)
+    _same(ix.draft(k, L), fresh.draft(k, L))
+    assert ix.status() == 0
