@@ -218,11 +218,13 @@ int csd_step(csd_index* index, const int32_t* d_tokens, const float* d_probs,
  *   d_tokens [n_steps][P][N], d_probs same; d_draft_tokens [n_steps][P][N][draft_len],
  *   d_draft_len [n_steps][P][N], d_token_scores / d_path_scores likewise or NULL,
  *   d_targets [n_steps][P][N][draft_len] and d_accept_len [n_steps][P][N] or both NULL.
- * fused != 0: the steps run side by side, since all their tokens are known: one launch
- * appends them, a second one drafts every path at every step from the pool as it is at that
- * step (vocab <= 2^24; up to min(max(max_len / 4, 16), 2^19 / (P*N)) steps at a time;
- * csd_set_steps_per_launch chooses other forms), else one csd_step launch per step; fused == 0: csd_append, csd_draft
- * and csd_accept launches per step.  All give identical results. */
+ * fused != 0: the steps run side by side, since all their tokens are known: a launch
+ * appends them, and one more (three, from 2^15 drafts on) drafts every path at every step
+ * from the pool as it is at that step (vocab <= 2^24; up to min(max(max_len / 4, 16),
+ * 2^19 / (P*N)) steps at a time; csd_set_steps_per_launch chooses other forms).  Where a
+ * buffer that is written overlaps another one (a step's input in an earlier step's output),
+ * one csd_step launch per step.  fused == 0: csd_append, csd_draft and csd_accept launches
+ * per step.  All give identical results. */
 int csd_replay(csd_index* index, int32_t n_steps, const int32_t* d_tokens, const float* d_probs,
                int32_t query_len, int32_t draft_len, int32_t* d_draft_tokens,
                int32_t* d_draft_len, float* d_token_scores, float* d_path_scores,

@@ -518,6 +518,20 @@ int csd_step(csd_index* h, const int32_t* d_tokens, const float* d_probs, const 
   return rc;
 }
 
+// Whether one of the `n` buffers from `outputs` on overlaps another one of them all (null: none).
+struct Buffer {
+  const void* at;
+  size_t bytes;
+};
+static bool overlap(const Buffer* b, int outputs, int n) {
+  for (int x = outputs; x < n; ++x)
+    for (int y = 0; y < x; ++y) {
+      const uintptr_t px = reinterpret_cast<uintptr_t>(b[x].at), py = reinterpret_cast<uintptr_t>(b[y].at);
+      if (px && py && px < py + b[y].bytes && py < px + b[x].bytes) return true;
+    }
+  return false;
+}
+
 int csd_replay(csd_index* h, int32_t n_steps, const int32_t* d_tokens, const float* d_probs,
                int32_t query_len, int32_t draft_len, int32_t* d_draft_tokens, int32_t* d_draft_len,
                float* d_token_scores, float* d_path_scores, const int32_t* d_targets,
@@ -530,7 +544,14 @@ int csd_replay(csd_index* h, int32_t n_steps, const int32_t* d_tokens, const flo
   if (h->len_lo + n_steps > h->cfg.max_len) return CSD_ERR_CAPACITY;
   size_t rows = (size_t)h->view.P * h->view.N;
   size_t L = (size_t)draft_len;
-  if (fused && h->steps_per_launch > 1 && multi_step_ok(h)) {
+  // Where a step may read what an earlier one has written (a draft of one token fed as the next
+  // step's token), or steps write the same cells, they run one launch after the other.
+  const size_t words = (size_t)n_steps * rows * 4;
+  const Buffer buffers[] = {{d_tokens, words},           {d_probs, words},         {d_targets, words * L},
+                            {d_draft_tokens, words * L}, {d_draft_len, words},     {d_token_scores, words * L},
+                            {d_path_scores, words},      {d_accept_len, words}};
+  const bool apart = !overlap(buffers, 3, 8);
+  if (fused && apart && h->steps_per_launch > 1 && multi_step_ok(h)) {
     // the device-side loop: up to steps_per_launch steps per launch
     const bool general = h->cfg.pool_mode != CSD_POOL_DAG || h->view.options != 0;
     for (int32_t t = 0; t < n_steps;) {
@@ -559,7 +580,7 @@ int csd_replay(csd_index* h, int32_t n_steps, const int32_t* d_tokens, const flo
     }
     return CSD_OK;
   }
-  if (fused && h->steps_per_launch == 0 && h->replay_steps > 1 && n_steps > 1) {
+  if (fused && apart && h->steps_per_launch == 0 && h->replay_steps > 1 && n_steps > 1) {
     for (int32_t t = 0; t < n_steps;) {
       const int32_t chunk = n_steps - t < h->replay_steps ? n_steps - t : h->replay_steps;
       const DraftArgs a{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode,

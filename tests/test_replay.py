@@ -148,3 +148,42 @@ def test_a_captured_replay_goes_on_from_where_it_was():
         want = by_call.replay(S, put(tokens[turn]), None, k, L)
         for key in KEYS[:4]:
             assert torch.equal(out[key], want[key]), (turn, key)
+
+
+@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17)])
+def test_a_step_fed_with_what_an_earlier_one_drafted(problems, paths, steps):
+    """Drafts of one token written where the next step's tokens are read from: the steps see each
+    other's drafts, as they do in a launch per step."""
+    print("fed", problems, paths, steps, flush=True)
+    dev, V, k, warm = torch.device("cuda:0"), 40, 3, 60
+    start = np.random.default_rng(steps).integers(0, 7, size=(problems, paths, 1))
+    past = ((start + np.arange(warm)) % 13).astype(np.int32)     # the same cycle from different places on
+    cells = torch.full((steps + 1, problems, paths), 39, dtype=torch.int32, device=dev)
+    cells[0] = torch.from_numpy((past[:, :, -1] + 1) % 13).to(dev)
+    out = dict(tokens=cells[1:], length=torch.empty((steps, problems, paths), dtype=torch.int32, device=dev))
+    ix = binding.Index(problems, paths, 400, V, k, 1, device=dev)
+    ix.append(torch.from_numpy(past).to(dev))
+    assert problems == 1 or problems * paths * steps >= 1 << 15    # both forms of a replay side by side
+    ix.replay(steps, cells[:-1], None, k, 1, out=out, scores=False)
+    want = (past[None, :, :, -1] + 1 + np.arange(steps + 1)[:, None, None]) % 13
+    assert np.array_equal(cells.cpu().numpy(), want)
+    assert ix.status() == 0
+
+
+@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17)])
+def test_accepted_lengths_in_the_place_of_the_drafts(problems, paths, steps):
+    """One buffer for both: it holds the accepted lengths, which are written last."""
+    rng = np.random.default_rng(steps + 1)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    V, k, L, S = (6 if problems == 1 else 40), 2, 4, steps  # (rows with few matches: four lanes each)
+    tokens, targets = (rng.integers(0, V, size=s).astype(np.int32) for s in ((S, problems, paths), (S, problems, paths, L)))
+    past = rng.integers(0, V, size=(problems, paths, 100)).astype(np.int32)
+    accepted = []
+    for shared in (False, True):
+        ix = binding.Index(problems, paths, 200, V, k, L, device="cuda:0")
+        ix.append(put(past))
+        out = ix._outputs(L, True, lead=(S,))
+        where = out["length"] if shared else torch.empty_like(out["length"])
+        ix.replay(S, put(tokens), None, k, L, out=out, targets=put(targets), accept_out=where)
+        accepted.append(where)
+    assert torch.equal(*accepted) and int(accepted[0].sum()) > 0
