@@ -64,6 +64,7 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
   size_t tok, pq, meta, status, gram, slices, done, step_meta, rest, rest_list, total;
+  size_t needed;                // up to `done`: what lies behind is there for speed
   int32_t n_slices;             // workgroups that share a row's scan (scan mode, few rows)
   int32_t replay_steps;         // steps of a replay that run side by side
   int32_t meta_stride, eshift;
@@ -170,7 +171,7 @@ Layout make_layout(const csd_config* c) {
     if (l.n_slices > 1)         // per row the match list and a state word
       at += align_up(rows * LdsScan::kMatch * sizeof(Match)) + align_up(rows * sizeof(u64));
   }
-  l.done = at;
+  l.needed = l.done = at;
   at += align_up((rows < kSplitRows ? rows : kSplitRows) * kBucketWords * sizeof(int32_t));
   // the paths' ends after each step of a replay, for as many steps as give kReplayDrafts drafts
   l.replay_steps = 0;
@@ -211,7 +212,7 @@ struct csd_index {
   int cur;
   size_t gram_words;
   ScanSlices slices;
-  int32_t* done;                // [min(P * N, kSplitRows)][16] see append_kernel
+  int32_t* done;                // [min(P * N, kSplitRows)][16] see append_kernel; null: one wave per row
   bool indexed;
   uint32_t alpha_q;
   int64_t len_lo, len_hi;       // host-side bounds on every path's length
@@ -298,9 +299,10 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
     kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
-  const int32_t block = (in.n <= kWave || rows > kSplitRows) ? kWave : 256;
+  const bool split = rows <= kSplitRows && h->done;
+  const int32_t block = (in.n <= kWave || !split) ? kWave : 256;
   int64_t chunks = (in.n + block - 1) / block;
-  const int64_t most = rows <= kSplitRows ? ((int64_t)1 << 23) / rows : 1;   // (bounds the grid; a workgroup loops over the rest)
+  const int64_t most = split ? ((int64_t)1 << 23) / rows : 1;   // (bounds the grid; a workgroup loops over the rest)
   chunks = chunks < most ? chunks : most;
   auto* kernel = !h->indexed ? append_kernel<false, false, 4>
                  : v.eps == 0 ? (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>)
@@ -394,7 +396,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   if (rc != CSD_OK) return rc;
   if (!d_workspace) return CSD_ERR_INVALID_ARG;
   Layout l = make_layout(cfg);
-  if (workspace_bytes < l.total || (reinterpret_cast<uintptr_t>(d_workspace) % kAlign) != 0)
+  if (workspace_bytes < l.needed || (reinterpret_cast<uintptr_t>(d_workspace) % kAlign) != 0)
     return CSD_ERR_WORKSPACE;
   csd_index* h = new (std::nothrow) csd_index;
   if (!h) return CSD_ERR_INVALID_ARG;
@@ -423,7 +425,8 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
     h->slices.state = reinterpret_cast<u64*>(base + l.slices +
                                              align_up(rows * LdsScan::kMatch * sizeof(Match)));
   }
-  h->done = reinterpret_cast<int32_t*>(base + l.done);
+  const bool whole = workspace_bytes >= l.total;         // else: as sized before there was that part
+  h->done = whole ? reinterpret_cast<int32_t*>(base + l.done) : nullptr;
   h->view.P = cfg->n_problems;
   h->view.N = cfg->n_paths;
   h->view.max_len = cfg->max_len;
@@ -436,7 +439,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   h->step_meta = reinterpret_cast<int32_t*>(base + l.step_meta);
   h->rest = reinterpret_cast<u64*>(base + l.rest);
   h->rest_list = reinterpret_cast<int32_t*>(base + l.rest_list);
-  h->replay_steps = l.replay_steps;
+  h->replay_steps = whole ? l.replay_steps : 0;
   rc = reset(h, true, stream);
   if (rc != CSD_OK) {
     delete h;

@@ -187,3 +187,38 @@ def test_accepted_lengths_in_the_place_of_the_drafts(problems, paths, steps):
         ix.replay(S, put(tokens), None, k, L, out=out, targets=put(targets), accept_out=where)
         accepted.append(where)
     assert torch.equal(*accepted) and int(accepted[0].sum()) > 0
+
+
+@pytest.mark.parametrize("edits,flags", [(0, binding.MATCH_INDEX), (1, binding.MATCH_INDEX), (1, binding.MATCH_SCAN)])
+def test_a_workspace_without_the_part_for_speed(monkeypatch, edits, flags):
+    """The size that histories, ends, index and shared scans take is enough; a byte less is not."""
+    P, N, T, V, k, L, S = 2, 5, 900, 20, 3, 6, 30
+    up = lambda n: (n + 255) // 256 * 256
+    indexed = flags == binding.MATCH_INDEX
+    stride = (1 + k + (1 if indexed and edits else 0) + 3) // 4 * 4
+    size = 2 * up((P * N * T + 32) * 4) + 2 * up(P * N * stride * 4) + up(16)
+    if indexed:
+        buckets = 4
+        while buckets * 8 < N * T * (k + 1 if edits else 1):
+            buckets *= 2
+        size += up(P * buckets * 64)
+    else:                                                  # a list of 4096 matches and a state word a path
+        size += up(P * N * 4096 * 8) + up(P * N * 8)
+    rng = np.random.default_rng(2)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    past, more, tokens = (put(rng.integers(0, V, size=s).astype(np.int32)) for s in ((P, N, 600), (P, N, 70), (S, P, N)))
+    make = lambda: binding.Index(P, N, T, V, k, L, 1.0, 0, flags, device="cuda:0", max_edits=edits)
+    got = []
+    full = binding.workspace_bytes(binding.Config(P, N, T, V, k, L, 1.0, 0, flags, edits, 0))
+    for nbytes in (full, size):
+        monkeypatch.setattr(binding, "workspace_bytes", lambda cfg: nbytes)
+        ix = make()
+        ix.append(past)
+        ix.append(more)
+        got.append(ix.replay(S, tokens, None, k, L, targets=torch.zeros((S, P, N, L), dtype=torch.int32, device="cuda:0")))
+        assert ix.status() == 0
+    _same(*got)
+    assert int(got[0]["length"].sum()) > 0 and size < full
+    monkeypatch.setattr(binding, "workspace_bytes", lambda cfg: size - 1)
+    with pytest.raises(binding.CsdError):
+        make()
