@@ -172,7 +172,7 @@ Layout make_layout(const csd_config* c) {
       at += align_up(rows * LdsScan::kMatch * sizeof(Match)) + align_up(rows * sizeof(u64));
   }
   l.needed = l.done = at;
-  at += align_up((rows < kSplitRows ? rows : kSplitRows) * kBucketWords * sizeof(int32_t));
+  at += align_up((rows < (size_t)kSplitRows ? rows : (size_t)kSplitRows) * kBucketWords * sizeof(int32_t));
   // the paths' ends after each step of a replay, for as many steps as give kReplayDrafts drafts
   l.replay_steps = 0;
   l.step_meta = l.rest = l.rest_list = at;
@@ -279,6 +279,10 @@ constexpr int32_t kOwnedProblems = 24;
 // 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
 constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
 
+// Workgroups of an append that the chip holds at once, and rows from which on one with counts has a
+// wave for each.
+constexpr int64_t kAppendGroups = 2048, kWaveRows = 4096;
+
 // Enqueues the append of a step's tokens.  The paths' ends are replaced in place and `cur` stays, as
 // with csd_draft: captured once, the launch appends again at every replay of the graph.
 // maybe_empty: no call has appended since the reset (a graph may have: the host does not see that).
@@ -299,11 +303,15 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
     kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
-  const bool split = rows <= kSplitRows && h->done;
-  const int32_t block = (in.n <= kWave || !split) ? kWave : 256;
-  int64_t chunks = (in.n + block - 1) / block;
-  const int64_t most = split ? ((int64_t)1 << 23) / rows : 1;   // (bounds the grid; a workgroup loops over the rest)
-  chunks = chunks < most ? chunks : most;
+  // several workgroups a row; with counts, which may leave most of them idle, no more than the chip
+  // holds at once, and beyond that a wave a row (us, histories half full, up to 16 of 2048 tokens taken
+  // of each path / half of them on average: 24 problems of 64 paths, a workgroup per 256 tokens offered
+  // 26 / 113, so 8 / 111; 1024 problems of 16 paths, 512 offered, 54 / 294, so 16 / 235)
+  const bool many = !h->done || rows > (in.counts ? kWaveRows : kSplitRows);
+  const int32_t block = (in.n <= kWave || many) ? kWave : 256;
+  int64_t chunks = (in.n + block - 1) / block;           // (bounds the grid; a workgroup loops over the rest)
+  const int64_t most = many ? 1 : (in.counts ? kAppendGroups : (int64_t)1 << 23) / rows;
+  chunks = chunks < most ? chunks : (most < 1 ? 1 : most);
   auto* kernel = !h->indexed ? append_kernel<false, false, 4>
                  : v.eps == 0 ? (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>)
                               : (q4 ? append_kernel<true, true, 4> : append_kernel<true, true, CSD_MAX_QUERY_LEN>);

@@ -509,8 +509,8 @@ struct NewTokens4 {
 // Stores a share of what a step appends to path i of problem p: tokens, quantised probabilities
 // and postings of the step's tokens t_first + tid, then every t_stride-th.  Called by whole waves,
 // tid counting the threads that share the work.  `head`: this share raises the status bit of a full
-// path.  at_end(end): called once by every wave, when all that it needs of the path's old end has
-// arrived; `end` is the new one (end_word).
+// path.  at_end(end, tokens taken): called once by every wave, when all that it needs of the path's
+// old end has arrived; `end` is the new one (end_word).
 template <bool INDEX, bool FUZZY, int QC, class AT_END>
 __device__ __forceinline__ void append_positions(const IndexView& ix, const StepIn& in, int32_t p,
                                                  int32_t i, int32_t t_first, int32_t t_stride,
@@ -532,7 +532,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
     auto sign_off = [&]() {
       if (!last) return;
       consume_here(end);
-      at_end(end);
+      at_end(end, cnt);
     };
     if constexpr (INDEX) {
 #pragma unroll
@@ -551,7 +551,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
 template <bool INDEX, bool FUZZY, int QC>
 __device__ __forceinline__ void append_path(const IndexView& ix, const StepIn& in, int32_t p, int32_t i,
                                             int32_t threads, int tid) {
-  append_positions<INDEX, FUZZY, QC>(ix, in, p, i, 0, threads, true, tid, [&](int32_t end) {
+  append_positions<INDEX, FUZZY, QC>(ix, in, p, i, 0, threads, true, tid, [&](int32_t end, int32_t) {
     if (tid < kWave) store_end_word(ix, (int64_t)p * ix.N + i, end, tid);   // uniform over the wave
   });
 }

@@ -12,9 +12,9 @@
 
 namespace csd {
 
-// Rows (problem, path) up to which several workgroups share the append of a path: more rows fill the
-// chip with one each.
-constexpr int64_t kSplitRows = 4096;
+// Rows (problem, path) up to which several waves share the append of a path: more rows fill the chip
+// with one each.
+constexpr int64_t kSplitRows = 1 << 16;
 
 static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t gram_words, ScanSlices sl,
                                                            int32_t* done) {
@@ -32,7 +32,8 @@ static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t
 
 // Append only, any number of tokens per path: `chunks` workgroups per (problem, path), a thread
 // per new position.  The path's end is replaced in place (a captured launch goes on from where the
-// one before it was) by the row's wave that reads the old end last.  done: for each row, a line
+// one before it was) by the row's wave that reads the old end last, of those that have a position
+// to append (another one finds nothing to do at the new end either).  done: for each row, a line
 // apart, the waves that have read its end; 0 between launches.  They sign off while their claims are
 // in flight: 64 paths x 4096 tokens take 22.5 us, with a second buffer for the new ends and no
 // sign-off 21.7, with the counts of sixteen rows to a line 47 (an atomic takes a line of memory 12 ns).
@@ -41,15 +42,19 @@ __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, in
   const int32_t row = (int32_t)blockIdx.x / chunks, chunk = (int32_t)blockIdx.x - row * chunks;
   const int32_t p = row / ix.N, tid = (int32_t)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t waves = chunks * (int32_t)(blockDim.x / kWave);   // of the row
-  int32_t before = -1, word = 0;                         // before: waves that signed off earlier
+  const int32_t wave = chunk * (int32_t)(blockDim.x / kWave) + (tid >> 6);
+  int32_t before = -1, busy = 0, word = 0;               // before: waves that signed off earlier
   append_positions<INDEX, FUZZY, QC>(
       ix, in, p, row - p * ix.N, chunk * (int32_t)blockDim.x, chunks * (int32_t)blockDim.x, chunk == 0, tid,
-      [&](int32_t end) {
+      [&](int32_t end, int32_t cnt) {
+        const int32_t parts = (cnt + kWave - 1) / kWave;
+        busy = __builtin_amdgcn_readfirstlane(parts < waves ? parts : waves);
         word = end;
-        if (waves == 1) store_end_word(ix, row, word, lane);
+        if (wave >= busy) return;
+        if (busy == 1) store_end_word(ix, row, word, lane);
         else if (lane == 0) before = atomicAdd(&done[row * kBucketWords], 1);
       });
-  if (waves > 1 && __builtin_amdgcn_readfirstlane(before) == waves - 1) {
+  if (busy > 1 && __builtin_amdgcn_readfirstlane(before) == busy - 1) {
     store_end_word(ix, row, word, lane);
     if (lane == 0) done[row * kBucketWords] = 0;
   }
