@@ -267,21 +267,36 @@ bool multi_step_ok(const csd_index* h) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->view.N <= 16;
 }
 
-// Problems from which on an append that fills a good part of their indexes runs with one workgroup
-// per problem.  Measured, us, a thread per position with atomics on memory / a workgroup per
-// problem (the time is the problem's, 256 of them run side by side), histories appended as a
-// whole: 16 paths x 1024 tokens: 1 problem 14 / 24, 16: 28 / 31, 32: 42 / 31, 64: 70 / 29,
-// 1024: 1379 / 110; 32 x 2048: 16: 64 / 76, 32: 129 / 91; 64 x 4096: 16: 286 / 360,
-// 32: 593 / 359; one edit, 8 x 1024: 16: 51 / 52, 64: 134 / 58.
-constexpr int32_t kOwnedProblems = 24;
-// ... and their fill counts fit a CU's LDS (128 KB); with up to 2048 buckets the buckets fit too
-// (136 KB: one stream of whole lines instead of a line written for every posting; 1024 problems of
-// 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
+// The fill counts of a problem that one workgroup appends to fit a CU's LDS (128 KB); with up to 2048
+// buckets the buckets fit too (136 KB: one stream of whole lines instead of a line written for every
+// posting; 1024 problems of 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
 constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
+
+// An append with a workgroup per problem (append_problem_kernel) reads and writes all fill counts,
+// whatever it files; its time is the problem's, 256 of them run side by side.  With a thread per
+// position and atomics on memory the time is that of all postings.  So the first form is taken from
+// as many problems P on as postings c of a problem and buckets b of its index make it the better one:
+//   (P - 8) c >= 96 b (64 b with one edit), c >= 5/8 b, and a few waves' worth of postings.
+// Measured, us, atomics / a workgroup per problem, 2048 buckets (16 paths x 1024), index half full:
+// c / b = 1/2, P = 24, 64, 256, 1024: 6.8 / 14, 9 / 15, 18 / 21, 75 / 68; c / b = 1: 8 / 14, 12 / 15,
+// 36 / 21, 112 / 69; 2: 11 / 15, 18 / 15, 63 / 21, 228 / 71; 4: 16 / 18, 30 / 19, 93 / 25, 481 / 90.
+// 8192 buckets (32 x 2048), c / b = 1, 4, P = 24: 15 / 23, 42 / 52; 128: 68 / 42, 178 / 82; 512:
+// 210 / 167, 840 / 396.  32768 (64 x 4096), P = 24: 31 / 58, 139 / 183; 128: 118 / 163, 402 / 365 (2).
+// One edit, 4096 (8 x 1024), c / b = 1/2, 2, 4: P = 24: 8 / 14, 16 / 17, 26 / 23; 128: 18 / 20, 74 / 25,
+// 129 / 36.  128 (4 x 256), c / b = 1, 2, 4: P = 1024: 12 / 16, 19 / 17, 42 / 18; 4096: 52 / 51, 89 / 53,
+// 162 / 57.
+bool own_problem(const csd_index* h, const IndexView& v, int32_t n) {
+  const int64_t b = (int64_t)v.bucket_mask + 1, c = (int64_t)v.N * n * (v.eps > 0 ? v.kmax + 1 : 1);
+  return h->indexed && b <= kOwnedBuckets && 8 * c >= 5 * b && c >= 4 * kWave &&
+         (v.P - 8) * c >= (v.eps > 0 ? 64 : 96) * b;
+}
 
 // Workgroups of an append that the chip holds at once, and rows from which on one with counts has a
 // wave for each.
 constexpr int64_t kAppendGroups = 2048, kWaveRows = 4096;
+// Postings of an append of many rows between which the claims look at the fill counts first, in
+// indexes of up to 128 MB in all (of 256 MB: 128 problems of 64 paths, 64 tokens, 39 / 45 us).
+constexpr int64_t kLookFrom = 3 << 17, kLookTo = 1 << 20, kLookBuckets = 1 << 21;
 
 // Enqueues the append of a step's tokens.  The paths' ends are replaced in place and `cur` stays, as
 // with csd_draft: captured once, the launch appends again at every replay of the graph.
@@ -291,8 +306,7 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
   const int64_t rows = (int64_t)v.P * v.N;
   const bool q4 = v.kmax <= 4;
   const int64_t n_buckets = (int64_t)v.bucket_mask + 1;
-  // (an append of fewer tokens is not worth reading and writing all fill counts)
-  if (h->indexed && v.P >= kOwnedProblems && n_buckets <= kOwnedBuckets && (int64_t)v.N * in.n * 2 >= n_buckets) {
+  if (own_problem(h, v, in.n)) {
     const bool table = n_buckets <= kTableBuckets;
     auto* kernel =
         v.eps > 0 ? (table ? (q4 ? append_problem_kernel<true, 4, true> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, true>)
@@ -307,14 +321,21 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
   // holds at once, and beyond that a wave a row (us, histories half full, up to 16 of 2048 tokens taken
   // of each path / half of them on average: 24 problems of 64 paths, a workgroup per 256 tokens offered
   // 26 / 113, so 8 / 111; 1024 problems of 16 paths, 512 offered, 54 / 294, so 16 / 235)
+  // many rows, a few tokens each: a look at the fill counts before the claims (us, without / with;
+  // 1024 problems of 16 paths, half full, 16 tokens: 18 / 19, 24: 31 / 26, 32: 40 / 32, 64: 77 / 56, 512:
+  // 450 / 534; 4096 of 4, 16: 20 / 20, 32: 44 / 33; 256 of 16, 64: 19 / 21, 128: 36 / 32, 512: 93 / 133;
+  // one edit, 128 of 8, 64: 18 / 30)
+  const bool look = rows >= kWaveRows && !in.counts && rows * in.n >= kLookFrom && rows * in.n <= kLookTo &&
+                    v.P * n_buckets <= kLookBuckets;
   const bool many = !h->done || rows > (in.counts ? kWaveRows : kSplitRows);
   const int32_t block = (in.n <= kWave || many) ? kWave : 256;
   int64_t chunks = (in.n + block - 1) / block;           // (bounds the grid; a workgroup loops over the rest)
   const int64_t most = many ? 1 : (in.counts ? kAppendGroups : (int64_t)1 << 23) / rows;
   chunks = chunks < most ? chunks : (most < 1 ? 1 : most);
   auto* kernel = !h->indexed ? append_kernel<false, false, 4>
-                 : v.eps == 0 ? (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>)
-                              : (q4 ? append_kernel<true, true, 4> : append_kernel<true, true, CSD_MAX_QUERY_LEN>);
+                 : v.eps > 0 ? (q4 ? append_kernel<true, true, 4> : append_kernel<true, true, CSD_MAX_QUERY_LEN>)
+                 : look      ? (q4 ? append_kernel<true, false, 4, true> : append_kernel<true, false, CSD_MAX_QUERY_LEN, true>)
+                             : (q4 ? append_kernel<true, false, 4> : append_kernel<true, false, CSD_MAX_QUERY_LEN>);
   kernel<<<(uint32_t)(rows * chunks), block, 0, st>>>(v, in, (int32_t)chunks, h->done);
 }
 

@@ -229,7 +229,8 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
 // on average when a problem's histories are full, so few claims miss.  Those go on as claims in
 // the next three buckets, a lane at a time for itself, and what is left then (the long chain of
 // a frequent gram) is the whole wave's.  meanwhile(): called while the first claims are in flight.
-template <bool FUZZY, int QC, class MEANWHILE>
+// LOOK: the fill counts are looked at before all the same (see launch_append).
+template <bool FUZZY, int QC, bool LOOK = false, class MEANWHILE>
 __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int32_t kmax,
                                                const int32_t (&G)[QC], bool mine, int32_t pos, int lane,
                                                MEANWHILE&& meanwhile) {
@@ -245,9 +246,16 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
     claimed[v] = kBucketSlots;
     todo |= live ? 1u << v : 0u;
   }
+  uint32_t claims = todo;
+  if (LOOK) {
+#pragma unroll
+    for (int v = 0; v < kVariants; ++v)
+      claims &= gram[(int64_t)at[v] * kBucketWords] < kBucketSlots ? ~0u : ~(1u << v);
+    consume_here(claims);
+  }
 #pragma unroll
   for (int v = 0; v < kVariants; ++v)
-    if (todo >> v & 1u) claimed[v] = atomicAdd(gram + (int64_t)at[v] * kBucketWords, 1);
+    if (claims >> v & 1u) claimed[v] = atomicAdd(gram + (int64_t)at[v] * kBucketWords, 1);
   meanwhile();
 #pragma unroll
   for (int v = 0; v < kVariants; ++v)
@@ -511,7 +519,7 @@ struct NewTokens4 {
 // tid counting the threads that share the work.  `head`: this share raises the status bit of a full
 // path.  at_end(end, tokens taken): called once by every wave, when all that it needs of the path's
 // old end has arrived; `end` is the new one (end_word).
-template <bool INDEX, bool FUZZY, int QC, class AT_END>
+template <bool INDEX, bool FUZZY, int QC, bool LOOK = false, class AT_END>
 __device__ __forceinline__ void append_positions(const IndexView& ix, const StepIn& in, int32_t p,
                                                  int32_t i, int32_t t_first, int32_t t_stride,
                                                  bool head, int tid, AT_END&& at_end) {
@@ -537,7 +545,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
     if constexpr (INDEX) {
 #pragma unroll
       for (int a = 0; a < QC; ++a) consume_here(x.G[a]);
-      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, sign_off);
+      file_positions<FUZZY, QC, LOOK>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, sign_off);
     } else {
       sign_off();
     }

@@ -37,14 +37,14 @@ static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t
 // apart, the waves that have read its end; 0 between launches.  They sign off while their claims are
 // in flight: 64 paths x 4096 tokens take 22.5 us, with a second buffer for the new ends and no
 // sign-off 21.7, with the counts of sixteen rows to a line 47 (an atomic takes a line of memory 12 ns).
-template <bool INDEX, bool FUZZY, int QC>
+template <bool INDEX, bool FUZZY, int QC, bool LOOK = false>
 __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, int32_t chunks, int32_t* done) {
   const int32_t row = (int32_t)blockIdx.x / chunks, chunk = (int32_t)blockIdx.x - row * chunks;
   const int32_t p = row / ix.N, tid = (int32_t)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t waves = chunks * (int32_t)(blockDim.x / kWave);   // of the row
   const int32_t wave = chunk * (int32_t)(blockDim.x / kWave) + (tid >> 6);
   int32_t before = -1, busy = 0, word = 0;               // before: waves that signed off earlier
-  append_positions<INDEX, FUZZY, QC>(
+  append_positions<INDEX, FUZZY, QC, LOOK>(
       ix, in, p, row - p * ix.N, chunk * (int32_t)blockDim.x, chunks * (int32_t)blockDim.x, chunk == 0, tid,
       [&](int32_t end, int32_t cnt) {
         const int32_t parts = (cnt + kWave - 1) / kWave;
@@ -64,7 +64,10 @@ __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, in
 // counts in LDS.  (Atomics on memory run at the memory's side of the fabric here, 1.1e10 per
 // second whatever the addresses.)  maybe_empty: the caller has appended nothing since the reset;
 // whether the index holds postings all the same (of a graph's appends) the paths' lengths tell, which
-// arrive while the LDS is cleared.  TABLE: the buckets
+// arrive while the LDS is cleared.  With counts a problem that takes less than a posting per bucket
+// files with atomics on memory after all (us, up to 16 tokens taken of those offered / half of them
+// on average, without and with that: 1024 problems of 16 paths, 512 offered: 77, 26 / 82, 82; 128 of 64,
+// 2048: 202, 21 / 405, 406; 4096 of 4, 128: 53, 32 / 55, 61).  TABLE: the buckets
 // themselves are in LDS too, and go to memory as a whole.  The paths' ends are replaced in place, by
 // way of `ends`, rows like theirs (1024 problems of 16 x 1024 tokens 110.4 us; where `ends` stay the
 // new ends 109; 114 to 118 by way of LDS, with a lane per word before or after the loop or with the
@@ -94,6 +97,20 @@ __global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, Step
     if (i < ix.N) next.load(ix, in, (int64_t)p * ix.N + i, run * kRun, lane);   // uniform over the wave
   };
   request();
+  if (in.counts) {                                       // (every wave adds them up for itself: no barrier)
+    int32_t sum = 0;
+    for (int32_t j = lane; j < ix.N; j += kWave) {
+      const int32_t want = in.counts[(int64_t)p * ix.N + j];
+      sum += want < 0 ? 0 : (want > in.n ? in.n : want);
+    }
+#pragma unroll
+    for (int x = 1; x < kWave; x *= 2) sum += __shfl_xor(sum, x);
+    if ((int64_t)__builtin_amdgcn_readfirstlane(sum) * (FUZZY ? ix.kmax + 1 : 1) < n_buckets) {
+      for (int32_t j = __builtin_amdgcn_readfirstlane(tid >> 6); j < ix.N; j += 16)
+        append_path<true, FUZZY, QC>(ix, in, p, j, kWave, lane);
+      return;
+    }
+  }
   bool empty = false;
   if (maybe_empty) {                                     // uniform over the launch
     int32_t lens = 0;

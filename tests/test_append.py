@@ -1,6 +1,6 @@
-"""Appends of many tokens per call against the oracle: the kernel with a thread per new position,
-the one with a workgroup per problem (24 problems and more), with the buckets and with the fill
-counts only in LDS, on an empty and on a filled index."""
+"""Appends of many tokens per call against the oracle: the kernel with a thread per new position and
+the one with a workgroup per problem, with the buckets and with the fill counts only in LDS, on an
+empty and on a filled index."""
 import numpy as np
 import pytest
 import torch
@@ -26,26 +26,64 @@ pytestmark = pytest.mark.gpu
 ])
 @pytest.mark.parametrize("ragged", (False, True))
 def test_appends_of_many_tokens(oracle, problems, vocab, query, edits, flags, sizes, ragged):
+    _appends(oracle, problems, 5, 720, vocab, query, edits, flags, sizes, ragged)
+
+
+# what takes a workgroup per problem: buckets in LDS (up to 2048 of them), fill counts only (more), grams
+# of up to four tokens and longer ones; with counts some problems take less than a posting per bucket.
+# (the assertion repeats the library's rule for the first size)
+@pytest.mark.parametrize("problems,paths,max_len,query,edits,sizes", [
+    (64, 5, 720, 3, 0, (255, 1, 257, 180)),
+    (64, 5, 720, 6, 0, (258, 5, 200)),
+    (40, 5, 720, 3, 1, (254, 253)),
+    (40, 5, 400, 6, 1, (130, 125, 120)),
+    (64, 20, 1000, 3, 0, (400, 370)),
+    (64, 20, 1000, 6, 0, (370, 361)),
+    (40, 8, 800, 3, 1, (300, 290)),
+    (40, 5, 720, 6, 1, (251, 3, 256)),
+])
+@pytest.mark.parametrize("ragged", (False, True))
+def test_appends_by_a_workgroup_per_problem(oracle, problems, paths, max_len, query, edits, sizes, ragged):
+    postings = query + 1 if edits else 1
+    buckets = 4
+    while buckets * 8 < paths * max_len * postings:
+        buckets *= 2
+    filed = paths * sizes[0] * postings
+    assert 8 * filed >= 5 * buckets and (problems - 8) * filed >= (64 if edits else 96) * buckets
+    _appends(oracle, problems, paths, max_len, 40, query, edits, binding.MATCH_INDEX, sizes, ragged, few=3)
+
+
+def test_appends_of_a_few_tokens_to_many_rows(oracle):
+    """8192 rows, 50 to 63 tokens each: the claims look at the fill counts first; two symbols: at full ones."""
+    for vocab, query in ((40, 3), (2, 5)):
+        _appends(oracle, 2048, 4, 200, vocab, query, 0, binding.MATCH_INDEX, (50, 63, 60), False)
+
+
+def _appends(oracle, problems, N, T, vocab, query, edits, flags, sizes, ragged, few=0):
+    """few: every so many problems take an eighth of the counts only."""
     rng = np.random.default_rng(problems * 1000 + vocab + query + edits)
-    N, T, L = 5, 720, 6
+    L = 6
     tokens = rng.integers(0, vocab, size=(problems, N, T)).astype(np.int32)
     motif = rng.integers(0, vocab, size=(problems, 1, 60)).astype(np.int32)
+    cells = T // 60 * 60
     shared = rng.random((problems, N, T // 60)) < 0.5          # segments that the paths have in common
-    tokens = np.where(np.repeat(shared, 60, axis=2), np.tile(motif, (1, 1, T // 60)), tokens)
+    tokens[:, :, :cells] = np.where(np.repeat(shared, 60, axis=2), np.tile(motif, (1, 1, T // 60)), tokens[:, :, :cells])
     probs = rng.random(tokens.shape).astype(np.float32)
     dev = torch.device("cuda:0")
     ix = binding.Index(problems, N, T, vocab, query, L, 0.5, 0, flags, device=dev, max_edits=edits)
     at = np.zeros((problems, N), dtype=np.int64)
     for turn, n in enumerate(sizes):
-        print("append", problems, vocab, query, edits, flags, n, ragged, flush=True)
+        print("append", problems, N, T, vocab, query, edits, flags, n, ragged, flush=True)
         counts = rng.integers(0, n + 1, size=at.shape) if ragged else np.full(at.shape, n)
+        if ragged and few:
+            counts[::few] //= 8
         idx = np.minimum(at[..., None] + np.arange(n), T - 1)
         step = lambda a: torch.from_numpy(np.ascontiguousarray(np.take_along_axis(a, idx, axis=2))).to(dev)
         ix.append(step(tokens), None if turn % 2 else step(probs),
                   torch.from_numpy(counts.astype(np.int32)).to(dev) if ragged else None, n)
         if turn % 2:                                           # no probabilities: all 1
-            for p, i in np.ndindex(at.shape):
-                probs[p, i, at[p, i]:at[p, i] + counts[p, i]] = 1.0
+            ones = np.arange(T) - at[..., None]
+            probs[(ones >= 0) & (ones < counts[..., None])] = 1.0
         at += counts
         lens = at.astype(np.int32)
         out = ix.draft(query, L)
@@ -53,8 +91,8 @@ def test_appends_of_many_tokens(oracle, problems, vocab, query, edits, flags, si
         assert np.array_equal(out["tokens"].cpu().numpy(), want["draft"])
         assert np.array_equal(out["length"].cpu().numpy(), want["draft_len"])
         assert np.array_equal(out["path_scores"].cpu().numpy(), want["path_scores"].astype(np.float32))
-    je, off = ix.dump_matches(query, cap=1 << 22)
-    for r in range(0, problems * N, 1 if problems == 1 else 7):
+    je, off = ix.dump_matches(query, cap=1 << 24)
+    for r in range(0, problems * N, 1 if problems == 1 else 7 if problems < 1000 else 97):
         p, i = divmod(r, N)
         assert np.array_equal(je[off[r]:off[r + 1]], oracle.matches(tokens[p], lens[p], i, query, eps=edits))
     assert ix.status() == 0
@@ -63,7 +101,7 @@ def test_appends_of_many_tokens(oracle, problems, vocab, query, edits, flags, si
 def test_an_append_that_does_not_fit_is_clipped(oracle):
     """Counts beyond max_len: clipped, with the status bit, by both kernels."""
     rng = np.random.default_rng(9)
-    for problems in (1, 24):
+    for problems in (1, 72):                                  # (a thread per position / a workgroup per problem)
         tokens = rng.integers(0, 30, size=(problems, 4, 200)).astype(np.int32)
         ix = binding.Index(problems, 4, 150, 30, 3, 4, flags=binding.MATCH_INDEX)
         dev = torch.device("cuda:0")

@@ -36,8 +36,8 @@ def _captured(call):
     return graph, kept
 
 
-# a workgroup for a path's tokens and several of them; a workgroup per problem (24 problems, a good
-# part of the index at once); matching by scan; a step that appends first (many tokens, or one-edit
+# a workgroup for a path's tokens and several of them; a workgroup per problem (many problems, a good
+# part of their indexes at once); matching by scan; a step that appends first (many tokens, or one-edit
 # matching); the ends of an odd number of appends
 @pytest.mark.parametrize("problems,paths,max_len,query,edits,flags,call,n", [
     (1, 4, 4000, 3, 0, binding.MATCH_INDEX, "append", 1),
@@ -46,11 +46,12 @@ def _captured(call):
     (1, 4, 2000, 3, 1, binding.MATCH_INDEX, "append", 300),
     (1, 4, 2000, 3, 0, binding.MATCH_SCAN, "append", 300),
     (1, 4, 700, 3, 1, binding.MATCH_SCAN, "append", 65),
-    (24, 5, 300, 3, 0, binding.MATCH_INDEX, "append", 40),
-    (24, 5, 720, 3, 1, binding.MATCH_INDEX, "append", 210),
+    (64, 5, 300, 3, 0, binding.MATCH_INDEX, "append", 90),
+    (64, 20, 1000, 3, 0, binding.MATCH_INDEX, "append", 352),
+    (40, 5, 720, 3, 1, binding.MATCH_INDEX, "append", 210),
     (1, 4, 900, 3, 0, binding.MATCH_INDEX, "step", 70),
     (2, 5, 400, 3, 1, binding.MATCH_INDEX, "step", 3),
-    (24, 5, 720, 3, 0, binding.MATCH_INDEX, "step", 100),
+    (112, 5, 720, 3, 0, binding.MATCH_INDEX, "step", 100),
     (2, 5, 400, 3, 0, binding.MATCH_INDEX, "replay", 3),
     (2, 5, 400, 3, 1, binding.MATCH_SCAN, "replay", 3),
     (2, 5, 400, 5, 0, binding.MATCH_INDEX, "loop", 3),
@@ -59,7 +60,8 @@ def _captured(call):
 def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, query, edits, flags, call, n):
     print("captured", problems, paths, max_len, query, edits, flags, call, n, flush=True)
     rng = np.random.default_rng(problems + paths + max_len + n)
-    turns, L, V, warm = (3 if n > 200 and problems > 1 else 5), 6, (30 if n > 3 else 3), 20
+    L, V, warm = 6, (30 if n > 3 else 3), 20
+    turns = min(5, (max_len - warm - 7) // n)
     fed_at = [_tokens(rng, problems, paths, n, V) for _ in range(turns)]
     if call == "replay":
         fed_at = [a.transpose(2, 0, 1) for a in fed_at]
@@ -106,13 +108,13 @@ def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, q
 
 
 # the buckets of a problem in LDS, and their fill counts only
-@pytest.mark.parametrize("paths,max_len,edits,n", [(5, 300, 0, 40), (6, 800, 1, 360)])
-def test_a_bulk_append_keeps_what_a_graph_has_appended(paths, max_len, edits, n):
+@pytest.mark.parametrize("problems,paths,max_len,edits,n", [(64, 5, 300, 0, 100), (40, 6, 800, 1, 360)])
+def test_a_bulk_append_keeps_what_a_graph_has_appended(problems, paths, max_len, edits, n):
     """An index that no call has appended to since its reset is not empty if a graph has: a bulk append
-    (24 problems: a workgroup per problem) keeps the graph's postings, captured or not."""
-    print("bulk behind a graph", paths, max_len, edits, n, flush=True)
+    (by a workgroup per problem) keeps the graph's postings, captured or not."""
+    print("bulk behind a graph", problems, paths, max_len, edits, n, flush=True)
     rng = np.random.default_rng(paths + n)
-    P, L, V, k = 24, 6, 6, 3
+    P, L, V, k = problems, 6, 6, 3
     make = lambda: binding.Index(P, paths, max_len, V, k, L, 0.5, 0, binding.MATCH_INDEX, device="cuda:0", max_edits=edits)
     part = [_put(_tokens(rng, P, paths, n, V)) for _ in range(2)]
     want = make()
@@ -152,14 +154,14 @@ def test_a_bulk_append_to_a_full_index_ends(edits):
     it finds no slot for is dropped), and a reset makes the handle whole again."""
     print("bulk, full index", edits, flush=True)
     rng = np.random.default_rng(edits)
-    P, N, T, V, k, L = 24, 4, 32, 5, 3, 4
+    P, N, T, V, k, L = 40, 16, 64, 5, 3, 4
     make = lambda: binding.Index(P, N, T, V, k, L, 0.5, 0, binding.MATCH_INDEX, device="cuda:0", max_edits=edits)
-    past, more = _put(_tokens(rng, P, N, 8, V)), _put(_tokens(rng, P, N, 16, V))
+    past, more = _put(_tokens(rng, P, N, 8, V)), _put(_tokens(rng, P, N, 24, V))
     ix = make()
     ix.append(past)
     token = past[:, :, 0].contiguous()
     graph, _ = _captured(lambda: ix.step(token, None, None, 1, k, L))
-    for turn in range(300):                                # 4 postings a replay, or up to 16; 240 or 960 slots
+    for turn in range(300):                                # 16 postings a replay, or up to 64; 1920 or 7680 slots
         token.copy_(past[:, :, turn % 8])
         graph.replay()
     torch.cuda.synchronize()
