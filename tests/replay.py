@@ -13,14 +13,16 @@ def gpu_replay(tokens, probs, k, L, alpha=1.0, score_mode=0, flags=0, steps=None
     how: "calls"  = csd_append + csd_draft (+ csd_accept) per step,
          "step"   = one fused csd_step per step,
          "replay" / "replay_unfused" = one csd_replay call for all steps (n_per_step == 1,
-                    no counts).
+                    no counts): a csd_step launch per step / append, draft and accept launches,
+         "side_by_side" = the same call as it is unless csd_set_steps_per_launch is called: its
+                    steps side by side.
     steps_per_launch > 1: csd_replay runs its device-side loop where the configuration allows."""
     P, N, T = tokens.shape
     steps = steps if steps is not None else T // n_per_step
     dev = torch.device("cuda:0")
     ix = binding.Index(P, N, T, int(tokens.max()) + 1 if tokens.size else 1, k, L, alpha,
                        score_mode, flags, device=dev, max_edits=max_edits, pool_mode=pool_mode)
-    if steps_per_launch > 1:
+    if how != "side_by_side":
         ix.set_steps_per_launch(steps_per_launch)
     out_tok = torch.empty((steps, P, N, L), dtype=torch.int32, device=dev)
     out_len = torch.empty((steps, P, N), dtype=torch.int32, device=dev)
@@ -30,7 +32,7 @@ def gpu_replay(tokens, probs, k, L, alpha=1.0, score_mode=0, flags=0, steps=None
     lens = np.zeros((steps, P, N), dtype=np.int32)
     cur = np.zeros((P, N), dtype=np.int64)
     n = n_per_step
-    if how.startswith("replay"):
+    if how.startswith("replay") or how == "side_by_side":
         assert n == 1 and counts is None
         d_tok = torch.from_numpy(np.ascontiguousarray(tokens[:, :, :steps].transpose(2, 0, 1))).to(dev)
         d_pr = None if probs is None else torch.from_numpy(
@@ -38,7 +40,7 @@ def gpu_replay(tokens, probs, k, L, alpha=1.0, score_mode=0, flags=0, steps=None
         d_tg = None if targets is None else torch.from_numpy(np.ascontiguousarray(targets[:steps])).to(dev)
         out = dict(tokens=out_tok, length=out_len, token_scores=out_ts, path_scores=out_ps)
         ix.replay(steps, d_tok, d_pr, k, L, out=out, targets=d_tg, accept_out=out_acc,
-                  fused=(how == "replay"))
+                  fused=(how != "replay_unfused"))
         lens[:] = (np.arange(steps) + 1)[:, None, None]
         steps_to_run = 0
     else:

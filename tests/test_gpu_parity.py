@@ -33,7 +33,8 @@ def check_dumps(oracle, ix, tokens, probs, lens_t, k, L, eps=0, rows=None):
 
 
 SCAN, INDEX = binding.MATCH_SCAN, binding.MATCH_INDEX
-ALL_VARIANTS = ((INDEX, "replay"), (INDEX, "calls"), (SCAN, "step"), (SCAN, "replay_unfused"))
+ALL_VARIANTS = ((INDEX, "replay"), (INDEX, "side_by_side"), (INDEX, "calls"), (SCAN, "step"), (SCAN, "side_by_side"),
+                (SCAN, "replay_unfused"))
 
 
 def oracle_steps(oracle, tokens, probs, steps, k, L, alpha, mode, targets=None, **kw):
@@ -136,19 +137,21 @@ def test_c2_match_sets_and_edge_tables_along_the_replay(oracle):
 def test_c3_every_step(oracle):
     w = synth.WORKLOADS["C3"]
     run_config(oracle, w, True, 1.0, 0, check_every=1, dump_at=(2048,),
-               variants=((INDEX, "replay"), (SCAN, "replay")))
+               variants=((INDEX, "replay"), (SCAN, "replay"), (INDEX, "side_by_side"), (SCAN, "side_by_side")))
 
 
 def test_c4_batched_problems(oracle):
     w = synth.WORKLOADS["C4"]
     run_config(oracle, w, True, 1.0, 0, check_every=1, dump_at=(1024,),
-               variants=((INDEX, "replay"), (SCAN, "replay"), (INDEX, "replay_unfused")))
+               variants=((INDEX, "replay"), (SCAN, "replay"), (INDEX, "replay_unfused"), (INDEX, "side_by_side"),
+                         (SCAN, "side_by_side")))
 
 
 def test_c5_sparse_matches_with_accept(oracle):
     w = synth.WORKLOADS["C5"]
     got = run_config(oracle, w, True, 1.0, 0, check_every=1, dump_at=(4096,), accept=True,
-                     variants=((INDEX, "replay"), (SCAN, "replay"), (INDEX, "calls")))
+                     variants=((INDEX, "replay"), (SCAN, "replay"), (INDEX, "side_by_side"), (SCAN, "side_by_side"),
+                               (INDEX, "calls")))
     assert got["accept_len"].max() > 0
 
 
@@ -565,11 +568,13 @@ def _fuzzy_replay(oracle, w, check_every, hows, dump_at=(), edges=True):
 
 def test_fuzzy_c1_every_step(oracle):
     _fuzzy_replay(oracle, synth.WORKLOADS["C1"], 1,
-                  ((INDEX, "replay"), (INDEX, "calls"), (SCAN, "replay"), (SCAN, "calls")), dump_at=(7, 256))
+                  ((INDEX, "replay"), (INDEX, "side_by_side"), (INDEX, "calls"), (SCAN, "replay"), (SCAN, "side_by_side"),
+                   (SCAN, "calls")), dump_at=(7, 256))
 
 
 def test_fuzzy_c2_sampled_steps(oracle):
-    _fuzzy_replay(oracle, synth.WORKLOADS["C2"], 32, ((INDEX, "replay"), (SCAN, "replay"), (INDEX, "step")),
+    _fuzzy_replay(oracle, synth.WORKLOADS["C2"], 32, ((INDEX, "replay"), (SCAN, "replay"), (INDEX, "side_by_side"), (SCAN, "side_by_side"),
+                                                        (INDEX, "step")),
                   dump_at=(300,), edges=False)
 
 
@@ -620,15 +625,15 @@ def test_fuzzy_full_size_c3_c4_c5(oracle):
     w = synth.WORKLOADS["C3"]
     T = w.max_len
     _fuzzy_sampled(oracle, w, list(range(0, 6)) + list(range(127, T, 128)) + [T - 2, T - 1],
-                   ((AUTO, "replay"), (SCAN, "replay")), dump=(700, range(0, w.n_paths, 5)))
+                   ((AUTO, "replay"), (SCAN, "replay"), (AUTO, "side_by_side")), dump=(700, range(0, w.n_paths, 5)))
     w = synth.WORKLOADS["C5"]
     T = w.max_len
     _fuzzy_sampled(oracle, w, list(range(0, 6)) + list(range(511, T, 512)) + [T - 2, T - 1],
-                   ((AUTO, "replay"), (SCAN, "replay")), dump=(1500, range(0, w.n_paths, 9)))
+                   ((AUTO, "replay"), (SCAN, "replay"), (AUTO, "side_by_side")), dump=(1500, range(0, w.n_paths, 9)))
     w = synth.scaled(synth.WORKLOADS["C4"], n_problems=8)
     T = w.max_len
     _fuzzy_sampled(oracle, w, list(range(0, 5)) + list(range(127, T, 128)) + [T - 1],
-                   ((AUTO, "replay"), (INDEX, "replay")), dump=(400, range(0, 128, 11)))
+                   ((AUTO, "replay"), (INDEX, "replay"), (AUTO, "side_by_side"), (INDEX, "side_by_side")), dump=(400, range(0, 128, 11)))
 
 
 def test_fuzzy_auto_picks_the_variant_index_and_many_rows(oracle):
@@ -641,14 +646,14 @@ def test_fuzzy_auto_picks_the_variant_index_and_many_rows(oracle):
                                                       w.draft_len, 1.0, 0, flags, 1, 0))
     w = synth.scaled(synth.WORKLOADS["C3"], n_problems=6, max_len=384, pool=96)       # 192 rows, k = 4
     assert ws(w, AUTO) == ws(w, INDEX) != ws(w, SCAN)          # AUTO's workspace holds the variant index
-    _fuzzy_sampled(oracle, w, range(0, w.max_len, 8), ((AUTO, "replay"), (AUTO, "calls")),
+    _fuzzy_sampled(oracle, w, range(0, w.max_len, 8), ((AUTO, "replay"), (AUTO, "side_by_side"), (AUTO, "calls")),
                    dump=(200, range(0, 192, 17)))
     w = synth.scaled(synth.WORKLOADS["C3"], n_problems=128, n_paths=16, max_len=96, pool=24)   # 2048 rows, k = 4
     assert ws(w, AUTO) == ws(w, INDEX) != ws(w, SCAN)
-    _fuzzy_sampled(oracle, w, range(0, w.max_len, 5), ((AUTO, "replay"),), dump=(96, range(0, 2048, 97)))
+    _fuzzy_sampled(oracle, w, range(0, w.max_len, 5), ((AUTO, "replay"), (AUTO, "side_by_side")), dump=(96, range(0, 2048, 97)))
     w = synth.scaled(synth.WORKLOADS["C4"], n_problems=128, max_len=96, pool=24)      # 2048 rows, k = 3: scan
     assert ws(w, AUTO) == ws(w, SCAN) != ws(w, INDEX)
-    _fuzzy_sampled(oracle, w, range(0, w.max_len, 5), ((AUTO, "replay"),), dump=(96, range(0, 2048, 97)))
+    _fuzzy_sampled(oracle, w, range(0, w.max_len, 5), ((AUTO, "replay"), (AUTO, "side_by_side")), dump=(96, range(0, 2048, 97)))
 
 
 def test_two_and_three_edits(oracle):
@@ -779,8 +784,8 @@ def test_fuzzy_ragged_multi_token_steps(oracle):
 # ---------------------------------------------------------------- tree and list pools (the ablation's variants)
 @pytest.mark.parametrize("pool_mode", [binding.POOL_TREE, binding.POOL_LIST])
 def test_pool_modes_replay(oracle, pool_mode):
-    for name, every, variants in (("C1", 1, ((INDEX, "replay"), (SCAN, "step"), (INDEX, "calls"))),
-                                  ("C2", 8, ((INDEX, "replay"), (SCAN, "replay")))):
+    for name, every, variants in (("C1", 1, ((INDEX, "replay"), (INDEX, "side_by_side"), (SCAN, "step"), (INDEX, "calls"))),
+                                  ("C2", 8, ((INDEX, "replay"), (SCAN, "replay"), (SCAN, "side_by_side")))):
         w = synth.WORKLOADS[name]
         tokens, probs = synth.make_paths(w)
         T, k, L = w.max_len, w.query_len, w.draft_len
@@ -942,12 +947,16 @@ def test_large_batch_uses_the_small_on_chip_layout(oracle):
     assert tokens.shape[0] * tokens.shape[1] >= 2048
     T, k, L = w.max_len, w.query_len, w.draft_len
     targets = np.stack([synth.make_noisy_targets(w, tokens, t + 1, L) for t in range(T)])
-    got = gpu_replay(tokens, probs, k, L, flags=INDEX, targets=targets, how="replay")
-    assert got["status"] == 0
+    want = {}
     for t in sorted(set(list(range(0, T, 24)) + [T - 1])):
         lens_t = np.full(tokens.shape[:2], t + 1, dtype=np.int32)
-        want = oracle.draft_all(tokens, probs, lens_t, k, L, 1.0, 0, targets[t])
-        assert_step_equal(got, want, t, "large batch")
+        want[t] = oracle.draft_all(tokens, probs, lens_t, k, L, 1.0, 0, targets[t])
+    # (side by side: 99840 drafts, with four and eight lanes each and the rest with a wave)
+    for how in ("replay", "side_by_side"):
+        got = gpu_replay(tokens, probs, k, L, flags=INDEX, targets=targets, how=how)
+        assert got["status"] == 0
+        for t in want:
+            assert_step_equal(got, want[t], t, "large batch " + how)
 
 
 def test_random_configurations_against_the_oracle(oracle):

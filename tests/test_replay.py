@@ -1,5 +1,5 @@
-"""csd_replay with its steps side by side against a launch per step (csd_set_steps_per_launch 1, the
-path that the other tests compare with the oracle): every output, the index left behind, status bits."""
+"""csd_replay with its steps side by side against a launch per step (csd_set_steps_per_launch 1; other
+tests compare both with the oracle): every output, the index left behind, status bits."""
 import numpy as np
 import pytest
 import torch
@@ -90,6 +90,16 @@ def test_steps_side_by_side(problems, paths, max_len, steps, query, draft, edits
     (130, 16, 100, 20, 3, 7, 9, 0, 0),
 ])
 def test_many_drafts_side_by_side(problems, paths, max_len, steps, query, draft, vocab, mode, warm):
+    _many(problems, paths, max_len, steps, query, query, draft, vocab, mode, warm)
+
+
+def test_many_drafts_of_a_shorter_query():
+    """Queries shorter than the index's grams are scanned for: a wave per draft, however many there are."""
+    _many(64, 16, 200, 40, 4, 2, 8, 60, 0, 150)
+    _many(64, 16, 200, 40, 6, 5, 12, 30, 1, 150)
+
+
+def _many(problems, paths, max_len, steps, longest, query, draft, vocab, mode, warm):
     rng = np.random.default_rng(problems + paths + vocab)
     print("many", problems, paths, max_len, steps, query, draft, vocab, mode, warm, flush=True)
     dev, T = torch.device("cuda:0"), max_len
@@ -107,7 +117,7 @@ def test_many_drafts_side_by_side(problems, paths, max_len, steps, query, draft,
     by_step = lambda a: put(a[:, :, warm:warm + steps].transpose(2, 0, 1))
     got = []
     for per_launch in (0, 1):
-        ix = binding.Index(problems, paths, T, vocab, query, draft, 0.7, mode, binding.MATCH_INDEX, device=dev)
+        ix = binding.Index(problems, paths, T, vocab, longest, draft, 0.7, mode, binding.MATCH_INDEX, device=dev)
         if warm:
             counts = np.where(np.arange(paths) % 5 == 4, warm // 3, warm) + np.zeros((problems, 1))
             ix.append(put(tokens[:, :, :warm]), put(probs[:, :, :warm]), put(counts.astype(np.int32)), warm)
