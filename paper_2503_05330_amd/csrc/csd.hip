@@ -185,7 +185,7 @@ Layout make_layout(const csd_config* c) {
     l.rest = at;
     at += align_up(((size_t)l.replay_steps * rows / kQuadRows + 1) * sizeof(u64));
     l.rest_list = at;
-    at += align_up(((size_t)l.replay_steps * rows + 1) * sizeof(int32_t));
+    at += align_up(((size_t)l.replay_steps * rows + RestList::kCounters + kRestPad) * sizeof(int32_t));
   }
   l.total = at;
   return l;
@@ -220,7 +220,7 @@ struct csd_index {
                                 //   0: not set, a replay's steps run side by side)
   int32_t* step_meta;           // [replay_steps][P][N][meta_stride] see replay_append_kernel
   u64* rest;                    // [replay_steps * P * N / 16 + 1] see replay_quad_kernel
-  int32_t* rest_list;           // [1 + replay_steps * P * N] see RestList
+  int32_t* rest_list;           // see RestList
   int32_t replay_steps;
 };
 
@@ -362,7 +362,7 @@ void launch_replay_steps(const csd_index* h, const IndexView& v, const ReplayIn&
   if (!h->indexed) launch_replay_scan(w, in.steps, a, st);
   else if (v.eps > 0) launch_replay_fuzzy(w, in.steps, a, st);
   else if (a.pool_mode != CSD_POOL_DAG || v.options != 0) launch_replay_general(w, in.steps, a, st);
-  else launch_replay(w, in.steps, a, h->rest, RestList{h->rest_list, h->rest_list + 1}, st);
+  else launch_replay(w, in.steps, a, h->rest, h->rest_list, st);
 }
 
 // Host-side bounds on the paths' lengths as they were before a call: put back when the call's

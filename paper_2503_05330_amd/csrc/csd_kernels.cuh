@@ -725,7 +725,7 @@ struct ReplayIn {
 template <bool INDEX, bool FUZZY, int QC>
 __global__ __launch_bounds__(256) void replay_append_kernel(IndexView ix, ReplayIn in, int32_t* step_meta,
                                                              int32_t paths_log2, int32_t* rest_count) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) *rest_count = 0;   // (of the drafts' launches behind this one)
+  if (blockIdx.x == 0 && threadIdx.x < 16) rest_count[threadIdx.x * kBucketWords] = 0;   // (of the drafts' launches behind this one)
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t paths = 1 << paths_log2, groups = (ix.N + paths - 1) >> paths_log2;
   const int32_t p = (int32_t)blockIdx.x / groups, i0 = ((int32_t)blockIdx.x - p * groups) << paths_log2;
@@ -799,15 +799,58 @@ __global__ __launch_bounds__(kWave) void replay_wave_kernel(IndexView ix, int32_
                                                (int)threadIdx.x);
 }
 
-// The rows that are left to a wave of their own.
-template <int LCAP, class LDS, int QC>
-__global__ __launch_bounds__(kWave) void replay_rest_kernel(IndexView ix, int32_t steps, DraftArgs a, RestList list) {
+// The rows that are left to a wave of their own.  A list of many rows is drafted with the small layout
+// (sixteen rows a CU: what counts is how many are under way), a list of few with the LARGE one
+// (four, but the rows with hundreds of matches, which set the time then, take 19 us instead of 92).
+// us, replay of 1024 problems x 16 paths x 24 steps, paths that agree in all but 20 %, 5 %, 2 % of their
+// tokens: all rows with the large layout 673, 2076, 2172, so 427, 1052, 1108; with every token four times
+// in each path 3163, so 1913; 64 problems x 48 steps, 5 %: 292, 148.  (A launch per step: 875, 1041,
+// 1054; 1943; 367.)
+// A wave takes many rows, one after the other.  It reads the arguments anew for each (kept over the
+// loop beside the row's own they were spilled, 500 instructions a row), and requests the next row's
+// unit before this one's work (two round trips a row).
+struct RestArgs {
+  IndexView ix;
+  int32_t steps;
+  DraftArgs a;
+  RestList list;
+};
+constexpr int32_t kFewRest = 1024;     // rows of a list
+__device__ __forceinline__ const RestArgs& rest_arguments() {
+  auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(kernarg));
+  return *(const RestArgs*)kernarg;
+}
+template <int LCAP, bool LARGE, int QC>
+__global__ __launch_bounds__(kWave) void replay_rest_kernel(RestArgs) {
+  using LDS = std::conditional_t<LARGE, LdsWave, LdsWaveSmall>;
   __shared__ LDS s;
-  const int32_t count = *list.count;
-  for (int32_t x = (int32_t)blockIdx.x; x < count; x += (int32_t)gridDim.x) {
-    IndexView v = ix;
-    DraftArgs b = a;
-    const int32_t row = replay_unit(v, b, steps, list.units[x]);
+  int32_t few, count;                  // this kernel's of the list of rows with few matches, of both
+  auto unit_of = [&](int32_t x) {      // (any unit behind the last)
+    const RestList list = rest_arguments().list;
+    const bool many = x >= few;
+    return *list.unit(blockIdx.x & 7, many, x < count ? (many ? x - few : x) : 0);
+  };
+  {
+    const RestList list = rest_arguments().list;
+    auto mine = [&](bool many) {
+      const int32_t n = *list.count(blockIdx.x & 7, many);
+      return __builtin_amdgcn_readfirstlane((n <= kFewRest) == LARGE ? n : 0);
+    };
+    few = mine(false);
+    count = few + mine(true);
+  }
+  int32_t x = (int32_t)(blockIdx.x >> 3);
+  if (x >= count) return;
+  int32_t next = unit_of(x);
+  while (x < count) {
+    const int32_t unit = __builtin_amdgcn_readfirstlane(next);
+    x += (int32_t)(gridDim.x >> 3);
+    next = unit_of(x);
+    const RestArgs& args = rest_arguments();
+    IndexView v = args.ix;
+    DraftArgs b = args.a;
+    const int32_t row = replay_unit(v, b, args.steps, unit);
     row_step<LCAP, false, LDS, false, QC, false>(s, v, StepIn{nullptr, nullptr, nullptr, 0}, b, NoTail{}, row,
                                                  (int)threadIdx.x);
     block_sync<kWave>();

@@ -28,7 +28,7 @@ void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);
 // replay_append_kernel; a: the outputs of the first step): exact matching through the index /
 // with the tree and list pools, own history, back-off / one edit through the index / by scan
 void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest,
-                   const RestList& list, hipStream_t st);
+                   int32_t* rest_list, hipStream_t st);
 void launch_replay_general(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);
 void launch_replay_fuzzy(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);
 void launch_replay_scan(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);

@@ -287,11 +287,18 @@ __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t 
   if (lane == 0 && on) rest[unit / kQuadRows] = left;
 }
 
-// Rows for the kernel with a wave per row: their number and their units.
+// Rows for the kernels with a wave per row: a list per XCD, of the units that it has drafted from its
+// L2 already, the rows with few matches from the front on, the others from the back.
 struct RestList {
-  int32_t* count;
-  int32_t* units;
+  static constexpr int kCounters = 16 * kBucketWords;    // a line for each (an atomic takes one 12 ns)
+  int32_t* words;               // the counters, then [8][capacity] units
+  int32_t capacity;             // units of an XCD
+  __device__ __forceinline__ int32_t* count(uint32_t xcd, bool many) const { return words + (2 * xcd + many) * kBucketWords; }
+  __device__ __forceinline__ int32_t* unit(uint32_t xcd, bool many, int32_t nth) const {
+    return words + kCounters + (int32_t)xcd * capacity + (many ? capacity - 1 - nth : nth);
+  }
 };
+constexpr int32_t kRestPad = 8 * 256;  // units by which the lists of all XCDs may exceed the drafts
 
 // The same with eight lanes per row, for the rows that replay_quad_kernel has left: the first
 // buckets of the query's chain, up to eight matches.  A workgroup pools the rows that WAVES waves of
@@ -299,7 +306,11 @@ struct RestList {
 // waves take eight each.  A turn is a chain of five to nine round trips, so what counts is one
 // turn for most waves and all of them resident at once: 1024 problems x 24 steps 74 us with the rows
 // of four waves pooled, 60 with those of sixteen.  It lists the rows with more matches or a
-// longer chain for the kernel with a wave per row (one reservation: atomics on one address take 12 ns each).
+// longer chain for the kernels with a wave per row (one reservation: atomics on one address take 12 ns
+// each).  A chain is followed to its end, or for kLongChain buckets, also when the row's matches
+// are too many: it tells the rows with more than kFewMatches, which those kernels may draft with
+// another layout (any serves any row).
+constexpr int32_t kFewMatches = 30;
 constexpr uint32_t kLongChain = 3;     // buckets after which the wave per row, which reads four at once, takes over
 template <int WAVES, int LCAP, int QC>
 __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
@@ -307,8 +318,8 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
   constexpr int G = 8, kWaves = 4, kRows = WAVES * kQuadRows;   // rows of the workgroup
   static_assert(WAVES <= kWave && kRows <= 256, "a lane per wave of the other kernel, a byte per row");
   __shared__ uint32_t found_all[kWaves][kWave];          // [row of the turn][8] matches
-  __shared__ uint8_t todo[kRows], left[kRows];
-  __shared__ int32_t n_todo, n_left, list_at;
+  __shared__ uint8_t todo[kRows], left[2][kRows];        // left: few matches, many
+  __shared__ int32_t n_todo, n_left[2], list_at[2];
   const int lane = (int)threadIdx.x & (kWave - 1), wave = (int)threadIdx.x >> 6, sub = lane & (G - 1);
   uint32_t* found = found_all[wave];
   const uint32_t units = (uint32_t)(ix.P * ix.N * steps), first = block_units(kRows);
@@ -325,7 +336,7 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     for (; rows; rows &= rows - 1) todo[at++] = (uint8_t)(lane * kQuadRows + (((int)__ffsll((long long)rows) - 1) >> 2));
     if (lane == 0) {
       n_todo = total;
-      n_left = 0;
+      n_left[0] = n_left[1] = 0;
     }
   }
   __syncthreads();
@@ -339,7 +350,8 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     const int32_t len = u.end(ix, Q);
     load_targets<G, LCAP>(a, u, sub, target);
     const GramHash gh = gram_hash_of(Q, ix.kmax);
-    bool leave = len < ix.kmax;
+    const bool is_short = len < ix.kmax;                 // no gram to look up: scanned for
+    bool leave = is_short;
     int32_t M = 0;
     bool looking = on && !leave;                         // the same in a group's lanes
     auto bucket = [&](uint32_t r) {
@@ -368,19 +380,24 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
         M += (int32_t)__popc(hits);
       }
       const bool goes_on = count >= kBucketSlots && r < ix.bucket_mask;
-      leave = leave || (looking && (M > G || (goes_on && r + 1 >= kLongChain)));
+      leave = leave || (looking && goes_on && r + 1 >= kLongChain);
       looking = looking && goes_on && !leave;
     }
+    leave = leave || M > G;
+    const bool many = is_short || M > kFewMatches;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS of this wave alone)
     group_draft<G, LCAP>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);
-    if (on && leave && sub == 0) left[atomicAdd(&n_left, 1)] = (uint8_t)which;
+    if (on && leave && sub == 0) left[many][atomicAdd(&n_left[many], 1)] = (uint8_t)which;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the next turn's matches go to the same cells)
   }
   __syncthreads();
-  if (threadIdx.x == 0 && n_left > 0) list_at = atomicAdd(list.count, n_left);
+  const uint32_t xcd = blockIdx.x & 7;                   // (see block_units)
+  if (threadIdx.x < 2 && n_left[threadIdx.x] > 0)
+    list_at[threadIdx.x] = atomicAdd(list.count(xcd, threadIdx.x != 0), n_left[threadIdx.x]);
   __syncthreads();
-  for (int x = (int)threadIdx.x; x < n_left; x += 256)
-    list.units[list_at + x] = (int32_t)(first + left[x]);
+  for (int m = 0; m < 2; ++m)
+    for (int x = (int)threadIdx.x; x < n_left[m]; x += 256)
+      *list.unit(xcd, m != 0, list_at[m] + x) = (int32_t)(first + left[m][x]);
 }
 
 }  // namespace csd

@@ -27,29 +27,32 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
 constexpr int64_t kPooledDrafts = 1 << 17;
 
 template <int LCAP, int QC>
-static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, const RestList& list,
+static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
                          hipStream_t st) {
   const int64_t drafts = (int64_t)v.P * v.N * steps;
   const auto grid = [&](int64_t rows) { return (uint32_t)((drafts + 8 * rows - 1) / (8 * rows) * 8); };   // rows per workgroup
   replay_quad_kernel<LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest);
-  if (drafts >= kPooledDrafts) replay_eight_kernel<16, LCAP, QC><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  const bool pooled = drafts >= kPooledDrafts;
+  const RestList list{rest_list, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows};
+  if (pooled) replay_eight_kernel<16, LCAP, QC><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   else replay_eight_kernel<4, LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
-  // (as many as the chip holds at once: they share the list)
-  replay_rest_kernel<LCAP, LdsWave, QC><<<1024, kWave, 0, st>>>(v, steps, a, list);
+  // (as many as the chip holds at once: they share the lists)
+  replay_rest_kernel<LCAP, false, QC><<<8192, kWave, 0, st>>>(RestArgs{v, steps, a, list});
+  replay_rest_kernel<LCAP, true, QC><<<1024, kWave, 0, st>>>(RestArgs{v, steps, a, list});
 }
 
-void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, const RestList& list,
+void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
                    hipStream_t st) {
   const int64_t drafts = (int64_t)v.P * v.N * steps;
   if (drafts >= kQuadDrafts && a.k == v.kmax) {
     if (v.kmax <= 4) {
-      if (a.L <= 8) launch_quads<8, 4>(v, steps, a, rest, list, st);
-      else if (a.L <= 16) launch_quads<16, 4>(v, steps, a, rest, list, st);
-      else launch_quads<32, 4>(v, steps, a, rest, list, st);
+      if (a.L <= 8) launch_quads<8, 4>(v, steps, a, rest, rest_list, st);
+      else if (a.L <= 16) launch_quads<16, 4>(v, steps, a, rest, rest_list, st);
+      else launch_quads<32, 4>(v, steps, a, rest, rest_list, st);
     } else {
-      if (a.L <= 8) launch_quads<8, 8>(v, steps, a, rest, list, st);
-      else if (a.L <= 16) launch_quads<16, 8>(v, steps, a, rest, list, st);
-      else launch_quads<32, 8>(v, steps, a, rest, list, st);
+      if (a.L <= 8) launch_quads<8, 8>(v, steps, a, rest, rest_list, st);
+      else if (a.L <= 16) launch_quads<16, 8>(v, steps, a, rest, rest_list, st);
+      else launch_quads<32, 8>(v, steps, a, rest, rest_list, st);
     }
     return;
   }
