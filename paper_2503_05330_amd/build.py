@@ -41,6 +41,24 @@ def build_library() -> str:
     return LIBRARY
 
 
+def timing_source() -> str:
+    """All sources as one, for the timing build: its kernels write their clock stamps to a device
+    array of the source that they are in, and csd_read_stamps reads that of csd.hip."""
+    return "#define CSD_STAMPS 1\n" + "".join(
+        '#define launch launch_%d\n#include "%s"\n#undef launch\n' % pair for pair in enumerate(SOURCES))
+
+
+def build_timing_library(path: str, flags=("-shared",)) -> str:
+    """The library with the clock stamps in its kernels (some minutes: one source)."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    with tempfile.TemporaryDirectory() as tmp:
+        source = os.path.join(tmp, "timing.hip")
+        with open(source, "w") as f:
+            f.write(timing_source())
+        subprocess.check_call([hipcc, *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), *flags, "-o", path, source])
+    return path
+
+
 def build_binding() -> str:
     """_csd_torch.so, linked to libcsd.so beside it."""
     import sysconfig

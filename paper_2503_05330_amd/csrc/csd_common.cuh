@@ -32,9 +32,10 @@ constexpr int kBucketSlots = kBucketWords - 1;
 constexpr int kTailCap = CSD_MAX_QUERY_LEN + 1;   // most tokens a meta row keeps
 
 // ---------------------------------------------------------------- timing build
-// With -DCSD_STAMPS (never in the shipped library) the first thread of a workgroup writes
-// the constant-rate device clock (10 ns units) at marked places of the step kernels into a
-// device array that a test harness reads back: where a step's time goes, row by row.
+// With -DCSD_STAMPS (never in the shipped library: build.build_timing_library) the first thread of
+// a workgroup writes the constant-rate device clock (10 ns units) at marked places of the step
+// kernels into a device array that a test harness reads back (csd_read_stamps): where a step's time
+// goes, row by row.  There has to be one such array, so that build compiles all sources as one.
 #ifdef CSD_STAMPS
 constexpr int kStampSlots = 32;
 static __device__ unsigned long long g_stamps[(1 << 14) * kStampSlots];

@@ -115,3 +115,15 @@ def test_bound_behind_the_table_full_status_bit():
     assert most_ids_in_a_class(1 << 24) == 65 and 2 * 65 <= 256
     assert most_ids_in_a_class((1 << 29) - 1) == 2045
     assert most_ids_in_a_class(152064) == 1                   # the largest vocabulary of the workloads
+
+
+def test_timing_build_has_one_array_of_stamps(tmp_path):
+    """csd_read_stamps copies the device array of the source it is in, so no kernel of the timing
+    build may come from another one: nothing of the library is undefined in its object (the host
+    part alone, which takes seconds)."""
+    import subprocess
+    from paper_2503_05330_amd import build
+    obj = build.build_timing_library(str(tmp_path / "timing.o"), ("-c", "--cuda-host-only", "-O0"))
+    names = subprocess.check_output(["nm", "-C", obj], text=True)
+    assert " T csd_read_stamps" in names
+    assert not re.findall(r" U (?:csd::|csd_).*", names)
