@@ -22,6 +22,13 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Every call except csd_status / csd_dump_* only enqueues work on `stream`
  *    and returns; nothing is allocated, freed or synchronised by them.
+ *  - These calls can be captured in a HIP graph.  csd_append, csd_draft, csd_accept, csd_reset
+ *    and a csd_step that appends first (two launches, see there) then do at every replay what
+ *    a call does.  A csd_step in one launch, a csd_replay of fused steps and the steps of
+ *    csd_accept_loop that are one launch each write the paths' ends into two buffers in turn:
+ *    capture an even number of such steps, so that the next replay finds the ends where the
+ *    first one did.  The host's bounds on the lengths (CSD_ERR_CAPACITY) do not see what
+ *    graphs append; the kernels clip.
  *  - The library owns only the small host-side handle.  All device state lives
  *    in the caller's workspace, which must stay allocated, and untouched by
  *    the caller, until csd_destroy.

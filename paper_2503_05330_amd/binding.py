@@ -261,7 +261,8 @@ class Index:
 
     def replay(self, n_steps, tokens, probs, query_len, draft_len, out=None, targets=None,
                accept_out=None, fused=True, scores=True):
-        """n_steps decode steps of a recorded trace, side by side in two launches.
+        """n_steps decode steps of a recorded trace, side by side in a few launches (one after the
+        other, a launch per step, where a written buffer overlaps another one).
         tokens / probs [n_steps][P][N]; outputs get a leading n_steps axis."""
         L, S = draft_len, n_steps
         if out is None:

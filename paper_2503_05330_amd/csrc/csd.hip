@@ -73,7 +73,9 @@ struct Layout {
 };
 
 // Drafts of a replay that run side by side at most (a chip full of workgroups many times over), and
-// the share of a path's tokens: their notes then take a fifth of the histories and their index.
+// the share of a path's tokens.  Their notes, a row like the paths' ends and 4.5 bytes each, take at
+// most 27 MB; of small pools' histories and index a third (queries of up to three tokens) to four
+// fifths (eight), without an index up to 1.6 times the histories.
 constexpr int64_t kReplayDrafts = 1 << 19;
 constexpr int32_t kReplayShare = 4, kReplayFewSteps = 16;
 // ... and with a larger vocabulary than this a layer of the DAG may not fit the tables of the layout

@@ -6,11 +6,13 @@ namespace csd {
 // From this many drafts on the small LDS layout is used (as in launch_step).
 constexpr int64_t kSmallLdsDrafts = 2048;
 
-// From this many drafts on those with few matches are made with four or eight lanes each.  Three
+// From this many drafts on those with few matches are made with four or eight lanes each.  Four
 // kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
 // drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31, 49152 (64
-// problems x 16 paths x 48 steps) 73 / 50 (10 + 20 + 19), 393216 (1024 problems, 24 steps) 533 / 195
-// (60 + 60 + 75).
+// problems x 16 paths x 48 steps) 73 / 50 (10 + 17 + 3 + 20), 393216 (1024 problems, 24 steps) 533 / 196
+// (60 + 60 + 4 + 72).  Where the paths agree in most tokens nearly all rows are left over and a wave
+// per draft would be the faster form (the whole call, all but 20 %, 5 % equal: 602 / 427, 748 / 1064; 64
+// problems 85 / 72, 107 / 150); the host does not know.
 constexpr int64_t kQuadDrafts = 1 << 15;
 
 template <class LDS, int QC>
@@ -36,7 +38,9 @@ static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, 
   const RestList list{rest_list, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows};
   if (pooled) replay_eight_kernel<16, LCAP, QC><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   else replay_eight_kernel<4, LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
-  // (as many as the chip holds at once: they share the lists)
+  // (the second as many as the chip holds at once, the first twice that: 4096, which it holds, do not
+  // spread evenly, 1281 us for 1024 problems whose paths agree, 8192: 1109, 49152: 1030, which cost 8 us
+  // where there is nothing to do for them)
   replay_rest_kernel<LCAP, false, QC><<<8192, kWave, 0, st>>>(RestArgs{v, steps, a, list});
   replay_rest_kernel<LCAP, true, QC><<<1024, kWave, 0, st>>>(RestArgs{v, steps, a, list});
 }
