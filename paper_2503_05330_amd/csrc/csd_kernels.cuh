@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void append_kernel(IndexView ix, StepIn in, in
 // on average, without and with that: 1024 problems of 16 paths, 512 offered: 77, 26 / 82, 82; 128 of 64,
 // 2048: 202, 21 / 405, 406; 4096 of 4, 128: 53, 32 / 55, 61).  TABLE: the buckets
 // themselves are in LDS too, and go to memory as a whole.  The paths' ends are replaced in place, by
-// way of `ends`, rows like theirs (1024 problems of 16 x 1024 tokens 110.4 us; where `ends` stay the
+// way of `ends`, rows like theirs (1024 problems of 16 x 1024 tokens 110 .. 112 us; where `ends` stay the
 // new ends 109; 114 to 118 by way of LDS, with a lane per word before or after the loop or with the
 // tokens from the lanes that have them: registers and instructions of the loop are what counts here).
 template <bool FUZZY, int QC, bool TABLE>
