@@ -1,7 +1,8 @@
 // csd — the per-call part of binding.py in native code: checks the tensors, allocates the outputs
 // and calls the C-ABI.  A decode loop calls step() once per token, and in Python that took five
-// times as long as the kernel that it launches (4 paths x 256 tokens, us a call: kernel 4.3, step()
-// 21 in Python and 10 here, draft() 15 and 7, accept() 13 and 8, reset() 6 and 3).
+// times as long as the kernel that it launches (4 paths x 256 tokens, us a call: kernel 4.2, step()
+// 21 in Python and 5.3 here, draft() 15 and 5.0, accept() 13 and 4.4, reset() 6 and 3.2, nearly all
+// of which is the launch).
 //
 // Every function returns None where an argument is not what the call usually gets (another type,
 // a tensor of another kind): binding.py then goes its own way, which raises the error or serves it.
@@ -10,6 +11,8 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ops/empty.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 
 #include "csd.h"
 
@@ -96,15 +99,52 @@ struct Pool {
     if (index < -1 || index > 127 || P <= 0 || N <= 0) c.usual = false;
     else device = c10::Device(c10::DeviceType::CUDA, (c10::DeviceIndex)index);
   }
-  // [steps][P][N][L]; without a leading axis (steps < 0), without a trailing one (L < 0)
-  at::Tensor output(at::ScalarType type, int64_t steps, int64_t L) const {
-    int64_t shape[4], n = 0;
-    if (steps >= 0) shape[n++] = steps;
-    shape[n++] = P;
-    shape[n++] = N;
-    if (L >= 0) shape[n++] = L;
-    return at::empty(at::IntArrayRef(shape, n), at::TensorOptions().dtype(type).device(device));
+};
+
+// The outputs of a call: int32 or float32 [steps][P][N][L] each, without the leading axis where
+// steps < 0, without the trailing one where L < 0.
+struct Shape {
+  int64_t at[4], n = 0, numel = 1;
+  Shape(const Pool& p, int64_t steps, int64_t L) {
+    if (steps >= 0) put(steps);
+    put(p.P);
+    put(p.N);
+    if (L >= 0) put(L);
   }
+  void put(int64_t x) {
+    at[n++] = x;
+    numel *= x;
+  }
+  c10::IntArrayRef sizes() const { return c10::IntArrayRef(at, n); }
+};
+
+// Allocates them: small ones as one block of memory, each from a multiple of 512 bytes on as the
+// allocator has it, so that a call pays for one allocation and not for five (0.7 us each: step() 7.8
+// and 5.3 us, draft() 7.1 and 5.0; twelve steps of 4 paths, with reset and append, 155 and 106 us).
+// Large ones are apart: there the kernel takes longer than the allocations, and one output that
+// the caller keeps would hold the memory of all of them.  A dispatch mode sees every output made.
+class Maker {
+ public:
+  static constexpr int64_t kLine = 512, kShared = 1 << 16;
+  static int64_t bytes(const Shape& s) { return (s.numel * 4 + kLine - 1) / kLine * kLine; }
+  Maker(const Pool& p, int64_t together) : device_(p.device) {
+    if (together <= kShared && !c10::impl::dispatch_mode_enabled())
+      block_ = at::empty({together}, at::TensorOptions().dtype(at::kByte).device(device_));
+  }
+  at::Tensor operator()(at::ScalarType type, const Shape& s) {
+    if (!block_.defined()) return at::empty(s.sizes(), at::TensorOptions().dtype(type).device(device_));
+    at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block_.storage()), block_.key_set(),
+                                                            c10::scalarTypeToTypeMeta(type));
+    t.unsafeGetTensorImpl()->set_storage_offset(at_ / 4);
+    t.unsafeGetTensorImpl()->set_sizes_contiguous(s.sizes());
+    at_ += bytes(s);
+    return t;
+  }
+
+ private:
+  c10::Device device_;
+  at::Tensor block_;
+  int64_t at_ = 0;
 };
 
 int32_t* int_data(const at::Tensor& t) { return t.defined() ? static_cast<int32_t*>(t.data_ptr()) : nullptr; }
@@ -117,17 +157,22 @@ bool put(PyObject* dict, const char* name, const at::Tensor& t) {
   return ok;
 }
 
-// a draft's outputs
+// a draft's outputs, and the accepted lengths
 struct Outputs {
-  at::Tensor tokens, length, token_scores, path_scores;
-  Outputs(const Pool& p, int64_t steps, int64_t L, bool scores)
-      : tokens(p.output(at::kInt, steps, L)), length(p.output(at::kInt, steps, -1)) {
-    if (!scores) return;
-    token_scores = p.output(at::kFloat, steps, L);
-    path_scores = p.output(at::kFloat, steps, -1);
+  at::Tensor tokens, length, token_scores, path_scores, accept;
+  Outputs(const Pool& p, int64_t steps, int64_t L, bool scores, bool with_accept = false) {
+    const Shape per_token(p, steps, L), per_row(p, steps, -1);
+    Maker make(p, (1 + scores) * (Maker::bytes(per_token) + Maker::bytes(per_row)) + with_accept * Maker::bytes(per_row));
+    tokens = make(at::kInt, per_token);
+    length = make(at::kInt, per_row);
+    if (scores) {
+      token_scores = make(at::kFloat, per_token);
+      path_scores = make(at::kFloat, per_row);
+    }
+    if (with_accept) accept = make(at::kInt, per_row);
   }
-  // (code, dict); accept: also the accepted lengths, a tensor made here or the caller's (`given`)
-  PyObject* result(int code, bool with_accept = false, const at::Tensor& accept = {}, PyObject* given = nullptr) const {
+  // (code, dict); with_accept: also the accepted lengths, made here or the caller's (`given`)
+  PyObject* result(int code, bool with_accept = false, PyObject* given = nullptr) const {
     PyObject* dict = PyDict_New();
     if (!dict) return nullptr;
     bool ok = put(dict, "tokens", tokens) && put(dict, "length", length) &&
@@ -201,7 +246,8 @@ PyObject* accept(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   const int32_t* length = c.ints(p.rows);
   const int32_t* targets = c.ints(p.rows * L);
   if (!c.usual) Py_RETURN_NONE;
-  const at::Tensor out = p.output(at::kInt, -1, -1);
+  const Shape per_row(p, -1, -1);
+  const at::Tensor out = at::empty(per_row.sizes(), at::TensorOptions().dtype(at::kInt).device(p.device));
   int code;
   Py_BEGIN_ALLOW_THREADS
   code = csd_accept(p.handle, tokens, length, targets, L, int_data(out), p.stream);
@@ -229,12 +275,8 @@ PyObject* step(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   PyObject* given = c.at < c.n ? c.args[c.at] : Py_None;
   int32_t* accepted = const_cast<int32_t*>(c.ints(rows, true));
   if (!c.usual) Py_RETURN_NONE;
-  const Outputs o(p, steps, L, scores);
-  at::Tensor mine;
-  if (targets && given == Py_None) {
-    mine = p.output(at::kInt, steps, -1);
-    accepted = int_data(mine);
-  }
+  const Outputs o(p, steps, L, scores, targets && given == Py_None);
+  if (o.accept.defined()) accepted = int_data(o.accept);
   int code;
   Py_BEGIN_ALLOW_THREADS
   code = REPLAY ? csd_replay(p.handle, n, tokens, probs, k, L, int_data(o.tokens), int_data(o.length),
@@ -243,7 +285,7 @@ PyObject* step(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
                 : csd_step(p.handle, tokens, probs, counts, n, k, L, int_data(o.tokens), int_data(o.length),
                            float_data(o.token_scores), float_data(o.path_scores), targets, accepted, p.stream);
   Py_END_ALLOW_THREADS
-  return o.result(code, true, mine, given == Py_None ? nullptr : given);
+  return o.result(code, true, given == Py_None ? nullptr : given);
   END_HANDLE_TH_ERRORS
 }
 

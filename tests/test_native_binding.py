@@ -77,3 +77,30 @@ def test_the_same_from_both_parts(scores):
                 continue
             assert a[key].dtype == b[key].dtype and a[key].shape == b[key].shape and a[key].is_contiguous(), key
             assert torch.equal(a[key], b[key]), key
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,N,L,S", ((1, 1, 1, 1), (1, 3, 7, 2), (2, 64, 8, 3), (1, 127, 32, 1), (1, 128, 32, 1), (1, 600, 16, 2)))
+def test_outputs_of_a_call_lie_apart(P, N, L, S):
+    """Small outputs come from one block of memory, large ones from blocks of their own: none overlaps
+    another, each starts where an allocation would, and one that is kept outlives the others."""
+    ix = binding.Index(P, N, 64, 50, 3, 32)
+    tokens = torch.randint(0, 4, (S, P, N), device="cuda", dtype=torch.int32)
+    targets = torch.zeros((S, P, N, L), device="cuda", dtype=torch.int32)
+    kept = []
+    for mode in (torch.inference_mode(False), torch.inference_mode(True)):
+        with mode:
+            ix.reset()
+            out = ix.replay(S, tokens, None, 3, L, targets=targets)
+            assert all(t.is_inference() == torch.is_inference_mode_enabled() for t in out.values())
+        spans = sorted((t.data_ptr(), t.data_ptr() + 4 * t.numel()) for t in out.values())
+        assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and all(a % 512 == 0 for a, _ in spans)
+        for t in out.values():
+            assert t.is_contiguous() and t._base is None and not t.requires_grad
+            assert t.storage_offset() * 4 + t.numel() * 4 <= t.untyped_storage().nbytes()
+        kept.append((out["length"], out["length"].clone()))
+        del out, t
+        ix.reset()
+        ix.replay(S, tokens.flip(0), None, 3, L)         # would take a freed block of the same size
+        assert torch.equal(*kept[-1])
+    assert torch.equal(kept[0][0], kept[1][0])
