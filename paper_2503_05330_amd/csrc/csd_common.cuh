@@ -220,6 +220,16 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
+// Sum over the lanes up to this one (the lane moves of wave_sum, which scan on their way).
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  x = dpp_add<0x111, 0xF>(x);
+  x = dpp_add<0x112, 0xF>(x);
+  x = dpp_add<0x114, 0xF>(x);
+  x = dpp_add<0x118, 0xF>(x);
+  x = dpp_add<0x142, 0xA>(x);
+  return dpp_add<0x143, 0xC>(x);
+}
+
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ uint32_t dpp_max(uint32_t x) {   // lanes the pattern does not reach see 0
   uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROW_MASK, 0xF, false);
@@ -388,14 +398,14 @@ struct Slot {
 // two), MATCH = matches kept (beyond: streaming tier), WIN = words for cached
 // continuations of matches, WAVES = waves of the workgroup, LENS = paths whose lengths
 // are cached (more paths: their lengths are read from memory).
-template <int TABLE, int MATCH, int WIN, int WAVES, int LENS = kLenCache>
+template <int TABLE, int MATCH, int WIN, int WAVES, int LENS = kLenCache, int LINK = (TABLE > MATCH ? TABLE : MATCH)>
 struct LdsT {
   static constexpr int kTable = TABLE;
   static constexpr int kMatch = MATCH;
   static constexpr int kWin = WIN;
   static constexpr int kLens = LENS;
   Slot table[TABLE];
-  uint16_t link[TABLE > MATCH ? TABLE : MATCH];   // edge slot -> slot of its target node (tier 1);
+  uint16_t link[LINK];          // edge slot -> slot of its target node (tier 1);
                                 // the tree pool keeps one flag per listed match here
   Match match[MATCH];
   int32_t win[WIN];             // per cached match: L continuation tokens, then their L probabilities
@@ -424,6 +434,10 @@ typedef LdsT<256, 128, 1024, 1, 16> LdsMulti;
 // thousands of matches): 128 KB, one row per CU (the windows are not used as such: the walk
 // that tabulates node weights first keeps its keys and slots there).
 typedef LdsT<4096, 4096, 6144, kScanBlock / kWave> LdsScan;
+// The same for replays, 79 KB: two rows per CU.  The match list is as long; the walks' tables are half
+// the size, and the links as many as the table (the tree pool, which keeps a flag per match there, does
+// not use this layout).
+typedef LdsT<2048, 4096, 2048, kScanBlock / kWave, kLenCache, 2048> LdsScanPair;
 
 struct Ctx {                    // one (problem, query path)
   Paths y;

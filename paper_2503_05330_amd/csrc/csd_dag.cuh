@@ -491,8 +491,8 @@ __device__ __forceinline__ Cand scan_successors(const LDS& s, Region r, int d, i
 // its (1, p) to the successor's cell (score_mode 1: only the candidates do); (C) the
 // thread that entered a successor ranks it and puts it on a short list, which every wave
 // then reads for the heaviest (ties: lowest token).  Same sums as the tables of tier 1, in
-// exact integers: the same draft.  Set, cells and list lie over the (otherwise unused)
-// table.  Waves without a match leave before the layers start (a workgroup barrier waits
+// exact integers: the same draft.  Set and cells lie over the (otherwise unused) table, the
+// lists over the matches, which the threads have read by then, and the windows.  Waves without a match leave before the layers start (a workgroup barrier waits
 // for the waves that are still running only), so a row with few matches pays for few waves.
 // Nothing after this function may synchronise the workgroup.
 // (Measured against two other forms with identical results: every instance of a layer added
@@ -504,11 +504,12 @@ template <int BLOCK, class LDS>
 __device__ __forceinline__ void walk_wide(LDS& s, const Ctx& c, int32_t M, int32_t L,
                                           uint32_t alpha_q, int score_mode, DraftOut& o) {
   constexpr uint32_t kSet = 2 * BLOCK;                 // at most BLOCK distinct successors: half load
-  static_assert(2 * kSet * sizeof(u64) + 2 * BLOCK * sizeof(Cand) <= sizeof(s.table),
-                "set, cells and the two successor lists fit the table");
+  static_assert(2 * kSet * sizeof(u64) <= sizeof(s.table), "set and cells fit the table");
+  static_assert(2 * BLOCK * sizeof(Cand) <= sizeof(s.match) + sizeof(s.win) && offsetof(LDS, match) % alignof(Cand) == 0 &&
+                offsetof(LDS, win) == offsetof(LDS, match) + sizeof(s.match), "the two lists over matches and windows");
   u64* keys = reinterpret_cast<u64*>(s.table);         // (layer << 32) | token, or kEmpty
   u64* cell = keys + kSet;                             // (count, probability sum) of the key's token
-  Cand* list = reinterpret_cast<Cand*>(cell + kSet);   // [2][BLOCK] successors of a layer, ranked
+  Cand* list = reinterpret_cast<Cand*>(s.match);    // [2][BLOCK] successors of a layer, ranked
   int32_t* listed = s.chosen;                          // [2] how many (the tree pool's array is free here)
   for (uint32_t h = c.tid; h < kSet; h += BLOCK) keys[h] = kEmpty;
   if (c.tid < 2) listed[c.tid] = 0;
@@ -632,28 +633,32 @@ __device__ __forceinline__ void walk_wide(LDS& s, const Ctx& c, int32_t M, int32
 //   atomic.
 // Needs score_mode 0 (edge weights depend on the walk: walk_wide), tokens below 2^21 (the
 // weight of at most 1024 instances takes 43 bits) and at most kTabInstances instances.  The
-// set has two to four times as many slots as there are instances, but at most kTabSlots; an
+// set has two to four times as many slots as there are instances, but at most tab_slots(); an
 // instance that finds no place within kTabProbes gives up, and the function then returns
 // false with nothing decided (thousands of distinct continuations: the caller takes walk_wide).  Same sums as the other tiers, in exact
 // integers: the same draft.  Cells lie over the table, the layers' maxima over the links,
 // keys and slots behind the first BLOCK entries of the match list (which stay).
 // After a return of true nothing may synchronise the workgroup.
-constexpr int kTabSlots = 8192;
 constexpr int kTabInstances = 8192;
 constexpr int kTabProbes = 128;
 constexpr int kTabTokenBits = 21;
+
+// Its key set: a place per cell that the table has room for (LdsScan 8192, LdsScanPair 4096).
+template <class LDS>
+constexpr uint32_t tab_slots() { return (uint32_t)(sizeof(Slot) * LDS::kTable / sizeof(u64)); }
 
 template <int BLOCK>
 __device__ __forceinline__ bool walk_tab_fits(int32_t M, int32_t L, int32_t vocab, int score_mode) {
   return score_mode == 0 && M <= BLOCK && M * L <= kTabInstances && vocab <= (1 << kTabTokenBits);
 }
 
-// Empties walk_tab's key set and zeroes its cells and the layers' maxima, all kTabSlots of
+// Empties walk_tab's key set and zeroes its cells and the layers' maxima, all of
 // them, with threads `first` .. BLOCK - 1 (the scan kernel has this done by the waves that
 // idle while one of them hands the row's matches over; the first BLOCK entries of the match
 // list are not touched).
 template <int BLOCK, class LDS>
 __device__ __forceinline__ void walk_tab_clear(LDS& s, int tid, int first) {
+  constexpr uint32_t kTabSlots = tab_slots<LDS>();
   uint2* cells2 = reinterpret_cast<uint2*>(s.table);
   uint2* keys2 = reinterpret_cast<uint2*>(&s.match[BLOCK]);
   u64* best = reinterpret_cast<u64*>(s.link);
@@ -668,6 +673,7 @@ __device__ __forceinline__ void walk_tab_clear(LDS& s, int tid, int first) {
 template <int BLOCK, class LDS>
 __device__ __forceinline__ bool walk_tab(LDS& s, const Ctx& c, int32_t M, int32_t L, uint32_t alpha_q,
                                          DraftOut& o, bool cleared = false) {
+  constexpr uint32_t kTabSlots = tab_slots<LDS>();
   static_assert(LDS::kMatch >= BLOCK && sizeof(s.table) >= kTabSlots * sizeof(u64) &&
                 sizeof(s.link) >= CSD_MAX_DRAFT_LEN * sizeof(u64),
                 "cells over the table, the layers' maxima over the links");
@@ -675,6 +681,7 @@ __device__ __forceinline__ bool walk_tab(LDS& s, const Ctx& c, int32_t M, int32_
                 kTabSlots * sizeof(uint32_t) + kTabInstances * sizeof(uint16_t),
                 "keys and slots behind the listed matches");
   static_assert(offsetof(LDS, win) == offsetof(LDS, match) + sizeof(s.match), "no gap before the windows");
+  constexpr int kMostBits = __builtin_ctz(kTabSlots);
   constexpr uint32_t kNoKey = ~0u;
   constexpr uint32_t kTokBits = (1u << kTabTokenBits) - 1u;
   u64* cell = reinterpret_cast<u64*>(s.table);         // [n_slots] (count, probability sum)
@@ -684,8 +691,8 @@ __device__ __forceinline__ bool walk_tab(LDS& s, const Ctx& c, int32_t M, int32_
   // two to four times as many slots as instances (a power of two, at most kTabSlots): what is
   // not used is not cleared
   int slot_bits = 32 - __clz(4 * M * L - 1);
-  slot_bits = slot_bits < 10 ? 10 : (slot_bits > 13 ? 13 : slot_bits);
-  if (cleared) slot_bits = 13;                         // (uniform) all of them are empty: use them
+  slot_bits = slot_bits < 10 ? 10 : (slot_bits > kMostBits ? kMostBits : slot_bits);
+  if (cleared) slot_bits = kMostBits;                         // (uniform) all of them are empty: use them
   const uint32_t n_slots = 1u << slot_bits;
   if (!cleared) {                                      // empty set, zero cells
     uint2* cells2 = reinterpret_cast<uint2*>(cell);

@@ -233,11 +233,11 @@ __device__ __forceinline__ void fetch_windows(LDS& s, const Ctx& c, int32_t M, i
 // FUZZY: matching tolerates one edit (compiled apart from the exact kernel: code a launch
 // does not run still costs it time).
 // QC: compile-time bound (4 or 8) of the query length: the comparison loops are unrolled to it.
-template <int QC, bool POOLS, bool FUZZY>
+template <int QC, bool POOLS, bool FUZZY, class LDS = LdsScan>
 __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in, const DraftArgs& a,
                                           const ScanSlices& sl, int32_t row, int32_t slice) {
   constexpr int BLOCK = kScanBlock;
-  __shared__ LdsScan s;
+  __shared__ LDS s;
   __shared__ int32_t sh_base, sh_total, sh_last;
   const int32_t unit = row * 8 + slice;                  // (timing build only)
   CSD_STAMP(unit, 0, CSD_CLOCK());
@@ -272,8 +272,12 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
   const int32_t L = a.L;
   CSD_STAMP(unit, 1, CSD_CLOCK());
   if (c.q > 0) {
-    ListSink<LdsScan> sink{&s};
-    match_scan<BLOCK, FUZZY, QC>(s, c, sink, slice, sl.n);
+    uint16_t* pool = reinterpret_cast<uint16_t*>(s.table) + (c.tid >> 6) * kPoolWords;   // (before the walk)
+    // (spans in flight: four where the registers hold their tokens)
+    constexpr int kSpans = (std::is_same<LDS, LdsScanPair>::value || QC > 4) ? 2 : 4;
+    static_assert(sizeof(s.table) >= BLOCK / kWave * kPoolWords * sizeof(uint16_t), "a pool per wave");
+    ListSink<LDS> sink{&s};
+    match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, slice, sl.n, pool);
     block_sync<BLOCK>();
     int32_t M = s.n_match;
     CSD_STAMP(unit, 2, CSD_CLOCK());
@@ -284,7 +288,7 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
       while (M == 0 && c.q > 1) {
         block_sync<BLOCK>();            // everybody has read the count before anybody pushes again
         --c.q;
-        match_scan<BLOCK, FUZZY, QC>(s, c, sink);
+        match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, 0, 1, pool);
         block_sync<BLOCK>();
         M = s.n_match;
       }
@@ -294,11 +298,11 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
       // holds the matches listed so far (low half) and the slices finished, over all
       // launches (high half): a slice reserves its part of the list with one atomic and
       // signs off with a second one, whose result tells the last slice the row's total
-      Match* listed = sl.matches + (int64_t)row * LdsScan::kMatch;
+      Match* listed = sl.matches + (int64_t)row * LDS::kMatch;
       if (c.tid == 0) sh_base = (int32_t)(uint32_t)atomicAdd(&sl.state[row], (u64)(uint32_t)M);
       block_sync<BLOCK>();
-      for (int32_t m = c.tid; m < M && m < LdsScan::kMatch; m += BLOCK)
-        if (sh_base + m < LdsScan::kMatch) listed[sh_base + m] = s.match[m];
+      for (int32_t m = c.tid; m < M && m < LDS::kMatch; m += BLOCK)
+        if (sh_base + m < LDS::kMatch) listed[sh_base + m] = s.match[m];
       block_sync<BLOCK>();              // every wave's stores have left the CU
       // (while wave 0 signs off, the others prepare the tables of the walk that rows of
       // 65 .. 1024 matches take: wasted on all slices but the last, which would wait here anyway)
@@ -319,7 +323,7 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
       CSD_STAMP(unit, 3, CSD_CLOCK());
       if (!sh_last) return;             // the last slice goes on with all matches of the row
       M = sh_total;
-      for (int32_t m = c.tid; m < M && m < LdsScan::kMatch; m += BLOCK) s.match[m] = listed[m];
+      for (int32_t m = c.tid; m < M && m < LDS::kMatch; m += BLOCK) s.match[m] = listed[m];
       if (c.tid == 0) s.n_match = M;
       block_sync<BLOCK>();
     }
@@ -327,7 +331,7 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
     CSD_STAMP(unit, 9, (unsigned long long)M);
     if (POOLS && M > 0 && a.pool_mode != CSD_POOL_DAG) {
       auto each = [&](auto f) {
-        if (M <= LdsScan::kMatch) {
+        if (M <= LDS::kMatch) {
           for (int32_t m = c.tid; m < M; m += BLOCK) f(s.match[m], m);
         } else {
           auto g = [&](Match found) { f(found, -1); };
@@ -368,7 +372,7 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
       }
       if (!done)
         walk_streaming<BLOCK>(s, c, WinInfo{M, 0}, M, L, a.alpha_q, a.score_mode, ix.status, o, [&](auto f) {
-          if (M <= LdsScan::kMatch) {
+          if (M <= LDS::kMatch) {
             for (int32_t m = c.tid; m < M; m += BLOCK) f(s.match[m], m);
           } else {
             auto g = [&](Match found) { f(found, -1); };
@@ -859,9 +863,25 @@ __global__ __launch_bounds__(kWave) void replay_rest_kernel(RestArgs) {
 
 template <int QC, bool POOLS, bool FUZZY>
 __global__ __launch_bounds__(kScanBlock) void replay_scan_kernel(IndexView ix, int32_t steps, DraftArgs a) {
+  fetch_kernel_arguments<sizeof(IndexView) + sizeof(int32_t) + sizeof(DraftArgs)>();
   const int32_t row = replay_unit(ix, a, steps, xcd_row(ix.P * ix.N * steps));
   if (row < 0) return;
   scan_step<QC, POOLS, FUZZY>(ix, StepIn{nullptr, nullptr, nullptr, 0}, a, ScanSlices{1, nullptr, nullptr}, row, 0);
+}
+
+// The same with two rows a CU (LdsScanPair, 64 registers a lane): the scan of one, bound by instruction
+// issue, beside the walk of the other, a chain of LDS round trips.  us, replay of 32 steps with one edit,
+// one row a CU / two: 16 x 1024 positions 57 / 46, 8 problems (24 steps) 215 / 145, 16 problems (12
+// steps) 249 / 161, 32 x 1024 (16 steps) 129 / 113, edge scoring 65 / 52.  Three things made up the
+// step: two rows (57 / 52), the wave's candidates pooled (49), two spans in flight and not four,
+// which spilled less (46).
+template <int QC, bool FUZZY>
+__global__ __launch_bounds__(kScanBlock) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void replay_scan_pair_kernel(IndexView ix, int32_t steps, DraftArgs a) {
+  fetch_kernel_arguments<sizeof(IndexView) + sizeof(int32_t) + sizeof(DraftArgs)>();
+  const int32_t row = replay_unit(ix, a, steps, xcd_row(ix.P * ix.N * steps));
+  if (row < 0) return;
+  scan_step<QC, false, FUZZY, LdsScanPair>(ix, StepIn{nullptr, nullptr, nullptr, 0}, a, ScanSlices{1, nullptr, nullptr}, row, 0);
 }
 
 static __global__ __launch_bounds__(256) void accept_kernel(int64_t rows, int32_t L,

@@ -244,19 +244,21 @@ __device__ __forceinline__ bool may_match(const Ctx& c, const int32_t (&t)[kFilt
 // with three history tokens before it is filtered on those; where the filter
 // does not settle the answer, and for the few positions it does not cover (the
 // first three of a path, which are only pre-filtered, and those that touch
-// tokens this launch appends), the full comparison runs once per round for the
-// lanes' next candidate, until no lane of the wave has one left.  Hits are
+// tokens this launch appends), the full comparison runs a candidate per lane: of
+// the wave's candidates POOLED in LDS (this wave's kPoolWords at `pool`), or of
+// each lane's own, in rounds until none has one left.  Hits are
 // pushed in no particular order; every wave runs its own trip counts (push() is
 // a wave-level operation).  A row's scan can be shared by n_slices workgroups:
 // this one, number `slice`, takes every n_slices-th share of the spans.
 // QK: compile-time bound of the query length.
-template <int BLOCK, bool FUZZY, int QK = CSD_MAX_QUERY_LEN, class LDS, class Sink>
+constexpr int kPoolWords = 16 * kWave;                     // candidates of a wave's turn at most
+template <int BLOCK, bool FUZZY, int QK = CSD_MAX_QUERY_LEN, bool POOLED = false, int SPANS = 4, class LDS, class Sink>
 __device__ __forceinline__ void match_scan(const LDS& s, const Ctx& c, Sink& sink, int32_t slice = 0,
-                                           int32_t n_slices = 1) {
+                                           int32_t n_slices = 1, uint16_t* pool = nullptr) {
   const int32_t n_waves = (BLOCK / kWave) * n_slices;       // waves that share the row
   constexpr int kPerLane = 4;                              // consecutive positions of a lane
   constexpr int kSpan = kWave * kPerLane;                  // positions of a span
-  constexpr int kSpans = 4;                                // spans in flight: 16 candidate bits
+  constexpr int kSpans = SPANS;                            // in flight: 4 candidate bits each
   // (consecutive spans go to different slices: a row with fewer spans than waves still keeps
   // all its workgroups busy)
   const int lane = c.tid & 63, wave = (c.tid >> 6) * n_slices + slice;
@@ -334,20 +336,39 @@ __device__ __forceinline__ void match_scan(const LDS& s, const Ctx& c, Sink& sin
         }
       }
     }
-    while (wave_ballot(todo != 0) != 0) {                     // uniform over the wave
-      bool have = todo != 0;
-      int32_t bit = have ? (int32_t)__ffs(todo) - 1 : 0;
-      todo &= todo - 1u;                                   // 0 stays 0
+    auto settle = [&](bool have, int32_t of, int32_t bit, bool decided) {   // candidate `bit` of lane `of`
       int32_t j, e, old_j = 1, new_j = 1;
       locate(g0 + (bit >> 2) * n_waves, j, e);
-      e += bit & 3;
+      e += (of - lane) * kPerLane + (bit & 3);
       bool hit = have;
       if (have) lens_of(s, c.y, j, old_j, new_j);
-      if (have && !(filter_decides && (filtered >> bit & 1u)))
+      if (have && !decided)
         hit = !FUZZY ? gram_equals_query<QK>(c, j, e, old_j)
                      : (c.eps > 1 ? gram_within_edits<QK>(c, j, e, old_j)     // uniform over the launch
                                   : gram_near_query<QK>(c, j, e, old_j));
       sink.push(c.y, hit, make_match(c.y, j, e, old_j, new_j));
+    };
+    const uint32_t decided = filter_decides ? filtered : 0u;
+    if constexpr (POOLED) {
+      const uint32_t up_to = wave_prefix(__popc(todo));    // candidates of the lanes up to this one
+      const int32_t total = __builtin_amdgcn_readlane((int)up_to, kWave - 1);
+      uint32_t at = up_to - __popc(todo);
+      for (; todo != 0; todo &= todo - 1u) {
+        const uint32_t bit = (uint32_t)__ffs(todo) - 1u;
+        pool[at++] = (uint16_t)(lane << 4 | bit | (decided >> bit & 1u) << 10);
+      }
+      block_sync<kWave>();                                 // (a wave's own part of the pool)
+      for (int32_t x0 = 0; x0 < total; x0 += kWave) {      // uniform over the wave
+        const bool have = x0 + lane < total;
+        const int32_t code = have ? pool[x0 + lane] : 0;
+        settle(have, code >> 4 & (kWave - 1), code & 15, (code >> 10) != 0);
+      }
+    } else {
+      while (wave_ballot(todo != 0) != 0) {                // uniform over the wave
+        const int32_t bit = todo != 0 ? (int32_t)__ffs(todo) - 1 : 0;
+        settle(todo != 0, lane, bit, (decided >> bit & 1u) != 0);
+        todo &= todo - 1u;                                 // 0 stays 0
+      }
     }
   }
 }

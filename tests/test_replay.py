@@ -232,3 +232,43 @@ def test_a_workspace_without_the_part_for_speed(monkeypatch, edits, flags):
     monkeypatch.setattr(binding, "workspace_bytes", lambda cfg: size - 1)
     with pytest.raises(binding.CsdError):
         make()
+
+
+# the scan with two rows a CU, its candidates pooled by wave: paths around a span of 256 positions and
+# the first positions of a path, around the largest problem that it takes (2^16 positions); symbols few
+# enough for rows of up to a wave's, a workgroup's and the match list's worth of matches and beyond
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,edits,mode", [
+    (1, 2, 9, 6, 3, 4, 4, 1, 0),
+    (2, 5, 255, 5, 3, 8, 30, 1, 0),
+    (1, 3, 257, 5, 2, 3, 9, 1, 1),
+    (3, 16, 258, 4, 4, 8, 12, 1, 0),
+    (1, 16, 1024, 3, 3, 8, 40, 1, 0),
+    (1, 32, 2048, 2, 3, 8, 150, 1, 0),
+    (1, 16, 1024, 2, 3, 32, 12, 1, 0),
+    (1, 9, 700, 3, 4, 16, 20, 1, 1),
+    (1, 9, 700, 3, 3, 6, 6, 0, 0),
+    (1, 8, 400, 2, 4, 5, 5, 2, 0),
+    (1, 33, 2048, 2, 3, 8, 150, 1, 0),                     # one row a CU
+    (1, 9, 700, 3, 6, 8, 8, 1, 0),
+])
+def test_scanned_rows_beside_each_other(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode):
+    rng = np.random.default_rng(paths * max_len + vocab)
+    print("scan", problems, paths, max_len, steps, query, draft, vocab, edits, mode, flush=True)
+    dev, warm = torch.device("cuda:0"), max_len - steps
+    tokens = rng.integers(0, vocab, size=(problems, paths, max_len)).astype(np.int32)
+    motif = rng.integers(0, vocab, size=(problems, 1, max_len)).astype(np.int32)
+    tokens = np.where(rng.random(tokens.shape) < 0.3, motif, tokens)
+    probs = rng.random(tokens.shape).astype(np.float32)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
+    ix = binding.Index(problems, paths, max_len, vocab, query, draft, 0.7, mode, binding.MATCH_SCAN, device=dev, max_edits=edits)
+    counts = rng.integers(warm // 2, warm + 1, size=(problems, paths)).astype(np.int32)
+    counts[:, 0] = warm
+    ix.append(put(tokens[:, :, :warm]), put(probs[:, :, :warm]), put(counts), warm)
+    later = np.take_along_axis(tokens, np.minimum(counts[..., None] + np.arange(steps), max_len - 1), axis=2)
+    later_probs = np.take_along_axis(probs, np.minimum(counts[..., None] + np.arange(steps), max_len - 1), axis=2)
+    out = ix.replay(steps, put(later.transpose(2, 0, 1)), put(later_probs.transpose(2, 0, 1)), query, draft)
+    lengths = (counts[None] + np.arange(1, steps + 1)[:, None, None]).astype(np.int32)
+    want = oracle.draft_many(tokens, probs, lengths, query, draft, 0.7, mode, eps=edits)
+    for key, name in (("tokens", "draft"), ("length", "draft_len"), ("token_scores", "token_scores"), ("path_scores", "path_scores")):
+        assert np.array_equal(out[key].cpu().numpy().view(np.int32), want[name].view(np.int32)), key
+    assert ix.status() == 0
