@@ -362,7 +362,7 @@ void launch_replay_steps(const csd_index* h, const IndexView& v, const ReplayIn&
   IndexView w = v;
   w.meta_old = w.meta_new = h->step_meta;
   if (!h->indexed) launch_replay_scan(w, in.steps, a, st);
-  else if (v.eps > 0) launch_replay_fuzzy(w, in.steps, a, st);
+  else if (v.eps > 0) launch_replay_fuzzy(w, in.steps, a, h->rest_list, st);
   else if (a.pool_mode != CSD_POOL_DAG || v.options != 0) launch_replay_general(w, in.steps, a, st);
   else launch_replay(w, in.steps, a, h->rest, h->rest_list, st);
 }

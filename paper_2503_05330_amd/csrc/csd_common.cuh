@@ -426,6 +426,8 @@ typedef LdsT<256, 256, 512, 1, 64> LdsWaveSmall;
 // One wave per row with one-edit matching through the index: such queries have
 // many more matches, so the list is longer (66 KB, two rows per CU).
 typedef LdsT<1024, 4096, 2048, 1> LdsWaveFuzzy;
+// The same for rows of up to 64 matches (replay_leave_kernel): 19 KB, eight rows a CU.
+typedef LdsT<512, 512, 1024, 1> LdsWaveLeave;
 // One wave per row, all rows of a problem (at most 16) in one workgroup that runs many
 // steps per launch (the device-side loops): 10 KB per row, 160 KB per workgroup.  Rows with
 // more than 64 matches (at a draft length of 8) take the bounded-memory tiers.

@@ -500,7 +500,8 @@ __device__ __forceinline__ Cand scan_successors(const LDS& s, Region r, int d, i
 // slower on the one-edit step; the ranks of all instances of all layers tabulated before the
 // walk, which then needs one argmax and one barrier per layer, 20 % slower: unrolled over the
 // layers its code is long, and code that runs once per launch is fetched cold.)
-template <int BLOCK, class LDS>
+// LEAVE: waves without a match do leave.
+template <int BLOCK, bool LEAVE = true, class LDS>
 __device__ __forceinline__ void walk_wide(LDS& s, const Ctx& c, int32_t M, int32_t L,
                                           uint32_t alpha_q, int score_mode, DraftOut& o) {
   constexpr uint32_t kSet = 2 * BLOCK;                 // at most BLOCK distinct successors: half load
@@ -546,7 +547,7 @@ __device__ __forceinline__ void walk_wide(LDS& s, const Ctx& c, int32_t M, int32
   request(1, tok_a, prob_a);
   request(2, tok_b, prob_b);
   lds_barrier<BLOCK>();                               // the set is empty
-  if (c.tid >= ((M + kWave - 1) & ~(kWave - 1))) return;   // waves without a match
+  if (LEAVE && c.tid >= ((M + kWave - 1) & ~(kWave - 1))) return;   // waves without a match
   const int lane = c.tid & (kWave - 1);
   for (int32_t d = 1; d <= L; ++d) {
     consume_here(tok_a);
@@ -670,7 +671,8 @@ __device__ __forceinline__ void walk_tab_clear(LDS& s, int tid, int first) {
 }
 
 // cleared: walk_tab_clear has been called (and a barrier passed) since the table was last used.
-template <int BLOCK, class LDS>
+// LEAVE: waves without a match leave before the walk.
+template <int BLOCK, bool LEAVE = true, class LDS>
 __device__ __forceinline__ bool walk_tab(LDS& s, const Ctx& c, int32_t M, int32_t L, uint32_t alpha_q,
                                          DraftOut& o, bool cleared = false) {
   constexpr uint32_t kTabSlots = tab_slots<LDS>();
@@ -785,7 +787,7 @@ __device__ __forceinline__ bool walk_tab(LDS& s, const Ctx& c, int32_t M, int32_
   lds_barrier<BLOCK>();                                // Eq. 5's sums are complete
   CSD_STAMP(c.unit, 11, CSD_CLOCK());
   if (s.overflow) return false;                        // uniform over the workgroup
-  if (c.tid >= ((M + kWave - 1) & ~(kWave - 1))) return true;   // waves without a match of their own
+  if (LEAVE && c.tid >= ((M + kWave - 1) & ~(kWave - 1))) return true;   // waves without a match of their own
   const int lane = c.tid & (kWave - 1);
   const bool mine_too = c.tid < M;                     // here r = 0, t = tid
   // A layer's node of this thread's match is no part of the choice: its slot is read two

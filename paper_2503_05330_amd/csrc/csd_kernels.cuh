@@ -233,7 +233,9 @@ __device__ __forceinline__ void fetch_windows(LDS& s, const Ctx& c, int32_t M, i
 // FUZZY: matching tolerates one edit (compiled apart from the exact kernel: code a launch
 // does not run still costs it time).
 // QC: compile-time bound (4 or 8) of the query length: the comparison loops are unrolled to it.
-template <int QC, bool POOLS, bool FUZZY, class LDS = LdsScan>
+// INDEXED: queries of kmax tokens are looked up in the variant index instead, and the workgroup goes on
+// to another row: no wave leaves.
+template <int QC, bool POOLS, bool FUZZY, class LDS = LdsScan, bool INDEXED = false>
 __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in, const DraftArgs& a,
                                           const ScanSlices& sl, int32_t row, int32_t slice) {
   constexpr int BLOCK = kScanBlock;
@@ -277,7 +279,8 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
     constexpr int kSpans = (std::is_same<LDS, LdsScanPair>::value || QC > 4) ? 2 : 4;
     static_assert(sizeof(s.table) >= BLOCK / kWave * kPoolWords * sizeof(uint16_t), "a pool per wave");
     ListSink<LDS> sink{&s};
-    match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, slice, sl.n, pool);
+    if (INDEXED && c.q == ix.kmax) match_variants<BLOCK, QC>(s, c, sink);
+    else match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, slice, sl.n, pool);
     block_sync<BLOCK>();
     int32_t M = s.n_match;
     CSD_STAMP(unit, 2, CSD_CLOCK());
@@ -366,8 +369,8 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
         // one thread per match: node weights tabulated first, or layer by layer
         // (the second where the first does not apply or finds too many distinct continuations)
         if (!walk_tab_fits<BLOCK>(M, L, ix.vocab, a.score_mode) ||
-            !walk_tab<BLOCK>(s, c, M, L, a.alpha_q, o, sl.n > 1))
-          walk_wide<BLOCK>(s, c, M, L, a.alpha_q, a.score_mode, o);
+            !walk_tab<BLOCK, !INDEXED>(s, c, M, L, a.alpha_q, o, sl.n > 1))
+          walk_wide<BLOCK, !INDEXED>(s, c, M, L, a.alpha_q, a.score_mode, o);
         done = true;
       }
       if (!done)
@@ -438,6 +441,13 @@ struct LoopTail {
   int32_t n, max_len;
 };
 
+// Rows that a wave leaves to a workgroup (replay_leave_kernel): those with more matches than the walks
+// with a lane per match take.
+struct LeaveTail {
+  RestList list;
+  int32_t unit;                 // see replay_unit
+};
+
 // One decode step of one row by one wave: front end, DAG, walk, outputs, accept, tail.
 // APPENDS: the wave also appends the row's tokens and files them in the index (false: another
 // wave of the workgroup does, see wave_append).  s: the row's on-chip state.
@@ -461,7 +471,8 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
   InsertTicket ticket;
   VariantTicket tickets;
   bool ticket_used;
-  int32_t M = FUZZY ? wave_front_end_fuzzy<LCAP, QC, APPENDS>(s, c, ix, p, a.k, L, wi, tickets, ticket_used)
+  constexpr bool kLeaves = std::is_same<TAIL, LeaveTail>::value;
+  int32_t M = FUZZY ? wave_front_end_fuzzy<LCAP, QC, APPENDS, kLeaves ? kWave : INT_MAX>(s, c, ix, p, a.k, L, wi, tickets, ticket_used)
                     : wave_front_end<LCAP, QC, APPENDS, MULTI>(s, c, ix, p, a.k, L, wi, ticket, ticket_used);
   block_sync<kWave>();
 #ifdef CSD_STAMPS
@@ -498,6 +509,14 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
       block_sync<kWave>();
     }
   }
+  if constexpr (kLeaves) {
+    const int32_t windows = LDS::kWin / (2 * L) + (a.pool_mode == CSD_POOL_DAG ? (int32_t)sizeof(s.table) / (2 * L * (int32_t)sizeof(int32_t)) : 0);
+    if (M > kWave || (M > 8 && M > windows)) {           // uniform over the wave
+      const uint32_t xcd = blockIdx.x & 7;
+      if (lane == 0) *tail.list.unit(xcd, false, atomicAdd(tail.list.count(xcd, false), 1)) = tail.unit;
+      return;
+    }
+  }
 
   DraftOut o;
   if (POOLS && M > 0 && a.pool_mode != CSD_POOL_DAG) {
@@ -529,6 +548,8 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
     // are laid over the table, which this walk does not use
     walk_matches(s, c, M, L, wi, s.win, a.alpha_q, a.score_mode, o, reinterpret_cast<int32_t*>(s.table),
                  LDS::kWin / (2 * L));
+  } else if (kLeaves) {
+    // (M is 0)
   } else if (M > 0 && M <= 2 * kWave && M <= LDS::kWin / (2 * L)) {
     walk_matches<false, 2>(s, c, M, L, wi, s.win, a.alpha_q, a.score_mode, o);   // two matches per lane
   } else if (M > 0 && walk_tab_wave_fits<LDS>(M, ix.vocab, a.score_mode) &&
@@ -858,6 +879,33 @@ __global__ __launch_bounds__(kWave) void replay_rest_kernel(RestArgs) {
     row_step<LCAP, false, LDS, false, QC, false>(s, v, StepIn{nullptr, nullptr, nullptr, 0}, b, NoTail{}, row,
                                                  (int)threadIdx.x);
     block_sync<kWave>();
+  }
+}
+
+// One edit through the index, many drafts: most rows have few matches and are done by a wave, on a small
+// layout so that all of them start at once; the few with more than 64, which set the time (front end
+// 25 us, walk 60), are listed, each XCD's apart, for workgroups that look up with all waves and walk like
+// the scan.
+template <int LCAP, int QC>
+__global__ __launch_bounds__(kWave) void replay_leave_kernel(IndexView ix, int32_t steps, DraftArgs a, RestList list) {
+  fetch_kernel_arguments<sizeof(IndexView) + sizeof(int32_t) + sizeof(DraftArgs) + sizeof(RestList)>();
+  __shared__ LdsWaveLeave s;
+  const int32_t unit = xcd_row(ix.P * ix.N * steps), row = replay_unit(ix, a, steps, unit);
+  if (row < 0) return;
+  row_step<LCAP, true, LdsWaveLeave, true, QC, false>(s, ix, StepIn{nullptr, nullptr, nullptr, 0}, a, LeaveTail{list, unit}, row,
+                                                      (int)threadIdx.x);
+}
+
+template <int QC, bool POOLS>
+__global__ __launch_bounds__(kScanBlock) void replay_left_kernel(IndexView ix, int32_t steps, DraftArgs a, RestList list) {
+  const uint32_t xcd = blockIdx.x & 7;
+  const int32_t count = __builtin_amdgcn_readfirstlane(*list.count(xcd, false));
+  for (int32_t x = (int32_t)(blockIdx.x >> 3); x < count; x += (int32_t)(gridDim.x >> 3)) {   // uniform over the workgroup
+    IndexView v = ix;
+    DraftArgs b = a;
+    const int32_t row = replay_unit(v, b, steps, __builtin_amdgcn_readfirstlane(*list.unit(xcd, false, x)));
+    scan_step<QC, POOLS, true, LdsScan, true>(v, StepIn{nullptr, nullptr, nullptr, 0}, b, ScanSlices{1, nullptr, nullptr}, row, 0);
+    __syncthreads();
   }
 }
 

@@ -30,7 +30,8 @@ void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);
 void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest,
                    int32_t* rest_list, hipStream_t st);
 void launch_replay_general(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);
-void launch_replay_fuzzy(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);
+void launch_replay_fuzzy(const IndexView& v, int32_t steps, const DraftArgs& a, int32_t* rest_list,
+                         hipStream_t st);
 void launch_replay_scan(const IndexView& v, int32_t steps, const DraftArgs& a, hipStream_t st);
 
 }  // namespace csd

@@ -960,7 +960,8 @@ __device__ __forceinline__ bool consume_variant_bucket(LDS& s, const Ctx& c, int
 // past the end of a chain is harmless: buckets behind the first one that is not full are
 // empty).  `word` / `word_beyond`: the lane's word of bucket 0 of its group's variant in the
 // first batch (variants 0 .. 3) / the second (4 .. 7), both already requested.
-template <int LCAP, int K, class LDS>
+// LIMIT: the look-up may end when it has found more matches (the caller leaves such a row to others).
+template <int LCAP, int K, int LIMIT = INT_MAX, class LDS>
 __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& c, int32_t L,
                                                              int32_t win_cap, int32_t& n_match,
                                                              int32_t word, int32_t word_beyond) {
@@ -1034,7 +1035,7 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
 #pragma unroll 1
   for (int chain = 0; chain < 12; ++chain) {
     const u64 goes_on = chain < 4 ? on_a : chain < 8 ? on_b : on_c;
-    if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0) continue;        // uniform over the wave
+    if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0 || n_match > LIMIT) continue;   // uniform over the wave
     const GramHash gh = variant_hash(c.Q, c.q, chain);                // the same in every lane
     uint32_t r0 = 1;
     int32_t tail = gram_bucket(tbl, gh, r0 + grp < n_buckets ? r0 + grp : 0u, c.bucket_mask)[sub];
@@ -1044,9 +1045,68 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
       uint32_t rn = r0 + 4 + grp;                                     // next batch: in flight meanwhile
       int32_t next_tail = gram_bucket(tbl, gh, rn < n_buckets ? rn : 0u, c.bucket_mask)[sub];
       bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail);
-      if (wave_ballot(!tail_full) != 0) break;                         // the chain ends in this batch
+      if (wave_ballot(!tail_full) != 0 || n_match > LIMIT) break;      // the chain ends in this batch
       tail = next_tail;
     }
+  }
+}
+
+// The same by all waves of a workgroup, without windows, for rows of many matches: a wave per chain, or
+// several that take every so many batches of four buckets of it.  For queries of kmax tokens, in
+// launches that append nothing; the lengths are in LDS.
+template <int BLOCK, int K, class LDS, class Sink>
+__device__ __forceinline__ void match_variants(const LDS& s, const Ctx& c, Sink& sink) {
+  const int lane = c.tid & (kWave - 1), sub = lane & 15, grp = lane >> 4;
+  const int32_t wave = __builtin_amdgcn_readfirstlane(c.tid >> 6);
+  const Paths& y = c.y;
+  // position kmax - 1 of each path: no posting exists for it
+  for (int32_t j0 = wave * kWave; j0 < y.N; j0 += BLOCK) {   // uniform over the wave
+    const int32_t j = j0 + lane;
+    int32_t t[K + 1], old_j = 0, new_j = 0;
+    const bool have = j < y.N && j != c.skip;
+    if (have) lens_of(s, y, j, old_j, new_j);
+#pragma unroll
+    for (int a = 0; a <= K; ++a) {
+      const bool is_one = a < c.kmax - 1;
+      t[a] = y.tok[y.cell(have ? j : 0, is_one ? c.kmax - 2 - a : 0)];
+      t[a] = is_one ? t[a] : 0;
+    }
+    const bool hit = have && c.kmax - 1 < old_j && near_query<K>(c, c.kmax - 1, t);
+    sink.push(y, hit, make_match(y, j, c.kmax - 1, old_j, new_j));
+  }
+  const int32_t chains = c.q + 1, shares = BLOCK / kWave / chains, chain = wave % chains, share = wave / chains;
+  static_assert(BLOCK / kWave > CSD_MAX_QUERY_LEN, "a wave for every chain");
+  if (share >= shares || !variant_is_new(c.Q, chain)) return;      // uniform over the wave
+  const uint32_t n_buckets = c.bucket_mask + 1;
+  int32_t* tbl = const_cast<int32_t*>(c.gram);
+  const GramHash gh = variant_hash(c.Q, c.q, chain);
+  auto request = [&](uint32_t r) { return gram_bucket(tbl, gh, r < n_buckets ? r : 0u, c.bucket_mask)[sub]; };
+  uint32_t r0 = 4u * (uint32_t)share;
+  int32_t next = request(r0 + grp);
+  for (; r0 < n_buckets; r0 += 4u * (uint32_t)shares) {            // (past a chain's end: see above)
+    int32_t word = next;
+    next = request(r0 + 4u * (uint32_t)shares + grp);              // in flight meanwhile
+    consume_here(word);
+    if (r0 + grp >= n_buckets) word = -1;
+    bool full;
+    bool cand = bucket_has_posting(word, lane, full);
+    const int32_t filed_as = word >> kVariantShift, pos = word & ((1 << kVariantShift) - 1);
+    const int32_t j = y.pos_path(pos), e = y.pos_index(pos);
+    int32_t tv[K + 1], old_j = 0, new_j = 0;
+    cand = cand && j != c.skip && j < y.N && e >= c.q;             // postings are filed for e >= kmax only
+    if (cand) {
+      lens_of(s, y, j, old_j, new_j);
+      cand = e < old_j;
+    }
+#pragma unroll
+    for (int a = 0; a <= K; ++a) {                                 // e >= q: only token q may not exist
+      const bool is_one = cand && a <= c.q && a < e;
+      tv[a] = y.tok[is_one ? y.cell(j, e - 1 - a) : 0];
+      tv[a] = is_one ? tv[a] : 0;
+    }
+    const bool hit = cand && near_query<K>(c, e, tv) && variant_counts<K>(c, tv, chain, filed_as);
+    sink.push(y, hit, make_match(y, j, e, old_j, new_j));
+    if (wave_ballot(!full) != 0) break;                            // the chain ends in this batch
   }
 }
 
@@ -1082,7 +1142,8 @@ __device__ __forceinline__ void wave_append_fuzzy(const Ctx& c, const IndexView&
 // K: compile-time bound (4 or 8) of the index's gram length: the predicates are unrolled to it.
 // APPENDS: this wave also appends the row's token and files it (false: another wave does, see
 // wave_append_fuzzy).
-template <int LCAP, int K = CSD_MAX_QUERY_LEN, bool APPENDS = true, class LDS>
+// LIMIT: see lookup_variants_with_windows.
+template <int LCAP, int K = CSD_MAX_QUERY_LEN, bool APPENDS = true, int LIMIT = INT_MAX, class LDS>
 __device__ __forceinline__ int32_t wave_front_end_fuzzy(LDS& s, Ctx& c, const IndexView& ix,
                                                         int32_t p, int32_t k, int32_t L, WinInfo& wi,
                                                         VariantTicket& ticket, bool& ticket_used) {
@@ -1158,7 +1219,7 @@ __device__ __forceinline__ int32_t wave_front_end_fuzzy(LDS& s, Ctx& c, const In
   wi.n_fresh = n_match;
   wi.win_cap = use_index ? LDS::kWin / (2 * L) : 0;
   if (use_index) {
-    lookup_variants_with_windows<LCAP, K>(s, c, L, wi.win_cap, n_match, word, word_beyond);
+    lookup_variants_with_windows<LCAP, K, LIMIT>(s, c, L, wi.win_cap, n_match, word, word_beyond);
   } else if (c.q > 0) {
     WaveListSink<LDS> sink{&s, &n_match, lane};
     match_plain<true>(s, c, sink);                      // covers old and new positions alike

@@ -252,15 +252,40 @@ def test_a_workspace_without_the_part_for_speed(monkeypatch, edits, flags):
     (1, 9, 700, 3, 6, 8, 8, 1, 0),
 ])
 def test_scanned_rows_beside_each_other(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode):
+    _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, binding.MATCH_SCAN)
+
+
+# one edit through the index with more drafts than are under way at once: rows of up to 64 matches, of a
+# workgroup's worth and of more (few symbols), drafts whose windows hold fewer matches than a wave has
+# lanes, chains of many buckets and queries of up to eight tokens, paths shorter than a gram, all pools
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,mode,pool", [
+    (1, 16, 256, 40, 4, 8, 12, 0, 0),
+    (2, 9, 300, 30, 4, 16, 9, 1, 0),
+    (3, 20, 100, 10, 2, 4, 14, 0, 0),
+    (1, 66, 130, 8, 5, 32, 7, 0, 0),
+    (1, 26, 120, 20, 8, 10, 3, 0, 0),
+    (1, 30, 400, 18, 3, 8, 5, 1, 0),
+    (1, 70, 200, 8, 4, 8, 4, 0, 0),
+    (60, 3, 12, 3, 4, 5, 3, 0, 0),
+    (1, 20, 300, 26, 4, 7, 10, 0, 1),
+    (1, 40, 260, 13, 3, 6, 6, 0, 2),
+])
+def test_rows_left_to_workgroups(oracle, problems, paths, max_len, steps, query, draft, vocab, mode, pool):
+    assert problems * paths * steps > 512 and steps <= max(max_len // 4, 16)
+    _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, 1, mode, binding.MATCH_INDEX, pool)
+
+
+def _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, matcher, pool=0):
     rng = np.random.default_rng(paths * max_len + vocab)
-    print("scan", problems, paths, max_len, steps, query, draft, vocab, edits, mode, flush=True)
+    print("oracle", matcher, pool, problems, paths, max_len, steps, query, draft, vocab, edits, mode, flush=True)
     dev, warm = torch.device("cuda:0"), max_len - steps
     tokens = rng.integers(0, vocab, size=(problems, paths, max_len)).astype(np.int32)
     motif = rng.integers(0, vocab, size=(problems, 1, max_len)).astype(np.int32)
     tokens = np.where(rng.random(tokens.shape) < 0.3, motif, tokens)
     probs = rng.random(tokens.shape).astype(np.float32)
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
-    ix = binding.Index(problems, paths, max_len, vocab, query, draft, 0.7, mode, binding.MATCH_SCAN, device=dev, max_edits=edits)
+    ix = binding.Index(problems, paths, max_len, vocab, query, draft, 0.7, mode, matcher, device=dev, max_edits=edits,
+                       pool_mode=pool)
     counts = rng.integers(warm // 2, warm + 1, size=(problems, paths)).astype(np.int32)
     counts[:, 0] = warm
     ix.append(put(tokens[:, :, :warm]), put(probs[:, :, :warm]), put(counts), warm)
@@ -268,7 +293,7 @@ def test_scanned_rows_beside_each_other(oracle, problems, paths, max_len, steps,
     later_probs = np.take_along_axis(probs, np.minimum(counts[..., None] + np.arange(steps), max_len - 1), axis=2)
     out = ix.replay(steps, put(later.transpose(2, 0, 1)), put(later_probs.transpose(2, 0, 1)), query, draft)
     lengths = (counts[None] + np.arange(1, steps + 1)[:, None, None]).astype(np.int32)
-    want = oracle.draft_many(tokens, probs, lengths, query, draft, 0.7, mode, eps=edits)
+    want = oracle.draft_many(tokens, probs, lengths, query, draft, 0.7, mode, eps=edits, pool_mode=pool)
     for key, name in (("tokens", "draft"), ("length", "draft_len"), ("token_scores", "token_scores"), ("path_scores", "path_scores")):
         assert np.array_equal(out[key].cpu().numpy().view(np.int32), want[name].view(np.int32)), key
     assert ix.status() == 0
