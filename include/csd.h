@@ -159,10 +159,12 @@ typedef struct {
 
 /* Size in bytes of the device workspace csd_create needs for this config.  The last part
  * of it is for speed only: the notes of csd_replay's steps side by side (up to
- * 2^19 rows (problem, path, step) of 16 to 48 bytes, and 4.5 bytes each) and the counts of
- * csd_append's workgroups (64 bytes for each of up to 2^16 paths).  csd_create also takes a
- * workspace without this part, as earlier builds sized it; csd_replay then takes a launch
- * per step and csd_append a wave per path, with the same results. */
+ * 2^19 rows (problem, path, step) of 16 to 48 bytes, and 4.5 bytes each), the counts of
+ * csd_append's workgroups (64 bytes for each of up to 2^16 paths) and, for an index of 2^19
+ * to 2^22 postings, the sorted postings of a bulk append (12 to 24 bytes each).  csd_create
+ * also takes a workspace without this part (csd_replay then takes a launch per step and
+ * csd_append a wave per path) or without the sorted postings, as earlier builds sized it,
+ * with the same results. */
 int csd_workspace_bytes(const csd_config* cfg, size_t* out_bytes);
 
 /* Creates an index (the draft pool of the Method section, "Dynamic Draft Pool

@@ -63,8 +63,10 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t tok, pq, meta, status, gram, slices, done, step_meta, rest, rest_list, total;
+  size_t tok, pq, meta, status, gram, slices, done, step_meta, rest, rest_list, bins, total;
   size_t needed;                // up to `done`: what lies behind is there for speed
+  size_t records, runs, over;   // bytes of the parts of `bins`
+  int32_t n_bins, bin_log2;     // bins of a problem (0: none), buckets of one
   int32_t n_slices;             // workgroups that share a row's scan (scan mode, few rows)
   int32_t replay_steps;         // steps of a replay that run side by side
   int32_t meta_stride, eshift;
@@ -133,6 +135,14 @@ int validate(const csd_config* c) {
   return CSD_OK;
 }
 
+// Postings of an append from which they may be sorted by bins of buckets (sorted_append), and postings that an
+// index holds up to which there is scratch memory for it (12 to 24 bytes for each).
+constexpr int64_t kBinPostings = 1 << 19, kMostBinPostings = 1 << 22;
+// Bins of a problem, so that a workgroup for each fills the chip, and their least size.
+constexpr int32_t kBinsWanted = 256, kBinBucketsLog2Least = 6;
+// Postings of an append to a bin, from which it pays.
+int64_t bin_least(bool one_edit) { return one_edit ? 256 : 768; }
+
 Layout make_layout(const csd_config* c) {
   Layout l;
   size_t cells = (size_t)c->n_problems * c->n_paths * c->max_len;
@@ -189,6 +199,25 @@ Layout make_layout(const csd_config* c) {
     l.rest_list = at;
     at += align_up(((size_t)l.replay_steps * rows + RestList::kCounters + kRestPad) * sizeof(int32_t));
   }
+  // the scratch memory of a bulk append that sorts its postings: 8 bytes for each that a path rounded up to whole
+  // sorting workgroups has room for, 4 for each that the index holds, and a word per bin and sorting workgroup
+  l.bins = at;
+  l.n_bins = 0;
+  const int64_t variants = c->max_edits > 0 ? c->max_query_len + 1 : 1;
+  const int64_t sources = (int64_t)c->n_paths * ((c->max_len + kBinSource - 1) / kBinSource);
+  if (l.n_buckets > 0 && (int64_t)cells * variants >= kBinPostings && (int64_t)cells * variants <= kMostBinPostings &&
+      sources <= kMostBins && c->max_len >= kBinSource / 2) {
+    l.bin_log2 = kBinBucketsLog2Least;
+    while (((l.n_buckets >> l.bin_log2) > (uint32_t)kBinsWanted) && (1 << l.bin_log2) < kBinBuckets) ++l.bin_log2;
+    const int64_t n_bins = l.n_buckets >> l.bin_log2;
+    if (n_bins >= 1 && n_bins <= kMostBins && (int64_t)c->n_paths * c->max_len * variants >= bin_least(c->max_edits > 0) * n_bins) {
+      l.n_bins = (int32_t)n_bins;
+      l.records = align_up((size_t)c->n_problems * sources * kBinSource * variants * sizeof(BinRecord));
+      l.runs = align_up((size_t)c->n_problems * l.n_bins * sources * sizeof(uint32_t));
+      l.over = align_up(cells * variants * sizeof(int32_t));
+      at += l.records + l.runs + l.over + align_up(((size_t)c->n_problems * l.n_bins * 2 + 1) * sizeof(int32_t));
+    }
+  }
   l.total = at;
   return l;
 }
@@ -224,6 +253,7 @@ struct csd_index {
   u64* rest;                    // [replay_steps * P * N / 16 + 1] see replay_quad_kernel
   int32_t* rest_list;           // see RestList
   int32_t replay_steps;
+  Bins bins;                    // see csd_bins.cuh (ends, chunks, sources: per launch); bins 0: none
 };
 
 namespace {
@@ -293,6 +323,20 @@ bool own_problem(const csd_index* h, const IndexView& v, int32_t n) {
          (v.P - 8) * c >= (v.eps > 0 ? 64 : 96) * b;
 }
 
+// An append whose postings are sorted by bins (csd_bins.cuh) is three launches, writes and reads every posting
+// once more, and sweeps the index by a workgroup per bin: it takes many postings, and many to a bin (with
+// counts, which may take few of those offered, it is not taken).  Measured, us, by atomics / sorted, one edit,
+// index empty and, behind it, half full or more: 1 problem of 64 paths, 4096 tokens 90 / 51; 2048, 48 / 37,
+// 56 / 43; 1024 (3.3e5 postings) 25 / 28, 35 / 35; 3 problems 192 / 73, 118 / 56, 63 / 44; 12 of 32, 2048
+// (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102.  Exact: 64
+// paths, 4096 tokens (1024 to a bin): 1 problem 21 / 20, 2 41 / 29, 4 70 / 46, 16 247 / 135; 2048 tokens (512):
+// 4 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.
+bool sorted_append(const csd_index* h, const IndexView& v, const StepIn& in) {
+  const int64_t c = (int64_t)v.N * in.n * (v.eps > 0 ? v.kmax + 1 : 1);
+  return h->bins.bins > 0 && !in.counts && in.n <= v.max_len && v.P * c >= kBinPostings &&
+         c >= bin_least(v.eps > 0) * h->bins.bins;
+}
+
 // Workgroups of an append that the chip holds at once, and rows from which on one with counts has a
 // wave for each.
 constexpr int64_t kAppendGroups = 2048, kWaveRows = 4096;
@@ -317,6 +361,14 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
                            : (q4 ? append_problem_kernel<false, 4, false> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, false>));
     const size_t lds = n_buckets * sizeof(int32_t) * (table ? 1 + kBucketWords : 1);
     kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
+    return;
+  }
+  if (sorted_append(h, v, in)) {
+    Bins b = h->bins;
+    b.ends = h->meta[h->cur ^ 1];
+    b.chunks = (in.n + kBinSource - 1) / kBinSource;
+    b.sources = v.N * b.chunks;
+    launch_append_bins(v, in, b, maybe_empty, st);
     return;
   }
   // several workgroups a row; with counts, which may leave most of them idle, no more than the chip
@@ -456,7 +508,20 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
     h->slices.state = reinterpret_cast<u64*>(base + l.slices +
                                              align_up(rows * LdsScan::kMatch * sizeof(Match)));
   }
-  const bool whole = workspace_bytes >= l.total;         // else: as sized before there was that part
+  const bool whole = workspace_bytes >= l.bins;          // else: as sized before there was that part
+  h->bins = Bins{};
+  if (l.n_bins > 0 && workspace_bytes >= l.total) {
+    char* bins = base + l.bins;
+    h->bins.records = reinterpret_cast<BinRecord*>(bins);
+    h->bins.runs = reinterpret_cast<uint32_t*>(bins + l.records);
+    h->bins.over = reinterpret_cast<int32_t*>(bins + l.records + l.runs);
+    h->bins.over_first = reinterpret_cast<int32_t*>(bins + l.records + l.runs + l.over);
+    h->bins.over_count = h->bins.over_first + (size_t)cfg->n_problems * l.n_bins;
+    h->bins.over_used = h->bins.over_count + (size_t)cfg->n_problems * l.n_bins;
+    h->bins.variants = cfg->max_edits > 0 ? cfg->max_query_len + 1 : 1;
+    h->bins.bins = l.n_bins;
+    h->bins.buckets_log2 = l.bin_log2;
+  }
   h->done = whole ? reinterpret_cast<int32_t*>(base + l.done) : nullptr;
   h->view.P = cfg->n_problems;
   h->view.N = cfg->n_paths;

@@ -736,7 +736,7 @@ __global__ __launch_bounds__(16 * kWave) void step_multi_kernel(IndexView ix, Mu
 // drafts a CU holds at once.  us for reset, append of the past and replay, a launch per step / this:
 // 16 paths x 1024 tokens, 64 steps 355 / 26; 64 x 4096, 48 steps 357 / 41; 64 problems of 16 x 1024,
 // 48 steps 504 / 85; 1024 problems, 24 steps 1477 / 370; one edit by scan, 16 x 1024, 32 steps
-// 622 / 61; one edit through the index, 64 x 4096, 24 steps 686 / 181 .. 202.
+// 622 / 48; one edit through the index, 64 x 4096, 24 steps 686 / 106.
 struct ReplayIn {
   const int32_t* tok;           // [steps][P][N]
   const float* prob;            // [steps][P][N] or null

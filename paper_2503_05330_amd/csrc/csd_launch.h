@@ -2,9 +2,13 @@
 // file of its own, so that they compile side by side.
 #pragma once
 
+#include "csd_bins.cuh"
 #include "csd_kernels.cuh"
 
 namespace csd {
+
+// a bulk append, sorted by bins of buckets (v.meta_new: v.meta_old)
+void launch_append_bins(const IndexView& v, const StepIn& in, const Bins& b, bool maybe_empty, hipStream_t st);
 
 // exact matching through the index, the usual step: DAG pool, at most one token per path
 void launch_step(const IndexView& v, const StepIn& in, const DraftArgs& a, hipStream_t st);

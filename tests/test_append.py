@@ -53,6 +53,28 @@ def test_appends_by_a_workgroup_per_problem(oracle, problems, paths, max_len, qu
     _appends(oracle, problems, paths, max_len, 40, query, edits, binding.MATCH_INDEX, sizes, ragged, few=3)
 
 
+# what sorts its postings by bins of buckets first: paths around a sorting workgroup's 1024 positions, one
+# and several problems, an empty index and one that holds postings, grams of up to four tokens and longer
+# ones, few symbols (chains of many buckets, which lead through other bins).  (the assertion repeats the
+# library's rule)
+@pytest.mark.parametrize("problems,paths,max_len,vocab,query,edits,sizes", [
+    (1, 64, 8300, 40, 3, 0, (8193, 3)),
+    (1, 130, 4150, 6, 4, 0, (5, 4096)),
+    (3, 50, 4200, 300, 6, 0, (70, 4097)),
+    (1, 30, 3600, 40, 4, 1, (3500, 1, 60)),
+    (2, 24, 1750, 12, 6, 1, (63, 1650)),
+])
+def test_appends_sorted_by_bins(oracle, problems, paths, max_len, vocab, query, edits, sizes):
+    postings = query + 1 if edits else 1
+    buckets = 4
+    while buckets * 8 < paths * max_len * postings:
+        buckets *= 2
+    filed = paths * max(sizes) * postings
+    assert buckets >= 1 << 14 and problems * paths * max_len * postings <= 1 << 22 and problems <= 8    # 256 bins
+    assert problems * filed >= 1 << 19 and filed >= 256 * (256 if edits else 768)
+    _appends(oracle, problems, paths, max_len, vocab, query, edits, binding.MATCH_INDEX, sizes, False)
+
+
 def test_appends_of_a_few_tokens_to_many_rows(oracle):
     """8192 rows, 50 to 63 tokens each: the claims look at the fill counts first; two symbols: at full ones."""
     for vocab, query in ((40, 3), (2, 5)):

@@ -37,7 +37,7 @@ def _captured(call):
 
 
 # a workgroup for a path's tokens and several of them; a workgroup per problem (many problems, a good
-# part of their indexes at once); matching by scan; a step that appends first (many tokens, or one-edit
+# part of their indexes at once); postings sorted first; matching by scan; a step that appends first (many tokens, or one-edit
 # matching); the ends of an odd number of appends
 @pytest.mark.parametrize("problems,paths,max_len,query,edits,flags,call,n", [
     (1, 4, 4000, 3, 0, binding.MATCH_INDEX, "append", 1),
@@ -49,6 +49,7 @@ def _captured(call):
     (64, 5, 300, 3, 0, binding.MATCH_INDEX, "append", 90),
     (64, 20, 1000, 3, 0, binding.MATCH_INDEX, "append", 352),
     (40, 5, 720, 3, 1, binding.MATCH_INDEX, "append", 210),
+    (1, 32, 8300, 3, 1, binding.MATCH_INDEX, "append", 4097),
     (1, 4, 900, 3, 0, binding.MATCH_INDEX, "step", 70),
     (2, 5, 400, 3, 1, binding.MATCH_INDEX, "step", 3),
     (112, 5, 720, 3, 0, binding.MATCH_INDEX, "step", 100),
