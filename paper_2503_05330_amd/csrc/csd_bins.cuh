@@ -2,13 +2,15 @@
 //
 // An append with a thread per position claims every slot with an atomic on memory, and those run at
 // the memory's side of the fabric, 1.1e10 per second for the whole chip: 2.6e5 postings 22 us, 1.3e6 (one
-// edit) 82 us.  Here a bin of buckets is one workgroup's, which claims in LDS:
+// edit) 88 us.  Sorted by bins they take 6 + 7 + 5 and 11 + 14 + 23: two passes over the records, one over the
+// index, and the longest chains.  A bin of buckets is one workgroup's, which claims in LDS:
 //   bin_sort_kernel   stores tokens and probabilities, and each workgroup's records (bucket, posting)
 //                     ordered by bin; a counting sort in LDS, no atomic on memory
 //   bin_file_kernel   a workgroup per bin gathers its runs of records, claims slots on its fill counts and
 //                     stores its buckets as whole lines; a posting whose first bucket is full is set aside
 //   bin_rest_kernel   files those along their chains, which lead to other bins, with atomics on memory, and
 //                     replaces the paths' ends
+// sorted_append (csd.hip) says which appends take it.
 #pragma once
 
 #include "csd_common.cuh"
