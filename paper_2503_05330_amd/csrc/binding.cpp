@@ -1,8 +1,8 @@
 // csd — the per-call part of binding.py in native code: checks the tensors, allocates the outputs
 // and calls the C-ABI.  A decode loop calls step() once per token, and in Python that took five
 // times as long as the kernel that it launches (4 paths x 256 tokens, us a call: kernel 4.2, step()
-// 21 in Python and 5.3 here, draft() 15 and 5.0, accept() 13 and 4.4, reset() 6 and 3.2, nearly all
-// of which is the launch).
+// 21 in Python and 6.7 here, draft() 15 and 6.1, accept() 13 and 4.5, reset() 6 and 3.3, most of
+// which is the launch).
 //
 // Every function returns None where an argument is not what the call usually gets (another type,
 // a tensor of another kind): binding.py then goes its own way, which raises the error or serves it.
@@ -10,9 +10,11 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <ATen/Context.h>
+#include <ATen/EmptyTensor.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
-#include <c10/core/impl/TorchDispatchModeTLS.h>
 
 #include "csd.h"
 
@@ -104,47 +106,45 @@ struct Pool {
 // The outputs of a call: int32 or float32 [steps][P][N][L] each, without the leading axis where
 // steps < 0, without the trailing one where L < 0.
 struct Shape {
-  int64_t at[4], n = 0, numel = 1;
+  int64_t at[4], n = 0;
   Shape(const Pool& p, int64_t steps, int64_t L) {
     if (steps >= 0) put(steps);
     put(p.P);
     put(p.N);
     if (L >= 0) put(L);
   }
-  void put(int64_t x) {
-    at[n++] = x;
-    numel *= x;
-  }
+  void put(int64_t x) { at[n++] = x; }
   c10::IntArrayRef sizes() const { return c10::IntArrayRef(at, n); }
 };
 
-// Allocates them: small ones as one block of memory, each from a multiple of 512 bytes on as the
-// allocator has it, so that a call pays for one allocation and not for five (0.7 us each: step() 7.8
-// and 5.3 us, draft() 7.1 and 5.0; twelve steps of 4 paths, with reset and append, 155 and 106 us).
-// Large ones are apart: there the kernel takes longer than the allocations, and one output that
-// the caller keeps would hold the memory of all of them.  A dispatch mode sees every output made.
+// Allocates them, each with a storage of its own: a caller may resize one, save it, free it or write to it
+// as out=.  The first comes from at::empty; the others straight from the allocator that served it,
+// without the dispatcher's part, half of an allocation (step() 8.1 and 6.7 us, draft() 7.2 and 6.1;
+// cut from one storage they take 5.3 and 5.1, but then an output that is resized grows into the next
+// one).  Whatever may want to see an output made (modes, tracing, function transforms, the filling
+// of new memory) gets at::empty for all.
 class Maker {
  public:
-  static constexpr int64_t kLine = 512, kShared = 1 << 16;
-  static int64_t bytes(const Shape& s) { return (s.numel * 4 + kLine - 1) / kLine * kLine; }
-  Maker(const Pool& p, int64_t together) : device_(p.device) {
-    if (together <= kShared && !c10::impl::dispatch_mode_enabled())
-      block_ = at::empty({together}, at::TensorOptions().dtype(at::kByte).device(device_));
-  }
+  explicit Maker(const Pool& p) : device_(p.device) {}
   at::Tensor operator()(at::ScalarType type, const Shape& s) {
-    if (!block_.defined()) return at::empty(s.sizes(), at::TensorOptions().dtype(type).device(device_));
-    at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(block_.storage()), block_.key_set(),
-                                                            c10::scalarTypeToTypeMeta(type));
-    t.unsafeGetTensorImpl()->set_storage_offset(at_ / 4);
-    t.unsafeGetTensorImpl()->set_sizes_contiguous(s.sizes());
-    at_ += bytes(s);
+    if (allocator_) return at::detail::empty_generic(s.sizes(), allocator_, at::DispatchKeySet(at::DispatchKey::CUDA), type, c10::nullopt);
+    at::Tensor t = at::empty(s.sizes(), at::TensorOptions().dtype(type).device(device_));
+    if (t.has_storage() && alone()) {
+      allocator_ = t.storage().allocator();
+      guard_.reset_device(t.device());                   // (an allocator serves the current device)
+    }
     return t;
   }
 
  private:
+  static bool alone() {
+    const at::DispatchKeySet usual = c10::default_included_set | c10::autocast_dispatch_keyset;
+    return (c10::impl::tls_local_dispatch_key_set().included_ - usual).empty() &&
+           !(at::globalContext().deterministicAlgorithms() && at::globalContext().deterministicFillUninitializedMemory());
+  }
   c10::Device device_;
-  at::Tensor block_;
-  int64_t at_ = 0;
+  c10::Allocator* allocator_ = nullptr;
+  c10::OptionalDeviceGuard guard_;
 };
 
 int32_t* int_data(const at::Tensor& t) { return t.defined() ? static_cast<int32_t*>(t.data_ptr()) : nullptr; }
@@ -162,7 +162,7 @@ struct Outputs {
   at::Tensor tokens, length, token_scores, path_scores, accept;
   Outputs(const Pool& p, int64_t steps, int64_t L, bool scores, bool with_accept = false) {
     const Shape per_token(p, steps, L), per_row(p, steps, -1);
-    Maker make(p, (1 + scores) * (Maker::bytes(per_token) + Maker::bytes(per_row)) + with_accept * Maker::bytes(per_row));
+    Maker make(p);
     tokens = make(at::kInt, per_token);
     length = make(at::kInt, per_row);
     if (scores) {

@@ -1,8 +1,11 @@
 """The native part of the binding: it takes the usual arguments only, and what it returns is what
 the Python part returns and raises."""
+import warnings
+
 import numpy as np
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 from paper_2503_05330_amd import binding
 
@@ -82,8 +85,8 @@ def test_the_same_from_both_parts(scores):
 @pytest.mark.gpu
 @pytest.mark.parametrize("P,N,L,S", ((1, 1, 1, 1), (1, 3, 7, 2), (2, 64, 8, 3), (1, 127, 32, 1), (1, 128, 32, 1), (1, 600, 16, 2)))
 def test_outputs_of_a_call_lie_apart(P, N, L, S):
-    """Small outputs come from one block of memory, large ones from blocks of their own: none overlaps
-    another, each starts where an allocation would, and one that is kept outlives the others."""
+    """No output overlaps another, each starts where an allocation would, and one that is kept outlives
+    the others."""
     ix = binding.Index(P, N, 64, 50, 3, 32)
     tokens = torch.randint(0, 4, (S, P, N), device="cuda", dtype=torch.int32)
     targets = torch.zeros((S, P, N, L), device="cuda", dtype=torch.int32)
@@ -104,3 +107,48 @@ def test_outputs_of_a_call_lie_apart(P, N, L, S):
         ix.replay(S, tokens.flip(0), None, 3, L)         # would take a freed block of the same size
         assert torch.equal(*kept[-1])
     assert torch.equal(kept[0][0], kept[1][0])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ("draft", "step", "replay"))
+def test_each_output_has_a_storage_of_its_own(call):
+    """What a caller does in place to one output (a resize, a write as out= of another shape, a storage given
+    back) leaves the others alone, and a saved output is no larger than itself."""
+    P, N, L, S = 2, 3, 5, 2
+    ix = binding.Index(P, N, 64, 50, 3, 8)
+    tokens = torch.randint(0, 4, (S, P, N), device="cuda", dtype=torch.int32)
+    targets = torch.zeros((S, P, N, L), device="cuda", dtype=torch.int32)
+    calls = {"draft": lambda: ix.draft(3, L), "step": lambda: ix.step(tokens[0], None, None, 1, 3, L, targets=targets[0]),
+             "replay": lambda: ix.replay(S, tokens, None, 3, L, targets=targets)}
+    names = list(calls[call]())
+    for changed in names:
+        for change in (lambda t: t.resize_(4 * t.numel() + 1000).fill_(77),
+                       lambda t: torch.full((t.numel() + 500,), 77, out=t, dtype=t.dtype, device="cuda"),
+                       lambda t: t.untyped_storage().resize_(0)):
+            ix.reset()
+            out = calls[call]()
+            assert len({t.untyped_storage().data_ptr() for t in out.values()}) == len(names)
+            for t in out.values():
+                assert t.storage_offset() == 0 and t.untyped_storage().nbytes() == 4 * t.numel()
+            before = {name: t.clone() for name, t in out.items()}
+            with warnings.catch_warnings():
+                warnings.simplefilter("ignore")          # (out= of another shape)
+                change(out[changed])
+            for name in names:
+                assert name == changed or torch.equal(out[name], before[name]), (changed, name)
+
+
+@pytest.mark.gpu
+def test_a_dispatch_mode_sees_every_output():
+    class Seen(TorchDispatchMode):
+        count = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.count += func is torch.ops.aten.empty.memory_format
+            return func(*args, **(kwargs or {}))
+
+    ix = binding.Index(1, 2, 64, 50, 3, 8)
+    tokens, targets = torch.zeros((1, 2), device="cuda", dtype=torch.int32), torch.zeros((1, 2, 4), device="cuda", dtype=torch.int32)
+    with Seen() as seen:
+        ix.step(tokens, None, None, 1, 3, 4, targets=targets)
+    assert seen.count == 5
