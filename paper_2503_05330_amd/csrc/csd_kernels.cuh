@@ -275,12 +275,17 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
   CSD_STAMP(unit, 1, CSD_CLOCK());
   if (c.q > 0) {
     uint16_t* pool = reinterpret_cast<uint16_t*>(s.table) + (c.tid >> 6) * kPoolWords;   // (before the walk)
-    // (spans in flight: four where the registers hold their tokens)
-    constexpr int kSpans = (std::is_same<LDS, LdsScanPair>::value || QC > 4) ? 2 : 4;
+    // Spans in flight: four where the registers hold their tokens; the wave's candidates pooled where each
+    // is compared token by token (without edits the filter settles most).  us a step, exact, queries of 6,
+    // few symbols, four spans unpooled / two pooled: 16 x 1024 8.6 / 9.1, 64 problems 32.5 / 33.6; of 3, 64
+    // problems of 8 x 512 14.2 / 14.6.  Edits and queries beyond four tokens, two spans / four, pooled: one edit,
+    // 16 x 1024 19.3 / 19.6, 64 problems 84 / 79, 64 x 4096 71 / 61; two edits, 16 x 1024 30.6 / 34.6, 64
+    // problems 396 / 436 (one kernel serves both: its predicates spill).
+    constexpr int kSpans = (std::is_same<LDS, LdsScanPair>::value || (FUZZY && QC > 4)) ? 2 : 4;
     static_assert(sizeof(s.table) >= BLOCK / kWave * kPoolWords * sizeof(uint16_t), "a pool per wave");
     ListSink<LDS> sink{&s};
     if (INDEXED && c.q == ix.kmax) match_variants<BLOCK, QC>(s, c, sink);
-    else match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, slice, sl.n, pool);
+    else match_scan<BLOCK, FUZZY, QC, FUZZY, kSpans>(s, c, sink, slice, sl.n, pool);
     block_sync<BLOCK>();
     int32_t M = s.n_match;
     CSD_STAMP(unit, 2, CSD_CLOCK());
@@ -291,7 +296,7 @@ __device__ __forceinline__ void scan_step(const IndexView& ix, const StepIn& in,
       while (M == 0 && c.q > 1) {
         block_sync<BLOCK>();            // everybody has read the count before anybody pushes again
         --c.q;
-        match_scan<BLOCK, FUZZY, QC, true, kSpans>(s, c, sink, 0, 1, pool);
+        match_scan<BLOCK, FUZZY, QC, FUZZY, kSpans>(s, c, sink, 0, 1, pool);
         block_sync<BLOCK>();
         M = s.n_match;
       }
