@@ -916,7 +916,10 @@ __global__ __launch_bounds__(kScanBlock) void replay_left_kernel(IndexView ix, i
 
 template <int QC, bool POOLS, bool FUZZY>
 __global__ __launch_bounds__(kScanBlock) void replay_scan_kernel(IndexView ix, int32_t steps, DraftArgs a) {
-  fetch_kernel_arguments<sizeof(IndexView) + sizeof(int32_t) + sizeof(DraftArgs)>();
+  // (the early request keeps the arguments in registers, which the kernels for edits and queries beyond four
+  // tokens do not have: 53 of a lane's spilled instead of 16, 4 x 256, 24 steps 17.5 / 21.8 us; one edit,
+  // queries of three, 16 x 1024, 40 steps 45.1 / 46.6 without; exact, of three 42.4 / 41.5 without, of five 29.2 / 28.6)
+  if (FUZZY == (QC <= 4)) fetch_kernel_arguments<sizeof(IndexView) + sizeof(int32_t) + sizeof(DraftArgs)>();
   const int32_t row = replay_unit(ix, a, steps, xcd_row(ix.P * ix.N * steps));
   if (row < 0) return;
   scan_step<QC, POOLS, FUZZY>(ix, StepIn{nullptr, nullptr, nullptr, 0}, a, ScanSlices{1, nullptr, nullptr}, row, 0);
