@@ -928,7 +928,7 @@ __global__ __launch_bounds__(kScanBlock) void replay_scan_kernel(IndexView ix, i
 // The same with two rows a CU (LdsScanPair, 64 registers a lane): the scan of one, bound by instruction
 // issue, beside the walk of the other, a chain of LDS round trips.  us, replay of 32 steps with one edit,
 // one row a CU / two: 16 x 1024 positions 57 / 46, 8 problems (24 steps) 215 / 145, 16 problems (12
-// steps) 249 / 161, 32 x 1024 (16 steps) 129 / 113, edge scoring 65 / 52.  Three things made up the
+// steps) 249 / 161, edge scoring 65 / 52; scan_pairs says where it loses.  Three things made up the
 // step: two rows (57 / 52), the wave's candidates pooled (49), two spans in flight and not four,
 // which spilled less (46).
 template <int QC, bool FUZZY>

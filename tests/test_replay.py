@@ -234,9 +234,9 @@ def test_a_workspace_without_the_part_for_speed(monkeypatch, edits, flags):
         make()
 
 
-# the scan with two rows a CU, its candidates pooled by wave: paths around a span of 256 positions and
-# the first positions of a path, around the largest problem that it takes (2^16 positions); symbols few
-# enough for rows of up to a wave's, a workgroup's and the match list's worth of matches and beyond
+# the scan, one row a CU, its candidates pooled by wave: paths around a span of 256 positions and the
+# first positions of a path, large problems; symbols few enough for rows of up to a wave's, a workgroup's
+# and the match list's worth of matches and beyond
 @pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,edits,mode", [
     (1, 2, 9, 6, 3, 4, 4, 1, 0),
     (2, 5, 255, 5, 3, 8, 30, 1, 0),
@@ -248,10 +248,34 @@ def test_a_workspace_without_the_part_for_speed(monkeypatch, edits, flags):
     (1, 9, 700, 3, 4, 16, 20, 1, 1),
     (1, 9, 700, 3, 3, 6, 6, 0, 0),
     (1, 8, 400, 2, 4, 5, 5, 2, 0),
-    (1, 33, 2048, 2, 3, 8, 150, 1, 0),                     # one row a CU
+    (1, 33, 2048, 2, 3, 8, 150, 1, 0),
     (1, 9, 700, 3, 6, 8, 8, 1, 0),
 ])
 def test_scanned_rows_beside_each_other(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode):
+    _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, binding.MATCH_SCAN)
+
+
+# the same with two rows a CU, which takes more drafts: fewest of them, largest problems by the tokens that
+# an edit leaves of the query.  (the assertion repeats the library's rule)
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,edits,mode", [
+    (48, 2, 9, 6, 3, 4, 4, 1, 0),
+    (20, 5, 255, 6, 3, 8, 30, 1, 0),
+    (35, 3, 257, 5, 2, 3, 9, 1, 1),
+    (8, 16, 258, 4, 4, 8, 12, 1, 0),
+    (1, 16, 1024, 32, 3, 8, 40, 1, 0),
+    (1, 32, 2048, 16, 4, 8, 60, 1, 0),
+    (2, 16, 512, 16, 2, 32, 8, 1, 0),
+    (1, 16, 1024, 32, 3, 32, 12, 1, 0),
+    (10, 9, 700, 6, 4, 16, 20, 1, 1),
+    (7, 9, 700, 5, 3, 6, 6, 0, 0),
+    (1, 32, 2048, 9, 3, 8, 40, 0, 0),
+    (13, 8, 400, 5, 4, 5, 5, 2, 0),
+    (16, 4, 1024, 8, 1, 8, 5, 0, 0),
+])
+def test_scanned_rows_two_a_cu(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode):
+    left = query - edits
+    assert paths * max_len <= 1 << (16 if left >= 3 else 14 if left == 2 else 13 if edits else 12)
+    assert problems * paths * steps >= (512 if edits or left < 2 else 257)
     _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, binding.MATCH_SCAN)
 
 
