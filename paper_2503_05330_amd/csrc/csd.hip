@@ -135,6 +135,28 @@ int validate(const csd_config* c) {
   return CSD_OK;
 }
 
+// The fill counts of a problem that one workgroup appends to fit a CU's LDS (128 KB); with up to 2048
+// buckets the buckets fit too (136 KB: one stream of whole lines instead of a line written for every
+// posting; 1024 problems of 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
+constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
+
+// An append with a workgroup per problem (append_problem_kernel) reads and writes all fill counts,
+// whatever it files; its time is the problem's, 256 of them run side by side.  With a thread per
+// position and atomics on memory the time is that of all postings.  So the first form is taken from
+// as many problems P on as postings c of a problem and buckets b of its index make it the better one:
+//   (P - 8) c >= 96 b (64 b with one edit), c >= 5/8 b, and a few waves' worth of postings.
+// Measured, us, atomics / a workgroup per problem, 2048 buckets (16 paths x 1024), index half full:
+// c / b = 1/2, P = 24, 64, 256, 1024: 6.8 / 14, 9 / 15, 18 / 21, 75 / 68; c / b = 1: 8 / 14, 12 / 15,
+// 36 / 21, 112 / 69; 2: 11 / 15, 18 / 15, 63 / 21, 228 / 71; 4: 16 / 18, 30 / 19, 93 / 25, 481 / 90.
+// 8192 buckets (32 x 2048), c / b = 1, 4, P = 24: 15 / 23, 42 / 52; 128: 68 / 42, 178 / 82; 512:
+// 210 / 167, 840 / 396.  32768 (64 x 4096), P = 24: 31 / 58, 139 / 183; 128: 118 / 163, 402 / 365 (2).
+// One edit, 4096 (8 x 1024), c / b = 1/2, 2, 4: P = 24: 8 / 14, 16 / 17, 26 / 23; 128: 18 / 20, 74 / 25,
+// 129 / 36.  128 (4 x 256), c / b = 1, 2, 4: P = 1024: 12 / 16, 19 / 17, 42 / 18; 4096: 52 / 51, 89 / 53,
+// 162 / 57.
+bool own_problem(int64_t P, int64_t c, int64_t b, bool one_edit) {
+  return b <= kOwnedBuckets && 8 * c >= 5 * b && c >= 4 * kWave && (P - 8) * c >= (one_edit ? 64 : 96) * b;
+}
+
 // Postings of an append from which they may be sorted by bins of buckets (sorted_append), and postings that an
 // index holds up to which there is scratch memory for it (12 to 24 bytes for each).
 constexpr int64_t kBinPostings = 1 << 19, kMostBinPostings = 1 << 22;
@@ -142,6 +164,29 @@ constexpr int64_t kBinPostings = 1 << 19, kMostBinPostings = 1 << 22;
 constexpr int32_t kBinsWanted = 256, kBinBucketsLog2Least = 6;
 // Postings of an append to a bin, from which it pays.
 int64_t bin_least(bool one_edit) { return one_edit ? 256 : 768; }
+
+// An append whose postings are sorted by bins (csd_bins.cuh) is three launches, writes and reads every posting
+// once more, and sweeps the index by a workgroup per bin: it takes many postings, and many to a bin (with
+// counts, which may take few of those offered, it is not taken).  Measured, us, by atomics / sorted, one edit,
+// index empty and, behind it, half full or more: 1 problem of 64 paths, 4096 tokens 90 / 51; 2048, 48 / 37,
+// 56 / 43; 1024 (3.3e5 postings) 25 / 28, 35 / 35; 3 problems 192 / 73, 118 / 56, 63 / 44; 12 of 32, 2048
+// (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102.  Exact: 64
+// paths, 4096 tokens (1024 to a bin): 1 problem 21 / 20, 2 41 / 29, 4 70 / 46, 16 247 / 135; 2048 tokens (512):
+// 4 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.  Where own_problem applies too it comes
+// first (24 problems of 16 paths, 2048 tokens, one edit, a workgroup per problem / sorted: 147 / 123).
+bool sorted_append(int64_t P, int64_t c, int64_t bins, bool one_edit) {
+  return bins > 0 && P * c >= kBinPostings && c >= bin_least(one_edit) * bins;
+}
+
+// Whether any append to such problems is sorted: own_problem, which is asked first, says yes to all longer ones
+// where it does to one, so the shortest that the sorted form would take decides.
+bool ever_sorted(const csd_config* c, int64_t buckets, int64_t bins) {
+  const bool one_edit = c->max_edits > 0;
+  const int64_t of_token = (int64_t)c->n_paths * (one_edit ? c->max_query_len + 1 : 1);
+  const int64_t by_call = (kBinPostings + c->n_problems - 1) / c->n_problems, by_bins = bin_least(one_edit) * bins;
+  const int64_t tokens = ((by_call > by_bins ? by_call : by_bins) + of_token - 1) / of_token;
+  return tokens <= c->max_len && !own_problem(c->n_problems, tokens * of_token, buckets, one_edit);
+}
 
 Layout make_layout(const csd_config* c) {
   Layout l;
@@ -210,7 +255,7 @@ Layout make_layout(const csd_config* c) {
     l.bin_log2 = kBinBucketsLog2Least;
     while (((l.n_buckets >> l.bin_log2) > (uint32_t)kBinsWanted) && (1 << l.bin_log2) < kBinBuckets) ++l.bin_log2;
     const int64_t n_bins = l.n_buckets >> l.bin_log2;
-    if (n_bins >= 1 && n_bins <= kMostBins && (int64_t)c->n_paths * c->max_len * variants >= bin_least(c->max_edits > 0) * n_bins) {
+    if (n_bins >= 1 && n_bins <= kMostBins && ever_sorted(c, l.n_buckets, n_bins)) {
       l.n_bins = (int32_t)n_bins;
       l.records = align_up((size_t)c->n_problems * sources * kBinSource * variants * sizeof(BinRecord));
       l.runs = align_up((size_t)c->n_problems * l.n_bins * sources * sizeof(uint32_t));
@@ -299,44 +344,6 @@ bool multi_step_ok(const csd_index* h) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->view.N <= 16;
 }
 
-// The fill counts of a problem that one workgroup appends to fit a CU's LDS (128 KB); with up to 2048
-// buckets the buckets fit too (136 KB: one stream of whole lines instead of a line written for every
-// posting; 1024 problems of 16 x 1024 tokens 401 -> 110 us, with four tokens per lane).
-constexpr int64_t kOwnedBuckets = 32768, kTableBuckets = 2048;
-
-// An append with a workgroup per problem (append_problem_kernel) reads and writes all fill counts,
-// whatever it files; its time is the problem's, 256 of them run side by side.  With a thread per
-// position and atomics on memory the time is that of all postings.  So the first form is taken from
-// as many problems P on as postings c of a problem and buckets b of its index make it the better one:
-//   (P - 8) c >= 96 b (64 b with one edit), c >= 5/8 b, and a few waves' worth of postings.
-// Measured, us, atomics / a workgroup per problem, 2048 buckets (16 paths x 1024), index half full:
-// c / b = 1/2, P = 24, 64, 256, 1024: 6.8 / 14, 9 / 15, 18 / 21, 75 / 68; c / b = 1: 8 / 14, 12 / 15,
-// 36 / 21, 112 / 69; 2: 11 / 15, 18 / 15, 63 / 21, 228 / 71; 4: 16 / 18, 30 / 19, 93 / 25, 481 / 90.
-// 8192 buckets (32 x 2048), c / b = 1, 4, P = 24: 15 / 23, 42 / 52; 128: 68 / 42, 178 / 82; 512:
-// 210 / 167, 840 / 396.  32768 (64 x 4096), P = 24: 31 / 58, 139 / 183; 128: 118 / 163, 402 / 365 (2).
-// One edit, 4096 (8 x 1024), c / b = 1/2, 2, 4: P = 24: 8 / 14, 16 / 17, 26 / 23; 128: 18 / 20, 74 / 25,
-// 129 / 36.  128 (4 x 256), c / b = 1, 2, 4: P = 1024: 12 / 16, 19 / 17, 42 / 18; 4096: 52 / 51, 89 / 53,
-// 162 / 57.
-bool own_problem(const csd_index* h, const IndexView& v, int32_t n) {
-  const int64_t b = (int64_t)v.bucket_mask + 1, c = (int64_t)v.N * n * (v.eps > 0 ? v.kmax + 1 : 1);
-  return h->indexed && b <= kOwnedBuckets && 8 * c >= 5 * b && c >= 4 * kWave &&
-         (v.P - 8) * c >= (v.eps > 0 ? 64 : 96) * b;
-}
-
-// An append whose postings are sorted by bins (csd_bins.cuh) is three launches, writes and reads every posting
-// once more, and sweeps the index by a workgroup per bin: it takes many postings, and many to a bin (with
-// counts, which may take few of those offered, it is not taken).  Measured, us, by atomics / sorted, one edit,
-// index empty and, behind it, half full or more: 1 problem of 64 paths, 4096 tokens 90 / 51; 2048, 48 / 37,
-// 56 / 43; 1024 (3.3e5 postings) 25 / 28, 35 / 35; 3 problems 192 / 73, 118 / 56, 63 / 44; 12 of 32, 2048
-// (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102.  Exact: 64
-// paths, 4096 tokens (1024 to a bin): 1 problem 21 / 20, 2 41 / 29, 4 70 / 46, 16 247 / 135; 2048 tokens (512):
-// 4 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.
-bool sorted_append(const csd_index* h, const IndexView& v, const StepIn& in) {
-  const int64_t c = (int64_t)v.N * in.n * (v.eps > 0 ? v.kmax + 1 : 1);
-  return h->bins.bins > 0 && !in.counts && in.n <= v.max_len && v.P * c >= kBinPostings &&
-         c >= bin_least(v.eps > 0) * h->bins.bins;
-}
-
 // Workgroups of an append that the chip holds at once, and rows from which on one with counts has a
 // wave for each.
 constexpr int64_t kAppendGroups = 2048, kWaveRows = 4096;
@@ -352,7 +359,8 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
   const int64_t rows = (int64_t)v.P * v.N;
   const bool q4 = v.kmax <= 4;
   const int64_t n_buckets = (int64_t)v.bucket_mask + 1;
-  if (own_problem(h, v, in.n)) {
+  const int64_t postings = (int64_t)v.N * in.n * (v.eps > 0 ? v.kmax + 1 : 1);   // of a problem
+  if (h->indexed && own_problem(v.P, postings, n_buckets, v.eps > 0)) {
     const bool table = n_buckets <= kTableBuckets;
     auto* kernel =
         v.eps > 0 ? (table ? (q4 ? append_problem_kernel<true, 4, true> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, true>)
@@ -363,7 +371,7 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
     kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
-  if (sorted_append(h, v, in)) {
+  if (!in.counts && in.n <= v.max_len && sorted_append(v.P, postings, h->bins.bins, v.eps > 0)) {
     Bins b = h->bins;
     b.ends = h->meta[h->cur ^ 1];
     b.chunks = (in.n + kBinSource - 1) / kBinSource;

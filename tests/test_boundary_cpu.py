@@ -59,6 +59,27 @@ def test_workspace_size_and_validation(lib):
     assert lib.csd_workspace_bytes(ctypes.byref(b.Config(**good)), None) == b.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("problems,paths,max_len,query,edits,sorts", [
+    (1, 64, 4096, 4, 1, True), (12, 32, 2048, 4, 1, True), (4, 64, 4096, 4, 0, True), (23, 16, 1024, 4, 1, True),
+    (24, 16, 1024, 4, 1, False), (48, 16, 1024, 4, 1, False), (96, 8, 1024, 4, 1, False), (64, 16, 1024, 3, 0, False),
+    (1, 64, 1024, 3, 0, False), (16, 16, 4096, 3, 0, False), (16, 64, 4096, 3, 0, True),
+])
+def test_workspace_holds_sorted_postings_only_where_an_append_sorts_them(lib, problems, paths, max_len, query, edits, sorts):
+    from paper_2503_05330_amd import binding as b
+    size = b.workspace_bytes(b.Config(problems, paths, max_len, 32000, query, 8, 1.0, 0, b.MATCH_INDEX, edits, 0))
+    variants = query + 1 if edits else 1
+    buckets = 4
+    while buckets * 8 < paths * max_len * variants:
+        buckets *= 2
+    rows, cells = problems * paths, problems * paths * max_len
+    steps = min(max(max_len // 4, 16), max_len, (1 << 19) // rows)
+    end = (1 + query + (edits > 0) + 3) // 4 * 16
+    without = cells * 8 + problems * buckets * 64 + rows * (2 * end + 64) + steps * rows * (end + 4.5)
+    postings = cells * variants
+    assert (without <= size <= without + 16384) != sorts
+    assert not sorts or 12 * postings <= size - without <= 26 * postings
+
+
 def test_null_and_misaligned_arguments_are_rejected(lib):
     from paper_2503_05330_amd import binding as b
     cfg = b.Config(1, 4, 64, 100, 3, 5, 1.0, 0, 0)
