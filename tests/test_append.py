@@ -75,6 +75,54 @@ def test_appends_sorted_by_bins(oracle, problems, paths, max_len, vocab, query, 
     _appends(oracle, problems, paths, max_len, vocab, query, edits, binding.MATCH_INDEX, sizes, False)
 
 
+@pytest.mark.parametrize("problems,paths,max_len,vocab,query,edits,n", [
+    (1, 32, 4300, 40, 4, 1, 3600),
+    (3, 50, 4200, 300, 6, 0, 4097),
+])
+def test_a_sorted_append_as_without_the_room_for_it(oracle, monkeypatch, problems, paths, max_len, vocab, query, edits, n):
+    """Paths of different lengths, some of which the append fills up: clipped, with the status bit, by postings
+    sorted first and, in a workspace that ends before the room for them, by claims on memory.  An id outside
+    the vocabulary raises its bit."""
+    print("sorted and not", problems, paths, max_len, vocab, query, edits, n, flush=True)
+    rng = np.random.default_rng(n)
+    postings, L, dev = (query + 1 if edits else 1), 6, torch.device("cuda:0")
+    up = lambda size: (size + 255) // 256 * 256
+    sources, bins = paths * ((max_len + 1023) // 1024), 256
+    room = (up(problems * sources * 1024 * postings * 8) + up(problems * bins * sources * 4) +
+            up(problems * paths * max_len * postings * 4) + up((problems * bins * 2 + 1) * 4))
+    whole = binding.workspace_bytes(binding.Config(problems, paths, max_len, vocab, query, L, 1.0, 0, binding.MATCH_INDEX, edits, 0))
+    assert problems * paths * n * postings >= 1 << 19 and paths * n * postings >= bins * (256 if edits else 768)
+    offered = 2 * (max_len - n)
+    counts = rng.integers(0, offered + 1, size=(problems, paths)).astype(np.int32)
+    counts[:, 0], counts[:, 1] = offered, 0
+    past, part = (rng.integers(0, vocab, size=(problems, paths, k)).astype(np.int32) for k in (offered, n))
+    lens = np.minimum(counts + n, max_len).astype(np.int32)
+    tokens = np.zeros((problems, paths, max_len), dtype=np.int32)
+    for p, i in np.ndindex(problems, paths):
+        path = np.concatenate([past[p, i, :counts[p, i]], part[p, i]])[:max_len]
+        tokens[p, i, :len(path)] = path
+    want = oracle.draft_all(tokens, None, lens, query, L, 1.0, 0, eps=edits)
+    put = lambda a: torch.from_numpy(a).to(dev)
+    dumps = []
+    for nbytes in (whole, whole - room, whole - 256):
+        monkeypatch.setattr(binding, "workspace_bytes", lambda cfg: nbytes)
+        ix = binding.Index(problems, paths, max_len, vocab, query, L, 1.0, 0, binding.MATCH_INDEX, device=dev, max_edits=edits)
+        ix.append(put(past), None, put(counts), offered)
+        ix.append(put(part))
+        out = ix.draft(query, L)
+        assert np.array_equal(out["tokens"].cpu().numpy(), want["draft"])
+        assert np.array_equal(out["length"].cpu().numpy(), want["draft_len"])
+        assert ix.status() == binding.STATUS_CAPACITY
+        dumps.append(ix.dump_matches(query, cap=1 << 22))
+        ix.reset()
+        bad = part.copy()
+        bad[-1, -1, n // 2] = vocab
+        ix.append(put(bad))
+        assert ix.status() == binding.STATUS_TOKEN_RANGE
+    for other in dumps[1:]:
+        assert np.array_equal(dumps[0][0], other[0]) and np.array_equal(dumps[0][1], other[1])
+
+
 def test_appends_of_a_few_tokens_to_many_rows(oracle):
     """8192 rows, 50 to 63 tokens each: the claims look at the fill counts first; two symbols: at full ones."""
     for vocab, query in ((40, 3), (2, 5)):

@@ -108,11 +108,11 @@ def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, q
     assert by_graph.status() == by_call.status() == 0
 
 
-# the buckets of a problem in LDS, and their fill counts only
-@pytest.mark.parametrize("problems,paths,max_len,edits,n", [(64, 5, 300, 0, 100), (40, 6, 800, 1, 360)])
+# the buckets of a problem in LDS, and their fill counts only; postings sorted first
+@pytest.mark.parametrize("problems,paths,max_len,edits,n", [(64, 5, 300, 0, 100), (40, 6, 800, 1, 360), (1, 32, 8300, 1, 4097)])
 def test_a_bulk_append_keeps_what_a_graph_has_appended(problems, paths, max_len, edits, n):
     """An index that no call has appended to since its reset is not empty if a graph has: a bulk append
-    (by a workgroup per problem) keeps the graph's postings, captured or not."""
+    (by a workgroup per problem, or sorted by bins) keeps the graph's postings, captured or not."""
     print("bulk behind a graph", problems, paths, max_len, edits, n, flush=True)
     rng = np.random.default_rng(paths + n)
     P, L, V, k = problems, 6, 6, 3
@@ -124,7 +124,7 @@ def test_a_bulk_append_keeps_what_a_graph_has_appended(problems, paths, max_len,
     by_graph, mixed = make(), make()
     fed = part[0].clone()
     twice, _ = _captured(lambda: by_graph.append(fed))     # captured on an empty index, replayed twice
-    small = part[0][:, :, :1].contiguous()                 # (an append too small for a workgroup per problem)
+    small = part[0][:, :, :1].contiguous()                 # (an append too small for these forms)
     few, _ = _captured(lambda: mixed.append(small))
     mixed.reset()                                          # nothing of the capture has run: no call knows of the graph's tokens
     for tokens in part:

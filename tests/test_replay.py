@@ -299,16 +299,30 @@ def test_rows_left_to_workgroups(oracle, problems, paths, max_len, steps, query,
     _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, 1, mode, binding.MATCH_INDEX, pool)
 
 
-def _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, matcher, pool=0):
+# the same with a path's own history and with queries that lose tokens until they match (symbols enough for
+# rows without a match), in the launch of the waves and in that of the workgroups
+@pytest.mark.parametrize("flags", (binding.INCLUDE_SELF, binding.QUERY_BACKOFF, binding.INCLUDE_SELF | binding.QUERY_BACKOFF))
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,mode,pool", [
+    (1, 16, 256, 40, 4, 8, 12, 0, 0),
+    (2, 9, 300, 30, 4, 16, 60, 1, 0),
+    (40, 4, 60, 4, 5, 6, 90, 0, 1),
+    (1, 40, 260, 13, 3, 6, 6, 0, 2),
+])
+def test_rows_left_to_workgroups_with_options(oracle, problems, paths, max_len, steps, query, draft, vocab, mode, pool, flags):
+    assert problems * paths * steps > 512 and steps <= max(max_len // 4, 16)
+    _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, 1, mode, binding.MATCH_INDEX, pool, flags)
+
+
+def _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, vocab, edits, mode, matcher, pool=0, flags=0):
     rng = np.random.default_rng(paths * max_len + vocab)
-    print("oracle", matcher, pool, problems, paths, max_len, steps, query, draft, vocab, edits, mode, flush=True)
+    print("oracle", matcher, flags, pool, problems, paths, max_len, steps, query, draft, vocab, edits, mode, flush=True)
     dev, warm = torch.device("cuda:0"), max_len - steps
     tokens = rng.integers(0, vocab, size=(problems, paths, max_len)).astype(np.int32)
     motif = rng.integers(0, vocab, size=(problems, 1, max_len)).astype(np.int32)
     tokens = np.where(rng.random(tokens.shape) < 0.3, motif, tokens)
     probs = rng.random(tokens.shape).astype(np.float32)
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)
-    ix = binding.Index(problems, paths, max_len, vocab, query, draft, 0.7, mode, matcher, device=dev, max_edits=edits,
+    ix = binding.Index(problems, paths, max_len, vocab, query, draft, 0.7, mode, matcher | flags, device=dev, max_edits=edits,
                        pool_mode=pool)
     counts = rng.integers(warm // 2, warm + 1, size=(problems, paths)).astype(np.int32)
     counts[:, 0] = warm
@@ -317,7 +331,8 @@ def _against_the_oracle(oracle, problems, paths, max_len, steps, query, draft, v
     later_probs = np.take_along_axis(probs, np.minimum(counts[..., None] + np.arange(steps), max_len - 1), axis=2)
     out = ix.replay(steps, put(later.transpose(2, 0, 1)), put(later_probs.transpose(2, 0, 1)), query, draft)
     lengths = (counts[None] + np.arange(1, steps + 1)[:, None, None]).astype(np.int32)
-    want = oracle.draft_many(tokens, probs, lengths, query, draft, 0.7, mode, eps=edits, pool_mode=pool)
+    want = oracle.draft_many(tokens, probs, lengths, query, draft, 0.7, mode, eps=edits, pool_mode=pool,
+                             include_self=bool(flags & binding.INCLUDE_SELF), backoff=bool(flags & binding.QUERY_BACKOFF))
     for key, name in (("tokens", "draft"), ("length", "draft_len"), ("token_scores", "token_scores"), ("path_scores", "path_scores")):
         assert np.array_equal(out[key].cpu().numpy().view(np.int32), want[name].view(np.int32)), key
     assert ix.status() == 0
