@@ -161,7 +161,7 @@ typedef struct {
  * of it is for speed only: the notes of csd_replay's steps side by side (up to
  * 2^19 rows (problem, path, step) of 16 to 48 bytes, and 4.5 bytes each), the counts of
  * csd_append's workgroups (64 bytes for each of up to 2^16 paths) and, for an index of 2^19
- * to 2^22 postings, the sorted postings of a bulk append (12 to 24 bytes each).  csd_create
+ * to 2^22 postings of few problems, the sorted postings of a bulk append (12 to 24 bytes each).  csd_create
  * also takes a workspace without this part (csd_replay then takes a launch per step and
  * csd_append a wave per path) or without the sorted postings, as earlier builds sized it,
  * with the same results. */

@@ -6,8 +6,11 @@ namespace csd {
 // Two rows a CU are under way with LdsWaveFuzzy, so with more drafts than that some wait for others, and
 // the rows with many matches, which set the time, start last.  Beyond it they are left to workgroups (us for
 // reset, append of the past and replay, all by waves / so: 512 drafts, 16 paths x 1024 tokens, 32 / 33; 768,
-// 32 x 2048, 55 / 51; 1536, 64 x 4096, 170 / 153, of which the drafts 92 / 29 + 31; 4800, 40 problems of 5 x
-// 1000, 95 / 57; 6144, 12 problems of 16 x 1024, 269 / 171).
+// 32 x 2048, 55 / 51; 1536, 64 x 4096, 170 / 153; 4800, 40 problems of 5 x 1000, 95 / 57; 6144, 12 problems of 16 x
+// 1024, 269 / 171.  The drafts of 64 x 4096 alone, for two sets of inputs, 107 / 35 + 31 and 52 / 31 + 5, the same
+// behind either form of the append).  The replay alone, where it is near or loses: tree and list pool, 16 x 1024,
+// 640 drafts 71 / 74 and 48 / 53, paths nearly equal 68 / 53 and 67 / 55, 768 drafts 79 / 74 and 56 / 54; queries of
+// six over six symbols, 64 x 1024, 324 / 348.
 constexpr int64_t kOneTurn = 512;
 
 template <int QC>
