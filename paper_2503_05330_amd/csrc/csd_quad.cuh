@@ -14,22 +14,29 @@ template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
 }
-// x of lane ^ R, for the other lanes of a group of G = 4 or 8: R = 1 .. G - 1
+// x of another lane of a group of G, each of them for one R = 1 .. G - 1: lane ^ R, or (G = 16) the lane
+// that a rotation by R brings here
 template <int G, int R>
 __device__ __forceinline__ uint32_t group_other(uint32_t x) {
-  static_assert((G == 4 || G == 8) && R >= 1 && R < G, "a quad or half a DPP row");
+  static_assert((G == 4 || G == 8 || G == 16) && R >= 1 && R < G, "a quad, half a DPP row or a whole one");
+  if constexpr (G == 16) return dpp_move<0x120 + R>(x);
   constexpr int kFlip = R < 4 ? R : 7 - R;               // within a quad; R >= 4: behind the half row's mirror (^ 7)
   constexpr int kQuad = kFlip == 1 ? 0xB1 : kFlip == 2 ? 0x4E : 0x1B;
   if constexpr (R >= 4) x = dpp_move<0x141>(x);
   return kFlip == 0 ? x : dpp_move<kQuad>(x);
 }
-// f(R) for lanes R apart, so that every lane of the group ends with what all of them have, for
-// operations that may meet a value twice
+// f(a lane move), so that every lane of the group ends with what all of them have, for operations
+// that may meet a value twice
+template <int CTRL>
+struct DppMove {
+  __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return dpp_move<CTRL>(x); }
+};
 template <int G, class F>
 __device__ __forceinline__ void group_stages(F&& f) {
-  f(std::integral_constant<int, 1>{});
-  f(std::integral_constant<int, 2>{});
-  if constexpr (G == 8) f(std::integral_constant<int, 7>{});
+  f(DppMove<0xB1>{});                                    // lane ^ 1
+  f(DppMove<0x4E>{});                                    // ^ 2
+  if constexpr (G >= 8) f(DppMove<0x141>{});             // the half row's mirror
+  if constexpr (G >= 16) f(DppMove<0x140>{});            // the row's
 }
 
 struct __attribute__((packed, aligned(4))) Run4 { int32_t x[4]; };   // four words at any of them
@@ -40,6 +47,7 @@ struct UnitRow {
   const int32_t *tok, *lens;    // the problem's histories; its paths' ends at this step
   const uint32_t* pq;
   int64_t buckets;              // the problem's first bucket
+  UnitRow() = default;
   __device__ __forceinline__ UnitRow(const IndexView& ix, uint32_t steps, uint32_t unit) {
     const uint32_t N = (uint32_t)ix.N;
     const uint32_t p = unit / (N * steps), in_problem = unit - p * (N * steps), t = in_problem / N;
@@ -112,15 +120,16 @@ struct Posting {
   }
 };
 
-// The row's draft from its matches, one per lane of its group (`match`: as packed above; 0: none):
-// continuations into registers, then layer by layer Eq. 5's sums and the greedy rule (as in
-// walk_instances) by exchanges within the group, and the outputs of the rows with `write`.
-template <int G, int LCAP>
-__device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
-                                            bool write, int sub, const int32_t (&target)[(LCAP + G - 1) / G]) {
-  constexpr int kKept = (LCAP + G - 1) / G;              // layers whose choice a lane keeps and writes
-  constexpr int kCount = 24;                             // count (<= 8) above the probability sum (<= 2^19)
-  const int32_t L = a.L, rem = (int32_t)(match >> 25);
+// The greedy walk of a row from its matches, one per lane of its group (`match`: as packed above; 0:
+// none): continuations into registers, then layer by layer Eq. 5's sums and the greedy rule (as in
+// walk_instances) by exchanges within the group.  going: the same in a group's lanes.
+// EDGE: edges are weighed, not nodes (score_mode 1; asked at every exchange of every layer it was a
+// branch each).  chosen(layer, going, best): the layer's choice, where going.
+template <int G, int LCAP, bool EDGE, class CHOSEN>
+__device__ __forceinline__ void group_walk(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
+                                           bool going, CHOSEN&& chosen) {
+  constexpr int kCount = 24;                             // count (<= 16) above the probability sum (<= 2^20)
+  const int32_t rem = (int32_t)(match >> 25);            // (at most L)
   int32_t v[LCAP], pr[LCAP];
   {
     const int32_t pos = (int32_t)(match & ((1u << 25) - 1u));
@@ -142,17 +151,11 @@ __device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs
     consume_here(v[d]);
     consume_here(pr[d]);
   }
-  int32_t kept_tok[kKept], n = 0, cur = 0;
-  u64 kept_key[kKept], key_sum = 0;
-#pragma unroll
-  for (int x = 0; x < kKept; ++x) {
-    kept_tok[x] = -1;
-    kept_key[x] = 0;
-  }
-  bool going = write;                                    // the same in a group's lanes
+  int32_t cur = 0;
   static_for<1, LCAP + 1>([&](auto layer) {
     constexpr int d = layer();
-    if (d > L || wave_ballot(going) == 0) return;        // uniform over the wave
+    constexpr bool kByEdge = EDGE && d > 1;
+    if (wave_ballot(going) == 0) return;                 // uniform over the wave; so from the layer behind L on
     const bool alive = d <= rem;
     const uint32_t vd = (uint32_t)v[d - 1], ud = d > 1 ? (uint32_t)v[d > 1 ? d - 2 : 0] : 0u;
     const bool from_cur = alive && going && (d == 1 || (int32_t)ud == cur);
@@ -161,25 +164,49 @@ __device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs
     uint32_t cs = own;
     // (the moves are made before the comparisons: in a lane that a condition rules out, a move
     // delivers nothing to the others)
-    const bool by_edge = a.score_mode != 0 && d > 1;     // uniform over the launch
     static_for<1, G>([&](auto r) {
       const uint32_t other_v = group_other<G, r()>(vd), other = group_other<G, r()>(own);
       bool same_node = other_v == vd;
-      if (by_edge) {
+      if constexpr (kByEdge) {
         const uint32_t other_u = group_other<G, r()>(ud);
         same_node = same_node && other_u == ud;
       }
       cs += same_node ? other : 0u;
     });
-    Cand best = cand_none();
-    if (from_cur) best = Cand{weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q), (int32_t)vd};
-    group_stages<G>([&](auto r) {
-      const uint32_t lo = group_other<G, r()>((uint32_t)best.key), hi = group_other<G, r()>((uint32_t)(best.key >> 32));
-      const uint32_t tv = group_other<G, r()>((uint32_t)best.v);
-      best = cand_best(best, Cand{((u64)hi << 32) | lo, (int32_t)tv});
+    // the heaviest weight, then the lowest token that has it
+    const u64 weight = weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q);
+    u64 key = from_cur ? weight : 0ull;
+    group_stages<G>([&](auto other) {
+      const uint32_t lo = other((uint32_t)key), hi = other((uint32_t)(key >> 32));
+      const u64 theirs = ((u64)hi << 32) | lo;
+      key = theirs > key ? theirs : key;
     });
-    going = going && best.v != INT_MAX;                  // else a leaf: no edge leaves cur
-    cur = best.v;
+    int32_t token = from_cur && weight == key ? (int32_t)vd : INT_MAX;
+    group_stages<G>([&](auto other) {
+      const int32_t theirs = (int32_t)other((uint32_t)token);
+      token = theirs < token ? theirs : token;
+    });
+    going = going && token != INT_MAX;                   // else a leaf: no edge leaves cur
+    cur = token;
+    chosen(layer, going, Cand{key, token});
+  });
+}
+
+// The row's draft, and its outputs for the rows with `write`.
+template <int G, int LCAP, bool EDGE>
+__device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
+                                            bool write, int sub, const int32_t (&target)[(LCAP + G - 1) / G]) {
+  constexpr int kKept = (LCAP + G - 1) / G;              // layers whose choice a lane keeps and writes
+  const int32_t L = a.L;
+  int32_t kept_tok[kKept], n = 0;
+  u64 kept_key[kKept], key_sum = 0;
+#pragma unroll
+  for (int x = 0; x < kKept; ++x) {
+    kept_tok[x] = -1;
+    kept_key[x] = 0;
+  }
+  group_walk<G, LCAP, EDGE>(ix, a, u, match, write, [&](auto layer, bool going, const Cand& best) {
+    constexpr int d = layer();
     n = going ? d : n;
     key_sum += going ? best.key : 0ull;
     const bool keep = going && sub == (d - 1) / kKept;
@@ -200,8 +227,8 @@ __device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs
   }
   if (a.targets) {                                       // the first layer that differs
     uint32_t stop = all ? (uint32_t)LCAP : (uint32_t)(sub * kKept + same);
-    group_stages<G>([&](auto r) {
-      const uint32_t other = group_other<G, r()>(stop);
+    group_stages<G>([&](auto move) {
+      const uint32_t other = move(stop);
       stop = other < stop ? other : stop;
     });
     if (write && sub == 0) a.accept_len[u.row] = (int32_t)stop < n ? (int32_t)stop : n;
@@ -239,7 +266,7 @@ __device__ __forceinline__ uint32_t block_units(uint32_t per_block) {
 // kernel: bit 4 r of rest[w] is row r of wave w.  (A list of them with one counter took 12 ns per
 // wave, the rate of atomics on one address, and its order spread a problem's rows over all L2s.)
 // ix.meta_old and a are those of the first step.
-template <int LCAP, int QC>
+template <int LCAP, int QC, bool EDGE>
 __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t steps, DraftArgs a, u64* rest) {
   __shared__ uint32_t found[256];                        // [row of the workgroup][4] matches
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), sub = tid & 3;
@@ -282,7 +309,7 @@ __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t 
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (a row's lanes are of one wave)
   // ---- round trip 4: the matches' continuations; walk, outputs
-  group_draft<4, LCAP>(ix, a, u, !leave && sub < M ? found[tid] : 0u, on && !leave, sub, target);
+  group_draft<4, LCAP, EDGE>(ix, a, u, !leave && sub < M ? found[tid] : 0u, on && !leave, sub, target);
   const u64 left = wave_ballot(on && leave && sub == 0);
   if (lane == 0 && on) rest[unit / kQuadRows] = left;
 }
@@ -312,7 +339,7 @@ constexpr int32_t kRestPad = 8 * 256;  // units by which the lists of all XCDs m
 // another layout (any serves any row).
 constexpr int32_t kFewMatches = 30;
 constexpr uint32_t kLongChain = 3;     // buckets after which the wave per row, which reads four at once, takes over
-template <int WAVES, int LCAP, int QC>
+template <int WAVES, int LCAP, int QC, bool EDGE>
 __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
                                                            RestList list) {
   constexpr int G = 8, kWaves = 4, kRows = WAVES * kQuadRows;   // rows of the workgroup
@@ -383,10 +410,10 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
       leave = leave || (looking && goes_on && r + 1 >= kLongChain);
       looking = looking && goes_on && !leave;
     }
-    leave = leave || M > G;
     const bool many = is_short || M > kFewMatches;
+    leave = leave || M > G;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS of this wave alone)
-    group_draft<G, LCAP>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);
+    group_draft<G, LCAP, EDGE>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);
     if (on && leave && sub == 0) left[many][atomicAdd(&n_left[many], 1)] = (uint8_t)which;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (the next turn's matches go to the same cells)
   }

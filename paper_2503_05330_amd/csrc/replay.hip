@@ -28,16 +28,16 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
 // drafts, 20 us; 1024 problems x 24 steps, 393216 drafts, 74 us with four waves' rows, 60 with sixteen).
 constexpr int64_t kPooledDrafts = 1 << 17;
 
-template <int LCAP, int QC>
+template <int LCAP, int QC, bool EDGE>
 static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
                          hipStream_t st) {
   const int64_t drafts = (int64_t)v.P * v.N * steps;
   const auto grid = [&](int64_t rows) { return (uint32_t)((drafts + 8 * rows - 1) / (8 * rows) * 8); };   // rows per workgroup
-  replay_quad_kernel<LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest);
+  replay_quad_kernel<LCAP, QC, EDGE><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest);
   const bool pooled = drafts >= kPooledDrafts;
   const RestList list{rest_list, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows};
-  if (pooled) replay_eight_kernel<16, LCAP, QC><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
-  else replay_eight_kernel<4, LCAP, QC><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  if (pooled) replay_eight_kernel<16, LCAP, QC, EDGE><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
+  else replay_eight_kernel<4, LCAP, QC, EDGE><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   // (the second as many as the chip holds at once, the first twice that: 4096, which it holds, do not
   // spread evenly, 1281 us for 1024 problems whose paths agree, 8192: 1109, 49152: 1030, which cost 8 us
   // where there is nothing to do for them)
@@ -45,19 +45,20 @@ static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, 
   replay_rest_kernel<LCAP, true, QC><<<1024, kWave, 0, st>>>(RestArgs{v, steps, a, list});
 }
 
+template <int QC>
+static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
+                         hipStream_t st) {
+  auto* launch = a.score_mode == 0 ? (a.L <= 8 ? launch_quads<8, QC, false> : a.L <= 16 ? launch_quads<16, QC, false> : launch_quads<32, QC, false>)
+                                   : (a.L <= 8 ? launch_quads<8, QC, true> : a.L <= 16 ? launch_quads<16, QC, true> : launch_quads<32, QC, true>);
+  launch(v, steps, a, rest, rest_list, st);
+}
+
 void launch_replay(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
                    hipStream_t st) {
   const int64_t drafts = (int64_t)v.P * v.N * steps;
   if (drafts >= kQuadDrafts && a.k == v.kmax) {
-    if (v.kmax <= 4) {
-      if (a.L <= 8) launch_quads<8, 4>(v, steps, a, rest, rest_list, st);
-      else if (a.L <= 16) launch_quads<16, 4>(v, steps, a, rest, rest_list, st);
-      else launch_quads<32, 4>(v, steps, a, rest, rest_list, st);
-    } else {
-      if (a.L <= 8) launch_quads<8, 8>(v, steps, a, rest, rest_list, st);
-      else if (a.L <= 16) launch_quads<16, 8>(v, steps, a, rest, rest_list, st);
-      else launch_quads<32, 8>(v, steps, a, rest, rest_list, st);
-    }
+    if (v.kmax <= 4) launch_quads<4>(v, steps, a, rest, rest_list, st);
+    else launch_quads<8>(v, steps, a, rest, rest_list, st);
     return;
   }
   const bool many = drafts >= kSmallLdsDrafts;
