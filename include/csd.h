@@ -258,7 +258,11 @@ int csd_replay(csd_index* index, int32_t n_steps, const int32_t* d_tokens, const
  * per step one small kernel that gathers the step's input and csd_step with
  * draft_len + 1 tokens per path and counts (with the index matcher, exact
  * matching and twice the minimum of scratch memory: one launch per step, whose
- * tail gathers the next step's input).
+ * tail gathers the next step's input).  With the index matcher, exact matching,
+ * the DAG pool without options, up to 16 paths, draft_len <= 16 and query_len =
+ * max_query_len of 3 or 4 (2: from 512 paths in all) all steps run in one launch
+ * behind one that copies the futures to the histories behind the paths' ends
+ * (unless a buffer that is written overlaps another one).
  *   d_scratch: device memory, 4-byte aligned, scratch_bytes >=
  *     P*N*(3*draft_len + 3)*4 (step tokens, probabilities, targets, counts);
  *     with twice as much, steps alternate between the two halves;
@@ -273,8 +277,8 @@ int csd_accept_loop(csd_index* index, int32_t n_steps, const int32_t* d_future_t
 
 /* How many steps one launch of csd_replay (fused != 0) and csd_accept_loop runs one after
  * the other.  Until it is called csd_replay runs its steps side by side and csd_accept_loop
- * a launch per step.  1: a launch per step (what a decode loop with a model between the steps
- * does: csd_replay then takes as long per step).  More: a device-side loop — one workgroup per
+ * all of them in one launch where it can.  1: a launch per step (what a decode loop with a model
+ * between the steps does: both then take as long per step).  More: a device-side loop — one workgroup per
  * problem, one wave per path, a workgroup barrier between steps — runs up to `steps`
  * steps per launch where the configuration allows it: exact matching through the index,
  * max_query_len <= 4, n_paths <= 16 (csd_accept_loop also needs twice the minimum of

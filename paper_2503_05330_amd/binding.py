@@ -172,7 +172,8 @@ class Index:
 
     def set_steps_per_launch(self, steps: int):
         """Steps that a launch of replay() and accept_loop() runs one after the other (1 = a launch
-        per step).  Until it is called replay() runs its steps side by side."""
+        per step).  Until it is called replay() runs its steps side by side and accept_loop() all of
+        them in one launch where it can."""
         self._check(load().csd_set_steps_per_launch(self._h, steps), "csd_set_steps_per_launch")
 
     def reset(self):
@@ -291,7 +292,8 @@ class Index:
         """n_steps of the propose / verify / accept loop with each path's own future
         (future_tokens / future_probs [P][N][max_len]) standing in for the model.  Returns
         dict(tokens [S][P][N][L], length, accept, path_len [S][P][N]).  min_scratch: hand over
-        the minimum of scratch memory instead of twice as much (same results, more launches)."""
+        the minimum of scratch memory instead of twice as much (same results; more launches where the
+        steps do not run in one)."""
         L, S = draft_len, n_steps
         if out is None:
             out = dict(tokens=torch.empty((S, self.P, self.N, L), dtype=torch.int32, device=self.device))

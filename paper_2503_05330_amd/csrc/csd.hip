@@ -39,6 +39,7 @@
 #include "csd_index.cuh"
 #include "csd_kernels.cuh"
 #include "csd_launch.h"
+#include "csd_loop.cuh"
 #include "csd_match.cuh"
 
 using namespace csd;
@@ -342,6 +343,16 @@ void launch_draft(const csd_index* h, const IndexView& v, const StepIn& in, cons
 // per problem).
 bool multi_step_ok(const csd_index* h) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->view.N <= 16;
+}
+
+// csd_accept_loop in one launch (see loop_kernel).  Queries of two tokens, many of which have more than
+// sixteen matches, only where the rows of a launch per step would not have a CU each (us, 16 paths x
+// 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 753 / 813).
+constexpr int64_t kLoopRows = 512;
+bool one_launch_loop_ok(const csd_index* h, int32_t query_len, int32_t draft_len) {
+  return multi_step_ok(h) && h->cfg.pool_mode == CSD_POOL_DAG && h->view.options == 0 && h->view.N <= kLoopPaths &&
+         query_len == h->view.kmax && draft_len <= kLoopLanes &&
+         (query_len > 2 || (query_len == 2 && (int64_t)h->view.P * h->view.N >= kLoopRows));
 }
 
 // Workgroups of an append that the chip holds at once, and rows from which on one with counts has a
@@ -750,6 +761,24 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
   int32_t* targets = reinterpret_cast<int32_t*>(step_prob + rows * n);
   int32_t* step_cnt = targets + rows * L;
   hipStream_t st = as_stream(stream);
+  const Buffer buffers[] = {{d_future_tokens, rows * (size_t)h->cfg.max_len * 4}, {d_future_probs, rows * (size_t)h->cfg.max_len * 4},
+                            {d_draft_tokens, n_steps * rows * L * 4}, {d_draft_len, n_steps * rows * 4},
+                            {d_accept_len, n_steps * rows * 4}, {d_path_len, n_steps * rows * 4}};
+  if (h->steps_per_launch == 0 && one_launch_loop_ok(h, query_len, draft_len) && n_steps > 0 && !overlap(buffers, 2, 6)) {
+    IndexView v = h->view;
+    v.meta_old = h->meta[h->cur];
+    v.meta_new = h->meta[h->cur ^ (n_steps & 1)];        // (where a launch per step would leave the ends)
+    const LoopArgs m{v, n_steps, targets, d_path_len,
+                     DraftArgs{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode, d_draft_tokens,
+                               d_draft_len, nullptr, nullptr, nullptr, d_accept_len}};
+    LengthBounds before(h);
+    const int64_t most = h->len_hi + (int64_t)n_steps * (int64_t)n;
+    h->len_hi = most < h->cfg.max_len ? most : h->cfg.max_len;
+    launch_loop(m, d_future_tokens, d_future_probs, st);
+    rc = before.launched("csd_accept_loop");
+    if (rc == CSD_OK) h->cur ^= n_steps & 1;
+    return rc;
+  }
   if (h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && n_steps > 0 &&
       scratch_bytes >= 2 * rows * (2 * n + L + 1) * 4) {
     // one launch per step: the fused step of up to L + 1 tokens per path, whose tail works out

@@ -446,6 +446,11 @@ struct LoopTail {
   int32_t n, max_len;
 };
 
+// Hands a row's accept length back to the workgroup (see loop_kernel).
+struct AcceptTail {
+  int32_t* accepted;            // [paths of the problem]
+};
+
 // Rows that a wave leaves to a workgroup (replay_leave_kernel): those with more matches than the walks
 // with a lane per match take.
 struct LeaveTail {
@@ -594,6 +599,9 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
 #ifdef CSD_STAMPS
   if (lane == 0 && row < (1 << 14)) g_stamps[row * kStampSlots + 6] = CSD_CLOCK();
 #endif
+  if constexpr (std::is_same<TAIL, AcceptTail>::value) {
+    if (c.tid == 0) tail.accepted[c.i] = accepted;
+  }
   if constexpr (std::is_same<TAIL, LoopTail>::value) {
     const int32_t len = c.len_i;                        // after this step's append
     int32_t grow = accepted + 1;

@@ -24,6 +24,11 @@ void launch_step_scan(const IndexView& v, const StepIn& in, const DraftArgs& a, 
 // one step of the accept-driven loop
 void launch_step_loop(const IndexView& v, const StepIn& in, const DraftArgs& a, const LoopTail& tail,
                       hipStream_t st);
+// the same with all its steps in one launch (exact matching through the index, DAG pool without options,
+// queries of kmax = 2 .. 4 tokens, at most kLoopPaths paths, drafts of up to kLoopLanes tokens)
+struct LoopArgs;
+void launch_loop(const LoopArgs& m, const int32_t* future_tok, const float* future_prob, hipStream_t st);
+void launch_loop_long(const LoopArgs& m, hipStream_t st);   // its steps, drafts of more than eight tokens
 // many steps per launch: a replay (general: tree and list pools, own history) / the accept-driven loop
 void launch_multi(const IndexView& v, const MultiArgs& m, bool general, hipStream_t st);
 void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);

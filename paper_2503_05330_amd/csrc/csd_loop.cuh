@@ -1,0 +1,318 @@
+// csd — the accept-driven loop in one launch: a workgroup per problem, sixteen lanes per path.
+#pragma once
+
+#include "csd_kernels.cuh"
+
+namespace csd {
+
+constexpr int kLoopLanes = 16;         // lanes of a path: a row of DPP moves
+constexpr int kLoopPaths = 16;         // most paths of a problem (four waves of four)
+
+// What the loop's steps may append is known when the call is made: each path's own future.  It goes
+// to the histories behind the paths' ends beforehand (what lies there is not seen, see append and
+// replay), so that a step has no histories to write and all that it reads of them is settled.
+static __global__ __launch_bounds__(256) void loop_fill_kernel(IndexView ix, const int32_t* future_tok,
+                                                               const float* future_prob, int32_t ahead, int32_t chunks) {
+  const int32_t row = (int32_t)blockIdx.x / chunks, chunk = (int32_t)blockIdx.x - row * chunks;
+  const int32_t len = ix.meta_old[(int64_t)row * ix.meta_stride], t = chunk * 256 + (int32_t)threadIdx.x;
+  if (t >= ahead || t >= ix.max_len - len) return;
+  const int64_t at = (int64_t)row * ix.max_len + len + t;
+  ix.tok[at] = future_tok[at];
+  ix.pq[at] = future_prob ? quantize_prob(future_prob[at]) : 65536u;
+}
+
+struct LoopArgs {
+  IndexView ix;
+  int32_t steps;
+  int32_t* targets;             // [rows][L] scratch, for the rows that a wave drafts
+  int32_t* path_len;            // [steps][rows]
+  DraftArgs a;                  // outputs of step 0; step t writes slice t
+};
+
+// The kernel's arguments, read anew: what is done with them here is not kept over the code around
+// (of which there is not much room in scalar registers).
+__device__ __forceinline__ const LoopArgs& loop_arguments() {
+  auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(kernarg));
+  return *(const LoopArgs*)kernarg;
+}
+
+// The steps of csd_accept_loop, one after the other.  A launch per step is bound by its latency:
+// dispatch, then three round trips on caches that are cold at every launch, 6.6 us at 16 x 1024.
+// Here a step's chain is the query's bucket, the postings' tokens, the matches' continuations and the
+// walk, in caches that stay warm, and two barriers of the workgroup; the paths' ends and newest tokens
+// are in LDS, the positions that the step itself appends are matched from a list of their hashes
+// there, their postings are stored while the walk goes on, and the outputs of a step behind the next
+// one's barrier.  3.9 us a step (top to bucket 0.45, claims 0.2, look-up 0.8, postings 0.15, walk up to
+// 1.7, the wait for the slowest wave's); one wave issues an instruction every 7 cycles here, so the
+// instructions of the chain count.  With a wave per path (step_multi_kernel) the four SIMDs of the one
+// CU had 1500 instructions a row and step to issue, 14 us; with sixteen lanes a path they have four
+// waves of a few hundred.
+// A row with more than sixteen matches, a long chain or a path shorter than a gram is drafted by a
+// wave on the layout of a launch per step, behind a barrier, when the step's postings are in the
+// index: code apart from the steps' (inlined into their loop it spilled their registers, 5.6 us a step).
+// us a call, a launch per step / this (queries of three, drafts of eight, 48 steps): 1 problem of 16 paths
+// x 1024 tokens 352 / 205, of 4 x 256 (24 steps) 152 / 81; 64 problems 531 / 252, 1024 of 16 x 512 (24
+// steps) 2307 / 443.  Where most rows have more than sixteen matches four waves draft sixteen of
+// them in turn: 537 / 1096 for paths of which each holds each gram four times.
+// Exact matching through the index, DAG pool, queries of kmax = K tokens.
+template <int LCAP, int WAVES, int K>
+__global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
+  constexpr int G = kLoopLanes, kPaths = WAVES * kWave / G, BLOCK = WAVES * kWave;
+  constexpr int kBefore = 4;                             // tokens before a path's end that are kept
+  constexpr int kOwn = (2 * LCAP + kBefore + 1 + G - 1) / G;   // words of a path's window that a lane has
+  static_assert(K >= 2 && K <= kBefore, "a gram's tokens in one load");
+  __shared__ LdsWave wide[WAVES];
+  __shared__ int32_t own_all[kPaths][kOwn * G];          // tokens from kBefore before a path's end on, up to 2 L behind it
+  __shared__ int2 fresh[kPaths * (LCAP + 1)];            // the step's new positions: packed, hash of the gram before them
+  __shared__ int2 ends[kPaths];                          // lengths before and after the step's append
+  __shared__ uint32_t found_all[kPaths][G];              // matches
+  __shared__ int32_t draft_all[kPaths][LCAP], accepted_by_wave[kPaths];
+  __shared__ int32_t n_fresh[2], n_crowded[2];           // (a step clears the next one's)
+  __shared__ uint8_t crowded[kPaths];
+  const IndexView& ix = m.ix;
+  const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), sub = lane & (G - 1);
+  const int32_t path = tid / G, p = (int32_t)blockIdx.x, N = ix.N, L = m.a.L;
+  const bool on = path < N;
+  const int64_t rows = (int64_t)ix.P * N;
+  UnitRow u;
+  u.i = path;
+  u.first = p * N;
+  u.row = u.first + (on ? path : 0);
+  u.tok = ix.tok + (int64_t)u.first * ix.max_len;
+  u.pq = ix.pq + (int64_t)u.first * ix.max_len;
+  u.lens = nullptr;
+  u.buckets = (int64_t)p * ((int64_t)ix.bucket_mask + 1);
+  int32_t* gram = ix.gram + u.buckets * kBucketWords;
+  const int32_t* history = ix.tok + (int64_t)u.row * ix.max_len;
+  int32_t* own = own_all[path];
+  uint32_t* found = found_all[path];
+  auto group_bits = [&](bool x) { return (uint32_t)(wave_ballot(x) >> (lane & ~(G - 1))) & ((1u << G) - 1u); };
+  int32_t window[kOwn];
+  auto request_window = [&](int32_t end) {
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) {
+      const int32_t t = end - kBefore + sub + x * G;
+      window[x] = history[t < 0 ? 0 : (t < ix.max_len ? t : ix.max_len - 1)];
+    }
+  };
+  auto keep_window = [&](int32_t end) {                  // (-1 beyond max_len: what no draft can meet)
+#pragma unroll
+    for (int x = 0; x < kOwn; ++x) own[sub + x * G] = end - kBefore + sub + x * G < ix.max_len ? window[x] : -1;
+    block_sync<kWave>();                                 // (a path's lanes are of one wave)
+  };
+  int32_t old = ix.meta_old[(int64_t)u.row * ix.meta_stride];
+  int32_t cnt = on && old < ix.max_len ? 1 : 0;          // tokens of this step
+  if (tid < 2) n_fresh[tid] = n_crowded[tid] = 0;
+  request_window(old);
+  keep_window(old);
+  lds_barrier<BLOCK>();
+  uint32_t flags = 0;
+  // outputs of the step before
+  int32_t out_tok = 0, out_n = 0, accepted = 0;
+  bool out_drafted = false;
+  auto store_outputs = [&](int32_t t, int32_t len) {
+    const int64_t row = t * rows + u.row;
+    if (on && out_drafted) {
+      if (sub < L) m.a.draft_tokens[row * L + sub] = out_tok;
+      if (sub == 0) {
+        m.a.draft_len[row] = out_n;
+        m.a.accept_len[row] = accepted;
+      }
+    }
+    if (on && sub == 0) m.path_len[row] = len;
+  };
+  bool leave = false;
+  auto advance = [&]() {                                 // to what the next step appends
+    const int32_t room = ix.max_len - (old + cnt);
+    int32_t grow = accepted < L ? accepted + 1 : L + 1;
+    grow = grow < room ? grow : room;
+    old += cnt;
+    cnt = on ? grow : 0;
+    keep_window(old);
+  };
+  for (int32_t step = 0;;) {
+    int32_t n_left = 0;
+    while (step < m.steps) {                             // uniform over the workgroup, as n_left
+      const int parity = step & 1;
+      const int32_t now = old + cnt;
+      int32_t Q[K], G0[K];
+#pragma unroll
+      for (int a = 0; a < K; ++a) Q[a] = own[kBefore - 1 + cnt - a];
+      const GramHash gh = gram_hash_of(Q, K);
+      // ---- round trip 1: the query's first bucket, past the CU's own cache (slots are claimed in the L2);
+      // all postings of the steps before are there
+      auto bucket = [&](uint32_t r) {
+        return __hip_atomic_load(gram + (int64_t)((gh.h + r * gh.step) & ix.bucket_mask) * kBucketWords + sub, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+      };
+      int32_t next = bucket(0);
+      request_window(now);
+      // the step's new positions, a lane each (drafts of sixteen tokens: one may go round again)
+      auto gram_before = [&](int32_t t, int32_t (&g)[K]) {
+#pragma unroll
+        for (int a = 0; a < K; ++a) g[a] = own[kBefore - 1 + (t < cnt ? t : 0) - a];
+      };
+      auto filed = [&](int32_t t) { return t < cnt && old + t >= K; };
+      auto packed = [&](int32_t t) { return (path << ix.eshift) | (old + t); };
+      auto list = [&](int32_t t, const int32_t (&g)[K]) {
+        const int32_t token = own[kBefore + (t < cnt ? t : 0)];
+        flags |= t < cnt && (token < 0 || token >= ix.vocab) ? CSD_STATUS_TOKEN_RANGE : 0u;
+        if (filed(t)) fresh[atomicAdd(&n_fresh[parity], 1)] = int2{packed(t), (int32_t)gram_hash_of(g, K).h};
+      };
+      gram_before(sub, G0);
+      list(sub, G0);
+      if (LCAP >= G && wave_ballot(sub + G < cnt) != 0) {
+        int32_t g[K];
+        gram_before(sub + G, g);
+        list(sub + G, g);
+      }
+      if (sub == 0) ends[path] = int2{old, now};
+      lds_barrier<BLOCK>();                              // the list, the ends
+      if (tid == 0) n_fresh[parity ^ 1] = n_crowded[parity ^ 1] = 0;   // (everybody has read them, nobody adds to them before the next barrier)
+      if (step > 0) store_outputs(step - 1, old);
+      const bool is_short = now < K;
+      bool looking = on && !is_short;
+      int32_t M = 0;
+      leave = is_short;
+      // ---- round trip 2: a candidate's gram (with the continuations of all candidates it takes 1.9 us
+      // instead of 1.1: the four waves share one cache that looks up a line a cycle)
+      auto verify = [&](bool cand, int32_t word, bool is_new) {
+        const int32_t j = word >> ix.eshift, e = word & ((1 << ix.eshift) - 1);
+        cand = cand && word >= 0 && j != path && j < N;
+        const int2 end = ends[cand ? j : 0];
+        cand = cand && (is_new || e < end.x);            // (newer postings may be in flight: those are in the list)
+        const int32_t cell = cand ? (int32_t)__umul24((uint32_t)j, (uint32_t)ix.max_len) + e : K;
+        const Run4 r = *reinterpret_cast<const Run4*>(u.tok + cell - K);
+        int32_t differ = 0;
+#pragma unroll
+        for (int y = 0; y < K; ++y) differ |= r.x[y] ^ Q[K - 1 - y];
+        const bool hit = cand && differ == 0;
+        const uint32_t hits = group_bits(hit);
+        const int32_t to = M + (int32_t)__popc(hits & ((1u << sub) - 1u)), rem = end.y - e;
+        if (hit && to < G) found[to] = (uint32_t)word | (uint32_t)(rem < L ? rem : L) << 25;
+        M += (int32_t)__popc(hits);
+      };
+      auto look_up = [&]() {
+        // four of the list's positions a lane at once (as a loop of one, every turn was a round trip in LDS)
+        const int32_t listed = __builtin_amdgcn_readfirstlane(n_fresh[parity]);
+        for (int32_t x0 = 0; x0 < listed; x0 += 4 * G) {
+          int2 f[4];
+#pragma unroll
+          for (int y = 0; y < 4; ++y) f[y] = fresh[x0 + y * G + sub < listed ? x0 + y * G + sub : 0];
+          uint32_t cands = 0;
+#pragma unroll
+          for (int y = 0; y < 4; ++y)
+            cands |= looking && x0 + y * G + sub < listed && f[y].y == (int32_t)gh.h && f[y].x >> ix.eshift != path ? 1u << y : 0u;
+          if (wave_ballot(cands != 0) != 0)
+#pragma unroll
+            for (int y = 0; y < 4; ++y) verify((cands >> y & 1u) != 0, f[y].x, true);
+        }
+        for (uint32_t r = 0; wave_ballot(looking) != 0; ++r) {   // uniform over the wave
+          const int32_t word = next, count = (int32_t)dpp_move<0x150>((uint32_t)word);   // (of the group's first lane)
+          const bool goes_on = looking && count >= kBucketSlots && r < ix.bucket_mask;
+          if (wave_ballot(goes_on) != 0) next = bucket(r + 1);   // (in flight while this one is looked through)
+          verify(looking && sub >= 1 && sub - 1 < count, word, false);
+          leave = leave || (goes_on && r + 1 >= kLongChain);
+          looking = goes_on && !leave;
+        }
+      };
+      file_positions<false, K>(gram, ix.bucket_mask, K, G0, filed(sub), packed(sub), lane, look_up);
+      if (LCAP >= G && wave_ballot(sub + G < cnt) != 0) {
+        int32_t g[K];
+        gram_before(sub + G, g);
+        file_positions<false, K>(gram, ix.bucket_mask, K, g, filed(sub + G), packed(sub + G), lane, [] {});
+      }
+      // ---- the walk, by as many lanes of a path as the wave's paths have matches
+      leave = on && (leave || M > G);
+      block_sync<kWave>();
+      const bool drafts = on && !leave, walks = drafts && M > 0;
+      int32_t n = 0;
+      if (wave_ballot(walks) != 0) {                     // uniform over the wave
+        const uint32_t match = walks && sub < M ? found[sub] : 0u;
+        auto walk = [&](auto lanes, auto edge) {
+          group_walk<lanes(), LCAP, edge()>(ix, m.a, u, match, walks, [&](auto layer, bool going, const Cand& best) {
+            if (sub == 0) draft_all[path][layer() - 1] = best.v;
+            n = going ? layer() : n;
+          });
+        };
+        auto weighed = [&](auto edge) {
+          if (wave_ballot(walks && M > 8) != 0) walk(std::integral_constant<int, 16>{}, edge);
+          else if (wave_ballot(walks && M > 4) != 0) walk(std::integral_constant<int, 8>{}, edge);
+          else walk(std::integral_constant<int, 4>{}, edge);
+        };
+        if (m.a.score_mode == 0) weighed(std::false_type{});
+        else weighed(std::true_type{});
+      }
+      n = (int32_t)dpp_move<0x150>((uint32_t)n);
+      block_sync<kWave>();                               // the draft's tokens
+      const int32_t drafted = draft_all[path][sub < LCAP ? sub : 0];
+      const uint32_t stops = group_bits(!(sub < n && drafted == own[kBefore + cnt + (sub < L ? sub : 0)])) | 1u << G;
+      accepted = (int32_t)__ffs(stops) - 1;
+      out_tok = sub < n ? drafted : -1;
+      out_n = n;
+      out_drafted = drafts;
+      if (leave && sub == 0) crowded[atomicAdd(&n_crowded[parity], 1)] = (uint8_t)path;
+      __syncthreads();                                   // the step's postings are in the L2
+      n_left = __builtin_amdgcn_readfirstlane(n_crowded[parity]);
+      if (n_left > 0) break;
+      advance();
+      ++step;
+    }
+    if (n_left == 0) {
+      if (step > 0) store_outputs(step - 1, old);
+      break;
+    }
+    // ---- rows that are left to a wave
+    {
+      const LoopArgs& args = loop_arguments();
+      const IndexView& in_place = args.ix;
+      int32_t t = tid;
+      consume_here(t);
+      const int32_t wave = __builtin_amdgcn_readfirstlane(t >> 6), now = old + cnt;
+      if (on && sub <= in_place.tail_len)
+        in_place.meta_new[(int64_t)u.row * in_place.meta_stride + sub] = sub == 0 ? now : (sub <= now ? own[kBefore + cnt - sub] : 0);
+      if (leave && sub < args.a.L) args.targets[(int64_t)u.row * args.a.L + sub] = own[kBefore + cnt + sub];
+      __syncthreads();                                   // ends and targets are in memory, as the step's postings are
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      for (int32_t x = wave; x < n_left; x += WAVES) {
+        const LoopArgs& again = loop_arguments();
+        IndexView v = again.ix;
+        v.meta_old = v.meta_new;
+        DraftArgs b = again.a;
+        const int64_t before = step * ((int64_t)v.P * v.N);
+        b.draft_tokens += before * b.L;
+        b.draft_len += before;
+        b.accept_len += before;
+        b.targets = again.targets;
+        const int32_t row = (int32_t)blockIdx.x * v.N + __builtin_amdgcn_readfirstlane((int)crowded[x]);
+        row_step<LCAP, false, LdsWave, false, 4, false>(wide[wave], v, StepIn{nullptr, nullptr, nullptr, 0}, b,
+                                                        AcceptTail{accepted_by_wave}, row, t & (kWave - 1));
+        block_sync<kWave>();
+      }
+      __syncthreads();
+      accepted = leave ? accepted_by_wave[path] : accepted;
+    }
+    advance();
+    ++step;
+  }
+  if (on && sub <= ix.tail_len)
+    ix.meta_new[(int64_t)u.row * ix.meta_stride + sub] = sub == 0 ? old : (sub <= old ? own[kBefore - sub] : 0);
+  if (flags) atomicOr(ix.status, flags);
+}
+
+template <int LCAP, int K>
+void launch_loop_kernel(const LoopArgs& m, hipStream_t st) {
+  const uint32_t grid = (uint32_t)m.ix.P;
+  if (m.ix.N <= 4) loop_kernel<LCAP, 1, K><<<grid, kWave, 0, st>>>(m);
+  else if (m.ix.N <= 8) loop_kernel<LCAP, 2, K><<<grid, 2 * kWave, 0, st>>>(m);
+  else loop_kernel<LCAP, 4, K><<<grid, 4 * kWave, 0, st>>>(m);
+}
+template <int LCAP>
+void launch_loop_steps(const LoopArgs& m, hipStream_t st) {
+  if (m.ix.kmax == 2) launch_loop_kernel<LCAP, 2>(m, st);
+  else if (m.ix.kmax == 3) launch_loop_kernel<LCAP, 3>(m, st);
+  else launch_loop_kernel<LCAP, 4>(m, st);
+}
+
+}  // namespace csd
