@@ -837,13 +837,17 @@ __global__ __launch_bounds__(kWave) void replay_wave_kernel(IndexView ix, int32_
                                                (int)threadIdx.x);
 }
 
-// The rows that are left to a wave of their own.  A list of many rows is drafted with the small layout
-// (sixteen rows a CU: what counts is how many are under way), a list of few with the LARGE one
-// (four, but the rows with hundreds of matches, which set the time then, take 19 us instead of 92).
-// us, replay of 1024 problems x 16 paths x 24 steps, paths that agree in all but 20 %, 5 %, 2 % of their
-// tokens: all rows with the large layout 673, 2076, 2172, so 427, 1052, 1108; with every token four times
-// in each path 3163, so 1913; 64 problems x 48 steps, 5 %: 292, 148.  (A launch per step: 875, 1041,
-// 1054; 1943; 367.)
+// The rows that are left to a wave of their own, in one launch of workgroups that hold either four waves
+// with the small layout or one with the large: the rows with few matches take the former (what counts is
+// how many are under way), those with many, whose hundreds of matches take 19 us instead of 92, the
+// latter.  An XCD's workgroups are split between its two lists by the room that their rows take, so that
+// both are done at once.  Where thousands of rows are left (paths that agree in most tokens) all take the
+// small layout, in twice as many workgroups as the chip holds at once.  us, the two launches that this was
+// before (the small layout for lists of more than 1024 rows, then the large for all others) / this:
+// 1024 problems x 16 paths x 24 steps, 8000 rows left, 4.7 + 68 / 46; 64 problems x 48 steps, 1000 rows,
+// 3.8 + 22.7 / 21; the whole replay where the paths agree in all but 20 %, 5 %, 2 % of their tokens: 1024 problems
+// 157, 315, 374 / 147, 269, 310, 64 problems 46, 73, 81 / 38, 66, 74.  Left to itself the compiler takes 182
+// registers for the three layouts' code, two waves a SIMD: 1024 problems 73 / 68.
 // A wave takes many rows, one after the other.  It reads the arguments anew for each (kept over the
 // loop beside the row's own they were spilled, 500 instructions a row), and requests the next row's
 // unit before this one's work (two round trips a row).
@@ -854,45 +858,69 @@ struct RestArgs {
   RestList list;
 };
 constexpr int32_t kFewRest = 1024;     // rows of a list
+constexpr int32_t kRestTurn = 128;   // workgroups of an XCD that are under way at once (of twice as many)
+struct LdsWaveRest : LdsWaveSmall {};  // (four buckets of a chain are read up front: most of these rows have long ones)
 __device__ __forceinline__ const RestArgs& rest_arguments() {
   auto* kernarg = __builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(kernarg));
   return *(const RestArgs*)kernarg;
 }
-template <int LCAP, bool LARGE, int QC>
-__global__ __launch_bounds__(kWave) void replay_rest_kernel(RestArgs) {
-  using LDS = std::conditional_t<LARGE, LdsWave, LdsWaveSmall>;
-  __shared__ LDS s;
-  int32_t few, count;                  // this kernel's of the list of rows with few matches, of both
+// The rows x, x + stride .. of `count`, of which the first `few` are of the list of rows with few matches.
+template <int LCAP, int QC, class LDS>
+__device__ __forceinline__ void rest_rows(LDS& s, int32_t x, int32_t stride, int32_t few, int32_t count, int lane) {
   auto unit_of = [&](int32_t x) {      // (any unit behind the last)
     const RestList list = rest_arguments().list;
     const bool many = x >= few;
     return *list.unit(blockIdx.x & 7, many, x < count ? (many ? x - few : x) : 0);
   };
-  {
-    const RestList list = rest_arguments().list;
-    auto mine = [&](bool many) {
-      const int32_t n = *list.count(blockIdx.x & 7, many);
-      return __builtin_amdgcn_readfirstlane((n <= kFewRest) == LARGE ? n : 0);
-    };
-    few = mine(false);
-    count = few + mine(true);
-  }
-  int32_t x = (int32_t)(blockIdx.x >> 3);
   if (x >= count) return;
   int32_t next = unit_of(x);
   while (x < count) {
     const int32_t unit = __builtin_amdgcn_readfirstlane(next);
-    x += (int32_t)(gridDim.x >> 3);
+    x += stride;
     next = unit_of(x);
     const RestArgs& args = rest_arguments();
     IndexView v = args.ix;
     DraftArgs b = args.a;
     const int32_t row = replay_unit(v, b, args.steps, unit);
-    row_step<LCAP, false, LDS, false, QC, false>(s, v, StepIn{nullptr, nullptr, nullptr, 0}, b, NoTail{}, row,
-                                                 (int)threadIdx.x);
+    row_step<LCAP, false, LDS, false, QC, false>(s, v, StepIn{nullptr, nullptr, nullptr, 0}, b, NoTail{}, row, lane);
     block_sync<kWave>();
   }
+}
+template <int LCAP, int QC>
+__global__ __launch_bounds__(4 * kWave) __attribute__((amdgpu_waves_per_eu(LCAP <= 8 ? 4 : LCAP <= 16 ? 3 : 2)))
+void replay_rest_kernel(RestArgs) {
+  constexpr int kWaves = 4;
+  __shared__ union Layouts {
+    LdsWaveRest small[kWaves];
+    LdsWave large;
+  } s;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & (kWave - 1));
+  const int32_t nth = (int32_t)(blockIdx.x >> 3);
+  int32_t few, many;
+  {
+    const RestList list = rest_arguments().list;
+    few = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, false));
+    many = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, true));
+  }
+  if (few + many == 0) return;
+  // (a row of the large layout takes the room of four; the large ones are spread over the workgroups'
+  // numbers, so that those under way first are of both kinds)
+  int32_t groups = 2 * kRestTurn, large = 0, before = 0;
+  if (many <= kFewRest) {
+    groups = few > kFewRest ? 2 * kRestTurn : kRestTurn;
+    if (nth >= groups) return;
+    large = (groups * kWaves * many + few + kWaves * many - 1) / (few + kWaves * many);
+    large = large < many ? large : many;
+    large = few > 0 && large >= groups ? groups - 1 : large;
+    before = nth * large / groups;                       // workgroups below this one that take the large layout
+    if ((nth + 1) * large / groups > before) {
+      if (wave == 0) rest_rows<LCAP, QC>(s.large, few + before, large, few, few + many, lane);
+      return;
+    }
+  }
+  rest_rows<LCAP, QC>(s.small[wave], (nth - before) * kWaves + wave, (groups - large) * kWaves, few,
+                      many <= kFewRest ? few : few + many, lane);
 }
 
 // One edit through the index, many drafts: most rows have few matches and are done by a wave, on a small

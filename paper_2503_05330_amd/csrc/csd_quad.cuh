@@ -335,9 +335,11 @@ constexpr int32_t kRestPad = 8 * 256;  // units by which the lists of all XCDs m
 // of four waves pooled, 60 with those of sixteen.  It lists the rows with more matches or a
 // longer chain for the kernels with a wave per row (one reservation: atomics on one address take 12 ns
 // each).  A chain is followed to its end, or for kLongChain buckets, also when the row's matches
-// are too many: it tells the rows with more than kFewMatches, which those kernels may draft with
-// another layout (any serves any row).
-constexpr int32_t kFewMatches = 30;
+// are too many: it tells the rows with more than few_matches, which that kernel may draft with
+// another layout (any serves any row), and where the chain goes on those that had more than eight so far.
+// 1024 problems x 24 steps leave 8000 of 393000 rows: 4130 whose chain has ended (3180 with 9 .. 16
+// matches, 950 up to 30, 18 more) and 3920 with longer chains (2320 with up to eight so far, 1120, 470).
+constexpr int32_t few_matches(int32_t L) { return L <= 24 ? 30 : 24; }   // (what the small layout has windows for)
 constexpr uint32_t kLongChain = 3;     // buckets after which the wave per row, which reads four at once, takes over
 template <int WAVES, int LCAP, int QC, bool EDGE>
 __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
       leave = leave || (looking && goes_on && r + 1 >= kLongChain);
       looking = looking && goes_on && !leave;
     }
-    const bool many = is_short || M > kFewMatches;
+    const bool many = is_short || M > (leave ? G : few_matches(a.L));   // (leave: the chain goes on)
     leave = leave || M > G;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (LDS of this wave alone)
     group_draft<G, LCAP, EDGE>(ix, a, u, on && !leave && sub < M ? found[lane] : 0u, on && !leave, sub, target);

@@ -38,11 +38,7 @@ static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, 
   const RestList list{rest_list, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows};
   if (pooled) replay_eight_kernel<16, LCAP, QC, EDGE><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   else replay_eight_kernel<4, LCAP, QC, EDGE><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
-  // (the second as many as the chip holds at once, the first twice that: 4096, which it holds, do not
-  // spread evenly, 1281 us for 1024 problems whose paths agree, 8192: 1109, 49152: 1030, which cost 8 us
-  // where there is nothing to do for them)
-  replay_rest_kernel<LCAP, false, QC><<<8192, kWave, 0, st>>>(RestArgs{v, steps, a, list});
-  replay_rest_kernel<LCAP, true, QC><<<1024, kWave, 0, st>>>(RestArgs{v, steps, a, list});
+  replay_rest_kernel<LCAP, QC><<<8 * 2 * kRestTurn, 4 * kWave, 0, st>>>(RestArgs{v, steps, a, list});
 }
 
 template <int QC>
