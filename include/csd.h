@@ -259,7 +259,7 @@ int csd_replay(csd_index* index, int32_t n_steps, const int32_t* d_tokens, const
  * draft_len + 1 tokens per path and counts (with the index matcher, exact
  * matching and twice the minimum of scratch memory: one launch per step, whose
  * tail gathers the next step's input).  With the index matcher, exact matching,
- * the DAG pool without options, up to 16 paths, draft_len <= 16 and query_len =
+ * the DAG pool without options, up to 32 paths, draft_len <= 16 and query_len =
  * max_query_len of 3 or 4 (2: from 512 paths in all) all steps run in one launch
  * behind one that copies the futures to the histories behind the paths' ends
  * (unless a buffer that is written overlaps another one).

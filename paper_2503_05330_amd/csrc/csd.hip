@@ -350,8 +350,8 @@ bool multi_step_ok(const csd_index* h) {
 // 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 753 / 813).
 constexpr int64_t kLoopRows = 512;
 bool one_launch_loop_ok(const csd_index* h, int32_t query_len, int32_t draft_len) {
-  return multi_step_ok(h) && h->cfg.pool_mode == CSD_POOL_DAG && h->view.options == 0 && h->view.N <= kLoopPaths &&
-         query_len == h->view.kmax && draft_len <= kLoopLanes &&
+  return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->cfg.pool_mode == CSD_POOL_DAG && h->view.options == 0 &&
+         h->view.N <= kLoopPaths && query_len == h->view.kmax && draft_len <= kLoopLanes &&
          (query_len > 2 || (query_len == 2 && (int64_t)h->view.P * h->view.N >= kLoopRows));
 }
 

@@ -6,7 +6,7 @@
 namespace csd {
 
 constexpr int kLoopLanes = 16;         // lanes of a path: a row of DPP moves
-constexpr int kLoopPaths = 16;         // most paths of a problem (four waves of four)
+constexpr int kLoopPaths = 32;         // most paths of a problem (eight waves of four)
 
 // What the loop's steps may append is known when the call is made: each path's own future.  It goes
 // to the histories behind the paths' ends beforehand (what lies there is not seen, see append and
@@ -53,16 +53,18 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
 // index: code apart from the steps' (inlined into their loop it spilled their registers, 5.6 us a step).
 // us a call, a launch per step / this (queries of three, drafts of eight, 48 steps): 1 problem of 16 paths
 // x 1024 tokens 352 / 205, of 4 x 256 (24 steps) 152 / 81; 64 problems 531 / 252, 1024 of 16 x 512 (24
-// steps) 2307 / 443.  Where most rows have more than sixteen matches four waves draft sixteen of
-// them in turn: 537 / 1096 for paths of which each holds each gram four times.
+// steps) 2307 / 443; 24 and 32 paths x 1024 395 / 249 and 447 / 310, 64 problems of 32 x 512 (24 steps)
+// 463 / 160.  Where most rows have more than sixteen matches a few waves (as many as have room for that
+// layout) draft them in turn: 537 / 1096 for 16 paths of which each holds each gram four times.
 // Exact matching through the index, DAG pool, queries of kmax = K tokens.
 template <int LCAP, int WAVES, int K>
 __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   constexpr int G = kLoopLanes, kPaths = WAVES * kWave / G, BLOCK = WAVES * kWave;
+  constexpr int kWide = WAVES < 4 ? WAVES : (WAVES == 4 ? 4 : 3);   // waves that draft the rows left (what the LDS has room for)
   constexpr int kBefore = 4;                             // tokens before a path's end that are kept
   constexpr int kOwn = (2 * LCAP + kBefore + 1 + G - 1) / G;   // words of a path's window that a lane has
   static_assert(K >= 2 && K <= kBefore, "a gram's tokens in one load");
-  __shared__ LdsWave wide[WAVES];
+  __shared__ LdsWave wide[kWide];
   __shared__ int32_t own_all[kPaths][kOwn * G];          // tokens from kBefore before a path's end on, up to 2 L behind it
   __shared__ int2 fresh[kPaths * (LCAP + 1)];            // the step's new positions: packed, hash of the gram before them
   __shared__ int2 ends[kPaths];                          // lengths before and after the step's append
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       if (leave && sub < args.a.L) args.targets[(int64_t)u.row * args.a.L + sub] = own[kBefore + cnt + sub];
       __syncthreads();                                   // ends and targets are in memory, as the step's postings are
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      for (int32_t x = wave; x < n_left; x += WAVES) {
+      for (int32_t x = wave; wave < kWide && x < n_left; x += kWide) {
         const LoopArgs& again = loop_arguments();
         IndexView v = again.ix;
         v.meta_old = v.meta_new;
@@ -306,7 +308,8 @@ void launch_loop_kernel(const LoopArgs& m, hipStream_t st) {
   const uint32_t grid = (uint32_t)m.ix.P;
   if (m.ix.N <= 4) loop_kernel<LCAP, 1, K><<<grid, kWave, 0, st>>>(m);
   else if (m.ix.N <= 8) loop_kernel<LCAP, 2, K><<<grid, 2 * kWave, 0, st>>>(m);
-  else loop_kernel<LCAP, 4, K><<<grid, 4 * kWave, 0, st>>>(m);
+  else if (m.ix.N <= 16) loop_kernel<LCAP, 4, K><<<grid, 4 * kWave, 0, st>>>(m);
+  else loop_kernel<LCAP, 8, K><<<grid, 8 * kWave, 0, st>>>(m);
 }
 template <int LCAP>
 void launch_loop_steps(const LoopArgs& m, hipStream_t st) {

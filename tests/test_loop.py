@@ -53,7 +53,8 @@ def _run(tok, probs, lens, steps, kmax, L, alpha, mode, per_launch, vocab=600):
     ("phrases", 5, 2, 130, 40, 2, 1), ("phrases", 1, 4, 200, 200, 3, 8), ("phrases", 2, 5, 257, 30, 3, 15),
     ("phrases", 1, 8, 300, 33, 4, 9), ("phrases", 40, 9, 120, 20, 1, 8), ("constant", 1, 16, 60, 8, 3, 8),
     ("periodic", 1, 16, 300, 40, 3, 16), ("periodic", 2, 7, 300, 40, 3, 7), ("symbols", 2, 16, 256, 25, 4, 8),
-    ("symbols", 1, 3, 150, 30, 2, 16)])
+    ("symbols", 1, 3, 150, 30, 2, 16), ("phrases", 1, 17, 300, 40, 3, 8), ("phrases", 2, 32, 400, 30, 4, 16),
+    ("periodic", 1, 29, 200, 12, 3, 8), ("phrases", 20, 30, 120, 20, 2, 5)])
 def test_one_launch_equals_a_launch_per_step(kind, P, N, T, steps, kmax, L):
     print("loop", kind, P, N, T, steps, kmax, L, flush=True)
     rng = np.random.default_rng(P * 1000 + N * 10 + L)
