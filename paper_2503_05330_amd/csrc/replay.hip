@@ -6,13 +6,12 @@ namespace csd {
 // From this many drafts on the small LDS layout is used (as in launch_step).
 constexpr int64_t kSmallLdsDrafts = 2048;
 
-// From this many drafts on those with few matches are made with four or eight lanes each.  Four
+// From this many drafts on those with few matches are made with four or eight lanes each.  Three
 // kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
-// drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31, 49152 (64
-// problems x 16 paths x 48 steps) 73 / 50 (10 + 17 + 3 + 20), 393216 (1024 problems, 24 steps) 533 / 196
-// (60 + 60 + 4 + 72).  Where the paths agree in most tokens nearly all rows are left over and a wave
-// per draft would be the faster form (the whole call, all but 20 %, 5 % equal: 602 / 427, 748 / 1064; 64
-// problems 85 / 72, 107 / 150); the host does not know.
+// drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31 (with a fourth kernel of
+// 4 us, before the rest were one), 49152 (64 problems x 16 paths x 48 steps) 73 / 42 (8 + 13 + 21), 393216 (1024
+// problems, 24 steps) 533 / 159 (56 + 57 + 46).  Where the paths agree in most tokens nearly all rows are
+// left over; the host does not know.
 constexpr int64_t kQuadDrafts = 1 << 15;
 
 template <class LDS, int QC>
