@@ -29,6 +29,10 @@ struct LoopArgs {
   DraftArgs a;                  // outputs of step 0; step t writes slice t
 };
 
+// A barrier behind which everything that the workgroup has stored is in the L2 (a workgroup's own fence waits
+// for LDS alone, since its waves share a vector cache; the buckets are read past it).
+__device__ __forceinline__ void memory_barrier() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // The kernel's arguments, read anew: what is done with them here is not kept over the code around
 // (of which there is not much room in scalar registers).
 __device__ __forceinline__ const LoopArgs& loop_arguments() {
@@ -255,7 +259,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       out_n = n;
       out_drafted = drafts;
       if (leave && sub == 0) crowded[atomicAdd(&n_crowded[parity], 1)] = (uint8_t)path;
-      __syncthreads();                                   // the step's postings are in the L2
+      memory_barrier();                                  // the step's postings are in the L2
       n_left = __builtin_amdgcn_readfirstlane(n_crowded[parity]);
       if (n_left > 0) break;
       advance();
@@ -275,7 +279,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       if (on && sub <= in_place.tail_len)
         in_place.meta_new[(int64_t)u.row * in_place.meta_stride + sub] = sub == 0 ? now : (sub <= now ? own[kBefore + cnt - sub] : 0);
       if (leave && sub < args.a.L) args.targets[(int64_t)u.row * args.a.L + sub] = own[kBefore + cnt + sub];
-      __syncthreads();                                   // ends and targets are in memory, as the step's postings are
+      memory_barrier();                                  // ends and targets are in memory, as the step's postings are
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       for (int32_t x = wave; wave < kWide && x < n_left; x += kWide) {
         const LoopArgs& again = loop_arguments();
