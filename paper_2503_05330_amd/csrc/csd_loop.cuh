@@ -47,7 +47,7 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
 // walk, in caches that stay warm, and two barriers of the workgroup; the paths' ends and newest tokens
 // are in LDS, the positions that the step itself appends are matched from a list of their hashes
 // there, their postings are stored while the walk goes on, and the outputs of a step behind the next
-// one's barrier.  3.9 us a step (top to bucket 0.45, claims 0.2, look-up 0.8, postings 0.15, walk up to
+// one's barrier.  3.7 us a step (top to bucket 0.45, claims 0.2, look-up 0.8, postings 0.15, walk up to
 // 1.7, the wait for the slowest wave's); one wave issues an instruction every 7 cycles here, so the
 // instructions of the chain count.  With a wave per path (step_multi_kernel) the four SIMDs of the one
 // CU had 1500 instructions a row and step to issue, 14 us; with sixteen lanes a path they have four
