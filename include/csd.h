@@ -22,9 +22,11 @@
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Every call except csd_status / csd_dump_* only enqueues work on `stream`
  *    and returns; nothing is allocated, freed or synchronised by them.
- *  - These calls can be captured in a HIP graph.  csd_append, csd_draft, csd_accept, csd_reset
- *    and a csd_step that appends first (two launches, see there) then do at every replay what
- *    a call does.  A csd_step in one launch, a csd_replay of fused steps and the steps of
+ *  - These calls can be captured in a HIP graph.  csd_append, csd_draft, csd_accept, csd_reset,
+ *    a csd_step that appends first (two launches, see there) and, with the index matcher, a
+ *    csd_accept_loop with all its steps in one launch or with an append and a draft for each
+ *    then do at every replay what a call does.  A csd_step in one launch, a csd_replay of fused
+ *    steps, a device-side loop (csd_set_steps_per_launch) and the steps of
  *    csd_accept_loop that are one launch each write the paths' ends into two buffers in turn:
  *    capture an even number of such steps, so that the next replay finds the ends where the
  *    first one did.  The host's bounds on the lengths (CSD_ERR_CAPACITY) do not see what

@@ -765,19 +765,15 @@ static int accept_loop(csd_index* h, int32_t n_steps, const int32_t* d_future_to
                             {d_draft_tokens, n_steps * rows * L * 4}, {d_draft_len, n_steps * rows * 4},
                             {d_accept_len, n_steps * rows * 4}, {d_path_len, n_steps * rows * 4}};
   if (h->steps_per_launch == 0 && one_launch_loop_ok(h, query_len, draft_len) && n_steps > 0 && !overlap(buffers, 2, 6)) {
-    IndexView v = h->view;
-    v.meta_old = h->meta[h->cur];
-    v.meta_new = h->meta[h->cur ^ (n_steps & 1)];        // (where a launch per step would leave the ends)
-    const LoopArgs m{v, n_steps, targets, d_path_len,
+    // the ends are replaced in place and `cur` stays: captured once, the loop goes on at every replay of the graph
+    const LoopArgs m{view_in_place(h), n_steps, targets, d_path_len,
                      DraftArgs{query_len, draft_len, h->alpha_q, h->cfg.score_mode, h->cfg.pool_mode, d_draft_tokens,
                                d_draft_len, nullptr, nullptr, nullptr, d_accept_len}};
     LengthBounds before(h);
     const int64_t most = h->len_hi + (int64_t)n_steps * (int64_t)n;
     h->len_hi = most < h->cfg.max_len ? most : h->cfg.max_len;
     launch_loop(m, d_future_tokens, d_future_probs, st);
-    rc = before.launched("csd_accept_loop");
-    if (rc == CSD_OK) h->cur ^= n_steps & 1;
-    return rc;
+    return before.launched("csd_accept_loop");
   }
   if (h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && n_steps > 0 &&
       scratch_bytes >= 2 * rows * (2 * n + L + 1) * 4) {

@@ -57,6 +57,11 @@ def _captured(call):
     (2, 5, 400, 3, 1, binding.MATCH_SCAN, "replay", 3),
     (2, 5, 400, 5, 0, binding.MATCH_INDEX, "loop", 3),
     (2, 5, 400, 3, 1, binding.MATCH_INDEX, "loop", 3),
+    # all steps in one launch, with the minimum of scratch memory and with twice as much
+    (2, 5, 400, 3, 0, binding.MATCH_INDEX, "loop", 3),
+    (1, 16, 400, 4, 0, binding.MATCH_INDEX, "loop", 3),
+    (1, 20, 400, 4, 0, binding.MATCH_INDEX, "loop", 3),
+    (2, 5, 400, 3, 0, binding.MATCH_INDEX, "loop, twice the scratch", 3),
 ])
 def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, query, edits, flags, call, n):
     print("captured", problems, paths, max_len, query, edits, flags, call, n, flush=True)
@@ -66,7 +71,7 @@ def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, q
     fed_at = [_tokens(rng, problems, paths, n, V) for _ in range(turns)]
     if call == "replay":
         fed_at = [a.transpose(2, 0, 1) for a in fed_at]
-    elif call == "loop":
+    elif call.startswith("loop"):
         fed_at = [_tokens(rng, problems, paths, max_len, V)] * turns
     past, between = (_put(_tokens(rng, problems, paths, k, V)) for k in (warm, 7))
     by_graph, by_call = (binding.Index(problems, paths, max_len, V, query, L, 0.5, 0, flags, device="cuda:0", max_edits=edits)
@@ -83,12 +88,12 @@ def test_a_captured_append_goes_on_from_where_it_was(problems, paths, max_len, q
         elif call == "replay":
             out = ix.replay(n, tokens, None, query, L, out=out, fused=False)
         else:
-            out = ix.accept_loop(n, tokens, None, query, L, min_scratch=True)
+            out = ix.accept_loop(n, tokens, None, query, L, min_scratch=call == "loop")
         return out
     for ix in (by_graph, by_call):
         ix.append(past)
     graph, out = _captured(lambda: go(by_graph, fed, None))
-    keys = ("tokens", "length", "accept", "path_len") if call == "loop" else KEYS
+    keys = ("tokens", "length", "accept", "path_len") if call.startswith("loop") else KEYS
     drafted = 0
     for turn in range(turns):
         fed.copy_(_put(fed_at[turn]))
