@@ -11,14 +11,18 @@ constexpr int kLoopPaths = 32;         // most paths of a problem (eight waves o
 // What the loop's steps may append is known when the call is made: each path's own future.  It goes
 // to the histories behind the paths' ends beforehand (what lies there is not seen, see append and
 // replay), so that a step has no histories to write and all that it reads of them is settled.
+// A workgroup has the same 256 cells of every row_groups-th path.
 static __global__ __launch_bounds__(256) void loop_fill_kernel(IndexView ix, const int32_t* future_tok,
-                                                               const float* future_prob, int32_t ahead, int32_t chunks) {
-  const int32_t row = (int32_t)blockIdx.x / chunks, chunk = (int32_t)blockIdx.x - row * chunks;
-  const int32_t len = ix.meta_old[(int64_t)row * ix.meta_stride], t = chunk * 256 + (int32_t)threadIdx.x;
-  if (t >= ahead || t >= ix.max_len - len) return;
-  const int64_t at = (int64_t)row * ix.max_len + len + t;
-  ix.tok[at] = future_tok[at];
-  ix.pq[at] = future_prob ? quantize_prob(future_prob[at]) : 65536u;
+                                                               const float* future_prob, int32_t ahead, int32_t chunks,
+                                                               int32_t row_groups) {
+  const int32_t first = (int32_t)blockIdx.x / chunks, t = ((int32_t)blockIdx.x - first * chunks) * 256 + (int32_t)threadIdx.x;
+  for (int32_t row = first; row < ix.P * ix.N; row += row_groups) {
+    const int32_t len = ix.meta_old[(int64_t)row * ix.meta_stride];
+    if (t >= ahead || t >= ix.max_len - len) continue;
+    const int64_t at = (int64_t)row * ix.max_len + len + t;
+    ix.tok[at] = future_tok[at];
+    ix.pq[at] = future_prob ? quantize_prob(future_prob[at]) : 65536u;
+  }
 }
 
 struct LoopArgs {

@@ -8,7 +8,12 @@ void launch_loop(const LoopArgs& m, const int32_t* future_tok, const float* futu
   // as far as the steps and the last one's targets reach
   const int64_t reach = (int64_t)m.steps * (m.a.L + 1) + m.a.L;
   const int32_t ahead = reach < m.ix.max_len ? (int32_t)reach : m.ix.max_len, chunks = (ahead + 255) / 256;
-  loop_fill_kernel<<<(uint32_t)(m.ix.P * m.ix.N * chunks), 256, 0, st>>>(m.ix, future_tok, future_prob, ahead, chunks);
+  // (a grid's threads are less than 2^32; a workgroup takes several paths beyond this many workgroups)
+  constexpr int32_t kFillGroups = 1 << 22;
+  const int32_t rows = m.ix.P * m.ix.N, most = kFillGroups / chunks;   // (at most 2^16 chunks: CSD_MAX_POSITIONS)
+  const int32_t row_groups = rows < most ? rows : most;
+  loop_fill_kernel<<<(uint32_t)(row_groups * chunks), 256, 0, st>>>(m.ix, future_tok, future_prob, ahead, chunks, row_groups);
+  if (hipPeekAtLastError() != hipSuccess) return;        // (the caller sees it: no steps on histories that were not filled)
   if (m.a.L <= 8) launch_loop_steps<8>(m, st);
   else launch_loop_long(m, st);
 }

@@ -98,3 +98,28 @@ def test_tokens_out_of_range_and_a_captured_loop():
         for name in ("tokens", "length", "accept", "path_len"):
             assert torch.equal(out[name], want[name]), name
         d_tok.clone().sum().item()                         # work of the program's own between the replays
+
+
+def test_more_paths_than_a_grid_of_fills_has_workgroups():
+    """2^24 paths: a workgroup for each would be a grid of 2^32 threads, which is refused."""
+    P, N, T = 1 << 20, 16, 8
+    print("loop, many paths", P, N, T, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    k, L, steps = 3, 1, 3
+    phrase = torch.randint(0, 40, (P, 1, T), generator=gen, device="cuda", dtype=torch.int32)
+    tok = torch.where(torch.rand((P, N, T), generator=gen, device="cuda") < 0.1, phrase + 1, phrase).contiguous()
+    lens = torch.randint(0, T // 2 + 1, (P, N), generator=gen, device="cuda", dtype=torch.int32)
+    outs = []
+    for per_launch in (1, 0):
+        ix = binding.Index(P, N, T, 64, k, L, 1.0, 0, binding.MATCH_INDEX, device="cuda:0")
+        if per_launch:
+            ix.set_steps_per_launch(per_launch)
+        ix.append(tok[:, :, :T // 2].contiguous(), None, lens)
+        outs.append((ix.accept_loop(steps, tok, None, k, L), ix.draft(k, L), ix.status()))
+        del ix
+    (loop, then, status), (loop_got, then_got, status_got) = outs
+    assert int(loop["accept"].sum()) > 0 and status == status_got
+    for name in ("tokens", "length", "accept", "path_len"):
+        assert torch.equal(loop_got[name], loop[name]), name
+    for name in ("tokens", "length", "token_scores", "path_scores"):
+        assert torch.equal(then_got[name], then[name]), name
