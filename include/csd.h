@@ -261,10 +261,12 @@ int csd_replay(csd_index* index, int32_t n_steps, const int32_t* d_tokens, const
  * draft_len + 1 tokens per path and counts (with the index matcher, exact
  * matching and twice the minimum of scratch memory: one launch per step, whose
  * tail gathers the next step's input).  With the index matcher, exact matching,
- * the DAG pool without options, up to 32 paths, draft_len <= 16 and query_len =
+ * the DAG pool without options, up to 24 paths (32: from 64 problems on), draft_len <= 16 and query_len =
  * max_query_len of 3 or 4 (2: from 512 paths in all) all steps run in one launch
  * behind one that copies the futures to the histories behind the paths' ends
- * (unless a buffer that is written overlaps another one).
+ * (unless a buffer that is written overlaps another one).  Where most paths have
+ * more than 64 matches a launch per step is the faster form:
+ * csd_set_steps_per_launch(1).
  *   d_scratch: device memory, 4-byte aligned, scratch_bytes >=
  *     P*N*(3*draft_len + 3)*4 (step tokens, probabilities, targets, counts);
  *     with twice as much, steps alternate between the two halves;

@@ -347,11 +347,15 @@ bool multi_step_ok(const csd_index* h) {
 
 // csd_accept_loop in one launch (see loop_kernel).  Queries of two tokens, many of which have more than
 // sixteen matches, only where the rows of a launch per step would not have a CU each (us, 16 paths x
-// 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 753 / 813).
+// 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 753 / 813).  More than 24 paths only from
+// 64 problems on: paths that agree have more matches than a row's lanes take there, and a launch per step
+// has a CU for each row (each gram four times in a path, 24 steps: 32 paths, 1 problem (48 steps), 8, 32, 64
+// 691 / 932, 370 / 392, 457 / 598, 726 / 610; 28 paths, 64 problems 617 / 376).
 constexpr int64_t kLoopRows = 512;
+constexpr int32_t kLoopFewPaths = 24, kLoopProblems = 64;
 bool one_launch_loop_ok(const csd_index* h, int32_t query_len, int32_t draft_len) {
   return h->indexed && h->view.eps == 0 && h->view.kmax <= 4 && h->cfg.pool_mode == CSD_POOL_DAG && h->view.options == 0 &&
-         h->view.N <= kLoopPaths && query_len == h->view.kmax && draft_len <= kLoopLanes &&
+         h->view.N <= (h->view.P < kLoopProblems ? kLoopFewPaths : kLoopPaths) && query_len == h->view.kmax && draft_len <= kLoopLanes &&
          (query_len > 2 || (query_len == 2 && (int64_t)h->view.P * h->view.N >= kLoopRows));
 }
 

@@ -29,6 +29,8 @@ void launch_step_loop(const IndexView& v, const StepIn& in, const DraftArgs& a, 
 struct LoopArgs;
 void launch_loop(const LoopArgs& m, const int32_t* future_tok, const float* future_prob, hipStream_t st);
 void launch_loop_long(const LoopArgs& m, hipStream_t st);   // its steps, drafts of more than eight tokens
+void launch_loop_long_two(const LoopArgs& m, hipStream_t st);    // ... of queries of two
+void launch_loop_long_four(const LoopArgs& m, hipStream_t st);   // ... and four
 // many steps per launch: a replay (general: tree and list pools, own history) / the accept-driven loop
 void launch_multi(const IndexView& v, const MultiArgs& m, bool general, hipStream_t st);
 void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);

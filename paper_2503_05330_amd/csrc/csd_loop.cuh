@@ -7,6 +7,8 @@ namespace csd {
 
 constexpr int kLoopLanes = 16;         // lanes of a path: a row of DPP moves
 constexpr int kLoopPaths = 32;         // most paths of a problem (eight waves of four)
+constexpr int kLoopMatches = 64;       // most matches of a row that its sixteen lanes draft (four a lane in registers)
+constexpr uint32_t kLoopChain = 9;     // buckets of a chain that they look through: the first, and four at a time
 
 // What the loop's steps may append is known when the call is made: each path's own future.  It goes
 // to the histories behind the paths' ends beforehand (what lies there is not seen, see append and
@@ -45,6 +47,141 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
   return *(const LoopArgs*)kernarg;
 }
 
+// Files the new position of each lane (see file_positions) in three parts: the claims on the first buckets
+// of the chains, the fill counts of the next four where those were full, and the claims there.  What lies
+// between them, the look-up and the walk, has their round trips.
+template <int K>
+struct Filing {
+  static constexpr int kAhead = 4;
+  int32_t* gram;
+  uint32_t mask;
+  GramHash gh;
+  int32_t pos, claimed;
+  bool open;                    // no slot yet
+  int32_t fill[kAhead];
+  __device__ __forceinline__ void look(uint32_t r) {
+    if (!open) return;
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x)
+      fill[x] = __hip_atomic_load(gram_bucket(gram, gh, r + x, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void claim(int32_t* table, uint32_t bucket_mask, const int32_t (&G)[K], bool mine, int32_t packed) {
+    gram = table;
+    mask = bucket_mask;
+    gh = gram_hash_of(G, K);
+    pos = packed;
+    open = mine;
+    claimed = kBucketSlots;
+    if (mine) claimed = atomicAdd(gram_bucket(gram, gh, 0, mask), 1);
+  }
+  __device__ __forceinline__ void settle() {
+    if (claimed < kBucketSlots) {
+      gram_bucket(gram, gh, 0, mask)[1 + claimed] = pos;
+      open = false;
+    }
+    if (wave_ballot(open) != 0) look(1);
+  }
+  __device__ __forceinline__ void finish() {             // (what finds no slot in a full index is dropped)
+    for (uint32_t r = 1; r <= mask && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
+      if (r > 1) look(r);
+      uint32_t room = 0;
+#pragma unroll
+      for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x <= mask ? 1u << x : 0u;
+      while (wave_ballot(room != 0) != 0) {
+        if (room != 0) {
+          int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, mask);
+          const int32_t c = atomicAdd(b, 1);
+          if (c < kBucketSlots) b[1 + c] = pos;
+          open = c >= kBucketSlots;
+          room = open ? room & (room - 1u) : 0u;
+        }
+      }
+    }
+  }
+};
+
+// group_walk for rows of seventeen to sixty-four matches, S of them a lane of the sixteen: in each layer the
+// tokens that follow the last choice are taken up one after the other, the lowest first, each with what all
+// lanes have of it, until those left could not outweigh the heaviest together.  (Every lane against every other, as there, is 4 S times the exchanges of sixteen
+// matches; here it is as many rounds as there are different tokens, few where the paths agree.)
+template <int S, int LCAP, bool EDGE, class CHOSEN>
+__device__ __forceinline__ void lanes_walk(const IndexView& ix, const DraftArgs& a, const UnitRow& u,
+                                           const uint32_t (&match)[S], bool going, CHOSEN&& chosen) {
+  constexpr int kCount = 24;                             // count (<= 64) above the probability sum (<= 2^22)
+  static_assert(S <= 4, "the sums of a layer in one word");
+  int32_t v[S][LCAP], pr[S][LCAP];
+#pragma unroll
+  for (int x = 0; x < S; ++x) {
+    const int32_t pos = (int32_t)(match[x] & ((1u << 25) - 1u));
+    const int32_t cell = (int32_t)__umul24((uint32_t)(pos >> ix.eshift), (uint32_t)ix.max_len) +
+                         (pos & ((1 << ix.eshift) - 1));
+#pragma unroll
+    for (int d = 0; d < LCAP; d += 4) {
+      const Run4 r = *reinterpret_cast<const Run4*>(u.tok + cell + d);
+      const Run4 s = *reinterpret_cast<const Run4*>(u.pq + cell + d);
+#pragma unroll
+      for (int z = 0; z < 4; ++z) {
+        v[x][d + z] = r.x[z];
+        pr[x][d + z] = s.x[z];
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < S; ++x)
+#pragma unroll
+    for (int d = 0; d < LCAP; ++d) {
+      consume_here(v[x][d]);
+      consume_here(pr[x][d]);
+    }
+  int32_t cur = 0;
+  static_for<1, LCAP + 1>([&](auto layer) {
+    constexpr int d = layer();
+    if (wave_ballot(going) == 0) return;                 // uniform over the wave; so from the layer behind L on
+    uint32_t own[S];
+    int32_t left[S];                                     // successors of the last choice that are still to be taken up
+#pragma unroll
+    for (int x = 0; x < S; ++x) {
+      const bool alive = d <= (int32_t)(match[x] >> 25);
+      const bool from_cur = alive && going && (d == 1 || v[x][d > 1 ? d - 2 : 0] == cur);
+      own[x] = (EDGE ? from_cur : alive) ? (1u << kCount) + (uint32_t)pr[x][d - 1] : 0u;
+      left[x] = from_cur ? v[x][d - 1] : INT_MAX;
+    }
+    uint32_t rest = 0;                                   // what the layer's tokens that are not taken up yet have in all
+#pragma unroll
+    for (int x = 0; x < S; ++x) rest += own[x];
+    auto weight = [&](uint32_t cs) { return weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q); };
+    auto lowest_and_sum = [&](uint32_t& sum) {
+      int32_t token = left[0];
+#pragma unroll
+      for (int x = 1; x < S; ++x) token = left[x] < token ? left[x] : token;
+      group_stages<kLoopLanes>([&](auto other) {
+        const int32_t theirs = (int32_t)other((uint32_t)token);
+        token = theirs < token ? theirs : token;
+        sum += other(sum);                               // (each stage brings other lanes' sums)
+      });
+      return token;
+    };
+    int32_t token = lowest_and_sum(rest);
+    Cand best = cand_none();
+    while (wave_ballot(token != INT_MAX && (best.v == INT_MAX || weight(rest) > best.key)) != 0) {   // uniform over the wave
+      uint32_t cs = 0;
+#pragma unroll
+      for (int x = 0; x < S; ++x) {
+        cs += v[x][d - 1] == token ? own[x] : 0u;
+        left[x] = left[x] == token ? INT_MAX : left[x];
+      }
+      const int32_t next = lowest_and_sum(cs);
+      const u64 key = weight(cs);
+      if (token != INT_MAX && (best.v == INT_MAX || key > best.key)) best = Cand{key, token};
+      rest -= token != INT_MAX ? cs : 0u;
+      token = next;
+    }
+    going = going && best.v != INT_MAX;                  // else a leaf: no edge leaves cur
+    cur = best.v;
+    chosen(layer, going, best);
+  });
+}
+
 // The steps of csd_accept_loop, one after the other.  A launch per step is bound by its latency:
 // dispatch, then three round trips on caches that are cold at every launch, 6.6 us at 16 x 1024.
 // Here a step's chain is the query's bucket, the postings' tokens, the matches' continuations and the
@@ -56,14 +193,20 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
 // instructions of the chain count.  With a wave per path (step_multi_kernel) the four SIMDs of the one
 // CU had 1500 instructions a row and step to issue, 14 us; with sixteen lanes a path they have four
 // waves of a few hundred.
-// A row with more than sixteen matches, a long chain or a path shorter than a gram is drafted by a
+// A row with up to sixteen matches is walked by group_walk, one with up to sixty-four by lanes_walk.  A row
+// with more of them, a chain of more than kLoopChain buckets or a path shorter than a gram is drafted by a
 // wave on the layout of a launch per step, behind a barrier, when the step's postings are in the
 // index: code apart from the steps' (inlined into their loop it spilled their registers, 5.6 us a step).
 // us a call, a launch per step / this (queries of three, drafts of eight, 48 steps): 1 problem of 16 paths
 // x 1024 tokens 352 / 205, of 4 x 256 (24 steps) 152 / 81; 64 problems 531 / 252, 1024 of 16 x 512 (24
 // steps) 2307 / 443; 24 and 32 paths x 1024 395 / 249 and 447 / 310, 64 problems of 32 x 512 (24 steps)
-// 463 / 160.  Where most rows have more than sixteen matches a few waves (as many as have room for that
-// layout) draft them in turn: 537 / 1096 for 16 paths of which each holds each gram four times.
+// 463 / 160.  Paths of different lengths that agree in all but 5 %, 2 % of their tokens: 16 x 1024 456 / 319,
+// 455 / 323, 24 x 1024 481 / 423, 472 / 439.  Each gram twice, four times, six times in each path: 16 x 1024
+// 458 / 359, 474 / 425, 526 / 474, 24 x 1024 503 / 445, 550 / 526, 692 / 1112: where most rows have more than
+// sixty-four matches a few waves (as many as have room for that layout) draft them in turn.  (With sixteen
+// matches and three buckets as the bounds, and the chains of full buckets followed one by one, 16 x 1024
+// with each gram twice, four times took 779, 1019, and 24 x 1024, all but 2 % equal, 737.)  Each gram 64 times in
+// each of 16, 24 paths (24 steps): 2250 / 5270, 5270 / 19900.
 // Exact matching through the index, DAG pool, queries of kmax = K tokens.
 template <int LCAP, int WAVES, int K>
 __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
@@ -76,7 +219,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   __shared__ int32_t own_all[kPaths][kOwn * G];          // tokens from kBefore before a path's end on, up to 2 L behind it
   __shared__ int2 fresh[kPaths * (LCAP + 1)];            // the step's new positions: packed, hash of the gram before them
   __shared__ int2 ends[kPaths];                          // lengths before and after the step's append
-  __shared__ uint32_t found_all[kPaths][G];              // matches
+  __shared__ uint32_t found_all[kPaths][kLoopMatches];   // matches
   __shared__ int32_t draft_all[kPaths][LCAP], accepted_by_wave[kPaths];
   __shared__ int32_t n_fresh[2], n_crowded[2];           // (a step clears the next one's)
   __shared__ uint8_t crowded[kPaths];
@@ -187,21 +330,34 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       leave = is_short;
       // ---- round trip 2: a candidate's gram (with the continuations of all candidates it takes 1.9 us
       // instead of 1.1: the four waves share one cache that looks up a line a cycle)
-      auto verify = [&](bool cand, int32_t word, bool is_new) {
-        const int32_t j = word >> ix.eshift, e = word & ((1 << ix.eshift) - 1);
-        cand = cand && word >= 0 && j != path && j < N;
-        const int2 end = ends[cand ? j : 0];
-        cand = cand && (is_new || e < end.x);            // (newer postings may be in flight: those are in the list)
-        const int32_t cell = cand ? (int32_t)__umul24((uint32_t)j, (uint32_t)ix.max_len) + e : K;
-        const Run4 r = *reinterpret_cast<const Run4*>(u.tok + cell - K);
-        int32_t differ = 0;
+      auto verify = [&](auto n, const bool (&one)[n()], const int32_t (&words)[n()], bool is_new) {
+        bool cand[n()];
+        int2 end[n()];
+        Run4 r[n()];
 #pragma unroll
-        for (int y = 0; y < K; ++y) differ |= r.x[y] ^ Q[K - 1 - y];
-        const bool hit = cand && differ == 0;
-        const uint32_t hits = group_bits(hit);
-        const int32_t to = M + (int32_t)__popc(hits & ((1u << sub) - 1u)), rem = end.y - e;
-        if (hit && to < G) found[to] = (uint32_t)word | (uint32_t)(rem < L ? rem : L) << 25;
-        M += (int32_t)__popc(hits);
+        for (int x = 0; x < n(); ++x) {
+          const int32_t j = words[x] >> ix.eshift, e = words[x] & ((1 << ix.eshift) - 1);
+          cand[x] = one[x] && words[x] >= 0 && j != path && j < N;
+          end[x] = ends[cand[x] ? j : 0];
+          cand[x] = cand[x] && (is_new || e < end[x].x);   // (newer postings may be in flight: those are in the list)
+          const int32_t cell = cand[x] ? (int32_t)__umul24((uint32_t)j, (uint32_t)ix.max_len) + e : K;
+          r[x] = *reinterpret_cast<const Run4*>(u.tok + cell - K);
+        }
+#pragma unroll
+        for (int x = 0; x < n(); ++x)
+#pragma unroll
+          for (int y = 0; y < K; ++y) consume_here(r[x].x[y]);
+#pragma unroll
+        for (int x = 0; x < n(); ++x) {
+          int32_t differ = 0;
+#pragma unroll
+          for (int y = 0; y < K; ++y) differ |= r[x].x[y] ^ Q[K - 1 - y];
+          const bool hit = cand[x] && differ == 0;
+          const uint32_t hits = group_bits(hit);
+          const int32_t to = M + (int32_t)__popc(hits & ((1u << sub) - 1u)), rem = end[x].y - (words[x] & ((1 << ix.eshift) - 1));
+          if (hit && to < kLoopMatches) found[to] = (uint32_t)words[x] | (uint32_t)(rem < L ? rem : L) << 25;
+          M += (int32_t)__popc(hits);
+        }
       };
       auto look_up = [&]() {
         // four of the list's positions a lane at once (as a loop of one, every turn was a round trip in LDS)
@@ -216,44 +372,75 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
             cands |= looking && x0 + y * G + sub < listed && f[y].y == (int32_t)gh.h && f[y].x >> ix.eshift != path ? 1u << y : 0u;
           if (wave_ballot(cands != 0) != 0)
 #pragma unroll
-            for (int y = 0; y < 4; ++y) verify((cands >> y & 1u) != 0, f[y].x, true);
+            for (int y = 0; y < 4; ++y) verify(std::integral_constant<int, 1>{}, {(cands >> y & 1u) != 0}, {f[y].x}, true);
         }
-        for (uint32_t r = 0; wave_ballot(looking) != 0; ++r) {   // uniform over the wave
-          const int32_t word = next, count = (int32_t)dpp_move<0x150>((uint32_t)word);   // (of the group's first lane)
-          const bool goes_on = looking && count >= kBucketSlots && r < ix.bucket_mask;
-          if (wave_ballot(goes_on) != 0) next = bucket(r + 1);   // (in flight while this one is looked through)
-          verify(looking && sub >= 1 && sub - 1 < count, word, false);
-          leave = leave || (goes_on && r + 1 >= kLongChain);
-          looking = goes_on && !leave;
+        constexpr int kAhead = 4;                        // buckets of a chain that are looked through together
+        int32_t words[kAhead];
+        auto request = [&](uint32_t r) {
+#pragma unroll
+          for (int x = 0; x < kAhead; ++x) words[x] = bucket(r + x);
+        };
+        auto count_of = [&](int32_t word) { return (int32_t)dpp_move<0x150>((uint32_t)word); };   // (the group's first lane has it)
+        const int32_t count = count_of(next);
+        const bool has_some = looking && sub >= 1 && sub - 1 < count;
+        looking = looking && count >= kBucketSlots && ix.bucket_mask > 0;
+        if (wave_ballot(looking) != 0) request(1);       // (in flight while the bucket before is looked through)
+        verify(std::integral_constant<int, 1>{}, {has_some}, {next}, false);
+        for (uint32_t r = 1; wave_ballot(looking) != 0; r += kAhead) {   // uniform over the wave
+          int32_t these[kAhead];
+          bool one[kAhead];
+#pragma unroll
+          for (int x = 0; x < kAhead; ++x) { these[x] = words[x]; consume_here(these[x]); }
+#pragma unroll
+          for (int x = 0; x < kAhead; ++x) {
+            const int32_t filled = count_of(these[x]);
+            one[x] = looking && sub >= 1 && sub - 1 < filled;
+            looking = looking && filled >= kBucketSlots && r + x < ix.bucket_mask;
+          }
+          leave = leave || (looking && r + kAhead >= kLoopChain);
+          looking = looking && !leave;
+          if (wave_ballot(looking) != 0) request(r + kAhead);
+          verify(std::integral_constant<int, kAhead>{}, one, these, false);
         }
       };
-      file_positions<false, K>(gram, ix.bucket_mask, K, G0, filed(sub), packed(sub), lane, look_up);
+      Filing<K> filing;
+      filing.claim(gram, ix.bucket_mask, G0, filed(sub), packed(sub));
+      look_up();
+      filing.settle();
       if (LCAP >= G && wave_ballot(sub + G < cnt) != 0) {
         int32_t g[K];
         gram_before(sub + G, g);
         file_positions<false, K>(gram, ix.bucket_mask, K, g, filed(sub + G), packed(sub + G), lane, [] {});
       }
       // ---- the walk, by as many lanes of a path as the wave's paths have matches
-      leave = on && (leave || M > G);
+      leave = on && (leave || M > kLoopMatches);
       block_sync<kWave>();
       const bool drafts = on && !leave, walks = drafts && M > 0;
       int32_t n = 0;
       if (wave_ballot(walks) != 0) {                     // uniform over the wave
         const uint32_t match = walks && sub < M ? found[sub] : 0u;
-        auto walk = [&](auto lanes, auto edge) {
-          group_walk<lanes(), LCAP, edge()>(ix, m.a, u, match, walks, [&](auto layer, bool going, const Cand& best) {
-            if (sub == 0) draft_all[path][layer() - 1] = best.v;
-            n = going ? layer() : n;
-          });
+        auto chosen = [&](auto layer, bool going, const Cand& best) {
+          if (sub == 0) draft_all[path][layer() - 1] = best.v;
+          n = going ? layer() : n;
         };
+        auto walk = [&](auto lanes, auto edge) { group_walk<lanes(), LCAP, edge()>(ix, m.a, u, match, walks, chosen); };
         auto weighed = [&](auto edge) {
-          if (wave_ballot(walks && M > 8) != 0) walk(std::integral_constant<int, 16>{}, edge);
-          else if (wave_ballot(walks && M > 4) != 0) walk(std::integral_constant<int, 8>{}, edge);
-          else walk(std::integral_constant<int, 4>{}, edge);
+          auto several = [&](auto n) {                   // matches a lane
+            uint32_t matches[n()];
+#pragma unroll
+            for (int x = 0; x < n(); ++x) matches[x] = walks && sub + x * G < M ? found[sub + x * G] : 0u;
+            lanes_walk<n(), LCAP, edge()>(ix, m.a, u, matches, walks, chosen);
+          };
+          if (wave_ballot(walks && M > 4) == 0) walk(std::integral_constant<int, 4>{}, edge);
+          else if (wave_ballot(walks && M > 8) == 0) walk(std::integral_constant<int, 8>{}, edge);
+          else if (wave_ballot(walks && M > G) == 0) walk(std::integral_constant<int, G>{}, edge);
+          else if (wave_ballot(walks && M > 2 * G) == 0) several(std::integral_constant<int, 2>{});
+          else several(std::integral_constant<int, kLoopMatches / G>{});
         };
         if (m.a.score_mode == 0) weighed(std::false_type{});
         else weighed(std::true_type{});
       }
+      filing.finish();
       n = (int32_t)dpp_move<0x150>((uint32_t)n);
       block_sync<kWave>();                               // the draft's tokens
       const int32_t drafted = draft_all[path][sub < LCAP ? sub : 0];
@@ -318,12 +505,6 @@ void launch_loop_kernel(const LoopArgs& m, hipStream_t st) {
   else if (m.ix.N <= 8) loop_kernel<LCAP, 2, K><<<grid, 2 * kWave, 0, st>>>(m);
   else if (m.ix.N <= 16) loop_kernel<LCAP, 4, K><<<grid, 4 * kWave, 0, st>>>(m);
   else loop_kernel<LCAP, 8, K><<<grid, 8 * kWave, 0, st>>>(m);
-}
-template <int LCAP>
-void launch_loop_steps(const LoopArgs& m, hipStream_t st) {
-  if (m.ix.kmax == 2) launch_loop_kernel<LCAP, 2>(m, st);
-  else if (m.ix.kmax == 3) launch_loop_kernel<LCAP, 3>(m, st);
-  else launch_loop_kernel<LCAP, 4>(m, st);
 }
 
 }  // namespace csd

@@ -14,8 +14,10 @@ void launch_loop(const LoopArgs& m, const int32_t* future_tok, const float* futu
   const int32_t row_groups = rows < most ? rows : most;
   loop_fill_kernel<<<(uint32_t)(row_groups * chunks), 256, 0, st>>>(m.ix, future_tok, future_prob, ahead, chunks, row_groups);
   if (hipPeekAtLastError() != hipSuccess) return;        // (the caller sees it: no steps on histories that were not filled)
-  if (m.a.L <= 8) launch_loop_steps<8>(m, st);
-  else launch_loop_long(m, st);
+  if (m.a.L > 8) launch_loop_long(m, st);
+  else if (m.ix.kmax == 2) launch_loop_kernel<8, 2>(m, st);
+  else if (m.ix.kmax == 3) launch_loop_kernel<8, 3>(m, st);
+  else launch_loop_kernel<8, 4>(m, st);
 }
 
 }  // namespace csd

@@ -4,6 +4,10 @@
 
 namespace csd {
 
-void launch_loop_long(const LoopArgs& m, hipStream_t st) { launch_loop_steps<16>(m, st); }
+void launch_loop_long(const LoopArgs& m, hipStream_t st) {
+  if (m.ix.kmax == 4) launch_loop_long_four(m, st);
+  else if (m.ix.kmax == 3) launch_loop_kernel<16, 3>(m, st);
+  else launch_loop_long_two(m, st);
+}
 
 }  // namespace csd

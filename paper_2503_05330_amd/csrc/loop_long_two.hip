@@ -1,0 +1,10 @@
+// csd — launches of the accept-driven loop with all its steps in one launch: drafts of more than eight
+// tokens, queries of two (compiled beside the others).
+#include "csd_launch.h"
+#include "csd_loop.cuh"
+
+namespace csd {
+
+void launch_loop_long_two(const LoopArgs& m, hipStream_t st) { launch_loop_kernel<16, 2>(m, st); }
+
+}  // namespace csd

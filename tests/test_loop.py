@@ -16,6 +16,11 @@ def _inputs(kind, P, N, T, rng):
         order = rng.integers(0, 24, (P, N, -(-T // 12)))
         tok = np.concatenate([np.stack([phrases[p][order[p, i]].reshape(-1)[:T] for i in range(N)])[None] for p in range(P)])
         tok = np.where(rng.random((P, N, T)) < 0.05, rng.integers(0, 500, (P, N, T)), tok)
+    elif kind.startswith("agree"):                         # paths agree, each gram so many times in each of them
+        period = -(-T // int(kind[5:]))
+        tok = np.broadcast_to(rng.integers(0, 500, (P, 1, period)), (P, N, period))
+        tok = np.tile(tok, (1, 1, int(kind[5:])))[:, :, :T]
+        tok = np.where(rng.random((P, N, T)) < 0.03, rng.integers(0, 500, (P, N, T)), tok)
     elif kind == "constant":                               # thousands of matches
         tok = np.full((P, N, T), 7)
     elif kind == "periodic":                               # each gram many times in a path
@@ -50,12 +55,21 @@ def _run(tok, probs, lens, steps, kmax, L, alpha, mode, per_launch, vocab=600):
 
 @pytest.mark.parametrize("kind,P,N,T,steps,kmax,L", [
     ("phrases", 1, 16, 400, 60, 3, 8), ("phrases", 3, 13, 300, 41, 4, 16), ("phrases", 2, 1, 200, 9, 3, 5),
-    ("phrases", 5, 2, 130, 40, 2, 1), ("phrases", 1, 4, 200, 200, 3, 8), ("phrases", 2, 5, 257, 30, 3, 15),
-    ("phrases", 1, 8, 300, 33, 4, 9), ("phrases", 40, 9, 120, 20, 1, 8), ("constant", 1, 16, 60, 8, 3, 8),
+    ("phrases", 260, 2, 130, 12, 2, 1), ("phrases", 1, 4, 200, 200, 3, 8), ("phrases", 2, 5, 257, 30, 3, 15),
+    ("phrases", 1, 8, 300, 33, 4, 9), ("phrases", 3, 6, 120, 20, 3, 1), ("constant", 1, 16, 60, 8, 3, 8),
     ("periodic", 1, 16, 300, 40, 3, 16), ("periodic", 2, 7, 300, 40, 3, 7), ("symbols", 2, 16, 256, 25, 4, 8),
-    ("symbols", 1, 3, 150, 30, 2, 16), ("phrases", 1, 17, 300, 40, 3, 8), ("phrases", 2, 32, 400, 30, 4, 16),
-    ("periodic", 1, 29, 200, 12, 3, 8), ("phrases", 20, 30, 120, 20, 2, 5)])
+    ("phrases", 1, 17, 300, 40, 3, 8), ("phrases", 64, 32, 200, 12, 4, 16), ("periodic", 64, 29, 120, 8, 3, 8),
+    # queries of two tokens, from 512 rows on
+    ("phrases", 130, 4, 100, 12, 2, 8), ("symbols", 128, 4, 60, 10, 2, 16), ("phrases", 64, 8, 100, 12, 2, 16),
+    ("phrases", 40, 13, 100, 12, 2, 1), ("phrases", 32, 16, 100, 12, 2, 9), ("phrases", 64, 30, 120, 12, 2, 5),
+    # one to four matches a lane, and more: 15, 16 / 17, 32 / 33 .. 36, 60, 64 / 65, 69 matches where all agree
+    ("agree1", 2, 16, 300, 30, 3, 8), ("agree1", 3, 18, 200, 20, 3, 16), ("agree2", 1, 9, 300, 30, 3, 8),
+    ("agree2", 2, 17, 300, 20, 4, 7), ("agree3", 1, 13, 300, 25, 3, 12), ("agree4", 2, 16, 400, 20, 3, 8),
+    ("agree4", 1, 17, 400, 20, 3, 16), ("agree3", 1, 24, 300, 20, 4, 5), ("agree12", 2, 6, 400, 20, 3, 8),
+    ("agree40", 1, 4, 400, 20, 3, 3)])
 def test_one_launch_equals_a_launch_per_step(kind, P, N, T, steps, kmax, L):
+    assert kmax > 2 or P * N >= 512                        # (else both are a launch per step, as with more than 24 paths of few problems)
+    assert N <= 24 or P >= 64
     print("loop", kind, P, N, T, steps, kmax, L, flush=True)
     rng = np.random.default_rng(P * 1000 + N * 10 + L)
     tok, probs = _inputs(kind, P, N, T, rng)
