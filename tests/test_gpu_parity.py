@@ -832,13 +832,13 @@ def test_pool_modes_small_and_degenerate_cases(oracle, pool_mode):
 
 # ---------------------------------------------------------------- the propose / verify / accept loop
 def _accept_loop_case(oracle, w, n_steps, flags, eps=0, pool_mode=0, use_probs=True, warm=None,
-                      min_scratch=False, steps_per_launch=1):
+                      min_scratch=False, steps_per_launch=None):
     tokens, probs = synth.make_paths(w)
     pr = probs if use_probs else None
     dev = torch.device("cuda:0")
     P, N, T, k, L = w.n_problems, w.n_paths, w.max_len, w.query_len, w.draft_len
     ix = binding.Index(P, N, T, w.vocab, k, L, 1.0, 0, flags, device=dev, max_edits=eps, pool_mode=pool_mode)
-    if steps_per_launch > 1:
+    if steps_per_launch is not None:              # (None: all steps in one launch where the loop can)
         ix.set_steps_per_launch(steps_per_launch)
     lens0 = np.zeros((P, N), np.int32)
     if warm is not None:                          # start from ragged, partly filled paths
@@ -851,7 +851,7 @@ def _accept_loop_case(oracle, w, n_steps, flags, eps=0, pool_mode=0, use_probs=T
                          None if pr is None else torch.from_numpy(pr).to(dev), k, L,
                          min_scratch=min_scratch)
     want = oracle.accept_loop(tokens, pr, lens0, k, L, n_steps, eps=eps, pool_mode=pool_mode)
-    what = "%s flags=%d eps=%d pool=%d min_scratch=%d steps_per_launch=%d" % (
+    what = "%s flags=%d eps=%d pool=%d min_scratch=%d steps_per_launch=%s" % (
         w.name, flags, eps, pool_mode, min_scratch, steps_per_launch)
     print("accept loop", what, flush=True)
     assert np.array_equal(got["path_len"].cpu().numpy(), want["path_len"]), what
@@ -869,18 +869,23 @@ def test_accept_loop_diverging_path_lengths(oracle):
         assert want["accept_len"].sum() > 0 and want["path_len"][-1].max() > want["path_len"][-1].min()
         _accept_loop_case(oracle, c1, 120, flags, use_probs=False,
                           warm=np.array([[40, 3, 0, 17]]))
-    # with the minimum of scratch memory the index matcher takes two launches per step
-    _accept_loop_case(oracle, c1, 200, INDEX, min_scratch=True)
-    _accept_loop_case(oracle, c1, 120, INDEX, use_probs=False, warm=np.array([[40, 3, 0, 17]]), min_scratch=True)
-    # longer drafts (the loop's kernels for up to 16 and up to 32 draft tokens), more paths than the
-    # staged step holds (N * (L + 1) > 1024), a query of 4
+    # the index matcher: all steps in one launch, a launch per step, and, with the minimum of scratch memory, two
     c3 = synth.WORKLOADS["C3"]
-    _accept_loop_case(oracle, synth.scaled(c3, max_len=300), 80, INDEX)
-    _accept_loop_case(oracle, synth.scaled(c2, max_len=400, draft_len=16), 100, INDEX)
-    _accept_loop_case(oracle, synth.scaled(c2, n_paths=64, max_len=200, draft_len=32), 60, INDEX)
+    for how in (dict(), dict(min_scratch=True), dict(steps_per_launch=1), dict(steps_per_launch=1, min_scratch=True)):
+        _accept_loop_case(oracle, c1, 200, INDEX, **how)
+        _accept_loop_case(oracle, c1, 120, INDEX, use_probs=False, warm=np.array([[40, 3, 0, 17]]), **how)
+        # longer drafts (the loop's kernels for up to 16 and up to 32 draft tokens), more paths than the
+        # staged step holds (N * (L + 1) > 1024) and than one launch takes, a query of 4, one of 2
+        _accept_loop_case(oracle, synth.scaled(c3, max_len=300), 80, INDEX, **how)
+        _accept_loop_case(oracle, synth.scaled(c3, n_paths=20, max_len=300), 80, INDEX, **how)
+        _accept_loop_case(oracle, synth.scaled(c2, max_len=400, draft_len=16), 100, INDEX, **how)
+        _accept_loop_case(oracle, synth.scaled(c2, max_len=300, query_len=2), 60, INDEX, **how)
+        _accept_loop_case(oracle, synth.scaled(c2, n_paths=64, max_len=200, draft_len=32), 60, INDEX, **how)
+        _accept_loop_case(oracle, c1, 100, INDEX, pool_mode=binding.POOL_TREE, **how)
     _accept_loop_case(oracle, c1, 200, SCAN, eps=1)
     _accept_loop_case(oracle, c1, 200, INDEX, pool_mode=binding.POOL_TREE)
     _accept_loop_case(oracle, c1, 200, SCAN, eps=1, pool_mode=binding.POOL_LIST)
+    _accept_loop_case(oracle, c2, 700, INDEX, steps_per_launch=1)
     want = _accept_loop_case(oracle, c2, 700, INDEX)          # runs every path to its full length
     assert (want["final_len"] == c2.max_len).all()
     _accept_loop_case(oracle, synth.scaled(c4, n_problems=6), 60, INDEX)
