@@ -382,19 +382,25 @@ def main():
     # different numbers of tokens, so their lengths diverge and steps append several tokens
     d_future_tok = torch.from_numpy(r.tokens).to(dev)
     d_future_pr = torch.from_numpy(r.probs).to(dev)
-    r.ix.reset()
-    loop = r.ix.accept_loop(T, d_future_tok, d_future_pr, k, L)               # warm-up
-    torch.cuda.synchronize()
-    loop_us = []
-    for _ in range(5):
-        r.ix.reset()
-        ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def loop_times(ix):
+        """Microseconds per step of five whole loops from an empty index, and the last one's outputs."""
+        ix.reset()
+        out = ix.accept_loop(T, d_future_tok, d_future_pr, k, L)               # warm-up
         torch.cuda.synchronize()
-        ev0.record()
-        loop = r.ix.accept_loop(T, d_future_tok, d_future_pr, k, L, out=loop)
-        ev1.record()
-        torch.cuda.synchronize()
-        loop_us.append(ev0.elapsed_time(ev1) / T * 1e3)
+        by_event = []
+        for _ in range(5):
+            ix.reset()
+            ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            ev0.record()
+            out = ix.accept_loop(T, d_future_tok, d_future_pr, k, L, out=out)
+            ev1.record()
+            torch.cuda.synchronize()
+            by_event.append(ev0.elapsed_time(ev1) / T * 1e3)
+        return by_event, out
+
+    loop_us, loop = loop_times(r.ix)
     path_len = loop["path_len"].cpu().numpy().reshape(T, -1)
     growing = np.concatenate([np.ones((1, path_len.shape[1]), bool), path_len[:-1] < T])
     res["accept_loop"] = {"us_per_step": percentile(loop_us, 0.5),
@@ -402,21 +408,22 @@ def main():
                           "mean_accept_len_while_growing":
                               float(loop["accept"].cpu().numpy().reshape(T, -1)[growing].mean()),
                           "note": "csd_accept_loop over %d steps: draft -> accept against the path's own "
-                                  "future -> append accepted + 1; synthetic stand-in for the model" % T}
+                                  "future -> append accepted + 1; synthetic stand-in for the model; a launch "
+                                  "per step (csd_set_steps_per_launch 1)" % T}
+    # the same as a caller gets it who does not choose: all steps in one launch where the configuration allows it
+    plain_ix = binding.Index(r.P, r.N, T, r.w.vocab, k, L, 1.0, 0, r.flags, device=dev, max_edits=r.max_edits,
+                             pool_mode=POOLS[r.pool])
+    plain_us, plain = loop_times(plain_ix)
+    res["accept_loop_by_default"] = {
+        "us_per_step": percentile(plain_us, 0.5),
+        "equal_to_accept_loop": all(bool(torch.equal(plain[x], loop[x])) for x in ("tokens", "length", "accept", "path_len")),
+        "note": "the same loop without csd_set_steps_per_launch"}
+    del plain_ix, plain
     # the same two host-free loops with the device-side loop (many steps per launch): reported
     # beside the per-launch figures, never instead of them
     r.ix.set_steps_per_launch(1 << 20)
     dev_tail = r.time_tail(K, min(R, 10))
-    dev_loop_us = []
-    for _ in range(5):
-        r.ix.reset()
-        ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        torch.cuda.synchronize()
-        ev0.record()
-        loop = r.ix.accept_loop(T, d_future_tok, d_future_pr, k, L, out=loop)
-        ev1.record()
-        torch.cuda.synchronize()
-        dev_loop_us.append(ev0.elapsed_time(ev1) / T * 1e3)
+    dev_loop_us, _ = loop_times(r.ix)
     r.ix.set_steps_per_launch(1)
     res["device_side_loop"] = {
         "replay_us_per_step_at_full_history": percentile(dev_tail, 0.5),

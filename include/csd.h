@@ -305,7 +305,7 @@ int csd_set_steps_per_launch(csd_index* index, int32_t steps);
  *   The device current at the call must be the one the index's workspace is on.
  *   All calls on one GPU share the array: calls that overlap in time on one GPU (two
  *   streams, two indexes) race; serialise them.  Nothing in the array has to start at
- *   zero: every word is written by the launch before the one that reads it. */
+ *   zero: every call writes the words that it reads, before it reads them. */
 #define CSD_NOALLOC_SCRATCH_BYTES (1u << 20)
 int csd_accept_loop_noalloc(csd_index* index, int32_t n_steps, const int32_t* d_future_tokens,
                             const float* d_future_probs, int32_t query_len, int32_t draft_len,

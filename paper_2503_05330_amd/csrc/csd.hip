@@ -347,7 +347,7 @@ bool multi_step_ok(const csd_index* h) {
 
 // csd_accept_loop in one launch (see loop_kernel).  Queries of two tokens, many of which have more than
 // sixteen matches, only where the rows of a launch per step would not have a CU each (us, 16 paths x
-// 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 753 / 813).  More than 24 paths only from
+// 1024 tokens, 48 steps, a launch per step / one launch: 1 problem 767 / 760, 32 2288 / 1592).  More than 24 paths only from
 // 64 problems on: paths that agree have more matches than a row's lanes take there, and a launch per step
 // has a CU for each row (each gram four times in a path, 24 steps: 32 paths, 1 problem (48 steps), 8, 32, 64
 // 691 / 932, 370 / 392, 457 / 598, 726 / 610; 28 paths, 64 problems 617 / 376).
@@ -916,8 +916,9 @@ int csd_accept_loop_noalloc(csd_index* h, int32_t n_steps, const int32_t* d_futu
   if (!h) return CSD_ERR_INVALID_ARG;
   int rc = check_draft_args(h, query_len, draft_len);
   if (rc != CSD_OK) return rc;
-  // two sets of step buffers (one launch per step); every word of a set is written by the
-  // launch before the one that reads it, so nothing of an earlier call's contents is seen
+  // two sets of step buffers (one launch per step; one launch for all steps uses the first set's
+  // targets); a call writes every word of a set before it reads it, in the launch before or in the
+  // same one behind a barrier, so nothing of an earlier call's contents is seen
   const size_t rows = (size_t)h->view.P * h->view.N;
   const size_t need = 2 * rows * (3 * (size_t)draft_len + 3) * 4;
   if (need > kStaticScratchBytes) return CSD_ERR_SCRATCH_LIMIT;

@@ -847,7 +847,11 @@ __global__ __launch_bounds__(kWave) void replay_wave_kernel(IndexView ix, int32_
 // 1024 problems x 16 paths x 24 steps, 8000 rows left, 4.7 + 68 / 46; 64 problems x 48 steps, 1000 rows,
 // 3.8 + 22.7 / 21; the whole replay where the paths agree in all but 20 %, 5 %, 2 % of their tokens: 1024 problems
 // 157, 315, 374 / 147, 269, 310, 64 problems 46, 73, 81 / 38, 66, 74.  Left to itself the compiler takes 182
-// registers for the three layouts' code, two waves a SIMD: 1024 problems 73 / 68.
+// registers (252, 256 for drafts of up to 16, 32 tokens) for the two layouts' code, two waves a SIMD: 1024
+// problems 73 / 68.  Held to more waves it spills (29, 133, 58 registers; the launches before: none) and is the
+// faster all the same: the whole replay of 1024 problems, paths of few matches, agreeing in all but 5 %, drafts
+// of 8: 280, 318 before, 204, 287 at three waves, 198, 266 at four; of 16: 315, 435 / 280, 378 at two, 272, 340 at
+// three; of 32: 820, 720 / 577, 631 at one, 442, 495 at two.
 // A wave takes many rows, one after the other.  It reads the arguments anew for each (kept over the
 // loop beside the row's own they were spilled, 500 instructions a row), and requests the next row's
 // unit before this one's work (two round trips a row).

@@ -187,8 +187,8 @@ __device__ __forceinline__ void lanes_walk(const IndexView& ix, const DraftArgs&
 // Here a step's chain is the query's bucket, the postings' tokens, the matches' continuations and the
 // walk, in caches that stay warm, and two barriers of the workgroup; the paths' ends and newest tokens
 // are in LDS, the positions that the step itself appends are matched from a list of their hashes
-// there, their postings are stored while the walk goes on, and the outputs of a step behind the next
-// one's barrier.  3.7 us a step (top to bucket 0.45, claims 0.2, look-up 0.8, postings 0.15, walk up to
+// there, their claims travel during the look-up and the walk, and the outputs of a step behind the next
+// one's barrier.  4.1 us a step (top to bucket 0.45, claims 0.2, look-up 0.8, postings 0.15, walk up to
 // 1.7, the wait for the slowest wave's); one wave issues an instruction every 7 cycles here, so the
 // instructions of the chain count.  With a wave per path (step_multi_kernel) the four SIMDs of the one
 // CU had 1500 instructions a row and step to issue, 14 us; with sixteen lanes a path they have four
@@ -198,15 +198,15 @@ __device__ __forceinline__ void lanes_walk(const IndexView& ix, const DraftArgs&
 // wave on the layout of a launch per step, behind a barrier, when the step's postings are in the
 // index: code apart from the steps' (inlined into their loop it spilled their registers, 5.6 us a step).
 // us a call, a launch per step / this (queries of three, drafts of eight, 48 steps): 1 problem of 16 paths
-// x 1024 tokens 352 / 205, of 4 x 256 (24 steps) 152 / 81; 64 problems 531 / 252, 1024 of 16 x 512 (24
-// steps) 2307 / 443; 24 and 32 paths x 1024 395 / 249 and 447 / 310, 64 problems of 32 x 512 (24 steps)
-// 463 / 160.  Paths of different lengths that agree in all but 5 %, 2 % of their tokens: 16 x 1024 456 / 319,
-// 455 / 323, 24 x 1024 481 / 423, 472 / 439.  Each gram twice, four times, six times in each path: 16 x 1024
-// 458 / 359, 474 / 425, 526 / 474, 24 x 1024 503 / 445, 550 / 526, 692 / 1112: where most rows have more than
-// sixty-four matches a few waves (as many as have room for that layout) draft them in turn.  (With sixteen
-// matches and three buckets as the bounds, and the chains of full buckets followed one by one, 16 x 1024
-// with each gram twice, four times took 779, 1019, and 24 x 1024, all but 2 % equal, 737.)  Each gram 64 times in
-// each of 16, 24 paths (24 steps): 2250 / 5270, 5270 / 19900.
+// x 1024 tokens 360 / 208, of 4 x 256 (24 steps) 161 / 81; 64 problems 543 / 253, 1024 of 16 x 512 (24
+// steps) 2319 / 435; 24 paths x 1024 392 / 248, 64 problems of 32 x 512 (24 steps) 463 / 153.  Paths of
+// different lengths that agree in all but 5 %, 2 % of their tokens: 16 x 1024 456 / 319, 455 / 323, 24 x 1024
+// 481 / 423, 472 / 439.  Each gram twice, four times, six times in each path: 16 x 1024 458 / 359, 474 / 425,
+// 526 / 474, 24 x 1024 503 / 445, 550 / 526, 692 / 1112; 64 times (24 steps) 16, 24 x 1024 2250 / 5270,
+// 5270 / 19900: where most rows have more than sixty-four matches a few waves (as many as have room for that
+// layout) draft them in turn.  (With sixteen matches and three buckets as the bounds, and the chains of full
+// buckets followed one by one, 16 x 1024 with each gram twice, four times took 779, 1019, and 24 x 1024, all but
+// 2 % equal, 737.)
 // Exact matching through the index, DAG pool, queries of kmax = K tokens.
 template <int LCAP, int WAVES, int K>
 __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
