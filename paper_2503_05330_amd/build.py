@@ -49,7 +49,7 @@ def timing_source() -> str:
 
 
 def build_timing_library(path: str, flags=("-shared",)) -> str:
-    """The library with the clock stamps in its kernels (some minutes: one source)."""
+    """The library with the clock stamps in its kernels (a quarter of an hour: one source)."""
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     with tempfile.TemporaryDirectory() as tmp:
         source = os.path.join(tmp, "timing.hip")

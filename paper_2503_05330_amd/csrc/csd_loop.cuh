@@ -498,6 +498,9 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   if (flags) atomicOr(ix.status, flags);
 }
 
+// As many waves as the paths need, since the LDS of four has room for one workgroup a CU.  us, this / four
+// waves up to sixteen paths (24 steps): 1024 problems of 4 x 256 110 / 318, 1024 of 8 x 256 202 / 359, 64 of
+// 8 x 512 104 / 103, 1 of 4 x 256 82 / 85.
 template <int LCAP, int K>
 void launch_loop_kernel(const LoopArgs& m, hipStream_t st) {
   const uint32_t grid = (uint32_t)m.ix.P;
