@@ -420,6 +420,10 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
 // paths' ends in v.meta_new (may be v.meta_old), and all their drafts.
 void launch_replay_steps(const csd_index* h, const IndexView& v, const ReplayIn& in, const DraftArgs& a,
                          hipStream_t st) {
+  if (const int32_t shares = h->done && (int64_t)v.P * v.N <= kSplitRows ? replay_staged_shares(v, in.steps, a) : 0) {
+    launch_replay_staged(v, in, shares, a, h->step_meta, h->done, h->rest_list, st);
+    return;
+  }
   const bool q4 = v.kmax <= 4;
   // whole paths per workgroup: as many as its threads have steps for, at most 16 (a line of
   // tokens per step) and no more than there are (16 paths x 64 steps as one workgroup of 1024
@@ -488,7 +492,8 @@ static int reset(csd_index* h, bool created, void* stream) {
   if (blocks > 4096) blocks = 4096;
   reset_kernel<<<(uint32_t)blocks, 256, 0, as_stream(stream)>>>(view_in_place(h),
                                                                  (int64_t)h->gram_words, h->slices,
-                                                                 created ? h->done : nullptr);
+                                                                 created ? h->done : nullptr,
+                                                                 created && h->replay_steps > 0 ? h->rest_list : nullptr);
   CSD_HIP(hipGetLastError());
   h->len_lo = h->len_hi = 0;
   return CSD_OK;

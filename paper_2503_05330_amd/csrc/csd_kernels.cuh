@@ -16,8 +16,9 @@ namespace csd {
 // with one each.
 constexpr int64_t kSplitRows = 1 << 16;
 
+// done (see append_kernel), counters (see RestList): null unless the handle is new.
 static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t gram_words, ScanSlices sl,
-                                                           int32_t* done) {
+                                                           int32_t* done, int32_t* counters) {
   int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int64_t stride = (int64_t)gridDim.x * 256;
   int64_t rows = (int64_t)ix.P * ix.N;
@@ -26,6 +27,8 @@ static __global__ __launch_bounds__(256) void reset_kernel(IndexView ix, int64_t
   for (int64_t r = t; r < rows * ix.meta_stride; r += stride) ix.meta_new[r] = 0;
   if (done)
     for (int64_t r = t; r < rows && r < kSplitRows; r += stride) done[r * kBucketWords] = 0;
+  if (counters)
+    for (int64_t w = t; w < RestList::kCounters; w += stride) counters[w] = 0;
   for (int64_t w = t; w < gram_words; w += stride) ix.gram[w] = (w & (kBucketWords - 1)) ? -1 : 0;
   if (t == 0) *ix.status = 0u;
 }
@@ -907,7 +910,14 @@ void replay_rest_kernel(RestArgs) {
     few = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, false));
     many = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, true));
   }
-  if (few + many == 0) return;
+  if (few + many == 0) return;                           // (the same in all workgroups of the XCD)
+  if (threadIdx.x == 0) {
+    const RestList list = rest_arguments().list;
+    if (list.readers) {
+      int32_t* readers = list.readers + (blockIdx.x & 7) * kBucketWords;
+      if (atomicAdd(readers, 1) == (int32_t)(gridDim.x >> 3) - 1) *readers = *list.count(blockIdx.x & 7, false) = *list.count(blockIdx.x & 7, true) = 0;
+    }
+  }
   // (a row of the large layout takes the room of four; the large ones are spread over the workgroups'
   // numbers, so that those under way first are of both kinds)
   int32_t groups = 2 * kRestTurn, large = 0, before = 0;

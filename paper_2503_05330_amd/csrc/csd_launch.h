@@ -35,6 +35,13 @@ void launch_loop_long_four(const LoopArgs& m, hipStream_t st);   // ... and four
 void launch_multi(const IndexView& v, const MultiArgs& m, bool general, hipStream_t st);
 void launch_multi_loop(const IndexView& v, const MultiArgs& m, hipStream_t st);
 
+// a replay of many small problems, append and drafts in one launch: workgroups per problem (0: not to be launched
+// so), and the launch
+int32_t replay_staged_shares(const IndexView& v, int32_t steps, const DraftArgs& a);
+void launch_replay_staged(const IndexView& v, const ReplayIn& in, int32_t shares, const DraftArgs& a, int32_t* step_meta,
+                          int32_t* done, int32_t* rest_list, hipStream_t st);
+void launch_replay_rest(const RestArgs& args, hipStream_t st);   // the rows left to a wave each
+
 // a replay, all steps side by side (v.meta_old: the paths' ends after every step, see
 // replay_append_kernel; a: the outputs of the first step): exact matching through the index /
 // with the tree and list pools, own history, back-off / one edit through the index / by scan

@@ -47,141 +47,6 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
   return *(const LoopArgs*)kernarg;
 }
 
-// Files the new position of each lane (see file_positions) in three parts: the claims on the first buckets
-// of the chains, the fill counts of the next four where those were full, and the claims there.  What lies
-// between them, the look-up and the walk, has their round trips.
-template <int K>
-struct Filing {
-  static constexpr int kAhead = 4;
-  int32_t* gram;
-  uint32_t mask;
-  GramHash gh;
-  int32_t pos, claimed;
-  bool open;                    // no slot yet
-  int32_t fill[kAhead];
-  __device__ __forceinline__ void look(uint32_t r) {
-    if (!open) return;
-#pragma unroll
-    for (int x = 0; x < kAhead; ++x)
-      fill[x] = __hip_atomic_load(gram_bucket(gram, gh, r + x, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  __device__ __forceinline__ void claim(int32_t* table, uint32_t bucket_mask, const int32_t (&G)[K], bool mine, int32_t packed) {
-    gram = table;
-    mask = bucket_mask;
-    gh = gram_hash_of(G, K);
-    pos = packed;
-    open = mine;
-    claimed = kBucketSlots;
-    if (mine) claimed = atomicAdd(gram_bucket(gram, gh, 0, mask), 1);
-  }
-  __device__ __forceinline__ void settle() {
-    if (claimed < kBucketSlots) {
-      gram_bucket(gram, gh, 0, mask)[1 + claimed] = pos;
-      open = false;
-    }
-    if (wave_ballot(open) != 0) look(1);
-  }
-  __device__ __forceinline__ void finish() {             // (what finds no slot in a full index is dropped)
-    for (uint32_t r = 1; r <= mask && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
-      if (r > 1) look(r);
-      uint32_t room = 0;
-#pragma unroll
-      for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x <= mask ? 1u << x : 0u;
-      while (wave_ballot(room != 0) != 0) {
-        if (room != 0) {
-          int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, mask);
-          const int32_t c = atomicAdd(b, 1);
-          if (c < kBucketSlots) b[1 + c] = pos;
-          open = c >= kBucketSlots;
-          room = open ? room & (room - 1u) : 0u;
-        }
-      }
-    }
-  }
-};
-
-// group_walk for rows of seventeen to sixty-four matches, S of them a lane of the sixteen: in each layer the
-// tokens that follow the last choice are taken up one after the other, the lowest first, each with what all
-// lanes have of it, until those left could not outweigh the heaviest together.  (Every lane against every other, as there, is 4 S times the exchanges of sixteen
-// matches; here it is as many rounds as there are different tokens, few where the paths agree.)
-template <int S, int LCAP, bool EDGE, class CHOSEN>
-__device__ __forceinline__ void lanes_walk(const IndexView& ix, const DraftArgs& a, const UnitRow& u,
-                                           const uint32_t (&match)[S], bool going, CHOSEN&& chosen) {
-  constexpr int kCount = 24;                             // count (<= 64) above the probability sum (<= 2^22)
-  static_assert(S <= 4, "the sums of a layer in one word");
-  int32_t v[S][LCAP], pr[S][LCAP];
-#pragma unroll
-  for (int x = 0; x < S; ++x) {
-    const int32_t pos = (int32_t)(match[x] & ((1u << 25) - 1u));
-    const int32_t cell = (int32_t)__umul24((uint32_t)(pos >> ix.eshift), (uint32_t)ix.max_len) +
-                         (pos & ((1 << ix.eshift) - 1));
-#pragma unroll
-    for (int d = 0; d < LCAP; d += 4) {
-      const Run4 r = *reinterpret_cast<const Run4*>(u.tok + cell + d);
-      const Run4 s = *reinterpret_cast<const Run4*>(u.pq + cell + d);
-#pragma unroll
-      for (int z = 0; z < 4; ++z) {
-        v[x][d + z] = r.x[z];
-        pr[x][d + z] = s.x[z];
-      }
-    }
-  }
-#pragma unroll
-  for (int x = 0; x < S; ++x)
-#pragma unroll
-    for (int d = 0; d < LCAP; ++d) {
-      consume_here(v[x][d]);
-      consume_here(pr[x][d]);
-    }
-  int32_t cur = 0;
-  static_for<1, LCAP + 1>([&](auto layer) {
-    constexpr int d = layer();
-    if (wave_ballot(going) == 0) return;                 // uniform over the wave; so from the layer behind L on
-    uint32_t own[S];
-    int32_t left[S];                                     // successors of the last choice that are still to be taken up
-#pragma unroll
-    for (int x = 0; x < S; ++x) {
-      const bool alive = d <= (int32_t)(match[x] >> 25);
-      const bool from_cur = alive && going && (d == 1 || v[x][d > 1 ? d - 2 : 0] == cur);
-      own[x] = (EDGE ? from_cur : alive) ? (1u << kCount) + (uint32_t)pr[x][d - 1] : 0u;
-      left[x] = from_cur ? v[x][d - 1] : INT_MAX;
-    }
-    uint32_t rest = 0;                                   // what the layer's tokens that are not taken up yet have in all
-#pragma unroll
-    for (int x = 0; x < S; ++x) rest += own[x];
-    auto weight = [&](uint32_t cs) { return weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q); };
-    auto lowest_and_sum = [&](uint32_t& sum) {
-      int32_t token = left[0];
-#pragma unroll
-      for (int x = 1; x < S; ++x) token = left[x] < token ? left[x] : token;
-      group_stages<kLoopLanes>([&](auto other) {
-        const int32_t theirs = (int32_t)other((uint32_t)token);
-        token = theirs < token ? theirs : token;
-        sum += other(sum);                               // (each stage brings other lanes' sums)
-      });
-      return token;
-    };
-    int32_t token = lowest_and_sum(rest);
-    Cand best = cand_none();
-    while (wave_ballot(token != INT_MAX && (best.v == INT_MAX || weight(rest) > best.key)) != 0) {   // uniform over the wave
-      uint32_t cs = 0;
-#pragma unroll
-      for (int x = 0; x < S; ++x) {
-        cs += v[x][d - 1] == token ? own[x] : 0u;
-        left[x] = left[x] == token ? INT_MAX : left[x];
-      }
-      const int32_t next = lowest_and_sum(cs);
-      const u64 key = weight(cs);
-      if (token != INT_MAX && (best.v == INT_MAX || key > best.key)) best = Cand{key, token};
-      rest -= token != INT_MAX ? cs : 0u;
-      token = next;
-    }
-    going = going && best.v != INT_MAX;                  // else a leaf: no edge leaves cur
-    cur = best.v;
-    chosen(layer, going, best);
-  });
-}
-
 // The steps of csd_accept_loop, one after the other.  A launch per step is bound by its latency:
 // dispatch, then three round trips on caches that are cold at every launch, 6.6 us at 16 x 1024.
 // Here a step's chain is the query's bucket, the postings' tokens, the matches' continuations and the
@@ -404,7 +269,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
         }
       };
       Filing<K> filing;
-      filing.claim(gram, ix.bucket_mask, G0, filed(sub), packed(sub));
+      filing.claim(gram, ix.bucket_mask, K, G0, filed(sub), packed(sub));
       look_up();
       filing.settle();
       if (LCAP >= G && wave_ballot(sub + G < cnt) != 0) {
@@ -423,13 +288,19 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
           if (sub == 0) draft_all[path][layer() - 1] = best.v;
           n = going ? layer() : n;
         };
-        auto walk = [&](auto lanes, auto edge) { group_walk<lanes(), LCAP, edge()>(ix, m.a, u, match, walks, chosen); };
+        auto walk = [&](auto lanes, auto edge) {
+          int32_t v[1][LCAP], pr[1][LCAP];
+          read_windows<LCAP, 1>(ix, u, {match}, v, pr);
+          group_walk<lanes(), LCAP, edge()>(m.a, match, v[0], pr[0], walks, chosen);
+        };
         auto weighed = [&](auto edge) {
           auto several = [&](auto n) {                   // matches a lane
             uint32_t matches[n()];
 #pragma unroll
             for (int x = 0; x < n(); ++x) matches[x] = walks && sub + x * G < M ? found[sub + x * G] : 0u;
-            lanes_walk<n(), LCAP, edge()>(ix, m.a, u, matches, walks, chosen);
+            int32_t v[n()][LCAP], pr[n()][LCAP];
+            read_windows<LCAP, n()>(ix, u, matches, v, pr);
+            lanes_walk<n(), LCAP, edge()>(m.a, matches, v, pr, walks, chosen);
           };
           if (wave_ballot(walks && M > 4) == 0) walk(std::integral_constant<int, 4>{}, edge);
           else if (wave_ballot(walks && M > 8) == 0) walk(std::integral_constant<int, 8>{}, edge);

@@ -18,7 +18,7 @@ __device__ __forceinline__ uint32_t dpp_move(uint32_t x) {
 // that a rotation by R brings here
 template <int G, int R>
 __device__ __forceinline__ uint32_t group_other(uint32_t x) {
-  static_assert((G == 4 || G == 8 || G == 16) && R >= 1 && R < G, "a quad, half a DPP row or a whole one");
+  static_assert((G == 2 || G == 4 || G == 8 || G == 16) && R >= 1 && R < G, "a pair, a quad, half a DPP row or a whole one");
   if constexpr (G == 16) return dpp_move<0x120 + R>(x);
   constexpr int kFlip = R < 4 ? R : 7 - R;               // within a quad; R >= 4: behind the half row's mirror (^ 7)
   constexpr int kQuad = kFlip == 1 ? 0xB1 : kFlip == 2 ? 0x4E : 0x1B;
@@ -34,7 +34,7 @@ struct DppMove {
 template <int G, class F>
 __device__ __forceinline__ void group_stages(F&& f) {
   f(DppMove<0xB1>{});                                    // lane ^ 1
-  f(DppMove<0x4E>{});                                    // ^ 2
+  if constexpr (G >= 4) f(DppMove<0x4E>{});              // ^ 2
   if constexpr (G >= 8) f(DppMove<0x141>{});             // the half row's mirror
   if constexpr (G >= 16) f(DppMove<0x140>{});            // the row's
 }
@@ -82,6 +82,59 @@ __device__ __forceinline__ GramHash gram_hash_of(const int32_t (&Q)[QC], int32_t
   return gram_hash_end(acc, kmax);
 }
 
+// Files the new position of each lane (see file_positions) in three parts: the claims on the first buckets
+// of the chains, the fill counts of the next four where those were full, and the claims there.  What lies
+// between them (the look-up and the walk of a loop's step) has their round trips.  K: compile-time bound of kmax.
+template <int K>
+struct Filing {
+  static constexpr int kAhead = 4;
+  int32_t* gram = nullptr;
+  uint32_t mask = 0;
+  GramHash gh{0u, 1u};
+  int32_t pos = 0, claimed = kBucketSlots;
+  bool open = false;            // no slot yet
+  int32_t fill[kAhead];
+  __device__ __forceinline__ void look(uint32_t r) {
+    if (!open) return;
+#pragma unroll
+    for (int x = 0; x < kAhead; ++x)
+      fill[x] = __hip_atomic_load(gram_bucket(gram, gh, r + x, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ void claim(int32_t* table, uint32_t bucket_mask, int32_t kmax, const int32_t (&G)[K], bool mine, int32_t packed) {
+    gram = table;
+    mask = bucket_mask;
+    gh = gram_hash_of(G, kmax);
+    pos = packed;
+    open = mine;
+    claimed = kBucketSlots;
+    if (mine) claimed = atomicAdd(gram_bucket(gram, gh, 0, mask), 1);
+  }
+  __device__ __forceinline__ void settle() {
+    if (claimed < kBucketSlots) {
+      gram_bucket(gram, gh, 0, mask)[1 + claimed] = pos;
+      open = false;
+    }
+    if (wave_ballot(open) != 0) look(1);
+  }
+  __device__ __forceinline__ void finish() {             // (what finds no slot in a full index is dropped)
+    for (uint32_t r = 1; r <= mask && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
+      if (r > 1) look(r);
+      uint32_t room = 0;
+#pragma unroll
+      for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x <= mask ? 1u << x : 0u;
+      while (wave_ballot(room != 0) != 0) {
+        if (room != 0) {
+          int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, mask);
+          const int32_t c = atomicAdd(b, 1);
+          if (c < kBucketSlots) b[1 + c] = pos;
+          open = c >= kBucketSlots;
+          room = open ? room & (room - 1u) : 0u;
+        }
+      }
+    }
+  }
+};
+
 // A posting of a bucket: what it takes to verify it, loaded without a branch (an idle one reads the
 // problem's first cell).
 template <int QC>
@@ -120,19 +173,13 @@ struct Posting {
   }
 };
 
-// The greedy walk of a row from its matches, one per lane of its group (`match`: as packed above; 0:
-// none): continuations into registers, then layer by layer Eq. 5's sums and the greedy rule (as in
-// walk_instances) by exchanges within the group.  going: the same in a group's lanes.
-// EDGE: edges are weighed, not nodes (score_mode 1; asked at every exchange of every layer it was a
-// branch each).  chosen(layer, going, best): the layer's choice, where going.
-template <int G, int LCAP, bool EDGE, class CHOSEN>
-__device__ __forceinline__ void group_walk(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
-                                           bool going, CHOSEN&& chosen) {
-  constexpr int kCount = 24;                             // count (<= 16) above the probability sum (<= 2^20)
-  const int32_t rem = (int32_t)(match >> 25);            // (at most L)
-  int32_t v[LCAP], pr[LCAP];
-  {
-    const int32_t pos = (int32_t)(match & ((1u << 25) - 1u));
+// The continuations of S matches (as packed above; 0: none) from the problem's histories in memory.
+template <int LCAP, int S>
+__device__ __forceinline__ void read_windows(const IndexView& ix, const UnitRow& u, const uint32_t (&match)[S],
+                                             int32_t (&v)[S][LCAP], int32_t (&pr)[S][LCAP]) {
+#pragma unroll
+  for (int x = 0; x < S; ++x) {
+    const int32_t pos = (int32_t)(match[x] & ((1u << 25) - 1u));
     const int32_t cell = (int32_t)__umul24((uint32_t)(pos >> ix.eshift), (uint32_t)ix.max_len) +
                          (pos & ((1 << ix.eshift) - 1));
 #pragma unroll
@@ -141,16 +188,30 @@ __device__ __forceinline__ void group_walk(const IndexView& ix, const DraftArgs&
       const Run4 s = *reinterpret_cast<const Run4*>(u.pq + cell + d);
 #pragma unroll
       for (int z = 0; z < 4; ++z) {
-        v[d + z] = r.x[z];
-        pr[d + z] = s.x[z];
+        v[x][d + z] = r.x[z];
+        pr[x][d + z] = s.x[z];
       }
     }
   }
 #pragma unroll
-  for (int d = 0; d < LCAP; ++d) {
-    consume_here(v[d]);
-    consume_here(pr[d]);
-  }
+  for (int x = 0; x < S; ++x)
+#pragma unroll
+    for (int d = 0; d < LCAP; ++d) {
+      consume_here(v[x][d]);
+      consume_here(pr[x][d]);
+    }
+}
+
+// The greedy walk of a row from its matches, one per lane of its group (`match`: as packed above; 0:
+// none; v, pr: its continuation): layer by layer Eq. 5's sums and the greedy rule (as in
+// walk_instances) by exchanges within the group.  going: the same in a group's lanes.
+// EDGE: edges are weighed, not nodes (score_mode 1; asked at every exchange of every layer it was a
+// branch each).  chosen(layer, going, best): the layer's choice, where going.
+template <int G, int LCAP, bool EDGE, class CHOSEN>
+__device__ __forceinline__ void group_walk(const DraftArgs& a, uint32_t match, const int32_t (&v)[LCAP],
+                                           const int32_t (&pr)[LCAP], bool going, CHOSEN&& chosen) {
+  constexpr int kCount = 24;                             // count (<= 16) above the probability sum (<= 2^20)
+  const int32_t rem = (int32_t)(match >> 25);            // (at most L)
   int32_t cur = 0;
   static_for<1, LCAP + 1>([&](auto layer) {
     constexpr int d = layer();
@@ -192,51 +253,127 @@ __device__ __forceinline__ void group_walk(const IndexView& ix, const DraftArgs&
   });
 }
 
-// The row's draft, and its outputs for the rows with `write`.
+// group_walk for rows of seventeen to sixty-four matches, S of them a lane of the sixteen: in each layer the
+// tokens that follow the last choice are taken up one after the other, the lowest first, each with what all
+// lanes have of it, until those left could not outweigh the heaviest together.  (Every lane against every other, as there, is 4 S times the exchanges of sixteen
+// matches; here it is as many rounds as there are different tokens, few where the paths agree.)
+template <int S, int LCAP, bool EDGE, class CHOSEN>
+__device__ __forceinline__ void lanes_walk(const DraftArgs& a, const uint32_t (&match)[S], const int32_t (&v)[S][LCAP],
+                                           const int32_t (&pr)[S][LCAP], bool going, CHOSEN&& chosen) {
+  constexpr int kCount = 24;                             // count (<= 64) above the probability sum (<= 2^22)
+  static_assert(S <= 4, "the sums of a layer in one word");
+  int32_t cur = 0;
+  static_for<1, LCAP + 1>([&](auto layer) {
+    constexpr int d = layer();
+    if (wave_ballot(going) == 0) return;                 // uniform over the wave; so from the layer behind L on
+    uint32_t own[S];
+    int32_t left[S];                                     // successors of the last choice that are still to be taken up
+#pragma unroll
+    for (int x = 0; x < S; ++x) {
+      const bool alive = d <= (int32_t)(match[x] >> 25);
+      const bool from_cur = alive && going && (d == 1 || v[x][d > 1 ? d - 2 : 0] == cur);
+      own[x] = (EDGE ? from_cur : alive) ? (1u << kCount) + (uint32_t)pr[x][d - 1] : 0u;
+      left[x] = from_cur ? v[x][d - 1] : INT_MAX;
+    }
+    uint32_t rest = 0;                                   // what the layer's tokens that are not taken up yet have in all
+#pragma unroll
+    for (int x = 0; x < S; ++x) rest += own[x];
+    auto weight = [&](uint32_t cs) { return weight_key(pack_cs(cs >> kCount, cs & ((1u << kCount) - 1u)), a.alpha_q); };
+    auto lowest_and_sum = [&](uint32_t& sum) {
+      int32_t token = left[0];
+#pragma unroll
+      for (int x = 1; x < S; ++x) token = left[x] < token ? left[x] : token;
+      group_stages<16>([&](auto other) {
+        const int32_t theirs = (int32_t)other((uint32_t)token);
+        token = theirs < token ? theirs : token;
+        sum += other(sum);                               // (each stage brings other lanes' sums)
+      });
+      return token;
+    };
+    int32_t token = lowest_and_sum(rest);
+    Cand best = cand_none();
+    while (wave_ballot(token != INT_MAX && (best.v == INT_MAX || weight(rest) > best.key)) != 0) {   // uniform over the wave
+      uint32_t cs = 0;
+#pragma unroll
+      for (int x = 0; x < S; ++x) {
+        cs += v[x][d - 1] == token ? own[x] : 0u;
+        left[x] = left[x] == token ? INT_MAX : left[x];
+      }
+      const int32_t next = lowest_and_sum(cs);
+      const u64 key = weight(cs);
+      if (token != INT_MAX && (best.v == INT_MAX || key > best.key)) best = Cand{key, token};
+      rest -= token != INT_MAX ? cs : 0u;
+      token = next;
+    }
+    going = going && best.v != INT_MAX;                  // else a leaf: no edge leaves cur
+    cur = best.v;
+    chosen(layer, going, best);
+  });
+}
+
+// A draft as a group of lanes has it: lane `sub` keeps the choices of the layers sub * kKept + 1 and on.
+template <int G, int LCAP>
+struct GroupDraft {
+  static constexpr int kKept = (LCAP + G - 1) / G;
+  int32_t tok[kKept], n = 0;
+  u64 key[kKept], key_sum = 0;
+  __device__ __forceinline__ GroupDraft() {
+#pragma unroll
+    for (int x = 0; x < kKept; ++x) {
+      tok[x] = -1;
+      key[x] = 0;
+    }
+  }
+  __device__ __forceinline__ void choose(int32_t d, bool going, const Cand& best, int sub) {
+    n = going ? d : n;
+    key_sum += going ? best.key : 0ull;
+#pragma unroll
+    for (int x = 0; x < kKept; ++x) {
+      const bool keep = going && sub * kKept + x == d - 1;
+      tok[x] = keep ? best.v : tok[x];
+      key[x] = keep ? best.key : key[x];
+    }
+  }
+  // the outputs of the rows with `write` (n and key_sum: of the group's first lane)
+  __device__ __forceinline__ void store(const DraftArgs& a, int64_t row, bool write, int sub, const int32_t (&target)[kKept]) const {
+    const int32_t L = a.L;
+    int32_t same = 0;                                    // of this lane's layers, from its first on
+    bool all = true;
+#pragma unroll
+    for (int x = 0; x < kKept; ++x) {
+      const int32_t d = sub * kKept + x;
+      all = all && d < n && target[x] == tok[x];
+      same += all ? 1 : 0;
+      if (write && d < L) {
+        a.draft_tokens[row * L + d] = tok[x];
+        if (a.token_scores) a.token_scores[row * L + d] = key_to_score(key[x]);
+      }
+    }
+    if (a.targets) {                                     // the first layer that differs
+      uint32_t stop = all ? (uint32_t)LCAP : (uint32_t)(sub * kKept + same);
+      group_stages<G>([&](auto move) {
+        const uint32_t other = move(stop);
+        stop = other < stop ? other : stop;
+      });
+      if (write && sub == 0) a.accept_len[row] = (int32_t)stop < n ? (int32_t)stop : n;
+    }
+    if (write && sub == 0) {
+      a.draft_len[row] = n;
+      if (a.path_scores) a.path_scores[row] = key_to_score(key_sum);
+    }
+  }
+};
+
+// The draft of a row whose matches, one a lane, are in the histories in memory, and its outputs.
 template <int G, int LCAP, bool EDGE>
 __device__ __forceinline__ void group_draft(const IndexView& ix, const DraftArgs& a, const UnitRow& u, uint32_t match,
                                             bool write, int sub, const int32_t (&target)[(LCAP + G - 1) / G]) {
-  constexpr int kKept = (LCAP + G - 1) / G;              // layers whose choice a lane keeps and writes
-  const int32_t L = a.L;
-  int32_t kept_tok[kKept], n = 0;
-  u64 kept_key[kKept], key_sum = 0;
-#pragma unroll
-  for (int x = 0; x < kKept; ++x) {
-    kept_tok[x] = -1;
-    kept_key[x] = 0;
-  }
-  group_walk<G, LCAP, EDGE>(ix, a, u, match, write, [&](auto layer, bool going, const Cand& best) {
-    constexpr int d = layer();
-    n = going ? d : n;
-    key_sum += going ? best.key : 0ull;
-    const bool keep = going && sub == (d - 1) / kKept;
-    kept_tok[(d - 1) % kKept] = keep ? best.v : kept_tok[(d - 1) % kKept];
-    kept_key[(d - 1) % kKept] = keep ? best.key : kept_key[(d - 1) % kKept];
-  });
-  int32_t same = 0;                                      // of this lane's layers, from its first on
-  bool all = true;
-#pragma unroll
-  for (int x = 0; x < kKept; ++x) {
-    const int32_t d = sub * kKept + x;
-    all = all && d < n && target[x] == kept_tok[x];
-    same += all ? 1 : 0;
-    if (write && d < L) {
-      a.draft_tokens[(int64_t)u.row * L + d] = kept_tok[x];
-      if (a.token_scores) a.token_scores[(int64_t)u.row * L + d] = key_to_score(kept_key[x]);
-    }
-  }
-  if (a.targets) {                                       // the first layer that differs
-    uint32_t stop = all ? (uint32_t)LCAP : (uint32_t)(sub * kKept + same);
-    group_stages<G>([&](auto move) {
-      const uint32_t other = move(stop);
-      stop = other < stop ? other : stop;
-    });
-    if (write && sub == 0) a.accept_len[u.row] = (int32_t)stop < n ? (int32_t)stop : n;
-  }
-  if (write && sub == 0) {
-    a.draft_len[u.row] = n;
-    if (a.path_scores) a.path_scores[u.row] = key_to_score(key_sum);
-  }
+  int32_t v[1][LCAP], pr[1][LCAP];
+  read_windows<LCAP, 1>(ix, u, {match}, v, pr);
+  GroupDraft<G, LCAP> draft;
+  group_walk<G, LCAP, EDGE>(a, match, v[0], pr[0], write,
+                            [&](auto layer, bool going, const Cand& best) { draft.choose(layer(), going, best, sub); });
+  draft.store(a, u.row, write, sub, target);
 }
 
 // The targets of the layers that this lane keeps.
@@ -315,14 +452,24 @@ __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t 
 }
 
 // Rows for the kernels with a wave per row: a list per XCD, of the units that it has drafted from its
-// L2 already, the rows with few matches from the front on, the others from the back.
+// L2 already, the rows with few matches from the front on, the others from the back (of a staged replay, which
+// lists only those, from the front: the last XCD's part may be larger than its rows).
 struct RestList {
-  static constexpr int kCounters = 16 * kBucketWords;    // a line for each (an atomic takes one 12 ns)
-  int32_t* words;               // the counters, then [8][capacity] units
+  static constexpr int kSet = 16 * kBucketWords;         // a counter for each list, a line apart (an atomic takes one 12 ns)
+  static constexpr int kCounters = 2 * kSet + 8 * kBucketWords;
+  int32_t* counts;              // zeroed by the launch before the one that lists
+  int32_t* units;               // [8][capacity]
   int32_t capacity;             // units of an XCD
-  __device__ __forceinline__ int32_t* count(uint32_t xcd, bool many) const { return words + (2 * xcd + many) * kBucketWords; }
+  int32_t* readers;             // or null.  A line for each XCD: workgroups that have read its counters, of which
+                                //   the last zeroes them and this, for the next launch that lists
+  // words: of the workspace, all counters and then the units.  staged: the second set of counters, which nobody
+  // zeroes beforehand
+  static RestList in(int32_t* words, bool staged, int32_t capacity) {
+    return RestList{words + (staged ? kSet : 0), words + kCounters, capacity, staged ? words + 2 * kSet : nullptr};
+  }
+  __device__ __forceinline__ int32_t* count(uint32_t xcd, bool many) const { return counts + (2 * xcd + many) * kBucketWords; }
   __device__ __forceinline__ int32_t* unit(uint32_t xcd, bool many, int32_t nth) const {
-    return words + kCounters + (int32_t)xcd * capacity + (many ? capacity - 1 - nth : nth);
+    return units + (int32_t)xcd * capacity + (many && !readers ? capacity - 1 - nth : nth);
   }
 };
 constexpr int32_t kRestPad = 8 * 256;  // units by which the lists of all XCDs may exceed the drafts

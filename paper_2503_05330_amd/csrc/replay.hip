@@ -6,6 +6,8 @@ namespace csd {
 // From this many drafts on the small LDS layout is used (as in launch_step).
 constexpr int64_t kSmallLdsDrafts = 2048;
 
+// (Problems whose histories fit a workgroup's LDS take replay_staged_kernel from fewer drafts on; the figures
+// below are of such problems, before they did.)
 // From this many drafts on those with few matches are made with four or eight lanes each.  Three
 // kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
 // drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31 (with a fourth kernel of
@@ -27,6 +29,14 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
 // drafts, 20 us; 1024 problems x 24 steps, 393216 drafts, 74 us with four waves' rows, 60 with sixteen).
 constexpr int64_t kPooledDrafts = 1 << 17;
 
+void launch_replay_rest(const RestArgs& args, hipStream_t st) {
+  const bool q4 = args.ix.kmax <= 4;
+  auto* kernel = args.a.L <= 8    ? (q4 ? replay_rest_kernel<8, 4> : replay_rest_kernel<8, 8>)
+                 : args.a.L <= 16 ? (q4 ? replay_rest_kernel<16, 4> : replay_rest_kernel<16, 8>)
+                                  : (q4 ? replay_rest_kernel<32, 4> : replay_rest_kernel<32, 8>);
+  kernel<<<8 * 2 * kRestTurn, 4 * kWave, 0, st>>>(args);
+}
+
 template <int LCAP, int QC, bool EDGE>
 static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, u64* rest, int32_t* rest_list,
                          hipStream_t st) {
@@ -34,10 +44,10 @@ static void launch_quads(const IndexView& v, int32_t steps, const DraftArgs& a, 
   const auto grid = [&](int64_t rows) { return (uint32_t)((drafts + 8 * rows - 1) / (8 * rows) * 8); };   // rows per workgroup
   replay_quad_kernel<LCAP, QC, EDGE><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest);
   const bool pooled = drafts >= kPooledDrafts;
-  const RestList list{rest_list, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows};
+  const RestList list = RestList::in(rest_list, false, (int32_t)(grid((pooled ? 16 : 4) * kQuadRows) / 8) * (pooled ? 16 : 4) * kQuadRows);
   if (pooled) replay_eight_kernel<16, LCAP, QC, EDGE><<<grid(16 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
   else replay_eight_kernel<4, LCAP, QC, EDGE><<<grid(4 * kQuadRows), 256, 0, st>>>(v, steps, a, rest, list);
-  replay_rest_kernel<LCAP, QC><<<8 * 2 * kRestTurn, 4 * kWave, 0, st>>>(RestArgs{v, steps, a, list});
+  launch_replay_rest(RestArgs{v, steps, a, list}, st);
 }
 
 template <int QC>

@@ -18,7 +18,7 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, int32_
   const int64_t drafts = (int64_t)v.P * v.N * steps;
   const uint32_t grid = xcd_grid(drafts);
   if (drafts > kOneTurn) {
-    const RestList list{rest_list, (int32_t)(grid / 8)};
+    const RestList list = RestList::in(rest_list, false, (int32_t)(grid / 8));
     if (a.L <= 8) replay_leave_kernel<8, QC><<<grid, kWave, 0, st>>>(v, steps, a, list);
     else if (a.L <= 16) replay_leave_kernel<16, QC><<<grid, kWave, 0, st>>>(v, steps, a, list);
     else replay_leave_kernel<32, QC><<<grid, kWave, 0, st>>>(v, steps, a, list);
