@@ -160,23 +160,27 @@ bool own_problem(int64_t P, int64_t c, int64_t b, bool one_edit) {
 
 // Postings of an append from which they may be sorted by bins of buckets (sorted_append), and postings that an
 // index holds up to which there is scratch memory for it (12 to 24 bytes for each).
-constexpr int64_t kBinPostings = 1 << 19, kMostBinPostings = 1 << 22;
+constexpr int64_t kBinPostings = 1 << 17, kBinPostingsOneEdit = 1 << 19, kMostBinPostings = 1 << 22;
+int64_t bin_postings(bool one_edit) { return one_edit ? kBinPostingsOneEdit : kBinPostings; }
 // Bins of a problem, so that a workgroup for each fills the chip, and their least size.
 constexpr int32_t kBinsWanted = 256, kBinBucketsLog2Least = 6;
+static_assert(1 << kBinBucketsLog2Least >= kBlock, "a gram's home block within a bin");
 // Postings of an append to a bin, from which it pays.
 int64_t bin_least(bool one_edit) { return one_edit ? 256 : 768; }
 
 // An append whose postings are sorted by bins (csd_bins.cuh) is three launches, writes and reads every posting
 // once more, and sweeps the index by a workgroup per bin: it takes many postings, and many to a bin (with
-// counts, which may take few of those offered, it is not taken).  Measured, us, by atomics / sorted, one edit,
-// index empty and, behind it, half full or more: 1 problem of 64 paths, 4096 tokens 90 / 51; 2048, 48 / 37,
-// 56 / 43; 1024 (3.3e5 postings) 25 / 28, 35 / 35; 3 problems 192 / 73, 118 / 56, 63 / 44; 12 of 32, 2048
-// (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102.  Exact: 64
-// paths, 4096 tokens (1024 to a bin): 1 problem 21 / 20, 2 41 / 29, 4 70 / 46, 16 247 / 135; 2048 tokens (512):
-// 4 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.  Where own_problem applies too it comes
+// counts, which may take few of those offered, it is not taken: 64 paths, 4096 offered, exact, all, 3/4, 1/4 of them
+// taken, by atomics / sorted 23 / 19, 21 / 18, 10 / 17).  Measured, us with the reset, by atomics / sorted, one edit, index
+// empty, by Zipf's law and all alike: 1 problem of 64 paths, 4096 tokens 90 / 39, 32; 2048, 48 / 27, 26; 1024 (3.3e5
+// postings) 28, 22 / 23, 22; 32 paths, 1024 (1.6e5) 15, 14 / 19, 18, 2 problems (3.3e5) 23, 22 / 24, 24.  12 problems of 32
+// paths, 2048 tokens (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102 (these
+// before sequences kept to home blocks, which took a fifth off the sorted form).  Exact: 64 paths, 4096 tokens (1024 to a
+// bin): 1 problem 24 / 21, of 3200 tokens 19.5 / 18.4, 2 41 / 31, 4 70 / 47, 16 247 / 135; 2048 tokens (512): 1 13.0 / 13.4, 4
+// 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.  Where own_problem applies too it comes
 // first (24 problems of 16 paths, 2048 tokens, one edit, a workgroup per problem / sorted: 147 / 123).
 bool sorted_append(int64_t P, int64_t c, int64_t bins, bool one_edit) {
-  return bins > 0 && P * c >= kBinPostings && c >= bin_least(one_edit) * bins;
+  return bins > 0 && P * c >= bin_postings(one_edit) && c >= bin_least(one_edit) * bins;
 }
 
 // Whether any append to such problems is sorted: own_problem, which is asked first, says yes to all longer ones
@@ -184,7 +188,7 @@ bool sorted_append(int64_t P, int64_t c, int64_t bins, bool one_edit) {
 bool ever_sorted(const csd_config* c, int64_t buckets, int64_t bins) {
   const bool one_edit = c->max_edits > 0;
   const int64_t of_token = (int64_t)c->n_paths * (one_edit ? c->max_query_len + 1 : 1);
-  const int64_t by_call = (kBinPostings + c->n_problems - 1) / c->n_problems, by_bins = bin_least(one_edit) * bins;
+  const int64_t by_call = (bin_postings(one_edit) + c->n_problems - 1) / c->n_problems, by_bins = bin_least(one_edit) * bins;
   const int64_t tokens = ((by_call > by_bins ? by_call : by_bins) + of_token - 1) / of_token;
   return tokens <= c->max_len && !own_problem(c->n_problems, tokens * of_token, buckets, one_edit);
 }
@@ -251,7 +255,7 @@ Layout make_layout(const csd_config* c) {
   l.n_bins = 0;
   const int64_t variants = c->max_edits > 0 ? c->max_query_len + 1 : 1;
   const int64_t sources = (int64_t)c->n_paths * ((c->max_len + kBinSource - 1) / kBinSource);
-  if (l.n_buckets > 0 && (int64_t)cells * variants >= kBinPostings && (int64_t)cells * variants <= kMostBinPostings &&
+  if (l.n_buckets > 0 && (int64_t)cells * variants >= bin_postings(c->max_edits > 0) && (int64_t)cells * variants <= kMostBinPostings &&
       sources <= kMostBins && c->max_len >= kBinSource / 2) {
     l.bin_log2 = kBinBucketsLog2Least;
     while (((l.n_buckets >> l.bin_log2) > (uint32_t)kBinsWanted) && (1 << l.bin_log2) < kBinBuckets) ++l.bin_log2;
@@ -261,7 +265,7 @@ Layout make_layout(const csd_config* c) {
       l.records = align_up((size_t)c->n_problems * sources * kBinSource * variants * sizeof(BinRecord));
       l.runs = align_up((size_t)c->n_problems * l.n_bins * sources * sizeof(uint32_t));
       l.over = align_up(cells * variants * sizeof(int32_t));
-      at += l.records + l.runs + l.over + align_up(((size_t)c->n_problems * l.n_bins * 2 + 1) * sizeof(int32_t));
+      at += l.records + l.runs + l.over + align_up(((size_t)c->n_problems * l.n_bins * 2 + 2) * sizeof(int32_t));
     }
   }
   l.total = at;

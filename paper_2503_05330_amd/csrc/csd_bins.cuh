@@ -2,14 +2,16 @@
 //
 // An append with a thread per position claims every slot with an atomic on memory, and those run at
 // the memory's side of the fabric, 1.1e10 per second for the whole chip: 2.6e5 postings 22 us, 1.3e6 (one
-// edit) 88 us.  Sorted by bins they take 6 + 7 + 5 and 11 + 14 + 23: two passes over the records, one over the
-// index, and the longest chains.  A bin of buckets is one workgroup's, which claims in LDS:
+// edit) 88 us.  Sorted by bins they take 8 + 10 + 2 and 11 + 19 .. 24 + 5: two passes over the records, one over the
+// index.  A bin of buckets is one workgroup's, which claims in LDS, and whole home blocks, so that nearly all of a
+// chain is: (with sequences through the whole table the last launch filed what found its first bucket full, 15 .. 21 us
+// behind 14 with one edit):
 //   bin_sort_kernel   stores tokens and probabilities, and each workgroup's records (bucket, posting)
 //                     ordered by bin; a counting sort in LDS, no atomic on memory
 //   bin_file_kernel   a workgroup per bin gathers its runs of records, claims slots on its fill counts and
-//                     stores its buckets as whole lines; a posting whose first bucket is full is set aside
-//   bin_rest_kernel   files those along their chains, which lead to other bins, with atomics on memory, and
-//                     replaces the paths' ends
+//                     stores its buckets as whole lines; a posting that finds no slot near is set aside
+//   bin_rest_kernel   files those (hundreds of one gram) along their chains, which lead to other bins, with atomics
+//                     on memory, and replaces the paths' ends
 // sorted_append (csd.hip) says which appends take it.
 #pragma once
 
@@ -24,15 +26,16 @@ constexpr int32_t kBinBuckets = 1024;  // of a bin at most: 64 KB of LDS
 constexpr int32_t kRestGroups = 512;   // workgroups of bin_rest_kernel per problem
 
 struct BinRecord {
-  int32_t bucket, posting;
+  int32_t bucket, posting;      // bucket: above kBinStep bits the gram's step within its home block
 };
+constexpr int kBinStep = 24;
 struct Bins {
   BinRecord* records;           // [P][sources][kBinSource * variants]
   uint32_t* runs;               // [P][bins][sources]: a bin's records of a source, first << 16 | how many
-  int32_t* over;                // postings whose first bucket is full; a part for each bin:
+  int32_t* over;                // postings that find no slot near; a part for each bin:
   int32_t* over_first;          // [P][bins]
   int32_t* over_count;          // [P][bins]
-  int32_t* over_used;           // parts given out in this append
+  int32_t* over_used;           // parts given out in this append; behind it: postings set aside in all
   int32_t* ends;                // rows like meta's: the paths' new ends
   int32_t chunks, sources;      // sorting workgroups per path, per problem
   int32_t variants;             // postings per position at most
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(kBinSource) void bin_sort_kernel(IndexView ix, Step
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
   const int32_t row = (int32_t)blockIdx.x / b.chunks, chunk = (int32_t)blockIdx.x - row * b.chunks;
   const int32_t p = row / ix.N, i = row - p * ix.N, source = i * b.chunks + chunk;
-  if (blockIdx.x == 0 && tid == 0) *b.over_used = 0;
+  if (blockIdx.x == 0 && tid < 2) b.over_used[tid] = 0;
   NewTokens<QC> x;
   x.load(ix, in, row, chunk * kBinSource + tid);
   for (int32_t c = tid; c < b.bins; c += kBinSource) count[c] = 0;
@@ -88,13 +91,15 @@ __global__ __launch_bounds__(kBinSource) void bin_sort_kernel(IndexView ix, Step
     store_end(ix, in, row, x.len, cnt, b.ends, lane);
   }
   if (flags) atomicOr(ix.status, flags);
-  int32_t at[kVariants], rank[kVariants];
+  int32_t at[kVariants], step[kVariants], rank[kVariants];
   uint32_t live = 0;
 #pragma unroll
   for (int v = 0; v < kVariants; ++v) {
     bool on = x.filed(ix, cnt) && v <= ix.kmax;
     if (v >= 2) on = on && x.G[v - 1] != x.G[v - 2];     // (else the same string as variant v - 1)
-    at[v] = (int32_t)(variant_hash(x.G, ix.kmax, v).h & ix.bucket_mask);
+    const GramHash gh = variant_hash(x.G, ix.kmax, v);
+    at[v] = (int32_t)(gh.h & ix.bucket_mask);
+    step[v] = (int32_t)(gh.step & (kBlock - 1u));
     live |= on ? 1u << v : 0u;
   }
   __syncthreads();
@@ -114,7 +119,7 @@ __global__ __launch_bounds__(kBinSource) void bin_sort_kernel(IndexView ix, Step
 #pragma unroll
   for (int v = 0; v < kVariants; ++v)
     if (live >> v & 1u)
-      sorted[count[at[v] >> b.buckets_log2] + rank[v]] = BinRecord{at[v], FUZZY ? variant_posting(pos, v) : pos};
+      sorted[count[at[v] >> b.buckets_log2] + rank[v]] = BinRecord{at[v] | step[v] << kBinStep, FUZZY ? variant_posting(pos, v) : pos};
   __syncthreads();
   BinRecord* records = b.records + ((int64_t)p * b.sources + source) * (kBinSource * b.variants);
   for (int32_t f = tid; f < total; f += kBinSource) records[f] = sorted[f];
@@ -156,6 +161,7 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
   int32_t* slots = reinterpret_cast<int32_t*>(table);
   auto file = [&](auto at_once) {                        // records of a thread that are in flight together
     constexpr int kAtOnce = decltype(at_once)::value;
+    constexpr uint32_t kTogether = 8;
     for (int32_t f0 = tid; f0 < total; f0 += kAtOnce * 1024) {
       BinRecord rec[kAtOnce];
 #pragma unroll
@@ -168,10 +174,30 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
       for (int y = 0; y < kAtOnce; ++y) {
         if (f0 + y * 1024 >= total) continue;
         const int32_t local = rec[y].bucket & (buckets - 1);
-        int32_t c = fill[local];                         // (a full bucket is passed without an atomic)
-        if (c < kBucketSlots) c = atomicAdd(&fill[local], 1);
-        if (c < kBucketSlots) slots[local * kBucketWords + 1 + c] = rec[y].posting;
-        else b.over[over_at + atomicAdd(&n_over, 1)] = rec[y].posting;
+        // the first bucket, then the others near (all this bin's) four at a time
+        const GramHash gh{(uint32_t)local, (uint32_t)rec[y].bucket >> kBinStep};
+        bool open = true;
+        auto claim = [&](uint32_t at) {
+          const int32_t c = atomicAdd(&fill[at], 1);
+          if (c < kBucketSlots) {
+            slots[at * kBucketWords + 1 + c] = rec[y].posting;
+            open = false;
+          }
+        };
+        if (fill[local] < kBucketSlots) claim((uint32_t)local);   // (a full bucket is passed without an atomic)
+        for (uint32_t r = 1; r < kNear && open; r += kTogether) {
+          uint32_t at[kTogether];
+          int32_t filled[kTogether];
+#pragma unroll
+          for (uint32_t z = 0; z < kTogether; ++z) {
+            at[z] = gram_near(gh, r + z, (uint32_t)buckets - 1u);
+            filled[z] = r + z < kNear ? fill[at[z]] : kBucketSlots;
+          }
+#pragma unroll
+          for (uint32_t z = 0; z < kTogether; ++z)
+            if (open && filled[z] < kBucketSlots) claim(at[z]);
+        }
+        if (open) b.over[over_at + atomicAdd(&n_over, 1)] = rec[y].posting;
       }
     }
   };
@@ -186,6 +212,7 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
   if (tid == 0) {
     b.over_first[blockIdx.x] = over_at;
     b.over_count[blockIdx.x] = n_over;
+    if (n_over > 0) atomicAdd(b.over_used + 1, n_over);
   }
 }
 
@@ -219,11 +246,11 @@ __device__ __forceinline__ void gram_insert_group(int32_t* tbl, uint32_t mask, G
   }
 }
 
-// The posting of each lane whose first bucket is full (`open`: the lane has one), on along its chain: lanes
+// The posting of each lane whose near buckets are full (`open`: the lane has one), on along its chain: lanes
 // that share one as a group; the others claim in the next three buckets, a lane for itself, and what is
 // left then (a long chain) is the whole wave's.
-// (us, bin_rest_kernel of 64 paths x 4096 tokens with one edit: a wave inserting posting by posting 65 with a
-// lane for every one, 31 with them spread over the waves, in groups 23.)
+// (us, bin_rest_kernel of 64 paths x 4096 tokens with one edit, when all that found their first bucket full came
+// here: a wave inserting posting by posting 65 with a lane for every one, 31 with them spread over the waves, in groups 23.)
 constexpr int kGroupLanes = 4;
 __device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, GramHash gh, int32_t posting,
                                                  bool open, int lane) {
@@ -240,8 +267,8 @@ __device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, G
       if (same >> lane & 1u) open = false;
     }
   };
-  file_groups(1u, kGroupLanes);
-  for (uint32_t r = 1; r < 4u && r <= mask; ++r) {
+  file_groups(kNear, kGroupLanes);
+  for (uint32_t r = kNear; r < kNear + 3u && r <= mask; ++r) {
     if (wave_ballot(open) == 0) return;
     int32_t* b = gram_bucket(gram, gh, r, mask);
     if (open && b[0] < kBucketSlots) {
@@ -252,7 +279,7 @@ __device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, G
       }
     }
   }
-  file_groups(4u, 1);
+  file_groups(kNear + 3u, 1);
 }
 
 template <bool FUZZY, int QC>
@@ -265,6 +292,7 @@ __global__ __launch_bounds__(256) void bin_rest_kernel(IndexView ix, Bins b) {
       const int64_t at = (int64_t)p * ix.N * ix.meta_stride + x;
       ix.meta_new[at] = b.ends[at];
     }
+  if (__builtin_amdgcn_readfirstlane(b.over_used[1]) == 0) return;
   constexpr int kEach = kMostBins / 256;                 // consecutive bins of a thread
   int32_t counts[kEach], sum = 0;
 #pragma unroll

@@ -6,10 +6,12 @@
 // decode loop only issues while a path is shorter than kmax, are matched by
 // scan).  A posting (j, e) — "the kmax tokens before index e of path j" — is
 // stored under the hash of those tokens when token e is appended, so a query
-// finds its matches (Eq. 3) without scanning histories.  Bucket r of a gram's
-// probe sequence is (h + r * step) mod n_buckets with an odd step; an insert
-// goes into the first bucket of the sequence that is not full, so a lookup may
-// stop at the first bucket that is not full.  Hash collisions are harmless:
+// finds its matches (Eq. 3) without scanning histories.  A gram's probe sequence
+// starts with kNear buckets of its home block of kBlock (a workgroup that has the
+// block in LDS files nearly every posting there, whatever else is appended
+// meanwhile) and goes on through all blocks, so that a frequent gram fills half of
+// one block at most.  An insert goes into the first bucket of the sequence that is
+// not full, so a lookup may stop at the first bucket that is not full.  Hash collisions are harmless:
 // every posting is verified against the history before it counts.
 #pragma once
 
@@ -34,9 +36,33 @@ __device__ __forceinline__ GramHash gram_hash_end(uint32_t acc, int g) {
   uint32_t step = ((x * 0x27D4EB2Fu) >> 7) | 1u;
   return GramHash{h, step};
 }
+// Bucket r of a gram's sequence (mask: n_buckets - 1; step is odd).  Of the first kNear, or of a table of one block:
+constexpr uint32_t kBlock = 64, kNear = 32;
+__device__ __forceinline__ uint32_t gram_near(GramHash gh, uint32_t r, uint32_t mask) {
+  return ((gh.h & ~(kBlock - 1u)) | ((gh.h + r * gh.step) & (kBlock - 1u))) & mask;
+}
+// Any: behind the first ones turn k through the blocks takes a bucket of each, the home block's last.  (That is bucket
+// k of the sequence again for k < kNear: an insert finds it full, a look-up passes it, see gram_again.)
+__device__ __forceinline__ uint32_t gram_far(GramHash gh, uint32_t r, uint32_t mask) {
+  const uint32_t blocks = mask / kBlock, t = r - kNear, k = t >> __popc(blocks);   // (blocks: a mask of their numbers)
+  const uint32_t block = gh.h / kBlock + ((t & blocks) + 1u) * ((gh.step / kBlock) | 1u);
+  return ((block & blocks) * kBlock) | ((gh.h + k * gh.step) & (kBlock - 1u));
+}
+__device__ __forceinline__ uint32_t gram_index(GramHash gh, uint32_t r, uint32_t mask) {
+  return r < kNear || mask < kBlock ? gram_near(gh, r, mask) : gram_far(gh, r, mask);
+}
+__device__ __forceinline__ bool gram_again(uint32_t r, uint32_t mask) {
+  if (r < kNear || mask < kBlock) return false;
+  const uint32_t blocks = mask / kBlock, t = r - kNear;
+  return (t & blocks) == blocks && t >> __popc(blocks) < kNear;
+}
 __device__ __forceinline__ int32_t* gram_bucket(int32_t* tbl, GramHash gh, uint32_t r,
                                                 uint32_t mask) {
-  return tbl + (int64_t)((gh.h + r * gh.step) & mask) * kBucketWords;
+  return tbl + (int64_t)gram_index(gh, r, mask) * kBucketWords;
+}
+// (where r is known to be small: the other half is code on the way of every launch, 0.3 us of small ones)
+__device__ __forceinline__ int32_t* gram_bucket_near(int32_t* tbl, GramHash gh, uint32_t r, uint32_t mask) {
+  return tbl + (int64_t)gram_near(gh, r, mask) * kBucketWords;
 }
 
 // General insert, by one whole wave: reads the fill counts of 64 buckets of
@@ -47,11 +73,13 @@ __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, Gr
                                                  uint32_t r0, int32_t pos, int lane) {
   for (; r0 <= mask; r0 += kWave) {
     uint32_t r = r0 + lane;
-    bool open = r <= mask && gram_bucket(tbl, gh, r, mask)[0] < kBucketSlots;
+    const uint32_t near = gram_near(gh, r, mask), far = gram_far(gh, r, mask);   // (no branch: lanes have both)
+    const uint32_t at = r < kNear || mask < kBlock ? near : far;
+    bool open = r <= mask && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
     u64 m = wave_ballot(open);
     while (m) {
-      uint32_t first = (uint32_t)__ffsll((long long)m) - 1u;
-      int32_t* b = gram_bucket(tbl, gh, r0 + first, mask);
+      int first = (int)__ffsll((long long)m) - 1;
+      int32_t* b = tbl + (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)at, first) * kBucketWords;
       int32_t c = 0;
       if (lane == 0) c = atomicAdd(b, 1);
       c = __builtin_amdgcn_readfirstlane(c);
@@ -59,7 +87,7 @@ __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, Gr
         if (lane == 0) b[1 + c] = pos;
         return;
       }
-      m &= m - 1;                                   // filled up meanwhile: next open bucket
+      m &= m - 1;                                       // filled up meanwhile: next open bucket
     }
   }
 }
@@ -97,7 +125,7 @@ __device__ __forceinline__ InsertTicket insert_begin(int32_t* gram, uint32_t mas
   t.first = -1;
   t.claimed = kBucketSlots;
   uint32_t r = (uint32_t)(lane & (LANES - 1));          // every lane loads: no branch, no early wait
-  t.fill = gram_bucket(gram, t.gh, r <= mask ? r : 0u, mask)[0];
+  t.fill = gram_bucket_near(gram, t.gh, r <= mask ? r : 0u, mask)[0];
   return t;
 }
 
@@ -109,7 +137,7 @@ __device__ __forceinline__ void insert_claim(InsertTicket& t, int32_t* gram, uin
   u64 m = wave_ballot(open);
   t.first = m ? (int32_t)__ffsll((long long)m) - 1 : -1;
   if (t.live && lane == 0 && t.first >= 0)
-    t.claimed = atomicAdd(gram_bucket(gram, t.gh, (uint32_t)t.first, mask), 1);
+    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask), 1);
 }
 
 // Phase 3: store the posting; if the buckets looked at were full (or the last
@@ -119,7 +147,7 @@ __device__ __forceinline__ void insert_finish(const InsertTicket& t, int32_t* gr
   if (!t.live) return;
   int32_t claimed = __builtin_amdgcn_readfirstlane(t.claimed);
   if (claimed < kBucketSlots) {
-    if (lane == 0) gram_bucket(gram, t.gh, (uint32_t)t.first, mask)[1 + claimed] = pos;
+    if (lane == 0) gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask)[1 + claimed] = pos;
     return;
   }
   gram_insert_from(gram, mask, t.gh, t.first < 0 ? (uint32_t)t.lanes : (uint32_t)t.first, pos,
@@ -182,7 +210,7 @@ __device__ __forceinline__ VariantTicket variants_begin(int32_t* gram, uint32_t 
   t.first = -1;
   t.claimed = kBucketSlots;
   uint32_t r = (uint32_t)(lane & 15);                   // every lane loads: no branch, no early wait
-  t.fill = gram_bucket(gram, t.gh, r <= mask ? r : 0u, mask)[0];
+  t.fill = gram_bucket_near(gram, t.gh, r <= mask ? r : 0u, mask)[0];
   return t;
 }
 
@@ -193,7 +221,7 @@ __device__ __forceinline__ void variants_claim(VariantTicket& t, int32_t* gram, 
   uint32_t mine = (uint32_t)(wave_ballot(open) >> (lane & 48)) & 0xFFFFu;   // this group's 16 lanes
   t.first = mine ? (int32_t)__ffs(mine) - 1 : -1;
   if (t.live && (lane & 15) == 0 && t.first >= 0)
-    t.claimed = atomicAdd(gram_bucket(gram, t.gh, (uint32_t)t.first, mask), 1);
+    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask), 1);
 }
 
 // Variants beyond the four the groups take (kmax >= 4): the general insert.
@@ -211,7 +239,7 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
                                                 int32_t pos, int lane) {
   if (!t.any) return;
   bool stored = t.live && (lane & 15) == 0 && t.claimed < kBucketSlots;
-  if (stored) gram_bucket(gram, t.gh, (uint32_t)t.first, mask)[1 + t.claimed] = variant_posting(pos, lane >> 4);
+  if (stored) gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask)[1 + t.claimed] = variant_posting(pos, lane >> 4);
   int32_t retry = (t.live && !stored) ? 1 : 0;          // meaningful on the group leaders
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
@@ -227,9 +255,10 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
 // claims of all lanes and variants are atomics on the first buckets of their chains, in flight
 // together, without a look at the fill counts before: at most 8 of a bucket's 15 slots are taken
 // on average when a problem's histories are full, so few claims miss.  Those go on as claims in
-// the next three buckets, a lane at a time for itself, and what is left then (the long chain of
+// the next kFileNear buckets, a lane at a time for itself, and what is left then (the long chain of
 // a frequent gram) is the whole wave's.  meanwhile(): called while the first claims are in flight.
 // LOOK: the fill counts are looked at before all the same (see launch_append).
+constexpr uint32_t kFileNear = 4;
 template <bool FUZZY, int QC, bool LOOK = false, class MEANWHILE>
 __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int32_t kmax,
                                                const int32_t (&G)[QC], bool mine, int32_t pos, int lane,
@@ -263,29 +292,34 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
       gram[(int64_t)at[v] * kBucketWords + 1 + claimed[v]] = FUZZY ? variant_posting(pos, v) : pos;
       todo &= ~(1u << v);
     }
-  while (wave_ballot(todo != 0) != 0) {                  // uniform over the wave
+  while (__builtin_expect(wave_ballot(todo != 0) != 0, 0)) {   // uniform over the wave (unlikely: the code behind it stays near)
     const int32_t v = todo != 0 ? (int32_t)__ffs(todo) - 1 : 0;
     const GramHash gh = variant_hash(G, kmax, v);
     const int32_t posting = FUZZY ? variant_posting(pos, v) : pos;
     bool open = todo != 0;
-    for (uint32_t r = 1; r < 4u && r <= mask; ++r) {
-      if (wave_ballot(open) == 0) break;
-      int32_t* b = gram_bucket(gram, gh, r, mask);
-      if (open && b[0] < kBucketSlots) {
-        const int32_t c = atomicAdd(b, 1);
-        if (c < kBucketSlots) {
-          b[1 + c] = posting;
-          open = false;
-        }
+    // (all their fill counts at once: one after the other each was a round trip)
+    int32_t fill[kFileNear];
+    if (open) {
+#pragma unroll
+      for (uint32_t x = 0; x < kFileNear; ++x) fill[x] = gram[(int64_t)gram_near(gh, x + 1u, mask) * kBucketWords];
+    }
+#pragma unroll
+    for (uint32_t x = 0; x < kFileNear; ++x) {
+      if (!open || fill[x] >= kBucketSlots || x + 1u > mask) continue;
+      int32_t* b = gram + (int64_t)gram_near(gh, x + 1u, mask) * kBucketWords;
+      const int32_t c = atomicAdd(b, 1);
+      if (c < kBucketSlots) {
+        b[1 + c] = posting;
+        open = false;
       }
     }
     u64 left = wave_ballot(open);
-    while (left) {                                       // their first four buckets were full
+    while (left) {                                       // those were full, too
       const int t = (int)__ffsll((long long)left) - 1;
       left &= left - 1;
       const GramHash g{(uint32_t)__builtin_amdgcn_readlane((int)gh.h, t),
                        (uint32_t)__builtin_amdgcn_readlane((int)gh.step, t)};
-      gram_insert_from(gram, mask, g, 4u, __builtin_amdgcn_readlane(posting, t), lane);
+      gram_insert_from(gram, mask, g, kFileNear + 1u, __builtin_amdgcn_readlane(posting, t), lane);
     }
     todo &= todo - 1u;                                   // 0 stays 0
   }
@@ -336,18 +370,24 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
 #pragma unroll
     for (int y = 0; y < kClaims; ++y) {
       bool looking = (todo >> y & 1u) != 0;
-      uint32_t b = (gh[y].h + gh[y].step) & mask;
-      for (uint32_t r = 1; r <= mask && wave_ballot(looking) != 0; ++r) {   // uniform over the wave
-        if (looking) {
-          int32_t c = fill[b];                           // (a full bucket is passed without an atomic)
-          if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
-          if (c < kBucketSlots) {
-            slots[b * kBucketWords + 1 + c] = posting[y];
-            looking = false;
-          }
-          b = (b + gh[y].step) & mask;
+      auto claim = [&](uint32_t b) {
+        int32_t c = fill[b];                             // (a full bucket is passed without an atomic)
+        if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
+        if (c < kBucketSlots) {
+          slots[b * kBucketWords + 1 + c] = posting[y];
+          looking = false;
         }
+      };
+      const uint32_t in_block = mask < kBlock ? mask : kBlock - 1u, home = gh[y].h & mask & ~in_block;
+      const uint32_t near = mask < kBlock ? mask + 1u : kNear;
+      uint32_t b = (gh[y].h + gh[y].step) & in_block;
+      for (uint32_t r = 1; r < near && wave_ballot(looking) != 0; ++r) {   // uniform over the wave
+        if (looking) claim(home | b);
+        b = (b + gh[y].step) & in_block;
       }
+      if (__builtin_expect(wave_ballot(looking) != 0, 0))
+        for (uint32_t r = near; r <= mask && wave_ballot(looking) != 0; ++r)   // uniform over the wave
+          if (looking) claim(gram_far(gh[y], r, mask));
     }
   }
 }

@@ -79,6 +79,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   constexpr int kWide = WAVES < 4 ? WAVES : (WAVES == 4 ? 4 : 3);   // waves that draft the rows left (what the LDS has room for)
   constexpr int kBefore = 4;                             // tokens before a path's end that are kept
   constexpr int kOwn = (2 * LCAP + kBefore + 1 + G - 1) / G;   // words of a path's window that a lane has
+  static_assert(kLoopChain + 4 <= kNear, "buckets of a gram's home block");
   static_assert(K >= 2 && K <= kBefore, "a gram's tokens in one load");
   __shared__ LdsWave wide[kWide];
   __shared__ int32_t own_all[kPaths][kOwn * G];          // tokens from kBefore before a path's end on, up to 2 L behind it
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       // ---- round trip 1: the query's first bucket, past the CU's own cache (slots are claimed in the L2);
       // all postings of the steps before are there
       auto bucket = [&](uint32_t r) {
-        return __hip_atomic_load(gram + (int64_t)((gh.h + r * gh.step) & ix.bucket_mask) * kBucketWords + sub, __ATOMIC_RELAXED,
+        return __hip_atomic_load(gram + (int64_t)gram_near(gh, r, ix.bucket_mask) * kBucketWords + sub, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
       };
       int32_t next = bucket(0);

@@ -536,7 +536,7 @@ __device__ __forceinline__ void lookup_with_windows(LDS& s, const Ctx& c, int32_
       uint32_t r = r0 + width + grp;
       next_word = gram_bucket(tbl, gh, r < n_buckets ? r : 0u, c.bucket_mask)[sub];
     }
-    bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count);
+    bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count) && !gram_again(r0 + grp, c.bucket_mask);
     int32_t j = y.pos_path(word), e = y.pos_index(word), old_j = 0, new_j = 0;
     cand = cand && j != (GENERAL ? c.skip : c.i) && j < y.N;
     if (cand) {
@@ -700,7 +700,7 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
     gh = query_hash<QC>(c);
     uint32_t r = (uint32_t)(lane >> 4);
     if (kFirst == 4 || r == 0)
-      word = gram_bucket(gram, gh, r <= c.bucket_mask ? r : 0u, c.bucket_mask)[lane & 15];
+      word = gram_bucket_near(gram, gh, r <= c.bucket_mask ? r : 0u, c.bucket_mask)[lane & 15];
   }
   // ---- while it travels: own append, lengths into LDS, matches among the new positions
   if (APPENDS && y.n == 1) append_own_single<QC>(ix, y, row, c.i, me, st_i, sp_i, lane);
@@ -942,14 +942,14 @@ __device__ __forceinline__ void consume_variant_postings(LDS& s, const Ctx& c, i
   }
 }
 
-// One batch by position: this lane's word of its group's bucket.  Returns whether the
-// group's bucket was full.
+// One batch by position: this lane's word of its group's bucket (again: which has been looked
+// through before).  Returns whether the group's bucket was full.
 template <int LCAP, int K, class LDS>
 __device__ __forceinline__ bool consume_variant_bucket(LDS& s, const Ctx& c, int32_t L,
                                                        int32_t win_cap, int32_t& n_match,
-                                                       int32_t my_u, int32_t word) {
+                                                       int32_t my_u, int32_t word, bool again) {
   bool full;
-  const bool cand = bucket_has_posting(word, c.tid, full);
+  const bool cand = bucket_has_posting(word, c.tid, full) && !again;
   consume_variant_postings<LCAP, K>(s, c, L, win_cap, n_match, my_u, word, cand);
   return full;
 }
@@ -1038,13 +1038,13 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
     if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0 || n_match > LIMIT) continue;   // uniform over the wave
     const GramHash gh = variant_hash(c.Q, c.q, chain);                // the same in every lane
     uint32_t r0 = 1;
-    int32_t tail = gram_bucket(tbl, gh, r0 + grp < n_buckets ? r0 + grp : 0u, c.bucket_mask)[sub];
+    int32_t tail = gram_bucket_near(tbl, gh, r0 + grp < n_buckets ? r0 + grp : 0u, c.bucket_mask)[sub];
     for (; r0 < n_buckets; r0 += 4) {
       consume_here(tail);
       if (r0 + grp >= n_buckets) tail = -1;
       uint32_t rn = r0 + 4 + grp;                                     // next batch: in flight meanwhile
       int32_t next_tail = gram_bucket(tbl, gh, rn < n_buckets ? rn : 0u, c.bucket_mask)[sub];
-      bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail);
+      bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail, gram_again(r0 + grp, c.bucket_mask));
       if (wave_ballot(!tail_full) != 0 || n_match > LIMIT) break;      // the chain ends in this batch
       tail = next_tail;
     }
@@ -1089,7 +1089,7 @@ __device__ __forceinline__ void match_variants(const LDS& s, const Ctx& c, Sink&
     consume_here(word);
     if (r0 + grp >= n_buckets) word = -1;
     bool full;
-    bool cand = bucket_has_posting(word, lane, full);
+    bool cand = bucket_has_posting(word, lane, full) && !gram_again(r0 + grp, c.bucket_mask);
     const int32_t filed_as = word >> kVariantShift, pos = word & ((1 << kVariantShift) - 1);
     const int32_t j = y.pos_path(pos), e = y.pos_index(pos);
     int32_t tv[K + 1], old_j = 0, new_j = 0;

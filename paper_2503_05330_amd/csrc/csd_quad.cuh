@@ -492,6 +492,7 @@ template <int WAVES, int LCAP, int QC, bool EDGE>
 __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t steps, DraftArgs a, const u64* rest,
                                                            RestList list) {
   constexpr int G = 8, kWaves = 4, kRows = WAVES * kQuadRows;   // rows of the workgroup
+  static_assert(kLongChain <= kNear, "buckets of a gram's home block");
   static_assert(WAVES <= kWave && kRows <= 256, "a lane per wave of the other kernel, a byte per row");
   __shared__ uint32_t found_all[kWaves][kWave];          // [row of the turn][8] matches
   __shared__ uint8_t todo[kRows], left[2][kRows];        // left: few matches, many
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     int32_t M = 0;
     bool looking = on && !leave;                         // the same in a group's lanes
     auto bucket = [&](uint32_t r) {
-      const int64_t b = u.buckets + ((gh.h + r * gh.step) & ix.bucket_mask);
+      const int64_t b = u.buckets + gram_near(gh, r, ix.bucket_mask);
       return *reinterpret_cast<const int2*>(ix.gram + b * kBucketWords + 2 * sub);
     };
     int2 next = bucket(0);

@@ -184,3 +184,37 @@ def test_an_append_that_does_not_fit_is_clipped(oracle):
         want = oracle.draft_all(np.ascontiguousarray(tokens[:, :, :150]), None,
                                 np.full((problems, 4), 150, dtype=np.int32), 3, 4, 1.0, 0)
         assert np.array_equal(out["tokens"].cpu().numpy(), want["draft"])
+
+
+# a gram's sequence of buckets: more postings of one gram than its home block holds (all tokens the same: its chain
+# goes through all blocks, and by the home block once more), filed posting by posting, by a workgroup per problem, by
+# bins and by single steps, in tables of one block, of a few and of many
+@pytest.mark.parametrize("problems,paths,max_len,query,edits,run,n", [
+    (1, 8, 1024, 3, 0, 1.0, 1000),
+    (1, 5, 60, 2, 0, 1.0, 50),
+    (1, 4, 300, 3, 1, 1.0, 280),
+    (12, 8, 300, 4, 0, 0.5, 290),
+    (40, 6, 500, 3, 0, 0.7, 480),
+    (1, 64, 4096, 4, 0, 0.02, 4000),
+    (1, 64, 2048, 4, 1, 0.03, 2000),
+])
+def test_grams_that_fill_their_home_block(problems, paths, max_len, query, edits, run, n):
+    print("home block", problems, paths, max_len, query, edits, run, flush=True)
+    rng = np.random.default_rng(paths + n)
+    tokens = rng.integers(1, 5000, size=(problems, paths, max_len)).astype(np.int32)
+    same = rng.random((problems, paths, max_len // 20 + 1)) < run                  # runs of twenty of one token
+    tokens = np.where(np.repeat(same, 20, axis=2)[:, :, :max_len], 7, tokens)
+    tokens[:, :, n - 12:] = 7                                                      # ... which every path ends with
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).to("cuda:0")
+    got = []
+    for flags in (binding.MATCH_INDEX, binding.MATCH_SCAN):
+        ix = binding.Index(problems, paths, max_len, 5000, query, 8, 1.0, 0, flags, device="cuda:0", max_edits=edits)
+        ix.append(put(tokens[:, :, :n - 8]))
+        for t in range(n - 8, n):
+            ix.step(put(tokens[:, :, t]), None, None, 1, query, 8)
+        got.append((ix.dump_matches(query, cap=1 << 24), ix.draft(query, 8), ix.status()))
+    (matches, draft, status), (matches1, draft1, status1) = got
+    assert np.array_equal(matches[1], matches1[1]) and np.array_equal(matches[0], matches1[0])
+    for key in ("tokens", "length", "token_scores", "path_scores"):
+        assert torch.equal(draft[key], draft1[key]), key
+    assert status == status1 == 0 and int(matches[1][-1]) > 100
