@@ -370,24 +370,21 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
 #pragma unroll
     for (int y = 0; y < kClaims; ++y) {
       bool looking = (todo >> y & 1u) != 0;
-      auto claim = [&](uint32_t b) {
-        int32_t c = fill[b];                             // (a full bucket is passed without an atomic)
-        if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
-        if (c < kBucketSlots) {
-          slots[b * kBucketWords + 1 + c] = posting[y];
-          looking = false;
-        }
-      };
       const uint32_t in_block = mask < kBlock ? mask : kBlock - 1u, home = gh[y].h & mask & ~in_block;
       const uint32_t near = mask < kBlock ? mask + 1u : kNear;
-      uint32_t b = (gh[y].h + gh[y].step) & in_block;
-      for (uint32_t r = 1; r < near && wave_ballot(looking) != 0; ++r) {   // uniform over the wave
-        if (looking) claim(home | b);
-        b = (b + gh[y].step) & in_block;
+      uint32_t turn = gh[y].h + gh[y].step;
+      for (uint32_t r = 1; r <= mask && wave_ballot(looking) != 0; ++r, turn += gh[y].step) {   // uniform over the wave
+        uint32_t b = home | (turn & in_block);
+        if (__builtin_expect(r >= near, 0)) b = gram_far(gh[y], r, mask);
+        if (looking) {
+          int32_t c = fill[b];                           // (a full bucket is passed without an atomic)
+          if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
+          if (c < kBucketSlots) {
+            slots[b * kBucketWords + 1 + c] = posting[y];
+            looking = false;
+          }
+        }
       }
-      if (__builtin_expect(wave_ballot(looking) != 0, 0))
-        for (uint32_t r = near; r <= mask && wave_ballot(looking) != 0; ++r)   // uniform over the wave
-          if (looking) claim(gram_far(gh[y], r, mask));
     }
   }
 }

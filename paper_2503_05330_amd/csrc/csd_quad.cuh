@@ -107,11 +107,11 @@ struct Filing {
     pos = packed;
     open = mine;
     claimed = kBucketSlots;
-    if (mine) claimed = atomicAdd(gram_bucket(gram, gh, 0, mask), 1);
+    if (mine) claimed = atomicAdd(gram_bucket_near(gram, gh, 0, mask), 1);
   }
   __device__ __forceinline__ void settle() {
     if (claimed < kBucketSlots) {
-      gram_bucket(gram, gh, 0, mask)[1 + claimed] = pos;
+      gram_bucket_near(gram, gh, 0, mask)[1 + claimed] = pos;
       open = false;
     }
     if (wave_ballot(open) != 0) look(1);
