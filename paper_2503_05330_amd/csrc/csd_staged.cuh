@@ -399,7 +399,7 @@ __global__ __launch_bounds__(kStagedThreads) void replay_staged_kernel(StagedArg
     M = leave ? 0 : M;
     const uint32_t up_to = wave_prefix((uint32_t)M);
     const int32_t first_of = wave_reserve(&s.n_placed, __builtin_amdgcn_readlane((int)up_to, kWave - 1), lane) + (int32_t)up_to - M;
-    leave = leave || first_of + M > most;
+    leave = leave || (M > 0 && first_of + M > most);     // (a lane without a row has none, wherever its wave's part ends)
     if (leave) s.n_found[tid] = kStagedLeft;
     if (leave) s.rest[atomicAdd(&s.n_rest, 1)] = (uint16_t)tid;
     if (has_row) s.first[tid] = (uint16_t)first_of;

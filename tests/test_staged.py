@@ -81,6 +81,36 @@ def test_staged_replay(problems, paths, T, steps, query, draft, vocab, mode, war
     assert sum(int(x["length"].sum()) for x in a) > 0
 
 
+def _matches(tokens, lens, steps, query):
+    """Matches of every row (step by step, path by path) of one problem; tokens: its paths with the steps' tokens."""
+    where, rows = {}, []
+    for j, path in enumerate(tokens):
+        for e in range(query, lens[j] + steps):
+            where.setdefault(tuple(path[e - query:e]), []).append((j, e))
+    for t in range(steps):
+        for i, path in enumerate(tokens):
+            end = lens[i] + t + 1
+            rows.append(sum(j != i and e < lens[j] + t + 1 for j, e in where.get(tuple(path[end - query:end]), ())))
+    return np.array(rows)
+
+
+def test_matches_without_room_in_a_share_that_ends_within_a_wave():
+    """More matches than are placed, and lanes without a row behind them: what is left over are rows of the share."""
+    problems, paths, T, steps, query, warm, noise = 300, 24, 200, 15, 3, 110, 0.03
+    tokens, _ = _inputs(problems, paths, T, 1000, noise, problems + paths + steps)
+    lens, placed = np.where(np.arange(paths) % 5 == 4, warm // 3, warm), []
+    for p in (0, problems - 1):
+        filed = [np.concatenate([tokens[p, i, :lens[i]], tokens[p, i, warm:warm + steps]]) for i in range(paths)]
+        placed.append(_matches(filed, lens, steps, query))
+        # one share; more than 6144 matches of rows that could be drafted, few enough that none gives up
+        assert len(placed[-1]) == 360 and placed[-1].max() <= 256 and 6144 < placed[-1].sum() <= 1 << 14
+    print("without room", [int(x.sum()) for x in placed], flush=True)
+    args = (problems, paths, T, steps, query, 8, 1000, 0, warm, noise)
+    (a, status), (b, status1) = _run(*args, calls=2), _run(*args, calls=2, per_launch=1)
+    _same(a, b)
+    assert status == status1 == 0
+
+
 def test_staged_replay_without_options():
     """No probabilities, targets and scores."""
     args = (200, 16, 300, 24, 3, 8, 200, 0, 200, 0.2)
