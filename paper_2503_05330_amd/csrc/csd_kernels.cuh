@@ -914,10 +914,13 @@ void replay_rest_kernel(RestArgs) {
     few = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, false));
     many = __builtin_amdgcn_readfirstlane(*list.count(blockIdx.x & 7, true));
   }
-  if (few + many == 0) return;                           // (the same in all workgroups of the XCD)
-  if (threadIdx.x == 0) {
-    const RestList list = rest_arguments().list;
-    if (list.readers) {
+  if (few + many == 0) return;                           // (the same in all waves of the XCD's workgroups)
+  if (rest_arguments().list.readers) {                   // uniform over the launch
+    // each wave has read the counters for itself: thread 0 signs off for all four behind the last of them (else
+    // the XCD's last reader zeroes them before a late wave, whose rows would stay as they are)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const RestList list = rest_arguments().list;
       int32_t* readers = list.readers + (blockIdx.x & 7) * kBucketWords;
       if (atomicAdd(readers, 1) == (int32_t)(gridDim.x >> 3) - 1) *readers = *list.count(blockIdx.x & 7, false) = *list.count(blockIdx.x & 7, true) = 0;
     }

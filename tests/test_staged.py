@@ -144,3 +144,30 @@ def test_staged_replay_behind_a_reset_and_captured():
             want_out = eager.replay(22, now, now_probs, 3, 8)
             for key in KEYS[:4]:
                 assert torch.equal(out[key], want_out[key]), (again, key)
+
+
+# all rows left over, in lists of 1024 rows an XCD (a wave a workgroup takes them) and of more (all four): every
+# wave of that launch has the lists' counts before they are zeroed for the next replay, so no row stays as it was
+@pytest.mark.parametrize("problems,steps", [(20, 25), (64, 30)])
+def test_every_row_left_over_is_drafted(problems, steps):
+    print("left over", problems, steps, flush=True)
+    dev = torch.device("cuda:0")
+    tokens, probs = (torch.from_numpy(x).to(dev) for x in _inputs(problems, 16, 1000, 2, 0.5, 3))
+    past, past_probs = tokens[:, :, :900].contiguous(), probs[:, :, :900].contiguous()
+    now, now_probs = (x[:, :, 900:900 + steps].permute(2, 0, 1).contiguous() for x in (tokens, probs))
+    outs = []
+    for per_launch in (1, 0):
+        ix = binding.Index(problems, 16, 1000, 2, 3, 8, 1.0, 0, binding.MATCH_INDEX, device=dev)
+        if per_launch:
+            ix.set_steps_per_launch(per_launch)
+        for _ in range(1 if per_launch else 6):
+            ix.reset()
+            ix.append(past, past_probs)
+            out = {"tokens": torch.full((steps, problems, 16, 8), -7, dtype=torch.int32, device=dev),
+                   "length": torch.full((steps, problems, 16), -7, dtype=torch.int32, device=dev),
+                   "token_scores": torch.full((steps, problems, 16, 8), -7.0, device=dev),
+                   "path_scores": torch.full((steps, problems, 16), -7.0, device=dev)}
+            ix.replay(steps, now, now_probs, 3, 8, out=out)
+            outs.append(out)
+    for out in outs[1:]:
+        _same(outs[:1], [out])
