@@ -223,9 +223,10 @@ __device__ __forceinline__ void gram_insert_group(int32_t* tbl, uint32_t mask, G
   const bool mine = (members >> lane & 1u) != 0;
   int32_t rank = (int32_t)__popcll(members & ((1ull << lane) - 1ull));   // among those without a slot
   int32_t left = (int32_t)__popcll(members);
-  for (; r0 <= mask; r0 += kWave) {
+  const uint32_t turns = gram_turns(mask);
+  for (; r0 < turns; r0 += kWave) {
     const uint32_t r = r0 + lane;
-    const int32_t fill = r <= mask ? gram_bucket(tbl, gh, r, mask)[0] : kBucketSlots;
+    const int32_t fill = r < turns ? gram_bucket(tbl, gh, r, mask)[0] : kBucketSlots;
     u64 m = wave_ballot(fill < kBucketSlots);
     while (m) {
       const int first = (int)__ffsll((long long)m) - 1;
@@ -268,7 +269,7 @@ __device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, G
     }
   };
   file_groups(kNear, kGroupLanes);
-  for (uint32_t r = kNear; r < kNear + 3u && r <= mask; ++r) {
+  for (uint32_t r = kNear; r < kNear + 3u && r < gram_turns(mask); ++r) {
     if (wave_ballot(open) == 0) return;
     int32_t* b = gram_bucket(gram, gh, r, mask);
     if (open && b[0] < kBucketSlots) {

@@ -51,6 +51,9 @@ __device__ __forceinline__ uint32_t gram_far(GramHash gh, uint32_t r, uint32_t m
 __device__ __forceinline__ uint32_t gram_index(GramHash gh, uint32_t r, uint32_t mask) {
   return r < kNear || mask < kBlock ? gram_near(gh, r, mask) : gram_far(gh, r, mask);
 }
+// Turns of a sequence, in which every bucket comes (a path's posting may be filed more than once, see file_positions_own,
+// so that more is filed than there are positions).
+__device__ __forceinline__ uint32_t gram_turns(uint32_t mask) { return mask < kBlock ? mask + 1u : mask + 1u + kNear; }
 __device__ __forceinline__ bool gram_again(uint32_t r, uint32_t mask) {
   if (r < kNear || mask < kBlock) return false;
   const uint32_t blocks = mask / kBlock, t = r - kNear;
@@ -71,11 +74,12 @@ __device__ __forceinline__ int32_t* gram_bucket_near(int32_t* tbl, GramHash gh, 
 // slots than there are positions.
 __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, GramHash gh,
                                                  uint32_t r0, int32_t pos, int lane) {
-  for (; r0 <= mask; r0 += kWave) {
+  const uint32_t turns = gram_turns(mask);
+  for (; r0 < turns; r0 += kWave) {
     uint32_t r = r0 + lane;
     const uint32_t near = gram_near(gh, r, mask), far = gram_far(gh, r, mask);   // (no branch: lanes have both)
     const uint32_t at = r < kNear || mask < kBlock ? near : far;
-    bool open = r <= mask && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
+    bool open = r < turns && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
     u64 m = wave_ballot(open);
     while (m) {
       int first = (int)__ffsll((long long)m) - 1;
@@ -371,9 +375,9 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
     for (int y = 0; y < kClaims; ++y) {
       bool looking = (todo >> y & 1u) != 0;
       const uint32_t in_block = mask < kBlock ? mask : kBlock - 1u, home = gh[y].h & mask & ~in_block;
-      const uint32_t near = mask < kBlock ? mask + 1u : kNear;
+      const uint32_t turns = gram_turns(mask), near = mask < kBlock ? turns : kNear;
       uint32_t turn = gh[y].h + gh[y].step;
-      for (uint32_t r = 1; r <= mask && wave_ballot(looking) != 0; ++r, turn += gh[y].step) {   // uniform over the wave
+      for (uint32_t r = 1; r < turns && wave_ballot(looking) != 0; ++r, turn += gh[y].step) {   // uniform over the wave
         uint32_t b = home | (turn & in_block);
         if (__builtin_expect(r >= near, 0)) b = gram_far(gh[y], r, mask);
         if (looking) {

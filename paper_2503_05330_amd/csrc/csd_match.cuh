@@ -519,22 +519,22 @@ __device__ __forceinline__ void lookup_with_windows(LDS& s, const Ctx& c, int32_
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const int sub = lane & 15;          // word of the bucket this lane reads
   const int grp = lane >> 4;          // which of the 4 buckets of a batch
-  const uint32_t n_buckets = c.bucket_mask + 1;
+  const uint32_t turns = gram_turns(c.bucket_mask);
   int32_t query_oldest_first[QC];     // [x] = Q[q - 1 - x]
 #pragma unroll
   for (int x = 0; x < QC; ++x) query_oldest_first[x] = pick_n<QC>(c.Q, c.q - 1 - x);
   uint32_t width = FIRST;             // buckets of this batch
-  for (uint32_t r0 = 0; r0 < n_buckets; r0 += width, width = 4) {
+  for (uint32_t r0 = 0; r0 < turns; r0 += width, width = 4) {
     consume_here(word);
     const bool in_batch = (uint32_t)grp < width;
-    if (!in_batch || r0 + grp >= n_buckets) word = -1;
+    if (!in_batch || r0 + grp >= turns) word = -1;
     int32_t count = __shfl(word, lane & ~15);
     bool full = count >= kBucketSlots;
-    bool seq_ends = wave_ballot(in_batch && (!full || r0 + grp >= n_buckets)) != 0;
+    bool seq_ends = wave_ballot(in_batch && (!full || r0 + grp >= turns)) != 0;
     int32_t next_word = -1;           // next batch: in flight while this one is processed
     if (!seq_ends) {
       uint32_t r = r0 + width + grp;
-      next_word = gram_bucket(tbl, gh, r < n_buckets ? r : 0u, c.bucket_mask)[sub];
+      next_word = gram_bucket(tbl, gh, r < turns ? r : 0u, c.bucket_mask)[sub];
     }
     bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count) && !gram_again(r0 + grp, c.bucket_mask);
     int32_t j = y.pos_path(word), e = y.pos_index(word), old_j = 0, new_j = 0;
@@ -969,7 +969,7 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const int sub = lane & 15;
   const int grp = lane >> 4;
-  const uint32_t n_buckets = c.bucket_mask + 1;
+  const uint32_t turns = gram_turns(c.bucket_mask);
   // variants 0 .. 3 and 4 .. 7: both batches of first buckets were requested together.  Buckets
   // are a third full on average, so the postings of the second batch nearly always find a
   // lane of their own among those that hold none of the first, and both are looked through at
@@ -1038,12 +1038,12 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
     if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0 || n_match > LIMIT) continue;   // uniform over the wave
     const GramHash gh = variant_hash(c.Q, c.q, chain);                // the same in every lane
     uint32_t r0 = 1;
-    int32_t tail = gram_bucket_near(tbl, gh, r0 + grp < n_buckets ? r0 + grp : 0u, c.bucket_mask)[sub];
-    for (; r0 < n_buckets; r0 += 4) {
+    int32_t tail = gram_bucket_near(tbl, gh, r0 + grp < turns ? r0 + grp : 0u, c.bucket_mask)[sub];
+    for (; r0 < turns; r0 += 4) {
       consume_here(tail);
-      if (r0 + grp >= n_buckets) tail = -1;
+      if (r0 + grp >= turns) tail = -1;
       uint32_t rn = r0 + 4 + grp;                                     // next batch: in flight meanwhile
-      int32_t next_tail = gram_bucket(tbl, gh, rn < n_buckets ? rn : 0u, c.bucket_mask)[sub];
+      int32_t next_tail = gram_bucket(tbl, gh, rn < turns ? rn : 0u, c.bucket_mask)[sub];
       bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail, gram_again(r0 + grp, c.bucket_mask));
       if (wave_ballot(!tail_full) != 0 || n_match > LIMIT) break;      // the chain ends in this batch
       tail = next_tail;
@@ -1077,17 +1077,17 @@ __device__ __forceinline__ void match_variants(const LDS& s, const Ctx& c, Sink&
   const int32_t chains = c.q + 1, shares = BLOCK / kWave / chains, chain = wave % chains, share = wave / chains;
   static_assert(BLOCK / kWave > CSD_MAX_QUERY_LEN, "a wave for every chain");
   if (share >= shares || !variant_is_new(c.Q, chain)) return;      // uniform over the wave
-  const uint32_t n_buckets = c.bucket_mask + 1;
+  const uint32_t turns = gram_turns(c.bucket_mask);
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const GramHash gh = variant_hash(c.Q, c.q, chain);
-  auto request = [&](uint32_t r) { return gram_bucket(tbl, gh, r < n_buckets ? r : 0u, c.bucket_mask)[sub]; };
+  auto request = [&](uint32_t r) { return gram_bucket(tbl, gh, r < turns ? r : 0u, c.bucket_mask)[sub]; };
   uint32_t r0 = 4u * (uint32_t)share;
   int32_t next = request(r0 + grp);
-  for (; r0 < n_buckets; r0 += 4u * (uint32_t)shares) {            // (past a chain's end: see above)
+  for (; r0 < turns; r0 += 4u * (uint32_t)shares) {            // (past a chain's end: see above)
     int32_t word = next;
     next = request(r0 + 4u * (uint32_t)shares + grp);              // in flight meanwhile
     consume_here(word);
-    if (r0 + grp >= n_buckets) word = -1;
+    if (r0 + grp >= turns) word = -1;
     bool full;
     bool cand = bucket_has_posting(word, lane, full) && !gram_again(r0 + grp, c.bucket_mask);
     const int32_t filed_as = word >> kVariantShift, pos = word & ((1 << kVariantShift) - 1);

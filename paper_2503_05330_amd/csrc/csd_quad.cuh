@@ -117,11 +117,12 @@ struct Filing {
     if (wave_ballot(open) != 0) look(1);
   }
   __device__ __forceinline__ void finish() {             // (what finds no slot in a full index is dropped)
-    for (uint32_t r = 1; r <= mask && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
+    const uint32_t turns = gram_turns(mask);
+    for (uint32_t r = 1; r < turns && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
       if (r > 1) look(r);
       uint32_t room = 0;
 #pragma unroll
-      for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x <= mask ? 1u << x : 0u;
+      for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x < turns ? 1u << x : 0u;
       while (wave_ballot(room != 0) != 0) {
         if (room != 0) {
           int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, mask);

@@ -179,3 +179,41 @@ def test_a_bulk_append_to_a_full_index_ends(edits):
         index.append(more)
     _same(ix.draft(k, L), fresh.draft(k, L))
     assert ix.status() == 0
+
+
+@pytest.mark.parametrize("paths,max_len", [(4, 64), (4, 128), (4, 256), (5, 700)])      # 32 .. 512 buckets
+@pytest.mark.parametrize("call", ["append", "step"])
+def test_a_gram_that_fills_its_index_takes_every_slot(paths, max_len, call):
+    """Replays of a single captured step file a gram again and again, until all slots but a few of its
+    index are taken: what is appended then finds those few, and is found there."""
+    print("every slot", paths, max_len, call, flush=True)
+    buckets = 4
+    while buckets * 8 < paths * max_len:
+        buckets *= 2
+    only = lambda *rows: _put(np.isin(np.arange(paths), rows).astype(np.int32))
+    past = _put(np.full((1, paths, 6), 7, dtype=np.int32))
+    others = _put(np.tile(np.array([7, 7, 7, 5, 6, 9, 8], dtype=np.int32), (1, paths, 1)))
+    token = past[:, :, 0].contiguous()
+
+    def last(ix):                                          # of path 0, from what the others append last
+        n = others.shape[2] if call == "append" else 3     # (no row but path 0, which passes over its own, asks for (777))
+        ix.append(others[:, :, :n].contiguous(), None, only(*range(1, paths)).reshape(1, paths) * n)
+        for t in range(n, others.shape[2]):
+            ix.step(others[:, :, t].contiguous(), None, only(*range(1, paths)).reshape(1, paths), 1, 3, 4)
+        out = ix.draft(3, 4)
+        return {key: out[key][0, 0] for key in KEYS}, ix.status()
+
+    make = lambda: binding.Index(1, paths, max_len, 10, 3, 4, 1.0, 0, binding.MATCH_INDEX, device="cuda:0")
+    ix, fresh = make(), make()
+    one = only(0).reshape(1, paths)
+    for index in (ix, fresh):
+        index.append(past, None, one * 6)
+    graph, _ = _captured(lambda: ix.step(token, None, one, 1, 3, 4))
+    fresh.step(token, None, one, 1, 3, 4)
+    # three of path 0's own before; of each other path (777), (775), (756), (569), and a rest
+    for _ in range(buckets * 15 - 3 - 4 * (paths - 1) - 4):
+        graph.replay()
+    torch.cuda.synchronize()
+    (got, status), (want, status1) = last(ix), last(fresh)
+    _same(got, want)
+    assert got["tokens"][:4].tolist() == [5, 6, 9, 8] and status == status1 == 0
