@@ -36,28 +36,29 @@ __device__ __forceinline__ GramHash gram_hash_end(uint32_t acc, int g) {
   uint32_t step = ((x * 0x27D4EB2Fu) >> 7) | 1u;
   return GramHash{h, step};
 }
-// Bucket r of a gram's sequence (mask: n_buckets - 1; step is odd).  Of the first kNear, or of a table of one block:
+// Bucket r of a gram's sequence (mask: n_buckets - 1; step is odd).  Of the first kNear, which in a table of fewer
+// buckets are all:
 constexpr uint32_t kBlock = 64, kNear = 32;
 __device__ __forceinline__ uint32_t gram_near(GramHash gh, uint32_t r, uint32_t mask) {
   return ((gh.h & ~(kBlock - 1u)) | ((gh.h + r * gh.step) & (kBlock - 1u))) & mask;
 }
-// Any: behind the first ones turn k through the blocks takes a bucket of each, the home block's last.  (That is bucket
-// k of the sequence again for k < kNear: an insert finds it full, a look-up passes it, see gram_again.)
+// Behind them: through the whole table by the odd step.  (The near buckets come again then: an insert finds them full, a
+// look-up passes them, see gram_again.  Two instructions, as in every row's way: block after block, with the home block's
+// last, it was seven, and thousands of rows a launch took 4 % longer.)
 __device__ __forceinline__ uint32_t gram_far(GramHash gh, uint32_t r, uint32_t mask) {
-  const uint32_t blocks = mask / kBlock, t = r - kNear, k = t >> __popc(blocks);   // (blocks: a mask of their numbers)
-  const uint32_t block = gh.h / kBlock + ((t & blocks) + 1u) * ((gh.step / kBlock) | 1u);
-  return ((block & blocks) * kBlock) | ((gh.h + k * gh.step) & (kBlock - 1u));
+  return (gh.h + (r - kNear) * gh.step) & mask;
 }
 __device__ __forceinline__ uint32_t gram_index(GramHash gh, uint32_t r, uint32_t mask) {
-  return r < kNear || mask < kBlock ? gram_near(gh, r, mask) : gram_far(gh, r, mask);
+  return r < kNear ? gram_near(gh, r, mask) : gram_far(gh, r, mask);
 }
-// Turns of a sequence, in which every bucket comes (a path's posting may be filed more than once, see file_positions_own,
-// so that more is filed than there are positions).
-__device__ __forceinline__ uint32_t gram_turns(uint32_t mask) { return mask < kBlock ? mask + 1u : mask + 1u + kNear; }
-__device__ __forceinline__ bool gram_again(uint32_t r, uint32_t mask) {
-  if (r < kNear || mask < kBlock) return false;
-  const uint32_t blocks = mask / kBlock, t = r - kNear;
-  return (t & blocks) == blocks && t >> __popc(blocks) < kNear;
+// Turns of a sequence, in which every bucket comes, also where more is filed than there are positions (see
+// file_positions_own): n_buckets, and kNear more where there are far ones.
+__device__ __forceinline__ uint32_t gram_turns(uint32_t mask) { return mask + 1u + (mask & kNear); }
+// Whether the bucket of turn r came before: one of the home block, from turns 32 .. 63 of every 64 (turn r is the block's
+// (r - 32) mod 64th in its own order, and the first 32 are the near ones).
+static_assert(kNear == 32 && kBlock == 64, "bit 5 of a turn");
+__device__ __forceinline__ bool gram_again(GramHash gh, uint32_t r, uint32_t mask) {
+  return r >= kNear && (r & kNear) != 0 && ((gram_far(gh, r, mask) ^ gh.h) & mask) < kBlock;
 }
 __device__ __forceinline__ int32_t* gram_bucket(int32_t* tbl, GramHash gh, uint32_t r,
                                                 uint32_t mask) {
@@ -68,18 +69,37 @@ __device__ __forceinline__ int32_t* gram_bucket_near(int32_t* tbl, GramHash gh, 
   return tbl + (int64_t)gram_near(gh, r, mask) * kBucketWords;
 }
 
-// General insert, by one whole wave: reads the fill counts of 64 buckets of
-// the sequence per round trip, starting at bucket r0, and claims a slot in the
-// first one that is not full.  Bounded by the table size; the tables hold more
-// slots than there are positions.
+// Word `sub` of bucket r0 + grp of a gram's sequence, for a look-up by batches of four buckets (r0: the batch's first,
+// uniform over the wave).  A bucket that came before is as one without postings that goes on; with SELECT the caller
+// passes over it.
+// SELECT: near or far without a branch, where registers are short (step_wave_many_kernel, 65536 rows 82.5 us, 92 with the
+// branch, whose other side needs a few at once); else the usual one alone on the way (one row 6.65 us, 6.9 without).
+template <bool SELECT = false>
+__device__ __forceinline__ int32_t gram_word(const int32_t* tbl, GramHash gh, uint32_t r0, int grp, int sub, uint32_t mask) {
+  uint32_t r = r0 + (uint32_t)grp;
+  if constexpr (SELECT) return tbl[(int64_t)gram_index(gh, r, mask) * kBucketWords + sub];
+  if (__builtin_expect(r0 + 4u <= kNear, 1)) return tbl[(int64_t)gram_near(gh, r, mask) * kBucketWords + sub];
+  consume_here(r);                                      // (else what follows is prepared ahead of the caller's loop)
+  consume_here(gh.h);
+  consume_here(gh.step);
+  int32_t word = sub == 0 ? kBucketSlots : -1;
+  if (!gram_again(gh, r, mask)) word = tbl[(int64_t)gram_index(gh, r, mask) * kBucketWords + sub];
+  return word;
+}
+
+// General insert, by one whole wave: reads the fill counts of the sequence's buckets from r0 on, the first few and then
+// 64 per round trip, and claims a slot in the first one that is not full.  Bounded by the table size; the
+// tables hold more slots than there are positions.
+// (The first few: of the rows whose first bucket is full most find one of the next open; 64 at once fetched as many
+// lines, 4096 problems at full history 129 us a step for 123.)
+constexpr uint32_t kInsertFirst = 4;
 __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, GramHash gh,
                                                  uint32_t r0, int32_t pos, int lane) {
-  const uint32_t turns = gram_turns(mask);
-  for (; r0 < turns; r0 += kWave) {
-    uint32_t r = r0 + lane;
-    const uint32_t near = gram_near(gh, r, mask), far = gram_far(gh, r, mask);   // (no branch: lanes have both)
-    const uint32_t at = r < kNear || mask < kBlock ? near : far;
-    bool open = r < turns && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
+  const uint32_t turns = gram_turns(mask), few = turns < kInsertFirst ? turns : kInsertFirst;
+  while (r0 < turns) {                                  // uniform over the wave
+    const uint32_t r = r0 + lane, end = r0 < few ? few : turns;
+    const uint32_t at = gram_index(gh, r, mask);
+    bool open = r < end && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
     u64 m = wave_ballot(open);
     while (m) {
       int first = (int)__ffsll((long long)m) - 1;
@@ -93,6 +113,7 @@ __device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, Gr
       }
       m &= m - 1;                                       // filled up meanwhile: next open bucket
     }
+    r0 = r0 < few ? few : r0 + kWave;
   }
 }
 

@@ -665,9 +665,12 @@ __global__ __launch_bounds__(step_wave_threads(FUZZY)) void step_wave_kernel(Ind
 
 // The same for launches of thousands of rows (exact matching, drafts of up to 8 tokens), where
 // the number of rows resident on a CU bounds the throughput: compiled for eight waves per SIMD
-// (at most 64 registers per lane), with the small on-chip layout: sixteen rows per CU.
+// (at most 64 registers per lane), with the small on-chip layout: sixteen rows per CU.  (Registers by number, of
+// which the attribute counts half: asked for by waves the compiler gives a wave 80 scalar registers, eight
+// arguments more are spilled and read back all over the kernel; with 102 a SIMD has seven waves.  65536 rows
+// from empty histories 82.5 us a step, at full histories 122.3; with 102 91.4 and 137.)
 template <int QC>
-__global__ __launch_bounds__(step_wave_threads(false)) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ __launch_bounds__(step_wave_threads(false)) __attribute__((amdgpu_num_vgpr(32), amdgpu_num_sgpr(96)))
 void step_wave_many_kernel(IndexView ix, StepIn in, DraftArgs a) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs)>();
   step_wave_body<8, false, LdsWaveSmall, false, QC, false>(ix, in, a, NoTail{});

@@ -530,13 +530,11 @@ __device__ __forceinline__ void lookup_with_windows(LDS& s, const Ctx& c, int32_
     if (!in_batch || r0 + grp >= turns) word = -1;
     int32_t count = __shfl(word, lane & ~15);
     bool full = count >= kBucketSlots;
-    bool seq_ends = wave_ballot(in_batch && (!full || r0 + grp >= turns)) != 0;
+    bool seq_ends = wave_ballot(in_batch && !full) != 0;   // (behind the sequence's last, too)
     int32_t next_word = -1;           // next batch: in flight while this one is processed
-    if (!seq_ends) {
-      uint32_t r = r0 + width + grp;
-      next_word = gram_bucket(tbl, gh, r < turns ? r : 0u, c.bucket_mask)[sub];
-    }
-    bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count) && !gram_again(r0 + grp, c.bucket_mask);
+    if (!seq_ends) next_word = gram_word<FIRST == 1>(tbl, gh, r0 + width, grp, sub, c.bucket_mask);
+    bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count);
+    if (FIRST == 1 && __builtin_expect(r0 + 4u > kNear, 0)) cand = cand && !gram_again(gh, r0 + grp, c.bucket_mask);
     int32_t j = y.pos_path(word), e = y.pos_index(word), old_j = 0, new_j = 0;
     cand = cand && j != (GENERAL ? c.skip : c.i) && j < y.N;
     if (cand) {
@@ -942,14 +940,14 @@ __device__ __forceinline__ void consume_variant_postings(LDS& s, const Ctx& c, i
   }
 }
 
-// One batch by position: this lane's word of its group's bucket (again: which has been looked
-// through before).  Returns whether the group's bucket was full.
+// One batch by position: this lane's word of its group's bucket.  Returns whether the
+// group's bucket was full.
 template <int LCAP, int K, class LDS>
 __device__ __forceinline__ bool consume_variant_bucket(LDS& s, const Ctx& c, int32_t L,
                                                        int32_t win_cap, int32_t& n_match,
-                                                       int32_t my_u, int32_t word, bool again) {
+                                                       int32_t my_u, int32_t word) {
   bool full;
-  const bool cand = bucket_has_posting(word, c.tid, full) && !again;
+  const bool cand = bucket_has_posting(word, c.tid, full);
   consume_variant_postings<LCAP, K>(s, c, L, win_cap, n_match, my_u, word, cand);
   return full;
 }
@@ -1038,13 +1036,12 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
     if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0 || n_match > LIMIT) continue;   // uniform over the wave
     const GramHash gh = variant_hash(c.Q, c.q, chain);                // the same in every lane
     uint32_t r0 = 1;
-    int32_t tail = gram_bucket_near(tbl, gh, r0 + grp < turns ? r0 + grp : 0u, c.bucket_mask)[sub];
+    int32_t tail = gram_word(tbl, gh, r0, grp, sub, c.bucket_mask);
     for (; r0 < turns; r0 += 4) {
       consume_here(tail);
       if (r0 + grp >= turns) tail = -1;
-      uint32_t rn = r0 + 4 + grp;                                     // next batch: in flight meanwhile
-      int32_t next_tail = gram_bucket(tbl, gh, rn < turns ? rn : 0u, c.bucket_mask)[sub];
-      bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail, gram_again(r0 + grp, c.bucket_mask));
+      int32_t next_tail = gram_word(tbl, gh, r0 + 4, grp, sub, c.bucket_mask);   // next batch: in flight meanwhile
+      bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail);
       if (wave_ballot(!tail_full) != 0 || n_match > LIMIT) break;      // the chain ends in this batch
       tail = next_tail;
     }
@@ -1080,16 +1077,16 @@ __device__ __forceinline__ void match_variants(const LDS& s, const Ctx& c, Sink&
   const uint32_t turns = gram_turns(c.bucket_mask);
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const GramHash gh = variant_hash(c.Q, c.q, chain);
-  auto request = [&](uint32_t r) { return gram_bucket(tbl, gh, r < turns ? r : 0u, c.bucket_mask)[sub]; };
+  auto request = [&](uint32_t first) { return gram_word(tbl, gh, first, grp, sub, c.bucket_mask); };
   uint32_t r0 = 4u * (uint32_t)share;
-  int32_t next = request(r0 + grp);
-  for (; r0 < turns; r0 += 4u * (uint32_t)shares) {            // (past a chain's end: see above)
+  int32_t next = request(r0);
+  for (; r0 < turns; r0 += 4u * (uint32_t)shares) {                // (past a chain's end: see above)
     int32_t word = next;
-    next = request(r0 + 4u * (uint32_t)shares + grp);              // in flight meanwhile
+    next = request(r0 + 4u * (uint32_t)shares);                    // in flight meanwhile
     consume_here(word);
     if (r0 + grp >= turns) word = -1;
     bool full;
-    bool cand = bucket_has_posting(word, lane, full) && !gram_again(r0 + grp, c.bucket_mask);
+    bool cand = bucket_has_posting(word, lane, full);
     const int32_t filed_as = word >> kVariantShift, pos = word & ((1 << kVariantShift) - 1);
     const int32_t j = y.pos_path(pos), e = y.pos_index(pos);
     int32_t tv[K + 1], old_j = 0, new_j = 0;

@@ -218,3 +218,38 @@ def test_grams_that_fill_their_home_block(problems, paths, max_len, query, edits
     for key in ("tokens", "length", "token_scores", "path_scores"):
         assert torch.equal(draft[key], draft1[key]), key
     assert status == status1 == 0 and int(matches[1][-1]) > 100
+
+
+# a row whose matches lie behind a gram's full home block: its own path, which it passes over, has that gram hundreds of
+# times.  A row's step with its first four buckets at once, thousands of rows (a bucket first), one edit
+@pytest.mark.parametrize("problems,paths,max_len,query,edits", [
+    (1, 8, 800, 3, 0),
+    (2, 40, 700, 6, 0),
+    (300, 8, 700, 3, 0),
+    (300, 7, 1300, 5, 0),
+    (2, 8, 800, 3, 1),
+])
+def test_steps_whose_matches_lie_behind_a_full_home_block(problems, paths, max_len, query, edits):
+    print("behind the block", problems, paths, max_len, query, edits, flush=True)
+    rng = np.random.default_rng(problems + paths)
+    n, n_steps = max_len - 40, 6
+    tokens = rng.integers(10, 5000, size=(problems, paths, max_len)).astype(np.int32)
+    tokens[:, 0] = 7                                                       # n postings of it, 15 to a bucket
+    for at in range(n - 60, n - 20, 20):
+        tokens[:, 1:, at:at + query + 1] = 7                               # ... and a few with other tokens behind
+        tokens[:, 1:, at + query + 1:at + query + 4] = rng.integers(10, 14, size=(problems, paths - 1, 3))
+    tokens[:, 1::2, n:n + n_steps] = 7
+    assert (n - 60) > 15 * 32 + query
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a).astype(np.int32)).to("cuda:0")
+    outs = []
+    for flags in (binding.MATCH_INDEX, binding.MATCH_SCAN):
+        ix = binding.Index(problems, paths, max_len, 5000, query, 8, 1.0, 0, flags, device="cuda:0", max_edits=edits)
+        ix.append(put(tokens[:, :1, :n].repeat(paths, axis=1)), None,
+                  put(np.where(np.arange(paths) == 0, n - 60, 0)[None].repeat(problems, axis=0)))
+        ix.append(put(tokens[:, :, :n]), None, put(np.where(np.arange(paths) == 0, 0, n)[None].repeat(problems, axis=0)))
+        outs.append([ix.step(put(tokens[:, :, t]), None, None, 1, query, 8) for t in range(n, n + n_steps)] + [ix.draft(query, 8)])
+        assert ix.status() == 0
+    for a, b in zip(*outs):
+        for key in ("tokens", "length", "token_scores", "path_scores"):
+            assert torch.equal(a[key], b[key]), key
+    assert int(outs[0][0]["length"][:, 0].min()) > 0 and int(outs[0][0]["tokens"][:, 0].max()) >= 10
