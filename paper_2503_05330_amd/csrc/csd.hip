@@ -160,11 +160,12 @@ bool own_problem(int64_t P, int64_t c, int64_t b, bool one_edit) {
 
 // Postings of an append from which they may be sorted by bins of buckets (sorted_append), and postings that an
 // index holds up to which there is scratch memory for it (12 to 24 bytes for each).
+// (Exact appends: bin_least is more than they, from 196608 postings of one problem on.)
 constexpr int64_t kBinPostings = 1 << 17, kBinPostingsOneEdit = 1 << 19, kMostBinPostings = 1 << 22;
 int64_t bin_postings(bool one_edit) { return one_edit ? kBinPostingsOneEdit : kBinPostings; }
 // Bins of a problem, so that a workgroup for each fills the chip, and their least size.
 constexpr int32_t kBinsWanted = 256, kBinBucketsLog2Least = 6;
-static_assert(1 << kBinBucketsLog2Least >= kBlock, "a gram's home block within a bin");
+static_assert(kMostBinPostings / 8 <= 1 << kBinStep && kBinBuckets <= 1 << (31 - kBinStep), "a record's bucket and step");
 // Postings of an append to a bin, from which it pays.
 int64_t bin_least(bool one_edit) { return one_edit ? 256 : 768; }
 
@@ -175,16 +176,17 @@ int64_t bin_least(bool one_edit) { return one_edit ? 256 : 768; }
 // empty, by Zipf's law and all alike: 1 problem of 64 paths, 4096 tokens 90 / 39, 32; 2048, 48 / 27, 26; 1024 (3.3e5
 // postings) 28, 22 / 23, 22; 32 paths, 1024 (1.6e5) 15, 14 / 19, 18, 2 problems (3.3e5) 23, 22 / 24, 24.  12 problems of 32
 // paths, 2048 tokens (1280 to a bin) 194 / 92; 512 (320) 67 / 63; 24 of 16, 1024 (320) 131 / 105; 512 (160) 67 / 102 (these
-// before sequences kept to home blocks, which took a fifth off the sorted form).  Exact: 64 paths, 4096 tokens (1024 to a
+// before sequences kept to home blocks, which took a fifth off the sorted form, and more where the blocks are the bins: 64
+// paths, 4096 tokens, paths that agree in all but 20 %, 5 %, exact 107, 256 / 25, 48, one edit 169, 322 / 48, 92).  Exact: 64 paths, 4096 tokens (1024 to a
 // bin): 1 problem 24 / 21, of 3200 tokens 19.5 / 18.4, 2 41 / 31, 4 70 / 47, 16 247 / 135; 2048 tokens (512): 1 13.0 / 13.4, 4
-// 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.  Where own_problem applies too it comes
-// first (24 problems of 16 paths, 2048 tokens, one edit, a workgroup per problem / sorted: 147 / 123).
+// 28 / 34, 16 93 / 90; 32 paths of 2048 (512): 8 31 / 35, 16 57 / 59.  It comes first where own_problem applies
+// too (20 problems of 16 paths, 2048 tokens, one edit, a workgroup per problem / sorted: 172 / 113, 285 / 149).
 bool sorted_append(int64_t P, int64_t c, int64_t bins, bool one_edit) {
   return bins > 0 && P * c >= bin_postings(one_edit) && c >= bin_least(one_edit) * bins;
 }
 
-// Whether any append to such problems is sorted: own_problem, which is asked first, says yes to all longer ones
-// where it does to one, so the shortest that the sorted form would take decides.
+// Whether appends to such problems are sorted: not where own_problem says yes to the shortest that the sorted form would
+// take, and so to all.  (Home blocks, which the sorted form needs, cost the other one up to a half.)
 bool ever_sorted(const csd_config* c, int64_t buckets, int64_t bins) {
   const bool one_edit = c->max_edits > 0;
   const int64_t of_token = (int64_t)c->n_paths * (one_edit ? c->max_query_len + 1 : 1);
@@ -377,20 +379,27 @@ void launch_append(const csd_index* h, const StepIn& in, bool maybe_empty, hipSt
   const IndexView v = view_in_place(h);
   const int64_t rows = (int64_t)v.P * v.N;
   const bool q4 = v.kmax <= 4;
-  const int64_t n_buckets = (int64_t)v.bucket_mask + 1;
+  const int64_t n_buckets = (int64_t)v.buckets.mask + 1;
   const int64_t postings = (int64_t)v.N * in.n * (v.eps > 0 ? v.kmax + 1 : 1);   // of a problem
-  if (h->indexed && own_problem(v.P, postings, n_buckets, v.eps > 0)) {
-    const bool table = n_buckets <= kTableBuckets;
-    auto* kernel =
-        v.eps > 0 ? (table ? (q4 ? append_problem_kernel<true, 4, true> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, true>)
-                           : (q4 ? append_problem_kernel<true, 4, false> : append_problem_kernel<true, CSD_MAX_QUERY_LEN, false>))
-                  : (table ? (q4 ? append_problem_kernel<false, 4, true> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, true>)
-                           : (q4 ? append_problem_kernel<false, 4, false> : append_problem_kernel<false, CSD_MAX_QUERY_LEN, false>));
+  const bool sorted = !in.counts && in.n <= v.max_len && sorted_append(v.P, postings, h->bins.bins, v.eps > 0);
+  if (h->indexed && !sorted && own_problem(v.P, postings, n_buckets, v.eps > 0)) {
+    const bool blocks = v.buckets.mask > v.buckets.block, table = !blocks && n_buckets <= kTableBuckets;
+    auto of = [&](auto fuzzy, auto qc) {
+      constexpr bool FUZZY = fuzzy();
+      constexpr int QC = qc();
+      return table    ? append_problem_kernel<FUZZY, QC, true, false>
+             : blocks ? append_problem_kernel<FUZZY, QC, false, true>
+                      : append_problem_kernel<FUZZY, QC, false, false>;
+    };
+    const std::integral_constant<int, 4> four;
+    const std::integral_constant<int, CSD_MAX_QUERY_LEN> most;
+    auto* kernel = v.eps > 0 ? (q4 ? of(std::true_type{}, four) : of(std::true_type{}, most))
+                             : (q4 ? of(std::false_type{}, four) : of(std::false_type{}, most));
     const size_t lds = n_buckets * sizeof(int32_t) * (table ? 1 + kBucketWords : 1);
     kernel<<<(uint32_t)v.P, 1024, lds, st>>>(v, in, maybe_empty ? 1 : 0, h->meta[h->cur ^ 1]);
     return;
   }
-  if (!in.counts && in.n <= v.max_len && sorted_append(v.P, postings, h->bins.bins, v.eps > 0)) {
+  if (sorted) {
     Bins b = h->bins;
     b.ends = h->meta[h->cur ^ 1];
     b.chunks = (in.n + kBinSource - 1) / kBinSource;
@@ -532,7 +541,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
   h->view.status = reinterpret_cast<uint32_t*>(base + l.status);
   h->indexed = uses_index(cfg);
   h->view.gram = h->indexed ? reinterpret_cast<int32_t*>(base + l.gram) : nullptr;
-  h->view.bucket_mask = h->indexed ? l.n_buckets - 1 : 0;
+  h->view.buckets = h->indexed ? Buckets{l.n_buckets - 1, l.n_buckets - 1} : Buckets{0, 0};
   h->gram_words = l.gram_words;
   h->slices = ScanSlices{l.n_slices, nullptr, nullptr};
   if (l.n_slices > 1) {
@@ -553,6 +562,7 @@ int csd_create(const csd_config* cfg, void* d_workspace, size_t workspace_bytes,
     h->bins.variants = cfg->max_edits > 0 ? cfg->max_query_len + 1 : 1;
     h->bins.bins = l.n_bins;
     h->bins.buckets_log2 = l.bin_log2;
+    h->view.buckets.block = (1u << l.bin_log2) - 1u;     // (a workgroup's of bin_file_kernel)
   }
   h->done = whole ? reinterpret_cast<int32_t*>(base + l.done) : nullptr;
   h->view.P = cfg->n_problems;

@@ -28,7 +28,7 @@ constexpr int32_t kRestGroups = 512;   // workgroups of bin_rest_kernel per prob
 struct BinRecord {
   int32_t bucket, posting;      // bucket: above kBinStep bits the gram's step within its home block
 };
-constexpr int kBinStep = 24;
+constexpr int kBinStep = 20;
 struct Bins {
   BinRecord* records;           // [P][sources][kBinSource * variants]
   uint32_t* runs;               // [P][bins][sources]: a bin's records of a source, first << 16 | how many
@@ -98,8 +98,8 @@ __global__ __launch_bounds__(kBinSource) void bin_sort_kernel(IndexView ix, Step
     bool on = x.filed(ix, cnt) && v <= ix.kmax;
     if (v >= 2) on = on && x.G[v - 1] != x.G[v - 2];     // (else the same string as variant v - 1)
     const GramHash gh = variant_hash(x.G, ix.kmax, v);
-    at[v] = (int32_t)(gh.h & ix.bucket_mask);
-    step[v] = (int32_t)(gh.step & (kBlock - 1u));
+    at[v] = (int32_t)(gh.h & ix.buckets.mask);
+    step[v] = (int32_t)(gh.step & ix.buckets.block);
     live |= on ? 1u << v : 0u;
   }
   __syncthreads();
@@ -133,7 +133,7 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
   const int tid = (int)threadIdx.x;
   const int32_t p = (int32_t)blockIdx.x / b.bins, bin = (int32_t)blockIdx.x - p * b.bins;
   const int32_t buckets = 1 << b.buckets_log2;
-  int32_t* gram = ix.gram + ((int64_t)p * ((int64_t)ix.bucket_mask + 1) + ((int64_t)bin << b.buckets_log2)) * kBucketWords;
+  int32_t* gram = ix.gram + ((int64_t)p * ((int64_t)ix.buckets.mask + 1) + ((int64_t)bin << b.buckets_log2)) * kBucketWords;
   const uint32_t run = tid < b.sources ? b.runs[(int64_t)blockIdx.x * b.sources + tid] : 0u;
   int32_t lens = 1;
   if (maybe_empty) {                                     // uniform over the launch
@@ -174,7 +174,7 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
       for (int y = 0; y < kAtOnce; ++y) {
         if (f0 + y * 1024 >= total) continue;
         const int32_t local = rec[y].bucket & (buckets - 1);
-        // the first bucket, then the others near (all this bin's) four at a time
+        // the first bucket, then the others near (all this bin's) eight at a time
         const GramHash gh{(uint32_t)local, (uint32_t)rec[y].bucket >> kBinStep};
         bool open = true;
         auto claim = [&](uint32_t at) {
@@ -190,7 +190,7 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
           int32_t filled[kTogether];
 #pragma unroll
           for (uint32_t z = 0; z < kTogether; ++z) {
-            at[z] = gram_near(gh, r + z, (uint32_t)buckets - 1u);
+            at[z] = (gh.h + (r + z) * gh.step) & ((uint32_t)buckets - 1u);
             filled[z] = r + z < kNear ? fill[at[z]] : kBucketSlots;
           }
 #pragma unroll
@@ -218,20 +218,20 @@ static __global__ __launch_bounds__(1024) void bin_file_kernel(IndexView ix, Bin
 
 // gram_insert_from for the postings of several lanes (`members`) that have one gram: a claim takes as many slots
 // of a bucket as it is seen to have left.  (Frequent grams: hundreds of waves after the same buckets.)
-__device__ __forceinline__ void gram_insert_group(int32_t* tbl, uint32_t mask, GramHash gh, uint32_t r0,
+__device__ __forceinline__ void gram_insert_group(int32_t* tbl, Buckets tb, GramHash gh, uint32_t r0,
                                                   u64 members, int32_t posting, int lane) {
   const bool mine = (members >> lane & 1u) != 0;
   int32_t rank = (int32_t)__popcll(members & ((1ull << lane) - 1ull));   // among those without a slot
   int32_t left = (int32_t)__popcll(members);
-  const uint32_t turns = gram_turns(mask);
+  const uint32_t turns = gram_turns(tb);
   for (; r0 < turns; r0 += kWave) {
     const uint32_t r = r0 + lane;
-    const int32_t fill = r < turns ? gram_bucket(tbl, gh, r, mask)[0] : kBucketSlots;
+    const int32_t fill = r < turns ? gram_bucket(tbl, gh, r, tb)[0] : kBucketSlots;
     u64 m = wave_ballot(fill < kBucketSlots);
     while (m) {
       const int first = (int)__ffsll((long long)m) - 1;
       m &= m - 1;
-      int32_t* b = gram_bucket(tbl, gh, r0 + (uint32_t)first, mask);
+      int32_t* b = gram_bucket(tbl, gh, r0 + (uint32_t)first, tb);
       const int32_t open = kBucketSlots - __builtin_amdgcn_readlane(fill, first);
       const int32_t want = open < left ? open : left;
       int32_t c = 0;
@@ -253,7 +253,7 @@ __device__ __forceinline__ void gram_insert_group(int32_t* tbl, uint32_t mask, G
 // (us, bin_rest_kernel of 64 paths x 4096 tokens with one edit, when all that found their first bucket full came
 // here: a wave inserting posting by posting 65 with a lane for every one, 31 with them spread over the waves, in groups 23.)
 constexpr int kGroupLanes = 4;
-__device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, GramHash gh, int32_t posting,
+__device__ __forceinline__ void file_along_chain(int32_t* gram, Buckets tb, GramHash gh, int32_t posting,
                                                  bool open, int lane) {
   auto file_groups = [&](uint32_t r0, int least) {
     u64 left = wave_ballot(open);
@@ -264,14 +264,14 @@ __device__ __forceinline__ void file_along_chain(int32_t* gram, uint32_t mask, G
       const u64 same = wave_ballot(gh.h == g.h && gh.step == g.step) & left;
       left &= ~same;
       if (__popcll(same) < least) continue;
-      gram_insert_group(gram, mask, g, r0, same, posting, lane);
+      gram_insert_group(gram, tb, g, r0, same, posting, lane);
       if (same >> lane & 1u) open = false;
     }
   };
   file_groups(kNear, kGroupLanes);
-  for (uint32_t r = kNear; r < kNear + 3u && r < gram_turns(mask); ++r) {
+  for (uint32_t r = kNear; r < kNear + 3u && r < gram_turns(tb); ++r) {
     if (wave_ballot(open) == 0) return;
-    int32_t* b = gram_bucket(gram, gh, r, mask);
+    int32_t* b = gram_bucket(gram, gh, r, tb);
     if (open && b[0] < kBucketSlots) {
       const int32_t c = atomicAdd(b, 1);
       if (c < kBucketSlots) {
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void bin_rest_kernel(IndexView ix, Bins b) {
     at += counts[y];
   }
   __syncthreads();
-  int32_t* gram = ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords;
+  int32_t* gram = ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords;
   // few to a wave where there are few: what a chain's first buckets do not take a wave files one by one
   constexpr int32_t kWaves = kRestGroups * (256 / kWave);
   int32_t each = (total + kWaves - 1) / kWaves;
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(256) void bin_rest_kernel(IndexView ix, Bins b) {
     int32_t G[QC];
 #pragma unroll
     for (int a = 0; a < QC; ++a) G[a] = tok[e - 1 - (a < ix.kmax ? a : 0)];
-    file_along_chain(gram, ix.bucket_mask, variant_hash(G, ix.kmax, v), posting, on, lane);
+    file_along_chain(gram, ix.buckets, variant_hash(G, ix.kmax, v), posting, on, lane);
   }
 }
 

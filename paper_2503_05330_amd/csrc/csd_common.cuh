@@ -283,6 +283,15 @@ __device__ __forceinline__ void block_sync() {
 
 // ---------------------------------------------------------------- device state
 
+// The buckets of a problem's index: how many, and of a gram's home block (see gram_near), both powers of two, less 1.
+// block == mask: no home blocks.  An index has them where bulk appends are sorted by bins (csd_bins.cuh), a block a bin.
+// Elsewhere they cost: blocks fill unevenly, and a workgroup that files a problem waits for its longest chain (us, whole
+// table / blocks of 64, paths that agree in all but 20 %, 5 %: 1024 problems of 16 x 1024 133, 167 / 136, 196, 256 of 64 x
+// 64 25, 49 / 26, 69, 24 of 16 x 2048 with one edit 173, 292 / 206, 479; with a thread per position no difference).
+struct Buckets {
+  uint32_t mask, block;
+};
+
 struct IndexView {              // device state inside the caller's workspace
   int32_t* tok;                 // [P][N][max_len] token histories
   uint32_t* pq;                 // [P][N][max_len] quantised generation probabilities
@@ -291,7 +300,7 @@ struct IndexView {              // device state inside the caller's workspace
   int32_t* meta_new;            // same rows after it (may alias meta_old when nothing else reads)
   uint32_t* status;             // sticky CSD_STATUS_* bits
   int32_t* gram;                // kmax-gram index [P][n_buckets][16], or null (scan mode)
-  uint32_t bucket_mask;         // n_buckets - 1 (power of two)
+  Buckets buckets;
   int32_t meta_stride;          // ints per meta row: 1 + tail_len rounded up to a multiple of 4
   int32_t tail_len;             // newest tokens kept in a meta row: kmax, or kmax + 1 when the
                                 //   index serves one-edit matching (a match may look one further back)
@@ -444,7 +453,7 @@ typedef LdsT<2048, 4096, 2048, kScanBlock / kWave, kLenCache, 2048> LdsScanPair;
 struct Ctx {                    // one (problem, query path)
   Paths y;
   const int32_t* gram;          // this problem's index tables, or null
-  uint32_t bucket_mask;
+  Buckets buckets;
   int32_t kmax;
   int32_t i;                    // query path
   int32_t skip;                 // the path that is not searched: i, or -1 (own history included)
@@ -548,8 +557,8 @@ __device__ __forceinline__ Ctx make_ctx(const IndexView& ix, const StepIn& in, i
   c.y.sc = (in.n && in.counts) ? in.counts + (int64_t)p * ix.N : nullptr;
   c.y.N = ix.N;
   c.y.max_len = ix.max_len;
-  c.gram = ix.gram ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
-  c.bucket_mask = ix.bucket_mask;
+  c.gram = ix.gram ? ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords : nullptr;
+  c.buckets = ix.buckets;
   c.kmax = ix.kmax;
   c.eps = ix.eps;
   c.len_i = 0;

@@ -6,11 +6,11 @@
 // decode loop only issues while a path is shorter than kmax, are matched by
 // scan).  A posting (j, e) — "the kmax tokens before index e of path j" — is
 // stored under the hash of those tokens when token e is appended, so a query
-// finds its matches (Eq. 3) without scanning histories.  A gram's probe sequence
-// starts with kNear buckets of its home block of kBlock (a workgroup that has the
-// block in LDS files nearly every posting there, whatever else is appended
-// meanwhile) and goes on through all blocks, so that a frequent gram fills half of
-// one block at most.  An insert goes into the first bucket of the sequence that is
+// finds its matches (Eq. 3) without scanning histories.  Bucket r of a gram's
+// probe sequence is (h + r * step) mod n_buckets with an odd step.  In an index with home blocks (see Buckets)
+// the first kNear are the home block's, by the same step (a workgroup that has the block in LDS files nearly
+// every posting there, whatever else is appended meanwhile), and then the sequence goes through the whole
+// table, so that a frequent gram fills kNear buckets of one block.  An insert goes into the first bucket of the sequence that is
 // not full, so a lookup may stop at the first bucket that is not full.  Hash collisions are harmless:
 // every posting is verified against the history before it counts.
 #pragma once
@@ -36,54 +36,55 @@ __device__ __forceinline__ GramHash gram_hash_end(uint32_t acc, int g) {
   uint32_t step = ((x * 0x27D4EB2Fu) >> 7) | 1u;
   return GramHash{h, step};
 }
-// Bucket r of a gram's sequence (mask: n_buckets - 1; step is odd).  Of the first kNear, which in a table of fewer
-// buckets are all:
-constexpr uint32_t kBlock = 64, kNear = 32;
-__device__ __forceinline__ uint32_t gram_near(GramHash gh, uint32_t r, uint32_t mask) {
-  return ((gh.h & ~(kBlock - 1u)) | ((gh.h + r * gh.step) & (kBlock - 1u))) & mask;
+// Bucket r of a gram's sequence (step is odd).  Of the first kNear ones, and where there are no home blocks of all:
+constexpr uint32_t kNear = 32;
+__device__ __forceinline__ uint32_t gram_near(GramHash gh, uint32_t r, Buckets t) {
+  return ((gh.h & ~t.block) | ((gh.h + r * gh.step) & t.block)) & t.mask;
 }
+// What precedes the way through the whole table: the near buckets, where there are others.
+__device__ __forceinline__ uint32_t gram_ahead(Buckets t) { return t.mask > t.block ? kNear : 0u; }
 // Behind them: through the whole table by the odd step.  (The near buckets come again then: an insert finds them full, a
-// look-up passes them, see gram_again.  Two instructions, as in every row's way: block after block, with the home block's
+// look-up passes them, see gram_again.  Few instructions, as in every row's way: block after block, with the home block's
 // last, it was seven, and thousands of rows a launch took 4 % longer.)
-__device__ __forceinline__ uint32_t gram_far(GramHash gh, uint32_t r, uint32_t mask) {
-  return (gh.h + (r - kNear) * gh.step) & mask;
+__device__ __forceinline__ uint32_t gram_far(GramHash gh, uint32_t r, Buckets t) {
+  return (gh.h + (r - gram_ahead(t)) * gh.step) & t.mask;
 }
-__device__ __forceinline__ uint32_t gram_index(GramHash gh, uint32_t r, uint32_t mask) {
-  return r < kNear ? gram_near(gh, r, mask) : gram_far(gh, r, mask);
+__device__ __forceinline__ uint32_t gram_index(GramHash gh, uint32_t r, Buckets t) {
+  return r < kNear ? gram_near(gh, r, t) : gram_far(gh, r, t);
 }
 // Turns of a sequence, in which every bucket comes, also where more is filed than there are positions (see
-// file_positions_own): n_buckets, and kNear more where there are far ones.
-__device__ __forceinline__ uint32_t gram_turns(uint32_t mask) { return mask + 1u + (mask & kNear); }
-// Whether the bucket of turn r came before: one of the home block, from turns 32 .. 63 of every 64 (turn r is the block's
-// (r - 32) mod 64th in its own order, and the first 32 are the near ones).
-static_assert(kNear == 32 && kBlock == 64, "bit 5 of a turn");
-__device__ __forceinline__ bool gram_again(GramHash gh, uint32_t r, uint32_t mask) {
-  return r >= kNear && (r & kNear) != 0 && ((gram_far(gh, r, mask) ^ gh.h) & mask) < kBlock;
+// file_positions_own).
+__device__ __forceinline__ uint32_t gram_turns(Buckets t) { return t.mask + 1u + gram_ahead(t); }
+// Whether the bucket of turn r came before: one of the home block that is among the first kNear of the block's own order.
+__device__ __forceinline__ bool gram_again(GramHash gh, uint32_t r, Buckets t) {
+  return r >= kNear && t.mask > t.block && ((r - kNear) & t.block) < kNear && ((gram_far(gh, r, t) ^ gh.h) & t.mask) <= t.block;
 }
 __device__ __forceinline__ int32_t* gram_bucket(int32_t* tbl, GramHash gh, uint32_t r,
-                                                uint32_t mask) {
-  return tbl + (int64_t)gram_index(gh, r, mask) * kBucketWords;
+                                                Buckets tb) {
+  return tbl + (int64_t)gram_index(gh, r, tb) * kBucketWords;
 }
 // (where r is known to be small: the other half is code on the way of every launch, 0.3 us of small ones)
-__device__ __forceinline__ int32_t* gram_bucket_near(int32_t* tbl, GramHash gh, uint32_t r, uint32_t mask) {
-  return tbl + (int64_t)gram_near(gh, r, mask) * kBucketWords;
+__device__ __forceinline__ int32_t* gram_bucket_near(int32_t* tbl, GramHash gh, uint32_t r, Buckets tb) {
+  return tbl + (int64_t)gram_near(gh, r, tb) * kBucketWords;
 }
 
 // Word `sub` of bucket r0 + grp of a gram's sequence, for a look-up by batches of four buckets (r0: the batch's first,
 // uniform over the wave).  A bucket that came before is as one without postings that goes on; with SELECT the caller
 // passes over it.
 // SELECT: near or far without a branch, where registers are short (step_wave_many_kernel, 65536 rows 82.5 us, 92 with the
-// branch, whose other side needs a few at once); else the usual one alone on the way (one row 6.65 us, 6.9 without).
+// branch, whose other side needs a few at once); else the usual one alone on the way (64 x 4096, a step 6.7 us, 6.9
+// without).  Where the kernel is compiled for an index without home blocks none of it is left.
 template <bool SELECT = false>
-__device__ __forceinline__ int32_t gram_word(const int32_t* tbl, GramHash gh, uint32_t r0, int grp, int sub, uint32_t mask) {
+__device__ __forceinline__ int32_t gram_word(const int32_t* tbl, GramHash gh, uint32_t r0, int grp, int sub, Buckets tb) {
   uint32_t r = r0 + (uint32_t)grp;
-  if constexpr (SELECT) return tbl[(int64_t)gram_index(gh, r, mask) * kBucketWords + sub];
-  if (__builtin_expect(r0 + 4u <= kNear, 1)) return tbl[(int64_t)gram_near(gh, r, mask) * kBucketWords + sub];
+  if (SELECT || (__builtin_constant_p(tb.mask > tb.block) && tb.mask <= tb.block))
+    return tbl[(int64_t)gram_index(gh, r, tb) * kBucketWords + sub];
+  if (__builtin_expect(r0 + 4u <= kNear, 1)) return tbl[(int64_t)gram_near(gh, r, tb) * kBucketWords + sub];
   consume_here(r);                                      // (else what follows is prepared ahead of the caller's loop)
   consume_here(gh.h);
   consume_here(gh.step);
   int32_t word = sub == 0 ? kBucketSlots : -1;
-  if (!gram_again(gh, r, mask)) word = tbl[(int64_t)gram_index(gh, r, mask) * kBucketWords + sub];
+  if (!gram_again(gh, r, tb)) word = tbl[(int64_t)gram_index(gh, r, tb) * kBucketWords + sub];
   return word;
 }
 
@@ -93,12 +94,12 @@ __device__ __forceinline__ int32_t gram_word(const int32_t* tbl, GramHash gh, ui
 // (The first few: of the rows whose first bucket is full most find one of the next open; 64 at once fetched as many
 // lines, 4096 problems at full history 129 us a step for 123.)
 constexpr uint32_t kInsertFirst = 4;
-__device__ __forceinline__ void gram_insert_from(int32_t* tbl, uint32_t mask, GramHash gh,
+__device__ __forceinline__ void gram_insert_from(int32_t* tbl, Buckets tb, GramHash gh,
                                                  uint32_t r0, int32_t pos, int lane) {
-  const uint32_t turns = gram_turns(mask), few = turns < kInsertFirst ? turns : kInsertFirst;
+  const uint32_t turns = gram_turns(tb), few = turns < kInsertFirst ? turns : kInsertFirst;
   while (r0 < turns) {                                  // uniform over the wave
     const uint32_t r = r0 + lane, end = r0 < few ? few : turns;
-    const uint32_t at = gram_index(gh, r, mask);
+    const uint32_t at = gram_index(gh, r, tb);
     bool open = r < end && tbl[(int64_t)at * kBucketWords] < kBucketSlots;
     u64 m = wave_ballot(open);
     while (m) {
@@ -135,7 +136,7 @@ struct InsertTicket {
 // Phase 1: hash of the gram that ends just before the new position (tail[a] =
 // a-th token before it) and the fill-count loads (not waited for here).
 template <int QC, int LANES = kInsertLanes>
-__device__ __forceinline__ InsertTicket insert_begin(int32_t* gram, uint32_t mask, int32_t kmax,
+__device__ __forceinline__ InsertTicket insert_begin(int32_t* gram, Buckets tb, int32_t kmax,
                                                      const int32_t (&tail)[kTailCap],
                                                      int32_t n_before, int lane) {
   static_assert(LANES >= 1 && (LANES & (LANES - 1)) == 0, "a power of two of buckets");
@@ -150,32 +151,32 @@ __device__ __forceinline__ InsertTicket insert_begin(int32_t* gram, uint32_t mas
   t.first = -1;
   t.claimed = kBucketSlots;
   uint32_t r = (uint32_t)(lane & (LANES - 1));          // every lane loads: no branch, no early wait
-  t.fill = gram_bucket_near(gram, t.gh, r <= mask ? r : 0u, mask)[0];
+  t.fill = gram_bucket_near(gram, t.gh, r <= tb.mask ? r : 0u, tb)[0];
   return t;
 }
 
 // Phase 2: lane 0 claims a slot in the first open bucket.
-__device__ __forceinline__ void insert_claim(InsertTicket& t, int32_t* gram, uint32_t mask,
+__device__ __forceinline__ void insert_claim(InsertTicket& t, int32_t* gram, Buckets tb,
                                              int lane) {
   consume_here(t.fill);
-  bool open = t.live && lane < t.lanes && (uint32_t)lane <= mask && t.fill < kBucketSlots;
+  bool open = t.live && lane < t.lanes && (uint32_t)lane <= tb.mask && t.fill < kBucketSlots;
   u64 m = wave_ballot(open);
   t.first = m ? (int32_t)__ffsll((long long)m) - 1 : -1;
   if (t.live && lane == 0 && t.first >= 0)
-    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask), 1);
+    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, tb), 1);
 }
 
 // Phase 3: store the posting; if the buckets looked at were full (or the last
 // slot was lost in a race) take the general insert.
-__device__ __forceinline__ void insert_finish(const InsertTicket& t, int32_t* gram, uint32_t mask,
+__device__ __forceinline__ void insert_finish(const InsertTicket& t, int32_t* gram, Buckets tb,
                                               int32_t pos, int lane) {
   if (!t.live) return;
   int32_t claimed = __builtin_amdgcn_readfirstlane(t.claimed);
   if (claimed < kBucketSlots) {
-    if (lane == 0) gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask)[1 + claimed] = pos;
+    if (lane == 0) gram_bucket_near(gram, t.gh, (uint32_t)t.first, tb)[1 + claimed] = pos;
     return;
   }
-  gram_insert_from(gram, mask, t.gh, t.first < 0 ? (uint32_t)t.lanes : (uint32_t)t.first, pos,
+  gram_insert_from(gram, tb, t.gh, t.first < 0 ? (uint32_t)t.lanes : (uint32_t)t.first, pos,
                    lane);
 }
 
@@ -224,7 +225,7 @@ struct VariantTicket {
   bool any;                     // the position has kmax tokens before it
 };
 
-__device__ __forceinline__ VariantTicket variants_begin(int32_t* gram, uint32_t mask, int32_t kmax,
+__device__ __forceinline__ VariantTicket variants_begin(int32_t* gram, Buckets tb, int32_t kmax,
                                                         const int32_t (&tail)[kTailCap],
                                                         int32_t n_before, int lane) {
   VariantTicket t;
@@ -235,43 +236,43 @@ __device__ __forceinline__ VariantTicket variants_begin(int32_t* gram, uint32_t 
   t.first = -1;
   t.claimed = kBucketSlots;
   uint32_t r = (uint32_t)(lane & 15);                   // every lane loads: no branch, no early wait
-  t.fill = gram_bucket_near(gram, t.gh, r <= mask ? r : 0u, mask)[0];
+  t.fill = gram_bucket_near(gram, t.gh, r <= tb.mask ? r : 0u, tb)[0];
   return t;
 }
 
-__device__ __forceinline__ void variants_claim(VariantTicket& t, int32_t* gram, uint32_t mask,
+__device__ __forceinline__ void variants_claim(VariantTicket& t, int32_t* gram, Buckets tb,
                                                int lane) {
   consume_here(t.fill);
-  bool open = t.live && (uint32_t)(lane & 15) <= mask && t.fill < kBucketSlots;
+  bool open = t.live && (uint32_t)(lane & 15) <= tb.mask && t.fill < kBucketSlots;
   uint32_t mine = (uint32_t)(wave_ballot(open) >> (lane & 48)) & 0xFFFFu;   // this group's 16 lanes
   t.first = mine ? (int32_t)__ffs(mine) - 1 : -1;
   if (t.live && (lane & 15) == 0 && t.first >= 0)
-    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask), 1);
+    t.claimed = atomicAdd(gram_bucket_near(gram, t.gh, (uint32_t)t.first, tb), 1);
 }
 
 // Variants beyond the four the groups take (kmax >= 4): the general insert.
 __device__ __forceinline__ void variants_beyond_four(const VariantTicket& t, int32_t* gram,
-                                                     uint32_t mask, int32_t kmax,
+                                                     Buckets tb, int32_t kmax,
                                                      const int32_t (&tail)[kTailCap], int32_t pos,
                                                      int lane) {
   if (!t.any) return;
   for (int32_t v = 4; v <= kmax; ++v)
     if (variant_is_new(tail, v))
-      gram_insert_from(gram, mask, variant_hash(tail, kmax, v), 0u, variant_posting(pos, v), lane);
+      gram_insert_from(gram, tb, variant_hash(tail, kmax, v), 0u, variant_posting(pos, v), lane);
 }
 
-__device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t* gram, uint32_t mask,
+__device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t* gram, Buckets tb,
                                                 int32_t pos, int lane) {
   if (!t.any) return;
   bool stored = t.live && (lane & 15) == 0 && t.claimed < kBucketSlots;
-  if (stored) gram_bucket_near(gram, t.gh, (uint32_t)t.first, mask)[1 + t.claimed] = variant_posting(pos, lane >> 4);
+  if (stored) gram_bucket_near(gram, t.gh, (uint32_t)t.first, tb)[1 + t.claimed] = variant_posting(pos, lane >> 4);
   int32_t retry = (t.live && !stored) ? 1 : 0;          // meaningful on the group leaders
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     if (__shfl(retry, 16 * g) == 0) continue;           // uniform over the wave
     GramHash gh{(uint32_t)__shfl((int)t.gh.h, 16 * g), (uint32_t)__shfl((int)t.gh.step, 16 * g)};
     int32_t first = __shfl(t.first, 16 * g);
-    gram_insert_from(gram, mask, gh, first < 0 ? 16u : (uint32_t)first, variant_posting(pos, g), lane);
+    gram_insert_from(gram, tb, gh, first < 0 ? 16u : (uint32_t)first, variant_posting(pos, g), lane);
   }
 }
 
@@ -285,7 +286,7 @@ __device__ __forceinline__ void variants_finish(const VariantTicket& t, int32_t*
 // LOOK: the fill counts are looked at before all the same (see launch_append).
 constexpr uint32_t kFileNear = 4;
 template <bool FUZZY, int QC, bool LOOK = false, class MEANWHILE>
-__device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int32_t kmax,
+__device__ __forceinline__ void file_positions(int32_t* gram, Buckets tb, int32_t kmax,
                                                const int32_t (&G)[QC], bool mine, int32_t pos, int lane,
                                                MEANWHILE&& meanwhile) {
   constexpr int kVariants = FUZZY ? QC + 1 : 1;
@@ -296,7 +297,7 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
   for (int v = 0; v < kVariants; ++v) {
     bool live = mine && v <= kmax;
     if (v >= 2) live = live && G[v - 1] != G[v - 2];     // (else the same string as variant v - 1)
-    at[v] = variant_hash(G, kmax, v).h & mask;
+    at[v] = variant_hash(G, kmax, v).h & tb.mask;
     claimed[v] = kBucketSlots;
     todo |= live ? 1u << v : 0u;
   }
@@ -326,12 +327,12 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
     int32_t fill[kFileNear];
     if (open) {
 #pragma unroll
-      for (uint32_t x = 0; x < kFileNear; ++x) fill[x] = gram[(int64_t)gram_near(gh, x + 1u, mask) * kBucketWords];
+      for (uint32_t x = 0; x < kFileNear; ++x) fill[x] = gram[(int64_t)gram_near(gh, x + 1u, tb) * kBucketWords];
     }
 #pragma unroll
     for (uint32_t x = 0; x < kFileNear; ++x) {
-      if (!open || fill[x] >= kBucketSlots || x + 1u > mask) continue;
-      int32_t* b = gram + (int64_t)gram_near(gh, x + 1u, mask) * kBucketWords;
+      if (!open || fill[x] >= kBucketSlots || x + 1u > tb.mask) continue;
+      int32_t* b = gram + (int64_t)gram_near(gh, x + 1u, tb) * kBucketWords;
       const int32_t c = atomicAdd(b, 1);
       if (c < kBucketSlots) {
         b[1 + c] = posting;
@@ -344,7 +345,7 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
       left &= left - 1;
       const GramHash g{(uint32_t)__builtin_amdgcn_readlane((int)gh.h, t),
                        (uint32_t)__builtin_amdgcn_readlane((int)gh.step, t)};
-      gram_insert_from(gram, mask, g, kFileNear + 1u, __builtin_amdgcn_readlane(posting, t), lane);
+      gram_insert_from(gram, tb, g, kFileNear + 1u, __builtin_amdgcn_readlane(posting, t), lane);
     }
     todo &= todo - 1u;                                   // 0 stays 0
   }
@@ -356,7 +357,7 @@ __device__ __forceinline__ void file_positions(int32_t* gram, uint32_t mask, int
 // are the QC tokens before the first of them, oldest first, and the W at the positions, `filed` has
 // a bit per position, `pos` is the first one's packed (path, index).
 template <bool FUZZY, int QC, int W>
-__device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill, uint32_t mask, int32_t kmax,
+__device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill, Buckets tb, int32_t kmax,
                                                    const int32_t (&tok)[QC + W], uint32_t filed, int32_t pos) {
   // positions that claim together: all of a lane's (one gram each), or one (its variants)
   constexpr int kTogether = FUZZY ? 1 : W, kVariants = FUZZY ? QC + 1 : 1, kClaims = kTogether * kVariants;
@@ -380,12 +381,12 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
 #pragma unroll
     for (int y = 0; y < kClaims; ++y) {
       claimed[y] = kBucketSlots;
-      if (todo >> y & 1u) claimed[y] = atomicAdd(&fill[gh[y].h & mask], 1);
+      if (todo >> y & 1u) claimed[y] = atomicAdd(&fill[gh[y].h & tb.mask], 1);
     }
 #pragma unroll
     for (int y = 0; y < kClaims; ++y)
       if (claimed[y] < kBucketSlots) {                   // (never without a claim)
-        slots[(gh[y].h & mask) * kBucketWords + 1 + claimed[y]] = posting[y];
+        slots[(gh[y].h & tb.mask) * kBucketWords + 1 + claimed[y]] = posting[y];
         todo &= ~(1u << y);
       }
     // first bucket full: on along the chain, once through all buckets at most (the table holds more
@@ -395,12 +396,11 @@ __device__ __forceinline__ void file_positions_own(int32_t* slots, int32_t* fill
 #pragma unroll
     for (int y = 0; y < kClaims; ++y) {
       bool looking = (todo >> y & 1u) != 0;
-      const uint32_t in_block = mask < kBlock ? mask : kBlock - 1u, home = gh[y].h & mask & ~in_block;
-      const uint32_t turns = gram_turns(mask), near = mask < kBlock ? turns : kNear;
+      const uint32_t turns = gram_turns(tb), home = gh[y].h & tb.mask & ~tb.block;
       uint32_t turn = gh[y].h + gh[y].step;
       for (uint32_t r = 1; r < turns && wave_ballot(looking) != 0; ++r, turn += gh[y].step) {   // uniform over the wave
-        uint32_t b = home | (turn & in_block);
-        if (__builtin_expect(r >= near, 0)) b = gram_far(gh[y], r, mask);
+        uint32_t b = home | (turn & tb.block);
+        if (__builtin_expect(tb.mask > tb.block && r >= kNear, 0)) b = gram_far(gh[y], r, tb);
         if (looking) {
           int32_t c = fill[b];                           // (a full bucket is passed without an atomic)
           if (c < kBucketSlots) c = atomicAdd(&fill[b], 1);
@@ -587,7 +587,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
                                                  bool head, int tid, AT_END&& at_end) {
   const int64_t row = (int64_t)p * ix.N + i;
   const int lane = tid & (kWave - 1);
-  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
+  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords : nullptr;
   uint32_t flags = 0;
   int32_t t0 = t_first + (tid - lane), cnt;
   do {                                                   // uniform over the wave
@@ -607,7 +607,7 @@ __device__ __forceinline__ void append_positions(const IndexView& ix, const Step
     if constexpr (INDEX) {
 #pragma unroll
       for (int a = 0; a < QC; ++a) consume_here(x.G[a]);
-      file_positions<FUZZY, QC, LOOK>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, sign_off);
+      file_positions<FUZZY, QC, LOOK>(gram, ix.buckets, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, sign_off);
     } else {
       sign_off();
     }

@@ -75,15 +75,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(96))) void appe
 // files with atomics on memory after all (us, up to 16 tokens taken of those offered / half of them
 // on average, without and with that: 1024 problems of 16 paths, 512 offered: 77, 26 / 82, 82; 128 of 64,
 // 2048: 202, 21 / 405, 406; 4096 of 4, 128: 53, 32 / 55, 61).  TABLE: the buckets
-// themselves are in LDS too, and go to memory as a whole.  The paths' ends are replaced in place, by
+// themselves are in LDS too, and go to memory as a whole.  BLOCKS: an index with home blocks (see Buckets).  The paths' ends are replaced in place, by
 // way of `ends`, rows like theirs (1024 problems of 16 x 1024 tokens 110 .. 112 us; where `ends` stay the
 // new ends 109; 114 to 118 by way of LDS, with a lane per word before or after the loop or with the
 // tokens from the lanes that have them: registers and instructions of the loop are what counts here).
-template <bool FUZZY, int QC, bool TABLE>
+template <bool FUZZY, int QC, bool TABLE, bool BLOCKS>
 __global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, StepIn in, int32_t maybe_empty, int32_t* ends) {
   extern __shared__ int4 shared[];
   const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
-  const int32_t p = (int32_t)blockIdx.x, n_buckets = (int32_t)ix.bucket_mask + 1;
+  const int32_t p = (int32_t)blockIdx.x, n_buckets = (int32_t)ix.buckets.mask + 1;
   int32_t* gram = ix.gram + (int64_t)p * n_buckets * kBucketWords;
   int32_t* fill = reinterpret_cast<int32_t*>(shared);
   int4* table = shared + n_buckets / 4;                  // (at least 4 buckets)
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(1024) void append_problem_kernel(IndexView ix, Step
     const int64_t row = (int64_t)p * ix.N + path;
     const int32_t cnt = x.count(ix);
     flags |= x.store(ix, in, row, cnt);
-    file_positions_own<FUZZY, QC, 4>(slots, fill, ix.bucket_mask, ix.kmax, x.tok, x.filed(ix, cnt), x.pos(ix, path));
+    file_positions_own<FUZZY, QC, 4>(slots, fill, Buckets{ix.buckets.mask, BLOCKS ? ix.buckets.block : ix.buckets.mask}, ix.kmax, x.tok, x.filed(ix, cnt), x.pos(ix, path));
     if (head) {                                          // the path's first run
       if (lane == 0 && x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
       store_end(ix, in, row, x.len, cnt, ends, lane);
@@ -595,10 +595,10 @@ __device__ __forceinline__ void row_step(LDS& s, const IndexView& ix, const Step
 #endif
   // the posting stores wait on atomics issued long ago: do them before the output stores
   if (ticket_used && FUZZY)
-    variants_finish(tickets, const_cast<int32_t*>(c.gram), c.bucket_mask, c.y.pos(c.i, c.len_i - 1),
+    variants_finish(tickets, const_cast<int32_t*>(c.gram), c.buckets, c.y.pos(c.i, c.len_i - 1),
                     c.tid);
   else if (ticket_used)
-    insert_finish(ticket, const_cast<int32_t*>(c.gram), c.bucket_mask,
+    insert_finish(ticket, const_cast<int32_t*>(c.gram), c.buckets,
                   c.y.pos(c.i, c.len_i - 1), c.tid);
   write_outputs<kWave>(a, row, o, c.tid);
   int32_t accepted = 0;
@@ -656,10 +656,12 @@ __device__ __forceinline__ void step_wave_body(const IndexView& ix, const StepIn
   row_step<LCAP, POOLS, LDS, FUZZY, QC, !SPLIT, TAIL, MULTI>(s, ix, in, a, tail, row, lane);
 }
 
-template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool MULTI = POOLS>
+// BLOCKS: for an index with home blocks (see Buckets).
+template <int LCAP, bool POOLS, class LDS, bool FUZZY, int QC, bool MULTI = POOLS, bool BLOCKS = true>
 __global__ __launch_bounds__(step_wave_threads(FUZZY)) void step_wave_kernel(IndexView ix, StepIn in,
                                                                              DraftArgs a) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs)>();
+  if (!BLOCKS) ix.buckets.block = ix.buckets.mask;
   step_wave_body<LCAP, POOLS, LDS, FUZZY, QC, MULTI>(ix, in, a, NoTail{});
 }
 
@@ -668,11 +670,13 @@ __global__ __launch_bounds__(step_wave_threads(FUZZY)) void step_wave_kernel(Ind
 // (at most 64 registers per lane), with the small on-chip layout: sixteen rows per CU.  (Registers by number, of
 // which the attribute counts half: asked for by waves the compiler gives a wave 80 scalar registers, eight
 // arguments more are spilled and read back all over the kernel; with 102 a SIMD has seven waves.  65536 rows
-// from empty histories 82.5 us a step, at full histories 122.3; with 102 91.4 and 137.)
-template <int QC>
+// from empty histories 81.6 us a step, at full histories 116.4, with 80 81.7 and 123.4, with 102 91 and 137.)
+// BLOCKS: see step_wave_kernel.
+template <int QC, bool BLOCKS>
 __global__ __launch_bounds__(step_wave_threads(false)) __attribute__((amdgpu_num_vgpr(32), amdgpu_num_sgpr(96)))
 void step_wave_many_kernel(IndexView ix, StepIn in, DraftArgs a) {
   fetch_kernel_arguments<sizeof(IndexView) + sizeof(StepIn) + sizeof(DraftArgs)>();
+  if (!BLOCKS) ix.buckets.block = ix.buckets.mask;
   step_wave_body<8, false, LdsWaveSmall, false, QC, false>(ix, in, a, NoTail{});
 }
 
@@ -780,7 +784,7 @@ __global__ __launch_bounds__(256) void replay_append_kernel(IndexView ix, Replay
   const int32_t i = i0 + (tid & (paths - 1)), at_once = (int32_t)blockDim.x >> paths_log2;
   const bool on = i < ix.N;
   const int64_t rows = (int64_t)ix.P * ix.N, row = (int64_t)p * ix.N + (on ? i : i0);
-  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.bucket_mask + 1) * kBucketWords : nullptr;
+  int32_t* gram = INDEX ? ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords : nullptr;
   uint32_t flags = 0;
   for (int32_t t0 = 0; t0 < in.steps; t0 += at_once) {   // uniform over the workgroup
     const int32_t t = on ? t0 + (tid >> paths_log2) : in.steps;   // (idle: behind the last step)
@@ -790,7 +794,7 @@ __global__ __launch_bounds__(256) void replay_append_kernel(IndexView ix, Replay
     if (x.most() > cnt) flags |= CSD_STATUS_CAPACITY;
     flags |= x.store(ix, in.prob != nullptr, row, cnt);
     if constexpr (INDEX)
-      file_positions<FUZZY, QC>(gram, ix.bucket_mask, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, [] {});
+      file_positions<FUZZY, QC>(gram, ix.buckets, ix.kmax, x.G, x.filed(ix, cnt), x.pos(ix, i), lane, [] {});
     if (t < in.steps) {
       int32_t* end = step_meta + (t * rows + row) * ix.meta_stride;
       end[0] = x.len + (t < cnt ? t + 1 : cnt);

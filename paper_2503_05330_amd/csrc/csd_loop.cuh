@@ -73,7 +73,7 @@ __device__ __forceinline__ const LoopArgs& loop_arguments() {
 // buckets followed one by one, 16 x 1024 with each gram twice, four times took 779, 1019, and 24 x 1024, all but
 // 2 % equal, 737.)
 // Exact matching through the index, DAG pool, queries of kmax = K tokens.
-template <int LCAP, int WAVES, int K>
+template <int LCAP, int WAVES, int K, bool BLOCKS>
 __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   constexpr int G = kLoopLanes, kPaths = WAVES * kWave / G, BLOCK = WAVES * kWave;
   constexpr int kWide = WAVES < 4 ? WAVES : (WAVES == 4 ? 4 : 3);   // waves that draft the rows left (what the LDS has room for)
@@ -101,8 +101,9 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
   u.tok = ix.tok + (int64_t)u.first * ix.max_len;
   u.pq = ix.pq + (int64_t)u.first * ix.max_len;
   u.lens = nullptr;
-  u.buckets = (int64_t)p * ((int64_t)ix.bucket_mask + 1);
+  u.buckets = (int64_t)p * ((int64_t)ix.buckets.mask + 1);
   int32_t* gram = ix.gram + u.buckets * kBucketWords;
+  const Buckets buckets{ix.buckets.mask, BLOCKS ? ix.buckets.block : ix.buckets.mask};
   const int32_t* history = ix.tok + (int64_t)u.row * ix.max_len;
   int32_t* own = own_all[path];
   uint32_t* found = found_all[path];
@@ -162,7 +163,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
       // ---- round trip 1: the query's first bucket, past the CU's own cache (slots are claimed in the L2);
       // all postings of the steps before are there
       auto bucket = [&](uint32_t r) {
-        return __hip_atomic_load(gram + (int64_t)gram_near(gh, r, ix.bucket_mask) * kBucketWords + sub, __ATOMIC_RELAXED,
+        return __hip_atomic_load(gram + (int64_t)gram_near(gh, r, buckets) * kBucketWords + sub, __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_AGENT);
       };
       int32_t next = bucket(0);
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
         auto count_of = [&](int32_t word) { return (int32_t)dpp_move<0x150>((uint32_t)word); };   // (the group's first lane has it)
         const int32_t count = count_of(next);
         const bool has_some = looking && sub >= 1 && sub - 1 < count;
-        looking = looking && count >= kBucketSlots && ix.bucket_mask > 0;
+        looking = looking && count >= kBucketSlots && ix.buckets.mask > 0;
         if (wave_ballot(looking) != 0) request(1);       // (in flight while the bucket before is looked through)
         verify(std::integral_constant<int, 1>{}, {has_some}, {next}, false);
         for (uint32_t r = 1; wave_ballot(looking) != 0; r += kAhead) {   // uniform over the wave
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
           for (int x = 0; x < kAhead; ++x) {
             const int32_t filled = count_of(these[x]);
             one[x] = looking && sub >= 1 && sub - 1 < filled;
-            looking = looking && filled >= kBucketSlots && r + x < ix.bucket_mask;
+            looking = looking && filled >= kBucketSlots && r + x < ix.buckets.mask;
           }
           leave = leave || (looking && r + kAhead >= kLoopChain);
           looking = looking && !leave;
@@ -270,13 +271,13 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
         }
       };
       Filing<K> filing;
-      filing.claim(gram, ix.bucket_mask, K, G0, filed(sub), packed(sub));
+      filing.claim(gram, buckets, K, G0, filed(sub), packed(sub));
       look_up();
       filing.settle();
       if (LCAP >= G && wave_ballot(sub + G < cnt) != 0) {
         int32_t g[K];
         gram_before(sub + G, g);
-        file_positions<false, K>(gram, ix.bucket_mask, K, g, filed(sub + G), packed(sub + G), lane, [] {});
+        file_positions<false, K>(gram, buckets, K, g, filed(sub + G), packed(sub + G), lane, [] {});
       }
       // ---- the walk, by as many lanes of a path as the wave's paths have matches
       leave = on && (leave || M > kLoopMatches);
@@ -375,11 +376,19 @@ __global__ __launch_bounds__(WAVES * kWave) void loop_kernel(LoopArgs m) {
 // 8 x 512 104 / 103, 1 of 4 x 256 82 / 85.
 template <int LCAP, int K>
 void launch_loop_kernel(const LoopArgs& m, hipStream_t st) {
-  const uint32_t grid = (uint32_t)m.ix.P;
-  if (m.ix.N <= 4) loop_kernel<LCAP, 1, K><<<grid, kWave, 0, st>>>(m);
-  else if (m.ix.N <= 8) loop_kernel<LCAP, 2, K><<<grid, 2 * kWave, 0, st>>>(m);
-  else if (m.ix.N <= 16) loop_kernel<LCAP, 4, K><<<grid, 4 * kWave, 0, st>>>(m);
-  else loop_kernel<LCAP, 8, K><<<grid, 8 * kWave, 0, st>>>(m);
+  auto of = [&](auto waves, auto blocks) {
+    constexpr int WAVES = waves();
+    loop_kernel<LCAP, WAVES, K, blocks()><<<(uint32_t)m.ix.P, WAVES * kWave, 0, st>>>(m);
+  };
+  const std::integral_constant<int, 4> four;
+  const std::integral_constant<int, 8> eight;
+  if (m.ix.buckets.mask > m.ix.buckets.block) {          // (of few problems: the LDS has room)
+    if (m.ix.N <= 16) of(four, std::true_type{});
+    else of(eight, std::true_type{});
+  } else if (m.ix.N <= 4) of(std::integral_constant<int, 1>{}, std::false_type{});
+  else if (m.ix.N <= 8) of(std::integral_constant<int, 2>{}, std::false_type{});
+  else if (m.ix.N <= 16) of(four, std::false_type{});
+  else of(eight, std::false_type{});
 }
 
 }  // namespace csd

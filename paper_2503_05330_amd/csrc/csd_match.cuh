@@ -519,7 +519,7 @@ __device__ __forceinline__ void lookup_with_windows(LDS& s, const Ctx& c, int32_
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const int sub = lane & 15;          // word of the bucket this lane reads
   const int grp = lane >> 4;          // which of the 4 buckets of a batch
-  const uint32_t turns = gram_turns(c.bucket_mask);
+  const uint32_t turns = gram_turns(c.buckets);
   int32_t query_oldest_first[QC];     // [x] = Q[q - 1 - x]
 #pragma unroll
   for (int x = 0; x < QC; ++x) query_oldest_first[x] = pick_n<QC>(c.Q, c.q - 1 - x);
@@ -532,9 +532,9 @@ __device__ __forceinline__ void lookup_with_windows(LDS& s, const Ctx& c, int32_
     bool full = count >= kBucketSlots;
     bool seq_ends = wave_ballot(in_batch && !full) != 0;   // (behind the sequence's last, too)
     int32_t next_word = -1;           // next batch: in flight while this one is processed
-    if (!seq_ends) next_word = gram_word<FIRST == 1>(tbl, gh, r0 + width, grp, sub, c.bucket_mask);
+    if (!seq_ends) next_word = gram_word<FIRST == 1>(tbl, gh, r0 + width, grp, sub, c.buckets);
     bool cand = sub >= 1 && word >= 0 && (sub - 1) < (full ? kBucketSlots : count);
-    if (FIRST == 1 && __builtin_expect(r0 + 4u > kNear, 0)) cand = cand && !gram_again(gh, r0 + grp, c.bucket_mask);
+    if (FIRST == 1 && __builtin_expect(r0 + 4u > kNear, 0)) cand = cand && !gram_again(gh, r0 + grp, c.buckets);
     int32_t j = y.pos_path(word), e = y.pos_index(word), old_j = 0, new_j = 0;
     cand = cand && j != (GENERAL ? c.skip : c.i) && j < y.N;
     if (cand) {
@@ -691,14 +691,14 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
   // what all rows together fetch and issue, not by a row's latency)
   constexpr int kFirst = std::is_same<LDS, LdsWaveSmall>::value ? 1 : 4;
   ticket_used = APPENDS && y.n == 1 && cnt_i == 1;   // (longer steps are appended by append_path)
-  if (ticket_used) ticket = insert_begin<QC, kFirst>(gram, c.bucket_mask, ix.kmax, me.tail, old_i, lane);
+  if (ticket_used) ticket = insert_begin<QC, kFirst>(gram, c.buckets, ix.kmax, me.tail, old_i, lane);
   GramHash gh{0u, 1u};
   int32_t word = -1;
   if (use_index) {
     gh = query_hash<QC>(c);
     uint32_t r = (uint32_t)(lane >> 4);
     if (kFirst == 4 || r == 0)
-      word = gram_bucket_near(gram, gh, r <= c.bucket_mask ? r : 0u, c.bucket_mask)[lane & 15];
+      word = gram_bucket_near(gram, gh, r <= c.buckets.mask ? r : 0u, c.buckets)[lane & 15];
   }
   // ---- while it travels: own append, lengths into LDS, matches among the new positions
   if (APPENDS && y.n == 1) append_own_single<QC>(ix, y, row, c.i, me, st_i, sp_i, lane);
@@ -749,7 +749,7 @@ __device__ __forceinline__ int32_t wave_front_end(LDS& s, Ctx& c, const IndexVie
       wave_push(s, n_match, hit, make_match(y, j, e, old_j, new_j), lane);
     }
   }
-  if (ticket_used) insert_claim(ticket, gram, c.bucket_mask, lane);   // round trip 3 starts
+  if (ticket_used) insert_claim(ticket, gram, c.buckets, lane);   // round trip 3 starts
   wi.n_fresh = n_match;
   wi.win_cap = use_index ? LDS::kWin / (2 * L) : 0;
   if (use_index) {
@@ -785,11 +785,11 @@ __device__ __forceinline__ void wave_append(const Ctx& c, const IndexView& ix, c
   const float sp_i = y.sp ? y.sp[c.i] : 1.0f;
   const bool ticket_used = me.new_len - me.old_len == 1;
   InsertTicket ticket;
-  if (ticket_used) ticket = insert_begin<QC, LANES>(gram, c.bucket_mask, ix.kmax, me.tail, me.old_len, lane);
+  if (ticket_used) ticket = insert_begin<QC, LANES>(gram, c.buckets, ix.kmax, me.tail, me.old_len, lane);
   append_own_single<QC>(ix, y, row, c.i, me, st_i, sp_i, lane);
   if (ticket_used) {
-    insert_claim(ticket, gram, c.bucket_mask, lane);
-    insert_finish(ticket, gram, c.bucket_mask, y.pos(c.i, me.new_len - 1), lane);
+    insert_claim(ticket, gram, c.buckets, lane);
+    insert_finish(ticket, gram, c.buckets, y.pos(c.i, me.new_len - 1), lane);
   }
 }
 
@@ -967,7 +967,7 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const int sub = lane & 15;
   const int grp = lane >> 4;
-  const uint32_t turns = gram_turns(c.bucket_mask);
+  const uint32_t turns = gram_turns(c.buckets);
   // variants 0 .. 3 and 4 .. 7: both batches of first buckets were requested together.  Buckets
   // are a third full on average, so the postings of the second batch nearly always find a
   // lane of their own among those that hold none of the first, and both are looked through at
@@ -983,7 +983,7 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
   if (!active_b) word_beyond = -1;
   int32_t word_ninth = -1;
   if (K >= 8 && c.q >= 8)             // (travels while the others are looked through)
-    word_ninth = gram_bucket(tbl, variant_hash(c.Q, c.q, 8), 0u, c.bucket_mask)[sub];
+    word_ninth = gram_bucket(tbl, variant_hash(c.Q, c.q, 8), 0u, c.buckets)[sub];
   bool full_a, full_b, full_c = false;
   const bool has_a = bucket_has_posting(word, lane, full_a);
   const bool has_b = bucket_has_posting(word_beyond, lane, full_b);
@@ -1036,11 +1036,11 @@ __device__ __forceinline__ void lookup_variants_with_windows(LDS& s, const Ctx& 
     if ((goes_on >> (16 * (chain & 3)) & 1ull) == 0 || n_match > LIMIT) continue;   // uniform over the wave
     const GramHash gh = variant_hash(c.Q, c.q, chain);                // the same in every lane
     uint32_t r0 = 1;
-    int32_t tail = gram_word(tbl, gh, r0, grp, sub, c.bucket_mask);
+    int32_t tail = gram_word(tbl, gh, r0, grp, sub, c.buckets);
     for (; r0 < turns; r0 += 4) {
       consume_here(tail);
       if (r0 + grp >= turns) tail = -1;
-      int32_t next_tail = gram_word(tbl, gh, r0 + 4, grp, sub, c.bucket_mask);   // next batch: in flight meanwhile
+      int32_t next_tail = gram_word(tbl, gh, r0 + 4, grp, sub, c.buckets);   // next batch: in flight meanwhile
       bool tail_full = consume_variant_bucket<LCAP, K>(s, c, L, win_cap, n_match, chain, tail);
       if (wave_ballot(!tail_full) != 0 || n_match > LIMIT) break;      // the chain ends in this batch
       tail = next_tail;
@@ -1074,10 +1074,10 @@ __device__ __forceinline__ void match_variants(const LDS& s, const Ctx& c, Sink&
   const int32_t chains = c.q + 1, shares = BLOCK / kWave / chains, chain = wave % chains, share = wave / chains;
   static_assert(BLOCK / kWave > CSD_MAX_QUERY_LEN, "a wave for every chain");
   if (share >= shares || !variant_is_new(c.Q, chain)) return;      // uniform over the wave
-  const uint32_t turns = gram_turns(c.bucket_mask);
+  const uint32_t turns = gram_turns(c.buckets);
   int32_t* tbl = const_cast<int32_t*>(c.gram);
   const GramHash gh = variant_hash(c.Q, c.q, chain);
-  auto request = [&](uint32_t first) { return gram_word(tbl, gh, first, grp, sub, c.bucket_mask); };
+  auto request = [&](uint32_t first) { return gram_word(tbl, gh, first, grp, sub, c.buckets); };
   uint32_t r0 = 4u * (uint32_t)share;
   int32_t next = request(r0);
   for (; r0 < turns; r0 += 4u * (uint32_t)shares) {                // (past a chain's end: see above)
@@ -1120,12 +1120,12 @@ __device__ __forceinline__ void wave_append_fuzzy(const Ctx& c, const IndexView&
   const float sp_i = y.sp ? y.sp[c.i] : 1.0f;
   const bool ticket_used = me.new_len - me.old_len == 1;
   VariantTicket ticket;
-  if (ticket_used) ticket = variants_begin(gram, c.bucket_mask, ix.kmax, me.tail, me.old_len, lane);
+  if (ticket_used) ticket = variants_begin(gram, c.buckets, ix.kmax, me.tail, me.old_len, lane);
   append_own_single(ix, y, row, c.i, me, st_i, sp_i, lane);
   if (ticket_used) {
-    variants_claim(ticket, gram, c.bucket_mask, lane);
-    variants_beyond_four(ticket, gram, c.bucket_mask, ix.kmax, me.tail, y.pos(c.i, me.old_len), lane);
-    variants_finish(ticket, gram, c.bucket_mask, y.pos(c.i, me.new_len - 1), lane);
+    variants_claim(ticket, gram, c.buckets, lane);
+    variants_beyond_four(ticket, gram, c.buckets, ix.kmax, me.tail, y.pos(c.i, me.old_len), lane);
+    variants_finish(ticket, gram, c.buckets, y.pos(c.i, me.new_len - 1), lane);
   }
 }
 
@@ -1173,12 +1173,12 @@ __device__ __forceinline__ int32_t wave_front_end_fuzzy(LDS& s, Ctx& c, const In
   const bool use_index = c.q == ix.kmax;                // shorter queries: scan (short paths)
   // ---- round trip 2 is requested: fill counts for the insert, bucket 0 of the first 4 variants
   ticket_used = APPENDS && cnt_i == 1;
-  if (ticket_used) ticket = variants_begin(gram, c.bucket_mask, ix.kmax, me.tail, old_i, lane);
+  if (ticket_used) ticket = variants_begin(gram, c.buckets, ix.kmax, me.tail, old_i, lane);
   int32_t word = -1, word_beyond = -1;
   if (use_index) {
-    word = gram_bucket(gram, variant_hash(c.Q, c.q, lane >> 4), 0u, c.bucket_mask)[lane & 15];
+    word = gram_bucket(gram, variant_hash(c.Q, c.q, lane >> 4), 0u, c.buckets)[lane & 15];
     const int32_t u_b = 4 + (lane >> 4);                // variants 4 .. 7 (queries of 4 tokens and more)
-    word_beyond = gram_bucket(gram, variant_hash(c.Q, c.q, u_b <= c.q ? u_b : 0), 0u, c.bucket_mask)[lane & 15];
+    word_beyond = gram_bucket(gram, variant_hash(c.Q, c.q, u_b <= c.q ? u_b : 0), 0u, c.buckets)[lane & 15];
   }
   // ---- while it travels: own append, lengths into LDS, matches that need no index
   if (APPENDS && y.n == 1) append_own_single(ix, y, row, c.i, me, st_i, sp_i, lane);
@@ -1210,8 +1210,8 @@ __device__ __forceinline__ int32_t wave_front_end_fuzzy(LDS& s, Ctx& c, const In
     wave_push(s, n_match, hit, make_match(y, j, ix.kmax - 1, hj.old_len, hj.new_len), lane);
   }
   if (ticket_used) {
-    variants_claim(ticket, gram, c.bucket_mask, lane);                  // round trip 3 starts
-    variants_beyond_four(ticket, gram, c.bucket_mask, ix.kmax, me.tail, y.pos(c.i, old_i), lane);
+    variants_claim(ticket, gram, c.buckets, lane);                  // round trip 3 starts
+    variants_beyond_four(ticket, gram, c.buckets, ix.kmax, me.tail, y.pos(c.i, old_i), lane);
   }
   wi.n_fresh = n_match;
   wi.win_cap = use_index ? LDS::kWin / (2 * L) : 0;

@@ -58,7 +58,7 @@ struct UnitRow {
     tok = ix.tok + cells;
     pq = ix.pq + cells;
     lens = ix.meta_old + (int64_t)first * ix.meta_stride;
-    buckets = (int64_t)p * ((int64_t)ix.bucket_mask + 1);
+    buckets = (int64_t)p * ((int64_t)ix.buckets.mask + 1);
   }
   // the path's length and newest tokens (newest first)
   template <int QC>
@@ -89,7 +89,7 @@ template <int K>
 struct Filing {
   static constexpr int kAhead = 4;
   int32_t* gram = nullptr;
-  uint32_t mask = 0;
+  Buckets buckets{0u, 0u};
   GramHash gh{0u, 1u};
   int32_t pos = 0, claimed = kBucketSlots;
   bool open = false;            // no slot yet
@@ -98,26 +98,26 @@ struct Filing {
     if (!open) return;
 #pragma unroll
     for (int x = 0; x < kAhead; ++x)
-      fill[x] = __hip_atomic_load(gram_bucket(gram, gh, r + x, mask), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      fill[x] = __hip_atomic_load(gram_bucket(gram, gh, r + x, buckets), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __device__ __forceinline__ void claim(int32_t* table, uint32_t bucket_mask, int32_t kmax, const int32_t (&G)[K], bool mine, int32_t packed) {
+  __device__ __forceinline__ void claim(int32_t* table, Buckets of_problem, int32_t kmax, const int32_t (&G)[K], bool mine, int32_t packed) {
     gram = table;
-    mask = bucket_mask;
+    buckets = of_problem;
     gh = gram_hash_of(G, kmax);
     pos = packed;
     open = mine;
     claimed = kBucketSlots;
-    if (mine) claimed = atomicAdd(gram_bucket_near(gram, gh, 0, mask), 1);
+    if (mine) claimed = atomicAdd(gram_bucket_near(gram, gh, 0, buckets), 1);
   }
   __device__ __forceinline__ void settle() {
     if (claimed < kBucketSlots) {
-      gram_bucket_near(gram, gh, 0, mask)[1 + claimed] = pos;
+      gram_bucket_near(gram, gh, 0, buckets)[1 + claimed] = pos;
       open = false;
     }
     if (wave_ballot(open) != 0) look(1);
   }
   __device__ __forceinline__ void finish() {             // (what finds no slot in a full index is dropped)
-    const uint32_t turns = gram_turns(mask);
+    const uint32_t turns = gram_turns(buckets);
     for (uint32_t r = 1; r < turns && wave_ballot(open) != 0; r += kAhead) {   // uniform over the wave
       if (r > 1) look(r);
       uint32_t room = 0;
@@ -125,7 +125,7 @@ struct Filing {
       for (int x = 0; x < kAhead; ++x) room |= open && fill[x] < kBucketSlots && r + x < turns ? 1u << x : 0u;
       while (wave_ballot(room != 0) != 0) {
         if (room != 0) {
-          int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, mask);
+          int32_t* b = gram_bucket(gram, gh, r + (uint32_t)__ffs(room) - 1u, buckets);
           const int32_t c = atomicAdd(b, 1);
           if (c < kBucketSlots) b[1 + c] = pos;
           open = c >= kBucketSlots;
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(256) void replay_quad_kernel(IndexView ix, int32_t 
   const int32_t len = u.end(ix, Q);
   load_targets<4, LCAP>(a, u, sub, target);
   // ---- round trip 2: the first bucket of the query
-  const int64_t bucket = u.buckets + (gram_hash_of(Q, ix.kmax).h & ix.bucket_mask);
+  const int64_t bucket = u.buckets + (gram_hash_of(Q, ix.kmax).h & ix.buckets.mask);
   const int4 w4 = *reinterpret_cast<const int4*>(ix.gram + bucket * kBucketWords + 4 * sub);
   const int32_t word[4] = {w4.x, w4.y, w4.z, w4.w};
   const int32_t count = (int32_t)dpp_move<0x00>((uint32_t)word[0]);
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
     int32_t M = 0;
     bool looking = on && !leave;                         // the same in a group's lanes
     auto bucket = [&](uint32_t r) {
-      const int64_t b = u.buckets + gram_near(gh, r, ix.bucket_mask);
+      const int64_t b = u.buckets + gram_near(gh, r, ix.buckets);
       return *reinterpret_cast<const int2*>(ix.gram + b * kBucketWords + 2 * sub);
     };
     int2 next = bucket(0);
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(256) void replay_eight_kernel(IndexView ix, int32_t
         if (hit && to < G) found[(lane & ~(G - 1)) + to] = post[x].packed(word[x], a.L);
         M += (int32_t)__popc(hits);
       }
-      const bool goes_on = count >= kBucketSlots && r < ix.bucket_mask;
+      const bool goes_on = count >= kBucketSlots && r < ix.buckets.mask;
       leave = leave || (looking && goes_on && r + 1 >= kLongChain);
       looking = looking && goes_on && !leave;
     }

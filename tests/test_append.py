@@ -220,19 +220,25 @@ def test_grams_that_fill_their_home_block(problems, paths, max_len, query, edits
     assert status == status1 == 0 and int(matches[1][-1]) > 100
 
 
-# a row whose matches lie behind a gram's full home block: its own path, which it passes over, has that gram hundreds of
-# times.  A row's step with its first four buckets at once, thousands of rows (a bucket first), one edit
-@pytest.mark.parametrize("problems,paths,max_len,query,edits", [
-    (1, 8, 800, 3, 0),
-    (2, 40, 700, 6, 0),
-    (300, 8, 700, 3, 0),
-    (300, 7, 1300, 5, 0),
-    (2, 8, 800, 3, 1),
+# a row whose matches lie far along a gram's sequence, behind the near part of a full home block where the index has such
+# (from 2^17 positions): its own path, which it passes over, has that gram hundreds of times.  A row's step with its first
+# four buckets at once, thousands of rows (a bucket first), one edit
+@pytest.mark.parametrize("problems,paths,max_len,query,edits,blocks", [
+    (1, 8, 800, 3, 0, False),
+    (2, 40, 700, 6, 0, False),
+    (300, 8, 700, 3, 0, False),
+    (300, 7, 1300, 5, 0, False),
+    (2, 8, 800, 3, 1, False),
+    (1, 64, 4096, 3, 0, True),
+    (1, 33, 6500, 5, 0, True),
+    (16, 128, 2048, 4, 0, True),
+    (1, 64, 2048, 3, 1, True),
 ])
-def test_steps_whose_matches_lie_behind_a_full_home_block(problems, paths, max_len, query, edits):
-    print("behind the block", problems, paths, max_len, query, edits, flush=True)
+def test_steps_whose_matches_lie_far_along_a_sequence(problems, paths, max_len, query, edits, blocks):
+    print("far along", problems, paths, max_len, query, edits, flush=True)
+    assert blocks == (paths * max_len > 1 << 17 or (edits > 0 and paths * max_len * (query + 1) >= 1 << 19))
     rng = np.random.default_rng(problems + paths)
-    n, n_steps = max_len - 40, 6
+    n, n_steps = max_len - 40, 4
     tokens = rng.integers(10, 5000, size=(problems, paths, max_len)).astype(np.int32)
     tokens[:, 0] = 7                                                       # n postings of it, 15 to a bucket
     for at in range(n - 60, n - 20, 20):
@@ -253,3 +259,75 @@ def test_steps_whose_matches_lie_behind_a_full_home_block(problems, paths, max_l
         for key in ("tokens", "length", "token_scores", "path_scores"):
             assert torch.equal(a[key], b[key]), key
     assert int(outs[0][0]["length"][:, 0].min()) > 0 and int(outs[0][0]["tokens"][:, 0].max()) >= 10
+
+
+# indexes with home blocks under the other kernels that file and look up: replays by lanes (2^15 drafts), the accept-driven
+# loop in one launch, and all steps of either by a workgroup per problem
+@pytest.mark.parametrize("problems,paths,max_len,query,steps", [(8, 64, 4096, 3, 64), (1, 16, 16000, 3, 40), (2, 12, 15000, 4, 30), (1, 6, 40000, 3, 30)])
+def test_home_blocks_under_replays_and_loops(problems, paths, max_len, query, steps):
+    print("home blocks", problems, paths, max_len, query, steps, flush=True)
+    assert paths * max_len > 1 << 17
+    rng = np.random.default_rng(paths)
+    tokens = rng.integers(1, 40000, size=(problems, paths, max_len)).astype(np.int32)
+    same = rng.random((problems, paths, max_len // 20 + 1)) < 0.004                # runs of twenty of one token, and
+    tokens = np.where(np.repeat(same, 20, axis=2)[:, :, :max_len], 7, tokens)
+    shared = rng.random((problems, paths, max_len // 20 + 1)) < 0.4                # ... of one path's earlier ones
+    tokens = np.where(np.repeat(shared, 20, axis=2)[:, :, :max_len], np.roll(tokens[:, :1], 60, axis=2), tokens).astype(np.int32)
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    n = max_len - steps
+    futures, now, past = put(tokens), put(tokens[:, :, n:].transpose(2, 0, 1)), put(tokens[:, :, :n])
+    outs = []
+    for per_launch in (1, 0, 1 << 20):
+        if per_launch > 1 and paths > 16:
+            continue
+        ix = binding.Index(problems, paths, max_len, 40000, query, 8, 0.5, 0, binding.MATCH_INDEX, device="cuda:0")
+        if per_launch:
+            ix.set_steps_per_launch(per_launch)
+        ix.append(past)
+        got = [ix.replay(steps, now, None, query, 8)]
+        if paths <= 16:
+            ix.reset()
+            ix.append(past)
+            got.append(ix.accept_loop(steps // 5, futures, None, query, 8))
+        outs.append((got + [ix.draft(query, 8)], ix.status()))
+    for got, status in outs[1:]:
+        assert status == outs[0][1]
+        for a, b in zip(outs[0][0], got):
+            for key in ("tokens", "length", "token_scores", "path_scores", "accept", "path_len"):
+                if a.get(key) is not None and b.get(key) is not None:
+                    assert torch.equal(a[key], b[key]), key
+    assert int(outs[0][0][0]["length"].sum()) > 0
+
+
+@pytest.mark.parametrize("problems,paths,max_len,query", [(20, 16, 2048, 3), (19, 8, 4096, 5)])
+def test_a_workgroup_per_problem_in_an_index_with_home_blocks(problems, paths, max_len, query):
+    """One edit: histories as a whole are sorted, with counts each problem is filed by a workgroup, from
+    behind what is there; a frequent gram fills its home block."""
+    print("home blocks, counts", problems, paths, max_len, query, flush=True)
+    rng = np.random.default_rng(problems)
+    tokens = rng.integers(1, 5000, size=(problems, paths, max_len)).astype(np.int32)
+    runs = rng.random((problems, paths, max_len // 20 + 1)) < 0.04
+    tokens = np.where(np.repeat(runs, 20, axis=2)[:, :, :max_len], 7, tokens).astype(np.int32)
+    tokens[:, 1:, -200:-40] = tokens[:, :1, -500:-340]
+    tokens[:, 0, -60:-40] = tokens[:, 0, -500:-480]
+    put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+    n, first = max_len - 40, 30
+    counts = np.full((problems, paths), n - first, dtype=np.int32)
+    counts[:, 1::3] -= 17
+    outs = []
+    for flags, sort in ((binding.MATCH_INDEX, False), (binding.MATCH_INDEX, True), (binding.MATCH_SCAN, False)):
+        ix = binding.Index(problems, paths, max_len, 5000, query, 8, 1.0, 0, flags, device="cuda:0", max_edits=1)
+        if sort:                                           # the same histories, without counts
+            ix.append(put(tokens[:, :, :n - 17]))
+            more = np.zeros_like(counts)
+            more[counts == n - first] = 17
+            ix.append(put(tokens[:, :, n - 17:n]), None, put(more))
+        else:
+            ix.append(put(tokens[:, :, :first]))
+            ix.append(put(tokens[:, :, first:n]), None, put(counts))
+        outs.append((ix.draft(query, 8), ix.dump_matches(query, cap=1 << 22), ix.status()))
+    for out, matches, status in outs[:2]:
+        for key in ("tokens", "length", "token_scores", "path_scores"):
+            assert torch.equal(out[key], outs[2][0][key]), key
+        assert np.array_equal(matches[0], outs[2][1][0]) and np.array_equal(matches[1], outs[2][1][1]) and status == 0
+    assert int(outs[0][0]["length"].sum()) > 0
