@@ -77,9 +77,9 @@ def test_steps_side_by_side(problems, paths, max_len, steps, query, draft, edits
     assert int(a["length"].sum()) > 0 or start == "empty"
 
 
-# enough drafts for the kernels with four and eight lanes per draft: drafts of one to 30 tokens, grams
-# of two to six, rows with no, few, many and hundreds of matches (two symbols: chains of full
-# buckets), edge scoring, more than 64 paths, short paths, a wave's sixteen rows across problems
+# enough drafts for the kernels with four and eight lanes per draft, which small problems take where it does not pay to hand
+# a CU to each: drafts of one to 30 tokens, grams of two to six, rows with no, few, many and hundreds of matches (two
+# symbols: chains of full buckets), edge scoring, more than 64 paths, short paths, a wave's sixteen rows across problems
 @pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,mode,warm", [
     (64, 16, 200, 40, 3, 8, 60, 0, 150),
     (64, 17, 160, 31, 4, 13, 60, 1, 120),
@@ -90,6 +90,20 @@ def test_steps_side_by_side(problems, paths, max_len, steps, query, draft, edits
     (130, 16, 100, 20, 3, 7, 9, 0, 0),
 ])
 def test_many_drafts_side_by_side(problems, paths, max_len, steps, query, draft, vocab, mode, warm):
+    _many(problems, paths, max_len, steps, query, query, draft, vocab, mode, warm)
+
+
+# the same with problems larger than a workgroup's LDS (2^14 positions), which all take those kernels: the usual grams and
+# drafts, both weights, an eighth's rows pooled by four and by sixteen waves (2^17 drafts), rows left over or none
+@pytest.mark.parametrize("problems,paths,max_len,steps,query,draft,vocab,mode,warm", [
+    (32, 20, 1024, 64, 3, 8, 3000, 0, 900),
+    (32, 20, 1024, 64, 3, 8, 60, 1, 900),
+    (64, 40, 512, 64, 4, 13, 2000, 1, 400),
+    (130, 33, 500, 31, 4, 8, 500, 0, 300),
+    (16, 70, 250, 40, 2, 5, 6, 1, 200),
+])
+def test_many_drafts_of_large_problems(problems, paths, max_len, steps, query, draft, vocab, mode, warm):
+    assert paths * ((max_len + 3) // 4 * 4) > 1 << 14
     _many(problems, paths, max_len, steps, query, query, draft, vocab, mode, warm)
 
 
@@ -160,7 +174,8 @@ def test_a_captured_replay_goes_on_from_where_it_was():
             assert torch.equal(out[key], want[key]), (turn, key)
 
 
-@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17)])
+# (a wave per draft; a workgroup per problem, its histories in LDS; four lanes a draft, problems of more than 2^14 positions)
+@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17), (64, 48, 17)])
 def test_a_step_fed_with_what_an_earlier_one_drafted(problems, paths, steps):
     """Drafts of one token written where the next step's tokens are read from: the steps see each
     other's drafts, as they do in a launch per step."""
@@ -173,19 +188,19 @@ def test_a_step_fed_with_what_an_earlier_one_drafted(problems, paths, steps):
     out = dict(tokens=cells[1:], length=torch.empty((steps, problems, paths), dtype=torch.int32, device=dev))
     ix = binding.Index(problems, paths, 400, V, k, 1, device=dev)
     ix.append(torch.from_numpy(past).to(dev))
-    assert problems == 1 or problems * paths * steps >= 1 << 15    # both forms of a replay side by side
+    assert problems == 1 or problems * paths * steps >= 1 << 15    # all forms of a replay side by side
     ix.replay(steps, cells[:-1], None, k, 1, out=out, scores=False)
     want = (past[None, :, :, -1] + 1 + np.arange(steps + 1)[:, None, None]) % 13
     assert np.array_equal(cells.cpu().numpy(), want)
     assert ix.status() == 0
 
 
-@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17)])
+@pytest.mark.parametrize("problems,paths,steps", [(1, 6, 20), (64, 32, 17), (64, 96, 17)])
 def test_accepted_lengths_in_the_place_of_the_drafts(problems, paths, steps):
     """One buffer for both: it holds the accepted lengths, which are written last."""
     rng = np.random.default_rng(steps + 1)
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
-    V, k, L, S = (6 if problems == 1 else 40), 2, 4, steps  # (rows with few matches: four lanes each)
+    V, k, L, S = (6 if problems == 1 else 40), 2, 4, steps  # (rows with few matches)
     tokens, targets = (rng.integers(0, V, size=s).astype(np.int32) for s in ((S, problems, paths), (S, problems, paths, L)))
     past = rng.integers(0, V, size=(problems, paths, 100)).astype(np.int32)
     accepted = []

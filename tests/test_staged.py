@@ -81,6 +81,46 @@ def test_staged_replay(problems, paths, T, steps, query, draft, vocab, mode, war
     assert sum(int(x["length"].sum()) for x in a) > 0
 
 
+def _shares(problems, paths, T, steps, draft):
+    """Workgroups of a problem, 0 where the launches for append and drafts are taken (as the library has it)."""
+    cells, rows, drafts = paths * ((T + 3) // 4 * 4), paths * steps, problems * paths * steps
+    if drafts < 5 << 10 or paths > 256 or cells > 1 << 14 or draft > 16:
+        return 0
+    shares = max(min(256 // problems, rows // 128), -(-rows // 384))
+    per = -(-rows // shares)
+    shares = -(-rows // per)
+    groups = problems * shares
+    staged = 6000 + -(-groups // 256) * (3000 + 100 * paths * ((T + 511) // 512) + cells // 2 + 23 * per) + 16 * groups
+    quads = max(0, drafts - (1 << 15))
+    launches = 14000 + (drafts - quads) // 2 + quads // 16 + problems * cells // 1500 + drafts * cells // 41000
+    return shares if 20 * staged < 19 * launches else 0
+
+
+# sizes that take the staged form by its rule, and beside its line: few problems of many shares; most paths a problem may
+# have; short paths, from empty and full before the last step; all rows left over by few problems
+@pytest.mark.parametrize("shares,problems,paths,T,steps,query,draft,vocab,mode,warm,noise", [
+    (26, 4, 16, 1000, 215, 3, 8, 300, 0, 700, 0.2),
+    (0, 4, 16, 1000, 213, 3, 8, 300, 0, 700, 0.2),
+    (4, 9, 8, 512, 72, 4, 7, 100, 1, 400, 0.3),
+    (4, 64, 256, 64, 4, 3, 8, 900, 0, 50, 0.3),
+    (4, 64, 190, 81, 6, 2, 16, 3000, 0, 40, 0.5),
+    (1, 300, 7, 100, 12, 6, 16, 30, 1, 60, 0.3),
+    (1, 256, 2, 100, 15, 4, 5, 50, 0, 0, 0.3),
+    (1, 300, 4, 64, 14, 3, 4, 60, 0, 60, 0.3),
+    (1, 256, 16, 1000, 4, 3, 8, 300, 0, 900, 0.2),
+    (0, 256, 16, 1000, 2, 3, 8, 300, 0, 900, 0.2),
+    (8, 20, 16, 1000, 64, 3, 8, 2, 0, 900, 0.5),
+])
+def test_staged_replay_along_its_rule(shares, problems, paths, T, steps, query, draft, vocab, mode, warm, noise):
+    print("staged rule", shares, problems, paths, T, steps, query, draft, vocab, mode, warm, noise, flush=True)
+    assert _shares(problems, paths, T, steps, draft) == shares and steps <= max(T // 4, 16)
+    args = (problems, paths, T, steps, query, draft, vocab, mode, warm, noise)
+    (a, status), (b, status1) = _run(*args), _run(*args, per_launch=1)
+    _same(a, b)
+    assert status == status1 and (status == 0 or warm + steps > T)
+    assert sum(int(x["length"].sum()) for x in a) > 0
+
+
 def _matches(tokens, lens, steps, query):
     """Matches of every row (step by step, path by path) of one problem; tokens: its paths with the steps' tokens."""
     where, rows = {}, []
@@ -148,7 +188,7 @@ def test_staged_replay_behind_a_reset_and_captured():
 
 # all rows left over, in lists of 1024 rows an XCD (a wave a workgroup takes them) and of more (all four): every
 # wave of that launch has the lists' counts before they are zeroed for the next replay, so no row stays as it was
-@pytest.mark.parametrize("problems,steps", [(20, 25), (64, 30)])
+@pytest.mark.parametrize("problems,steps", [(20, 25), (20, 60), (64, 30)])
 def test_every_row_left_over_is_drafted(problems, steps):
     print("left over", problems, steps, flush=True)
     dev = torch.device("cuda:0")
