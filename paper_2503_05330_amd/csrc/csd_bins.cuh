@@ -3,8 +3,8 @@
 // An append with a thread per position claims every slot with an atomic on memory, and those run at
 // the memory's side of the fabric, 1.1e10 per second for the whole chip: 2.6e5 postings 22 us, 1.3e6 (one
 // edit) 88 us.  Sorted by bins they take 8 + 10 + 2 and 11 + 19 .. 24 + 5: two passes over the records, one over the
-// index.  A bin of buckets is one workgroup's, which claims in LDS, and whole home blocks, so that nearly all of a
-// chain is: (with sequences through the whole table the last launch filed what found its first bucket full, 15 .. 21 us
+// index.  A bin of buckets is one workgroup's, which claims in LDS, and the home block of its grams, so that nearly all of a
+// chain is (with sequences through the whole table the last launch filed what found its first bucket full, 15 .. 21 us
 // behind 14 with one edit):
 //   bin_sort_kernel   stores tokens and probabilities, and each workgroup's records (bucket, posting)
 //                     ordered by bin; a counting sort in LDS, no atomic on memory

@@ -761,9 +761,8 @@ __global__ __launch_bounds__(16 * kWave) void step_multi_kernel(IndexView ix, Mu
 // from the ends of its own step: what lies beyond them in the histories and postings is not seen.
 // A launch per step leaves most of the chip idle and waits for its slowest row; this is bound by the
 // drafts a CU holds at once.  us for reset, append of the past and replay, a launch per step / this:
-// 16 paths x 1024 tokens, 64 steps 355 / 26; 64 x 4096, 48 steps 357 / 41; 64 problems of 16 x 1024,
-// 48 steps 504 / 85; 1024 problems, 24 steps 1477 / 370; one edit by scan, 16 x 1024, 32 steps
-// 622 / 48; one edit through the index, 64 x 4096, 24 steps 686 / 106.
+// 16 paths x 1024 tokens, 64 steps 355 / 22; 64 x 4096, 48 steps 357 / 36; one edit by scan, 16 x 1024, 32 steps 622 / 49; one
+// edit through the index, 64 x 4096, 24 steps 686 / 106.  (Many small problems: replay_staged_kernel, one launch for both.)
 struct ReplayIn {
   const int32_t* tok;           // [steps][P][N]
   const float* prob;            // [steps][P][N] or null

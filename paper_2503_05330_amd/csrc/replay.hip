@@ -6,14 +6,18 @@ namespace csd {
 // From this many drafts on the small LDS layout is used (as in launch_step).
 constexpr int64_t kSmallLdsDrafts = 2048;
 
-// (Problems whose histories fit a workgroup's LDS take replay_staged_kernel from fewer drafts on; the figures
-// below are of such problems, before they did.)
+// (Where a problem's rows are many enough to pay for a CU replay_staged_kernel comes first. The figures up to 1024 problems
+// are of such sizes, before it did; those behind of sizes that come here.)
 // From this many drafts on those with few matches are made with four or eight lanes each.  Three
 // kernels in a row have their latency: us, a wave per draft / by quads, eights and the rest: 1024
 // drafts (16 paths x 64 steps) 8.6 / 32, 3072 (64 x 48, long histories) 12.5 / 31 (with a fourth kernel of
 // 4 us, before the rest were one), 49152 (64 problems x 16 paths x 48 steps) 73 / 42 (8 + 13 + 21), 393216 (1024
-// problems, 24 steps) 533 / 159 (56 + 57 + 46).  Where the paths agree in most tokens nearly all rows are
-// left over; the host does not know.
+// problems, 24 steps) 533 / 159 (56 + 57 + 46).  Whole passes: 64 problems of 32 x 1024, 24 steps (49152 drafts) 144 / 132, 64
+// steps 255 / 213, 4 of 64 x 4096, 128 steps (32768) 369 / 355, 8 of 64 x 2048, 64 steps (32768) 305 / 302, 4096 of 4 x 64, 2
+// steps (32768) 96 / 77; but 16 of 32 x 2048, 64, 128 steps (32768, 65536) 203, 250 / 227, 284; below, 2000 of 8 x 512, 2
+// steps (32000) 112 / 99, 64 of 32 x 1024, 8 steps (16384) 97 / 103, 4 of 64 x 4096, 48 steps (12288) 241 / 266.  Where the paths
+// agree in most tokens nearly all rows are left over (8 of 64 x 2048, 64 steps, all but 5 % 7037 / 11865); the host
+// does not know.
 constexpr int64_t kQuadDrafts = 1 << 15;
 
 template <class LDS, int QC>
@@ -26,7 +30,9 @@ static void launch(const IndexView& v, int32_t steps, const DraftArgs& a, hipStr
 
 // From this many drafts on a workgroup of replay_eight_kernel pools sixteen waves' rows: below, its
 // workgroups with four fit the chip at once and have fewer turns (64 problems x 48 steps, 49152
-// drafts, 20 us; 1024 problems x 24 steps, 393216 drafts, 74 us with four waves' rows, 60 with sixteen).
+// drafts, 20 us; 1024 problems x 24 steps, 393216 drafts, 74 us with four waves' rows, 60 with sixteen; passes of sizes that come
+// here, four / sixteen: 64 problems of 32 x 1024, 24 steps, 49152 drafts, 132 / 145, 64 steps 206 / 213, 512 of 40 x 512, 24
+// steps, 491520, 445 / 450).
 constexpr int64_t kPooledDrafts = 1 << 17;
 
 void launch_replay_rest(const RestArgs& args, hipStream_t st) {
