@@ -271,7 +271,8 @@ __global__ __launch_bounds__(kStagedThreads) void replay_staged_kernel(StagedArg
     int32_t Q[QC], G[QC];
     tokens_before(r.i, len, Q);
     tokens_before(r.i, e < max_len ? e : 0, G);
-    filing.claim(ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords, ix.buckets, kmax, G,
+    // (no home blocks: an index has them from 12 positions a bucket on, eight is what its buckets are for)
+    filing.claim(ix.gram + (int64_t)p * ((int64_t)ix.buckets.mask + 1) * kBucketWords, Buckets{ix.buckets.mask, ix.buckets.mask}, kmax, G,
                  appended && e >= kmax, (r.i << ix.eshift) | e);
     if (has_row) flags = !appended ? CSD_STATUS_CAPACITY : (Q[0] < 0 || Q[0] >= ix.vocab) ? CSD_STATUS_TOKEN_RANGE : 0u;
     leave = has_row && len < kmax;                       // no gram to look for: scanned for by a wave
